@@ -10,16 +10,15 @@
 namespace gns {
 
 constexpr unsigned long long kWalkLimit = 1ull << 62;     // sums, products and the total stay below this
-constexpr int kWalkLanes = 16;                             // lanes per row in a step
 
 __global__ void __launch_bounds__(kBlock) k_walk_seed(const int32_t* train, int64_t num_train, int64_t n,
-                                                      unsigned long long unit, unsigned long long* cur, DeviceState* st)
+                                                      uint32_t* bits, DeviceState* st)
 {
     const int64_t t = (int64_t) blockIdx.x * kBlock + threadIdx.x;
     if (t >= num_train) return;
     const int32_t v = train[t];
     if (v < 0 || (int64_t) v >= n) { st->walk_error = 1; return; }
-    cur[v] = unit;
+    atomicOr(&bits[v >> 5], 1u << (v & 31));
 }
 
 // Addition that sticks at kWalkLimit.  Operands are at most kWalkLimit, so the plain sum fits in
@@ -31,36 +30,190 @@ __device__ __forceinline__ unsigned long long sat_add(unsigned long long a, unsi
     return s < kWalkLimit ? s : kWalkLimit;
 }
 
+// ---------------------------------------------------------------------------
 // One step: nxt[i] = cur[i] + floor(min(k, deg_i) * sum_{j in N(i)} cur[j] / deg_i).
-template <typename OffT>
-__global__ void __launch_bounds__(kBlock) k_walk_step(const void* indptr, const int32_t* indices, int64_t n, int32_t k,
-                                                      const unsigned long long* cur, unsigned long long* nxt,
-                                                      DeviceState* st)
+//
+// A step streams the adjacency once and reads one vector entry per CSR entry, at random.  Two things bound it:
+//  - how many of those reads are in flight.  Rows are short (tens of entries) and a row is a chain extent -> ids ->
+//    values, so a wave takes a run of consecutive rows and streams their entries, which are contiguous, as one list,
+//    kUnroll * 64 at a time; the row sums are differences of the list's running sum, which lane r picks up where row r
+//    begins.  Every lane then does one row's division.
+//  - how much of the vector the 4 MB L2 of an XCD holds.  So the vector is kept as narrow as its values allow.  A step
+//    multiplies the largest entry by at most 1 + k, hence W_l <= 2^scale * prod(1 + k_i): known on the host.
+//      kBits   P^0 is zero or one unit: one bit per node, staged in LDS where it fits (n <= 1.3 M)
+//      kNarrow every entry fits 32 bits
+//      kWide   64 bits
+// The last step writes 64 bits (the vector the caller sees).
+// 1 M nodes, 40 M entries, scale 24, fan-outs 15/10/5: 87 + 240 + 225 us for the three steps (the two narrow ones at
+// 174 G reads/s, the rate the L2s take scattered requests); one row per 16 lanes on 64-bit vectors took 3 x 490 us.
+enum { kBits = 0, kNarrow = 1, kWide = 2 };
+
+struct WalkStepArgs {
+    const void* indptr;
+    const int32_t* indices;
+    int64_t n;
+    int32_t k;
+    int32_t rows_per_wave;        // 1 .. 64
+    unsigned long long unit;      // kBits: what a set bit stands for
+    const void* cur;
+    void* nxt;
+    DeviceState* st;
+};
+
+// One DPP step of a wave-wide inclusive scan: adds the value kCtrl selects from a lower lane (0 where there is none).
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ unsigned long long dpp_add(unsigned long long v)
 {
-    constexpr int G = kWalkLanes;
-    const int64_t group = ((int64_t) blockIdx.x * kBlock + threadIdx.x) / G;
-    const int64_t num_groups = (int64_t) gridDim.x * kBlock / G;
-    for (int64_t i = group; i < n; i += num_groups) {
-        const int lane = opaque_lane_id() & (G - 1);             // see opaque(): the loop exchanges data between lanes
-        const int64_t b = load_off<OffT>(indptr, i), e = load_off<OffT>(indptr, i + 1);
-        unsigned long long sum = 0;
-        for (int64_t q = b + lane; q < e; q += G) sum = sat_add(sum, cur[indices[q]]);
+    const uint32_t lo = (uint32_t) __builtin_amdgcn_update_dpp(0, (int) (uint32_t) v, kCtrl, kRowMask, 0xf, false);
+    const uint32_t hi = (uint32_t) __builtin_amdgcn_update_dpp(0, (int) (uint32_t) (v >> 32), kCtrl, kRowMask, 0xf, false);
+    return v + (((unsigned long long) hi << 32) | lo);
+}
+
+__device__ __forceinline__ unsigned long long wave_inclusive_scan64(unsigned long long v)
+{
+    v = dpp_add<0x111, 0xf>(v);      // row_shr:1, 2, 4, 8 within the rows of 16 lanes
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);      // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+__device__ __forceinline__ unsigned long long last_lane64(unsigned long long v)
+{
+    const uint32_t lo = (uint32_t) __builtin_amdgcn_readlane((int) (uint32_t) v, kWave - 1);
+    const uint32_t hi = (uint32_t) __builtin_amdgcn_readlane((int) (uint32_t) (v >> 32), kWave - 1);
+    return ((unsigned long long) hi << 32) | lo;
+}
+
+template <typename OffT, int kIn, bool kWideOut, bool kLds>
+__global__ void __launch_bounds__(kLds ? 1024 : kBlock) k_walk_step(WalkStepArgs a)
+{
+    extern __shared__ uint32_t lds_bits[];
+    constexpr int kUnroll = kIn == kBits ? 16 : 8; // 64-entry chunks whose reads are in flight together
+    const uint32_t* bits = static_cast<const uint32_t*>(a.cur);
+    if (kLds) {
+        const int64_t words = (a.n + 31) >> 5;
+        for (int64_t w = threadIdx.x; w < words; w += blockDim.x) lds_bits[w] = bits[w];
+        __syncthreads();
+    }
+    auto value = [&](int64_t j) -> unsigned long long {
+        if (kIn == kBits) return ((kLds ? lds_bits[j >> 5] : bits[j >> 5]) >> (j & 31)) & 1u;
+        if (kIn == kNarrow) return static_cast<const uint32_t*>(a.cur)[j];
+        return static_cast<const unsigned long long*>(a.cur)[j];
+    };
+    const int waves_per_block = (int) (blockDim.x >> 6);
+    const int64_t wave = (int64_t) blockIdx.x * waves_per_block + __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
+    const int64_t num_waves = (int64_t) gridDim.x * waves_per_block;
+    const int R = a.rows_per_wave;
+    for (int64_t r0 = wave * R; r0 < a.n; r0 += num_waves * R) {
+        const int lane = opaque_lane_id();         // see opaque(): the loop exchanges data between lanes
+        const int rows = a.n - r0 < R ? (int) (a.n - r0) : R;
+        // lane r: where row r0 + r begins (lanes past the last row: where it ends)
+        const int64_t my_b = load_off<OffT>(a.indptr, r0 + (lane < rows ? lane : rows));
+        const int64_t end = load_off<OffT>(a.indptr, r0 + rows);          // wave-uniform
+        const int64_t first = load_off<OffT>(a.indptr, r0);
+        unsigned long long carry = 0, carry_hi = 0;          // sums of the list's entries so far (kWide: and of their upper halves)
+        unsigned long long at_b = 0, at_b_hi = 0;            // the same up to my_b
+        for (int64_t c0 = first & ~(int64_t) 15; c0 < end; c0 += kWave * kUnroll) {
+            // positions relative to c0 in 32 bits: 64-bit arithmetic per entry would cost as much as the reads
+            auto rel = [&](int64_t p) { return (int) (p < c0 ? 0 : p - c0 < 2 * kWave * kUnroll ? p - c0 : 2 * kWave * kUnroll); };
+            const int rel_first = rel(first), rel_end = rel(end), rel_b = rel(my_b);
+            const int32_t* ids = a.indices + c0;
+            int32_t j[kUnroll];
+            unsigned long long v[kUnroll];
 #pragma unroll
-        for (int d = G / 2; d > 0; d >>= 1) sum = sat_add(sum, __shfl_xor(sum, d, G));
-        if (lane == 0) {
-            const unsigned long long deg = (unsigned long long) (e - b);
-            bool bad = sum >= kWalkLimit;
-            unsigned long long out = cur[i];
+            for (int t = 0; t < kUnroll; ++t) {
+                const int q = t * kWave + lane;
+                j[t] = q >= rel_first && q < rel_end ? ids[q] : -1;
+            }
+#pragma unroll
+            for (int t = 0; t < kUnroll; ++t) v[t] = j[t] >= 0 ? value(j[t]) : 0ull;
+#pragma unroll
+            for (int t = 0; t < kUnroll; ++t) {
+                const int x = rel_b - t * kWave;                 // entries of this chunk before my_b
+                const bool here = x >= 1 && x <= kWave;
+                if (kIn == kBits) {
+                    const uint64_t m = __ballot(v[t] != 0ull);
+                    if (here) at_b = carry + (unsigned long long) __popcll(x == kWave ? m : m & ((1ull << x) - 1ull));
+                    carry += (unsigned long long) __popcll(m);
+                } else {
+                    const unsigned long long incl = wave_inclusive_scan64(v[t]);
+                    const unsigned long long got = __shfl(incl, here ? x - 1 : 0, kWave);
+                    if (here) at_b = carry + got;
+                    carry += last_lane64(incl);
+                    if (kIn == kWide) {
+                        const unsigned long long incl_hi = wave_inclusive_scan64(v[t] >> 32);
+                        const unsigned long long got_hi = __shfl(incl_hi, here ? x - 1 : 0, kWave);
+                        if (here) at_b_hi = carry_hi + got_hi;
+                        carry_hi += last_lane64(incl_hi);
+                    }
+                }
+            }
+        }
+        // row r ends where row r + 1 begins
+        unsigned long long at_e = __shfl_down(at_b, 1, kWave), at_e_hi = kIn == kWide ? __shfl_down(at_b_hi, 1, kWave) : 0ull;
+        int64_t my_e = __shfl_down(my_b, 1, kWave);
+        if (lane == kWave - 1) { at_e = carry; at_e_hi = carry_hi; my_e = end; }
+        if (lane < rows) {
+            const int64_t i = r0 + lane;
+            unsigned long long sum = at_e - at_b;                // exact modulo 2^64
+            const unsigned long long deg = (unsigned long long) (my_e - my_b);
+            unsigned long long out = value(i);
+            bool bad = false;
+            if (kIn == kBits) {                                  // a count so far
+                bad = sum >= kWalkLimit / a.unit;
+                sum *= a.unit;
+                out *= a.unit;
+            }
+            // fewer than 2^31 terms of at most 32 bits stay below 2^63; wider terms are judged by the sum of their upper
+            // halves, below which the 64-bit sum cannot have wrapped
+            if (kIn == kWide) bad = at_e_hi - at_b_hi >= (kWalkLimit >> 32);
+            bad |= sum >= kWalkLimit;
             if (deg > 0 && !bad) {
-                const unsigned long long kk = (unsigned long long) k < deg ? (unsigned long long) k : deg;
-                const unsigned long long quo = sum / deg, rem = sum % deg;
-                bad = quo >= kWalkLimit / 64;                  // kk <= 64: the product below stays under the limit
-                if (!bad) out = sat_add(out, kk * quo + (kk * rem) / deg);
+                const unsigned long long kk = (unsigned long long) a.k < deg ? (unsigned long long) a.k : deg;
+                if (kk * sum < (1ull << 32) && sum < (1ull << 32) && deg < (1ull << 32)) {
+                    out += (uint32_t) (kk * sum) / (uint32_t) deg;
+                } else {
+                    const unsigned long long quo = sum / deg, rem = sum % deg;
+                    bad = quo >= kWalkLimit / 64;                // kk <= 64: the product below stays under the limit
+                    if (!bad) out += kk * quo + (kk * rem) / deg;
+                }
             }
             bad |= out >= kWalkLimit;
-            nxt[i] = bad ? 0ull : out;
-            if (bad) st->walk_error = 2;
+            if (kWideOut) static_cast<unsigned long long*>(a.nxt)[i] = bad ? 0ull : out;
+            else          static_cast<uint32_t*>(a.nxt)[i] = bad ? 0u : (uint32_t) out;
+            if (bad) a.st->walk_error = 2;
         }
+    }
+}
+
+template <typename OffT>
+static void launch_walk_step(const gns_ctx* c, WalkStepArgs a, int in, bool wide_out, hipStream_t s)
+{
+    // runs of rows: long enough to keep a wave streaming, short enough that every wave the chip holds gets two
+    const int64_t per = a.n / ((int64_t) c->num_cus * 64);
+    a.rows_per_wave = (int) (per < 1 ? 1 : per > kWave ? kWave : per);
+    const int64_t waves = (a.n + a.rows_per_wave - 1) / a.rows_per_wave;
+    const size_t bit_bytes = (size_t) ((a.n + 31) / 32) * 4;
+    if (in == kBits && bit_bytes <= c->lds_bitmap_limit) {
+        const int64_t blocks = (waves + 15) / 16;
+        const dim3 grid((unsigned) (blocks < c->num_cus ? blocks : c->num_cus)), block(1024);
+        if (wide_out) hipLaunchKernelGGL((k_walk_step<OffT, kBits, true, true>), grid, block, bit_bytes, s, a);
+        else          hipLaunchKernelGGL((k_walk_step<OffT, kBits, false, true>), grid, block, bit_bytes, s, a);
+        return;
+    }
+    int64_t blocks = (waves + kBlock / kWave - 1) / (kBlock / kWave);
+    const int64_t cap = (int64_t) c->num_cus * 64;
+    if (blocks > cap) blocks = cap;
+    const dim3 grid((unsigned) blocks), block(kBlock);
+    switch (in * 2 + (wide_out ? 1 : 0)) {
+        case kBits * 2:       hipLaunchKernelGGL((k_walk_step<OffT, kBits, false, false>), grid, block, 0, s, a); break;
+        case kBits * 2 + 1:   hipLaunchKernelGGL((k_walk_step<OffT, kBits, true, false>), grid, block, 0, s, a); break;
+        case kNarrow * 2:     hipLaunchKernelGGL((k_walk_step<OffT, kNarrow, false, false>), grid, block, 0, s, a); break;
+        case kNarrow * 2 + 1: hipLaunchKernelGGL((k_walk_step<OffT, kNarrow, true, false>), grid, block, 0, s, a); break;
+        default:              hipLaunchKernelGGL((k_walk_step<OffT, kWide, true, false>), grid, block, 0, s, a); break;
     }
 }
 
@@ -182,21 +335,28 @@ gns_status run_walk_probability(gns_ctx* c, const int32_t* train_nodes, int64_t 
     unsigned long long* tile_sums = ws_ptr<unsigned long long>(c, L.walk_tiles);
     int32_t* tile_nz = ws_ptr<int32_t>(c, L.walk_tiles_nz);
 
-    hipError_t e = launch_fill_u64(cur, (size_t) n, 0ull, s);
+    // P^0 as a bitmap of the training nodes
+    hipError_t e = launch_fill_u64(cur, (size_t) (n + 63) / 64, 0ull, s);
     if (e == hipSuccess) e = launch_fill_u32(reinterpret_cast<uint32_t*>(&c->d_state->walk_error), 1, 0u, s);
     if (e != hipSuccess) return ctx_fail(c, GNS_EHIP, "walk init", e);
     hipLaunchKernelGGL(k_walk_seed, dim3((unsigned) ((num_train + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, train_nodes,
-                       num_train, n, 1ull << scale_log2, cur, c->d_state);
-    const bool i64 = c->graph.indptr_is_i64 != 0;
-    int64_t blocks = (n * kWalkLanes + kBlock - 1) / kBlock;
-    const int64_t cap = (int64_t) c->num_cus * 64;
-    if (blocks > cap) blocks = cap;
+                       num_train, n, reinterpret_cast<uint32_t*>(cur), c->d_state);
+    unsigned long long bound = 1ull << scale_log2;       // no entry of the current vector exceeds it
     for (int l = 0; l < c->config.num_layers; ++l) {
-        const int32_t k = c->config.fanout[l];
-        if (i64) hipLaunchKernelGGL((k_walk_step<int64_t>), dim3((unsigned) blocks), dim3(kBlock), 0, s, c->graph.indptr,
-                                    c->graph.indices, n, k, cur, nxt, c->d_state);
-        else     hipLaunchKernelGGL((k_walk_step<int32_t>), dim3((unsigned) blocks), dim3(kBlock), 0, s, c->graph.indptr,
-                                    c->graph.indices, n, k, cur, nxt, c->d_state);
+        WalkStepArgs a;
+        a.indptr = c->graph.indptr;
+        a.indices = c->graph.indices;
+        a.n = n;
+        a.k = c->config.fanout[l];
+        a.unit = 1ull << scale_log2;
+        a.cur = cur;
+        a.nxt = nxt;
+        a.st = c->d_state;
+        const int in = l == 0 ? kBits : (bound >> 32) == 0 ? kNarrow : kWide;
+        bound = bound >= kWalkLimit / 128 ? kWalkLimit : bound * (unsigned long long) (1 + a.k);
+        const bool wide_out = l == c->config.num_layers - 1 || (bound >> 32) != 0;
+        if (c->graph.indptr_is_i64) launch_walk_step<int64_t>(c, a, in, wide_out, s);
+        else                        launch_walk_step<int32_t>(c, a, in, wide_out, s);
         unsigned long long* t = cur; cur = nxt; nxt = t;
     }
     const int64_t tiles = (n + kTile - 1) / kTile;

@@ -359,6 +359,27 @@ def test_walk_probability_cache_and_weights(offsets):
         gns.close()
 
 
+@pytest.mark.parametrize("n,scale", [(1, 3), (65, 24), (1_310_000, 24), (1_310_000, 31)])
+def test_walk_probability_vector_widths(n, scale):
+    """Bit, 32-bit and 64-bit vectors of the walk steps, a training bitmap beyond LDS, runs of 64 rows, a hub row
+    over many chunks and empty rows."""
+    rng = np.random.default_rng(n)
+    hub = rng.choice(n, size=min(n, 3001), replace=False)
+    key = np.unique(np.concatenate([rng.integers(0, n * n, size=3 * n), np.int64(n // 2) * n + np.sort(hub)]))
+    ip = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(np.bincount(key // n, minlength=n), out=ip[1:])
+    ip, ix = torch.from_numpy(ip.astype(np.int32)), torch.from_numpy((key % n).astype(np.int32))
+    train = torch.from_numpy(rng.choice(n, size=max(1, n // 10), replace=False).astype(np.int32))
+    gns = GpuGns(ip, ix, None, fanouts=(3, 2, 2), policies=(U, U, C), cache_size=1, max_seeds=1,
+                 cache_probability=B.GNS_PROB_WALK)
+    try:
+        w, pre, _, _ = gns.walk_probability(train, scale)
+        w_ref, pre_ref = oracle.walk_weights(ip.numpy(), ix.numpy(), train.numpy(), [3, 2, 2], scale_log2=scale)
+        assert np.array_equal(w, w_ref) and np.array_equal(pre, pre_ref)
+    finally:
+        gns.close()
+
+
 def test_cache_nearly_all_nodes():
     # the cache takes every node that has a neighbor: the stream must run until the rarest node shows up
     ip, ix = _small(n=300, avg=6)
