@@ -1,28 +1,15 @@
 // The update step of one layer (paper Algorithm 1, h_u = g(W . (h_u, h_N(u))), GraphSAGE form of
 // Section 2.1), forward only:  out = g([h_self | h_neigh] . W + bias).  This is the one dense
-// contraction of the path, so it runs on the matrix cores: fp32 MFMA 32x32x2, fp32 accumulate.
+// contraction of the path, so it runs on the matrix cores: fp32 products, fp32 accumulate.
 //
-// Tiling: a block of 256 threads (4 waves, 2 x 2) owns a 128 x 128 tile of the output and walks K in
-// steps of 32.  The A (activations, concatenated on the fly from the two inputs) and B (weights)
-// tiles of a step are staged in LDS; lane l feeds A[m = l % 32][k = l / 32] and
-// B[k = l / 32][n = l % 32] of a 32 x 32 product.  A is kept row-major with a row stride of 33 floats,
-// B k-major: both the staging writes (a thread's four consecutive k of one row, or its float4 of one
-// k-row) and the operand reads (32 consecutive rows of one k, or 32 consecutive columns) then spread
-// over the LDS banks.  The tiles of the next step are fetched into registers while the current step
-// multiplies, and the operands of step kk + 2 are read before the products of step kk are issued.  Each
-// wave keeps 2 x 2 accumulator tiles of 32 x 32 (64 registers); element v of lane l is row
-// 8*(v/4) + 4*(l/32) + v%4, column l % 32 of its tile.
+// Two kernels: k_sage_rows keeps a slab of the weights in LDS and streams rows past it (from a few thousand rows on);
+// k_sage_split cuts k into four for everything the first has no rows or no LDS for.
 #include "gns_internal.h"
 #include "gns_device.hpp"
 
 namespace gns {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-
-constexpr int kDM = 128, kDN = 128, kDK = 32;
-constexpr int kDFetch = kDM * kDK / 4 / kBlock;  // float4 per thread and operand tile
-constexpr int kDPad = 4;                      // B rows: keeps their 16-byte alignment
-constexpr int kDAStride = kDK + 1;            // A rows: an odd stride spreads rows over the banks
 
 struct DenseArgs {
     const float* a1;
@@ -32,126 +19,298 @@ struct DenseArgs {
     float* out;
     int32_t f1, f2, hdim, relu;
     int32_t rows;
+    int32_t m_blocks, n_blocks;
     const int32_t* rows_dev;                  // if not null the row count is read here (rows is then the worst case)
 };
 
-// at least two blocks per CU: one block's fetch, staging and epilogue run under another's products
-__global__ void __launch_bounds__(kBlock, 2) k_sage_dense(DenseArgs a)
+template <int NT> struct alignas(4 * NT) FloatN { float v[NT]; };
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+constexpr int kRowsBlock = 512;               // eight waves: two per SIMD
+constexpr int kRowsTile = 16;
+
+// k_sage_rows: one block per CU holds a slab of kSlab columns of W in LDS (all K rows of it) and its waves walk tiles of
+// 16 rows, so W is read once per CU and not once per tile, and nothing but the rows themselves crosses L2 in the loop.
+// 16x16x4 products: a step is 16 k; lane l reads one float4 of row l % 16 of the activations, columns 4 * (l / 16) .. + 3
+// of the step (64-byte pieces), and for product i the weights of k-row 4 * (l / 16) + i from LDS, kVec consecutive
+// columns in one read that feeds kVec products: column c of column group h is 64 * h + kVec * (l % 16) + c of the slab.
+// Tiles of 16 rows rather than 32, because the time of the launch is that of the SIMD with the most tiles: 85,000 rows
+// x 256 columns are 5.2 tiles of 32 x 128 per SIMD (six rounds) but 10.4 of 16 x 128 (eleven, half as long each).  Two
+// waves per SIMD: one's first reads and its stores run under the other's products.
+// 85,000 rows, K = 256, 256 columns: 106 us = 105 TFLOP/s of the 137 that the fp32 products reach at the 2.1 GHz the chip
+// runs them at (128 x 128 tiles staged through LDS with two barriers per step: 128 us); what is left is the last round
+// and the slab's way into LDS.
+template <int kSlab>
+__global__ void __launch_bounds__(kRowsBlock) k_sage_rows(DenseArgs a)
 {
-    __shared__ float As[kDM][kDAStride];
-    __shared__ float Bs[kDK][kDN + kDPad];
-    const int32_t m0 = (int32_t) blockIdx.x * kDM, n0 = (int32_t) blockIdx.y * kDN;
-    if (m0 >= a.rows) return;
-    const int32_t K = a.f1 + a.f2;
-    const int tid = (int) threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-
-    float4 ra[kDFetch], rb[kDFetch];
-    constexpr int kA4 = kDK / 4;                     // float4 per A-tile row
-    auto fetch = [&](int32_t k0) {
-#pragma unroll
-        for (int j = 0; j < kDFetch; ++j) {
-            const int idx = tid + j * kBlock;
-            {   // A: 128 rows x kDK / 4 float4
-                const int row = idx / kA4, k = k0 + (idx % kA4) * 4;
-                const int64_t gr = (int64_t) m0 + row;
-                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (gr < a.rows && k < K) {              // a.rows: what the buffers hold (the device count may be smaller)
-                    const float* p = (k < a.f1) ? a.a1 + gr * a.f1 + k : a.a2 + gr * a.f2 + (k - a.f1);
-                    v = *reinterpret_cast<const float4*>(p);
-                }
-                ra[j] = v;
-            }
-            {   // B: kDK k-rows x 32 float4
-                const int kr = idx >> 5, n = n0 + (idx & 31) * 4, k = k0 + kr;
-                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (k < K && n < a.hdim) v = *reinterpret_cast<const float4*>(a.w + (int64_t) k * a.hdim + n);
-                rb[j] = v;
-            }
-        }
-    };
-    auto stage = [&]() {
-#pragma unroll
-        for (int j = 0; j < kDFetch; ++j) {
-            const int idx = tid + j * kBlock;
-            const int row = idx / kA4, kc = (idx % kA4) * 4;
-            As[row][kc + 0] = ra[j].x;
-            As[row][kc + 1] = ra[j].y;
-            As[row][kc + 2] = ra[j].z;
-            As[row][kc + 3] = ra[j].w;
-            const int kr = idx >> 5, nc = (idx & 31) * 4;
-            *reinterpret_cast<float4*>(&Bs[kr][nc]) = rb[j];
-        }
-    };
-
-    floatx16 acc[2][2];
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mt][nt][v] = 0.f;
-
-    fetch(0);
-    // the row count read on the device is needed for the early exit and the stores only, so the first
-    // fetch does not wait for it
+    constexpr int kVec = kSlab >= 64 ? 4 : kSlab / 16;
+    constexpr int kGroups = kSlab / (16 * kVec);
+    constexpr int kDepth = 4;                     // steps of activations in flight
+    typedef FloatN<kVec> BVec;
+    extern __shared__ float4 s_w16[];
+    float* s_w = reinterpret_cast<float*>(s_w16);
+    const int32_t K = a.f1 + a.f2, steps = K / 16;
+    const int32_t rows_k = (K + 15) / 16 * 16;
+    // block b runs on XCD b % 8: the slabs of one set of rows stay together there
+    const int32_t q = (int32_t) blockIdx.x / 8, xcd = (int32_t) blockIdx.x % 8;
+    const int32_t n0 = q % a.n_blocks * kSlab;
+    const int32_t strip = q / a.n_blocks * 8 + xcd;
     const int32_t rows = a.rows_dev ? *a.rows_dev : a.rows;
-    if (m0 >= rows) return;
-    stage();
+    constexpr int kRow4 = kSlab / 4;
+    constexpr int kFill = 8;                      // reads in flight per thread while the slab comes in
+    for (int32_t i0 = (int32_t) threadIdx.x; i0 < rows_k * kRow4; i0 += kRowsBlock * kFill) {
+        float4 v[kFill];
+#pragma unroll
+        for (int u = 0; u < kFill; ++u) {
+            const int32_t i = i0 + u * kRowsBlock, k = i / kRow4, col = n0 + i % kRow4 * 4;
+            v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (k < K && col < a.hdim) v[u] = *reinterpret_cast<const float4*>(a.w + (int64_t) k * a.hdim + col);
+        }
+#pragma unroll
+        for (int u = 0; u < kFill; ++u) {
+            const int32_t i = i0 + u * kRowsBlock;
+            if (i < rows_k * kRow4) s_w16[i] = v[u];
+        }
+    }
     __syncthreads();
-    const int kh = lane >> 5, l32 = lane & 31;
-    for (int32_t k0 = 0; k0 < K; k0 += kDK) {
-        const bool more = k0 + kDK < K;
-        if (more) fetch(k0 + kDK);
-        const float* arow = &As[wm * 64 + l32][kh];
-        const float* brow = &Bs[kh][wn * 64 + l32];
-        float af[2][2], bf[2][2];
+    const int wave = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
+    const int lane = (int) threadIdx.x & 63, g = lane >> 4, l16 = lane & 15;
+    float bias[kGroups][kVec];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            af[0][t] = arow[t * 32 * kDAStride];
-            bf[0][t] = brow[t * 32];
+    for (int h = 0; h < kGroups; ++h)
+#pragma unroll
+        for (int c = 0; c < kVec; ++c) {
+            const int32_t col = n0 + h * 64 + kVec * l16 + c;
+            bias[h][c] = a.bias && col < a.hdim ? a.bias[col] : 0.f;
         }
+    const float* my_w = s_w + (4 * g) * kSlab + kVec * l16;
+    const int32_t tiles = (rows + kRowsTile - 1) / kRowsTile;
+    // the strips' first waves take the first tiles: a remainder spreads over all CUs, one tile per SIMD
+    for (int32_t tile = wave * a.m_blocks + strip; tile < tiles; tile += a.m_blocks * (kRowsBlock / kWave)) {
+        const int64_t r0 = (int64_t) tile * kRowsTile;
+        const int64_t r = r0 + l16 < rows ? r0 + l16 : rows - 1;          // read, never stored
+        const float* row1 = a.a1 + r * a.f1;
+        const float* row2 = a.a2 + r * a.f2 - a.f1;
+        float4 x[kDepth];
+        auto fetch = [&](int d, int32_t step) {
+            const int32_t k = step * 16 + 4 * g;
+            x[d] = *reinterpret_cast<const float4*>((k < a.f1 ? row1 : row2) + k);
+        };
+        floatx4 acc[kGroups][kVec];
 #pragma unroll
-        for (int kk = 0; kk < kDK; kk += 2) {
-            const int cur = (kk >> 1) & 1;
-            if (kk + 2 < kDK) {
+        for (int h = 0; h < kGroups; ++h)
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    af[cur ^ 1][t] = arow[t * 32 * kDAStride + kk + 2];
-                    bf[cur ^ 1][t] = brow[(kk + 2) * (kDN + kDPad) + t * 32];
+            for (int c = 0; c < kVec; ++c) acc[h][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+        BVec w[2][kGroups];
+        auto read_w = [&](int p, int32_t step, int i) {
+#pragma unroll
+            for (int h = 0; h < kGroups; ++h)
+                w[p][h] = *reinterpret_cast<const BVec*>(my_w + (step * 16 + i) * kSlab + h * 64);
+        };
+        auto multiply = [&](const float4& v, int32_t step, int32_t next) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                read_w((i + 1) & 1, i < 3 ? step : next, (i + 1) & 3);
+                const float e = i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w;
+                __builtin_amdgcn_sched_barrier(0);                        // the read of the next weights stays ahead of these products
+#pragma unroll
+                for (int h = 0; h < kGroups; ++h)
+#pragma unroll
+                    for (int c = 0; c < kVec; ++c)
+                        acc[h][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(e, w[i & 1][h].v[c], acc[h][c], 0, 0, 0);
+            }
+        };
+        read_w(0, 0, 0);
+        // steps past the last re-read it (and the weights' first row), so that no read of the loop sits in a branch
+        auto clamped = [&](int32_t step) { return step < steps ? step : steps - 1; };
+        int32_t s = 0;
+        if (steps > 0) {
+#pragma unroll
+            for (int d = 0; d < kDepth; ++d) fetch(d, clamped(d));
+            for (; s + kDepth <= steps; s += kDepth) {
+#pragma unroll
+                for (int d = 0; d < kDepth; ++d) {
+                    multiply(x[d], s + d, (s + d + 1) * 16 < rows_k ? s + d + 1 : 0);
+                    fetch(d, clamped(s + d + kDepth));
                 }
             }
-            __builtin_amdgcn_sched_barrier(0);          // the reads above stay ahead of the products below
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[cur][0], bf[cur][0], acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[cur][0], bf[cur][1], acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[cur][1], bf[cur][0], acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[cur][1], bf[cur][1], acc[1][1], 0, 0, 0);
+#pragma unroll
+            for (int d = 0; d < kDepth; ++d)
+                if (s + d < steps) multiply(x[d], s + d, (s + d + 1) * 16 < rows_k ? s + d + 1 : 0);
         }
-        __syncthreads();
-        if (more) {
-            stage();
-            __syncthreads();
+        if (K % 16) {                                                     // lanes past K multiply zeros (and W's padding rows are zero)
+            const bool none = steps * 16 + 4 * g >= K;
+            const int32_t k = none ? 0 : steps * 16 + 4 * g;
+            float4 v = *reinterpret_cast<const float4*>((k < a.f1 ? row1 : row2) + k);
+            if (none) v = make_float4(0.f, 0.f, 0.f, 0.f);
+            multiply(v, steps, 0);
+        }
+#pragma unroll
+        for (int h = 0; h < kGroups; ++h) {
+            const int32_t col = n0 + h * 64 + kVec * l16;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                BVec o;
+#pragma unroll
+                for (int c = 0; c < kVec; ++c) {
+                    float y = acc[h][c][v] + bias[h][c];
+                    if (a.relu) y = fmaxf(y, 0.f);
+                    o.v[c] = y;
+                }
+                const int64_t row = r0 + 4 * g + v;
+                if (row < rows && col < a.hdim) *reinterpret_cast<BVec*>(a.out + row * a.hdim + col) = o;
+            }
         }
     }
+}
 
+// k_sage_split: a block of four waves owns 32 rows x 32 * NT columns and cuts k in four (the waves' sums meet in LDS), so
+// that a thousand rows still occupy every CU and no wave's chain of products is long.  32x32x2 products, k in steps of
+// 32: A comes in as whole 128-byte lines (eight lanes per row) and is turned through a piece of LDS of the wave's own;
+// lane l multiplies row l % 32, columns 16 * (l / 32) .. + 15 of the step, with the NT consecutive weights of columns
+// NT * (l % 32) .. of the same k-rows, which come straight from L2.  No barrier stands between the reads and the products.
+// 1024 rows, K = 512, 256 columns: 8 us (128 x 128 tiles: 49 us on 16 of the CUs).
+// Element v of lane l of an accumulator is row 8*(v/4) + 4*(l/32) + v%4.
+template <int NT>
+__global__ void __launch_bounds__(kBlock) k_sage_split(DenseArgs a)
+{
+    constexpr int WK = kBlock / kWave;
+    typedef FloatN<NT> BVec;
+    __shared__ float s_a[WK][32][36];         // rows of 32, padded: 16-byte reads of eight rows spread over all banks
+    __shared__ float s_part[WK][NT * 16][kWave];
+    const int32_t q = (int32_t) blockIdx.x / 8, xcd = (int32_t) blockIdx.x % 8;      // as in k_sage_rows
+    const int32_t mb = q / a.n_blocks * 8 + xcd, nb = q % a.n_blocks;
+    const int32_t rows = a.rows_dev ? *a.rows_dev : a.rows;
+    const int wave = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
+    const int lane = (int) threadIdx.x & 63, kh = lane >> 5, l32 = lane & 31;
+    const int64_t m0 = (int64_t) mb * 32;
+    if (m0 >= rows) return;
+    const int32_t col = nb * (NT * 32) + NT * l32;                     // first of this lane's NT columns
+    const int32_t colc = col < a.hdim ? col : 0;
+    const int32_t K = a.f1 + a.f2;
+    const float* base1 = a.a1 + m0 * a.f1;
+    const float* base2 = a.a2 + m0 * a.f2;
+    const int32_t last_row = (int32_t) (rows - 1 - m0 < 31 ? rows - 1 - m0 : 31);
+    const int32_t steps = K >> 5;
+    const int32_t s0 = steps * wave / WK, s1 = steps * (wave + 1) / WK;
+
+    float4 ga[4], ra[4];
+    BVec rb[4][4];
+    auto a_at = [&](int32_t row, int32_t k) -> float4 {
+        const int32_t r = row < last_row ? row : last_row;              // read, never stored
+        const bool self = k < a.f1;
+        return *reinterpret_cast<const float4*>((self ? base1 : base2 - a.f1) + ((int64_t) r * (self ? a.f1 : a.f2) + k));
+    };
+    auto fetch_a = [&](int32_t step) {
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt) {
+        for (int j = 0; j < 4; ++j) ga[j] = a_at(j * 8 + (lane >> 3), step * 32 + (lane & 7) * 4);
+    };
+    auto stage_a = [&]() {
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            const int32_t col = n0 + wn * 64 + nt * 32 + l32;
-            const float b = (a.bias && col < a.hdim) ? a.bias[col] : 0.f;
+        for (int j = 0; j < 4; ++j) *reinterpret_cast<float4*>(&s_a[wave][j * 8 + (lane >> 3)][(lane & 7) * 4]) = ga[j];
+    };
+    auto fetch_b = [&](int c, int32_t k) {
+        const float* w = a.w + (int64_t) k * a.hdim + colc;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int64_t row = (int64_t) m0 + wm * 64 + mt * 32 + 8 * (v >> 2) + 4 * kh + (v & 3);
-                if (row < rows && col < a.hdim) {
-                    float x = acc[mt][nt][v] + b;
-                    if (a.relu) x = fmaxf(x, 0.f);
-                    a.out[row * a.hdim + col] = x;
-                }
+        for (int i = 0; i < 4; ++i) rb[c][i] = *reinterpret_cast<const BVec*>(w + (int64_t) i * a.hdim);
+    };
+    floatx16 acc[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[nt][v] = 0.f;
+    auto multiply = [&](const float4& x4, int c) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float x = i == 0 ? x4.x : i == 1 ? x4.y : i == 2 ? x4.z : x4.w;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                acc[nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(x, rb[c][i].v[nt], acc[nt], 0, 0, 0);
+        }
+    };
+    if (s0 < s1) {
+        fetch_a(s0);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) fetch_b(c, s0 * 32 + kh * 16 + c * 4);
+        stage_a();
+        for (int32_t s = s0; s < s1; ++s) {
+            // steps past the last re-read it, so that no read of the loop sits in a branch
+            const int32_t next = s + 1 < s1 ? s + 1 : s1 - 1;
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int c = 0; c < 4; ++c) ra[c] = *reinterpret_cast<const float4*>(&s_a[wave][l32][kh * 16 + c * 4]);
+            fetch_a(next);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                multiply(ra[c], c);
+                fetch_b(c, next * 32 + kh * 16 + c * 4);
+                __builtin_amdgcn_sched_barrier(0);
             }
+            __builtin_amdgcn_wave_barrier();
+            stage_a();
         }
     }
+    if (wave == WK - 1) {
+        // what K leaves beyond a multiple of 32: eight k at a time, then four with lanes 32-63 at zero
+        for (int32_t k = steps * 32; k < K; k += 8) {
+            const bool none = k + kh * 4 >= K;
+            const int32_t kc = none ? k : k + kh * 4;
+            ra[0] = a_at(l32, kc);
+            fetch_b(0, kc);
+            if (none) {
+                ra[0] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) rb[0][i].v[t] = 0.f;
+            }
+            multiply(ra[0], 0);
+        }
+    }
+    // the four sums of an element meet in LDS; every wave finishes a quarter of the elements
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s_part[wave][v * NT + nt][lane] = acc[nt][v];
+    __syncthreads();
+    float bias[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) bias[nt] = a.bias ? a.bias[colc + nt] : 0.f;
+#pragma unroll
+    for (int e0 = 0; e0 < 16 / WK; ++e0) {
+        const int v = wave * (16 / WK) + e0;
+        BVec o;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            float x = 0.f;
+#pragma unroll
+            for (int p = 0; p < WK; ++p) x += s_part[p][v * NT + nt][lane];
+            x += bias[nt];
+            if (a.relu) x = fmaxf(x, 0.f);
+            o.v[nt] = x;
+        }
+        const int64_t row = m0 + 8 * (v >> 2) + 4 * kh + (v & 3);
+        if (row < rows && col < a.hdim) *reinterpret_cast<BVec*>(a.out + row * a.hdim + col) = o;
+    }
+}
+
+template <int kSlab>
+static void launch_rows(const gns_ctx* c, DenseArgs a, hipStream_t s)
+{
+    a.n_blocks = (a.hdim + kSlab - 1) / kSlab;
+    a.m_blocks = c->num_cus / 8 / a.n_blocks * 8;              // strips of rows
+    const size_t lds = (size_t) ((a.f1 + a.f2 + 15) / 16 * 16) * kSlab * 4;
+    hipLaunchKernelGGL(k_sage_rows<kSlab>, dim3((unsigned) (a.m_blocks * a.n_blocks)), dim3(kRowsBlock), lds, s, a);
+}
+
+template <int NT>
+static void launch_split(DenseArgs a, hipStream_t s)
+{
+    a.m_blocks = (a.rows + 31) / 32;
+    a.n_blocks = (a.hdim + NT * 32 - 1) / (NT * 32);
+    hipLaunchKernelGGL(k_sage_split<NT>, dim3((unsigned) ((a.m_blocks + 7) / 8 * 8 * a.n_blocks)), dim3(kBlock), 0, s, a);
 }
 
 hipError_t launch_sage_dense(gns_ctx* c, const float* h_self, int32_t f1, const float* h_neigh, int32_t f2,
@@ -170,8 +329,23 @@ hipError_t launch_sage_dense(gns_ctx* c, const float* h_self, int32_t f1, const 
         rows = (int32_t) c->lay.rows[layer];
     }
     a.rows = rows;
-    const dim3 grid((unsigned) ((rows + kDM - 1) / kDM), (unsigned) ((hdim + kDN - 1) / kDN));
-    hipLaunchKernelGGL(k_sage_dense, grid, dim3(kBlock), 0, s, a);
+    // The widest slab whose K rows fit LDS (no wider than the output needs).  k_sage_rows has one tile per SIMD at
+    // num_cus * 4 tiles; below three quarters of that, and where no slab fits, the split kernel is ahead (256 columns,
+    // K = 512: 13.0 against 8.2 us at 1024 rows, 14.4 against 15.8 us at 4000).
+    const int32_t K = f1 + f2;
+    const size_t k_bytes = (size_t) ((K + 15) / 16 * 16) * 4;
+    const int32_t want = hdim > 64 ? 128 : hdim > 32 ? 64 : 32;
+    int32_t slab = want;
+    while (slab >= 32 && k_bytes * slab > c->lds_bitmap_limit) slab /= 2;
+    const int64_t tiles = slab >= 32 ? ((int64_t) (rows + kRowsTile - 1) / kRowsTile) * ((hdim + slab - 1) / slab) : 0;
+    if (tiles >= (int64_t) c->num_cus * 3 && (hdim + slab - 1) / slab <= c->num_cus / 8) {
+        if (slab == 128)     launch_rows<128>(c, a, s);
+        else if (slab == 64) launch_rows<64>(c, a, s);
+        else                 launch_rows<32>(c, a, s);
+    } else {
+        if (hdim <= 32) launch_split<1>(a, s);
+        else            launch_split<2>(a, s);
+    }
     return hipGetLastError();
 }
 

@@ -881,6 +881,13 @@ def test_sage_dense_update_step(rows, f1, f2, hdim, relu, use_bias):
         gns.close()
 
 
+@pytest.mark.parametrize("rows,f1,f2,hdim", [(12_289, 64, 68, 128), (6_150, 36, 220, 200), (12_300, 8, 12, 64), (12_290, 4, 4, 20),
+                                             (6_145, 256, 256, 128), (3_073, 300, 400, 256), (40, 700, 600, 36), (33, 4, 28, 4)])
+def test_sage_dense_slabs_and_split(rows, f1, f2, hdim):
+    """Weight slabs of every width (edges of tiles, k remainders, columns past the last) and the split of k."""
+    test_sage_dense_update_step(rows, f1, f2, hdim, rows % 2 == 0, True)
+
+
 def _group_setup(gns, count):
     """count contexts (the created one and forks) with their own block buffers, feature buffers and a GroupCall."""
     ctxs, keep = [gns.ctx], []
