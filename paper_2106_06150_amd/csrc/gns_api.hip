@@ -157,19 +157,20 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     L.cache_block_begin = off;
     L.cache_bitmap = take((size_t) L.words * 8);
     L.cache_prefix = take((size_t) L.words * 4);
-    // A cache bitmap too big for LDS gets a coarse companion that does fit: one bit per 2^shift ids.  With a
-    // cache of about 1 % of the nodes it answers "not cached" for most entries without leaving the CU as long as
-    // the groups stay small.
+    // A cache bitmap too big for LDS gets a coarse companion that does fit: one bit per 2^shift ids.  With a cache of
+    // about 1 % of the nodes it answers "not cached" without leaving the CU for most entries while the groups are small,
+    // and for a good part of them up to groups of a few hundred; what passes costs one request to the exact bitmap, and
+    // the rate of those requests bounds the pass.  (40 M nodes, 400 M entries: one bit per 32 ids in LDS passes half of
+    // the entries, 1.33 ms; one bit per 16 ids in L2, a request for every entry and for 46 % of them a second, 2.67 ms.)
     L.coarse_shift = 0;
     L.coarse_words = 0;
     L.coarse_bitmap = 0;
     if (uses_cache && (size_t) L.words * 8 > kLdsBitmapBytes) {
         int sh = 1;
-        while (sh <= 4 && (size_t) (((n >> sh) + 63) / 64 + 1) * 8 > kLdsBitmapBytes) ++sh;
-        // Too big for LDS even at one bit per 16 ids: the coarse bitmap then stays in global memory, where it
-        // is small enough for every XCD's L2 (n / 128 bytes at one bit per 16 ids), and still spares most entries
-        // the read of the exact bitmap, which costs a 64-byte fetch over the fabric each time.
-        if (sh > 4) {
+        while (sh <= 9 && (size_t) (((n >> sh) + 63) / 64 + 1) * 8 > kLdsBitmapBytes) ++sh;
+        // Too big for LDS even at one bit per 512 ids (more than 650 M nodes): the coarse bitmap then stays in global
+        // memory at one bit per 16 ids, where it spares most entries the read of the exact bitmap.
+        if (sh > 9) {
             sh = 4;
             if (const char* e = getenv("GNS_COARSE_SHIFT")) { const int v = atoi(e); if (v >= 1 && v <= 6) sh = v; }
         }

@@ -290,23 +290,24 @@ __global__ void __launch_bounds__(kBlock) k_cache_pc(const int32_t* cache_nodes,
 }
 
 // Coarse companion of the cache bitmap: bit g of the result is set iff some node of
-// [g << shift, (g + 1) << shift) is cached.  One thread per 64-bit coarse word.
+// [g << shift, (g + 1) << shift) is cached.  One lane per coarse bit; a wave's ballot is a coarse word.
 __global__ void __launch_bounds__(kBlock) k_cache_coarse(const uint64_t* bitmap, int64_t words, int shift,
                                                          uint64_t* coarse, int64_t coarse_words)
 {
-    const int64_t cw = (int64_t) blockIdx.x * kBlock + threadIdx.x;
+    const int64_t cw = (int64_t) blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6);
     if (cw >= coarse_words) return;
-    const int fine_per_coarse = 1 << shift;                    // fine words folded into one coarse word
-    const int groups_per_fine = 64 >> shift;                   // coarse bits one fine word yields
-    const uint64_t group_mask = (shift == 6) ? ~0ull : ((1ull << (1 << shift)) - 1ull);
-    uint64_t out = 0;
-    for (int f = 0; f < fine_per_coarse; ++f) {
-        const int64_t w = cw * fine_per_coarse + f;
-        const uint64_t x = (w < words) ? bitmap[w] : 0ull;
-        for (int g = 0; g < groups_per_fine; ++g)
-            if ((x >> (g << shift)) & group_mask) out |= 1ull << (f * groups_per_fine + g);
+    const int64_t g = cw * kWave + lane_id();
+    bool any = false;
+    if (shift >= 6) {
+        const int64_t first = g << (shift - 6), last = (g + 1) << (shift - 6);
+        for (int64_t w = first; w < last && w < words; ++w) any = any || bitmap[w] != 0ull;
+    } else {
+        const int64_t w = g >> (6 - shift);
+        const uint64_t mask = (1ull << (1 << shift)) - 1ull;
+        any = w < words && ((bitmap[w] >> ((g << shift) & 63)) & mask) != 0ull;
     }
-    coarse[cw] = out;
+    const uint64_t out = __ballot(any);
+    if (lane_id() == 0) coarse[cw] = out;
 }
 
 // ---------------------------------------------------------------------------
@@ -474,7 +475,7 @@ gns_status run_sample_cache(gns_ctx* c, uint64_t seed, uint64_t epoch, bool wait
         GNS_HIP_TRY(hipGetLastError(), "cache weight table launch");
     }
     if (L.coarse_shift > 0) {
-        const unsigned cb = (unsigned) ((L.coarse_words + kBlock - 1) / kBlock);
+        const unsigned cb = (unsigned) ((L.coarse_words + kBlock / kWave - 1) / (kBlock / kWave));
         hipLaunchKernelGGL(k_cache_coarse, dim3(cb), dim3(kBlock), 0, s, bitmap, (int64_t) L.words, (int) L.coarse_shift,
                            cache_ptr<uint64_t>(c, L.coarse_bitmap, gen), (int64_t) L.coarse_words);
         GNS_HIP_TRY(hipGetLastError(), "coarse bitmap launch");
