@@ -52,9 +52,9 @@
  *        cache bitmap of graphs whose bitmap does not fit LDS
  *      GNS_NO_COARSE_L2=1  flag pass of such graphs without the coarse bitmap
  *      GNS_FLAG_BLOCKS_PER_CU=<n>  grid of that flag pass (default 2)
- *      GNS_LANE_ROWS_MIN=<n>  UNIFORM layers use the one-row-per-lane sampler
- *        from n rows per launch on (default 262144)
- *      GNS_NO_LANE_SAMPLER=1  never use the one-row-per-lane sampler
+ *      GNS_UNION_SPINS=<n>  how often a block of the union step polls for another
+ *        block's count before it counts that part of the bitmap itself
+ *        (default 256)
  *      GNS_NO_GRAPH=1  enqueue a mini-batch's kernels one by one instead of
  *        replaying a captured HIP graph
  */
@@ -312,14 +312,15 @@ gns_status gns_aggregate_group(gns_ctx* const* ctxs, int32_t count, const gns_bl
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): gns_sample_blocks with the per-batch scratch (device
- * counters, frontier mark bitmap, batch hash map, row extents, sampler scratch, scan partials)
+ * counters, frontier mark bitmaps, node table, row extents, sampler scratch, scan partials)
  * in a fixed array of GNS_STATIC_SCRATCH_BYTES bytes that the library holds on every GPU it is
  * loaded on, instead of in the context's workspace.  Same arguments, same results, same errors
  * as gns_sample_blocks; ctx may be the context made by gns_create or any of its forks (the
  * graph, config and current cache are theirs).  The call allocates nothing: no hipMalloc, no
  * host allocation, no HIP graph (the kernels are launched one by one on hip_stream, which is
  * synchronised before the call returns).  GNS_ECAPACITY if the per-batch scratch of this graph
- * and config (what gns_fork_workspace_bytes reports) exceeds the array: nothing is launched.
+ * and config (what gns_fork_workspace_bytes reports, without the 4 bytes per node of the node table, which
+ * large graphs keep in the context's workspace) exceeds the array: nothing is launched.
  * All calls on one GPU share that GPU's array, whatever their context: it is re-initialised at
  * the start of every call, and calls that overlap on one GPU race.  gns_gather_features and
  * gns_aggregate after it take the host counts the call filled in (the device-count

@@ -82,9 +82,13 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
         if (L.edges[i] >= (int64_t) 1 << 31) GNS_BAD("a layer's worst-case edge count exceeds 2^31");
     }
     L.row_tiles = (L.max_rows + kTile - 1) / kTile;
-    // the batch hash map addresses its slots with 32 bits at a load factor of at most 1/2
-    if (2 * (uint64_t) L.rows[cfg->num_layers] > (uint64_t) 1 << 31) GNS_BAD("worst-case frontier too large for the batch hash map (more than 2^30 nodes)");
-    L.hash_cap = pow2_at_least(2 * (uint64_t) L.rows[cfg->num_layers]);
+    // an entry of the node table holds a local id and a stamp of at least two bits
+    if (L.rows[cfg->num_layers] > (int64_t) 1 << 30) GNS_BAD("worst-case frontier too large for the node table (more than 2^30 nodes)");
+    L.table_shift = 1;
+    while (((int64_t) 1 << L.table_shift) < L.rows[cfg->num_layers]) ++L.table_shift;
+    L.max_stamp = (1u << (32 - L.table_shift)) - 1u;
+    for (int i = 0; i < cfg->num_layers; ++i)
+        if (!direct_layer(*cfg, i)) L.lists_hubs = true;
 
     L.draw_chunk = C;
     if (L.draw_chunk < 65536) L.draw_chunk = 65536;
@@ -105,22 +109,19 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
         L.summary_words = L.words >= min_words ? (L.words + 63) / 64 : 0;
         L.mark_summary = take((size_t) (L.summary_words > 0 ? L.summary_words : 1) * 8);
     }
+    L.seed_mark = take((size_t) L.words * 8);
     L.seed_copy = take((size_t) cfg->max_seeds * 4);
     L.row_ext = take((size_t) L.rows[cfg->num_layers] * 16);
-    L.hub_rows = take((size_t) L.rows[cfg->num_layers] * 4);
-    L.slot_list[0] = take((size_t) L.rows[cfg->num_layers] * 4);
-    L.slot_list[1] = take((size_t) L.rows[cfg->num_layers] * 4);
-    L.hash_slots[0] = take((size_t) L.hash_cap * 8);
-    L.hash_slots[1] = take((size_t) L.hash_cap * 8);
+    L.hub_rows = take(L.lists_hubs ? (size_t) L.rows[cfg->num_layers] * 4 : 0);
     for (int par = 0; par < 2; ++par) {
         L.s_nbr[par] = take((size_t) L.max_edges * 4);
         L.s_w[par] = take((size_t) L.max_edges * 4);
         L.s_cnt[par] = take((size_t) L.max_rows * 4);
     }
-    L.sums_rows = take((size_t) (L.row_tiles + 1) * 4);
+    L.sums_rows = take((size_t) (L.max_rows / (kBlock / kWave) + 1) * 4);
     const int64_t word_or_draw_tiles = L.word_tiles > L.draw_tiles ? L.word_tiles : L.draw_tiles;
     L.sums_words = take((size_t) (word_or_draw_tiles + 1) * 4);
-    L.sums_marks = take((size_t) (L.mark_tiles + 1) * 4);
+    L.tile_sums = take((size_t) L.mark_tiles * 8);
     L.sums_plan = take((size_t) (L.max_rows / kBlock + 2) * 4);
     if (uses_cache) {
         // a dst row of deg entries touches at most deg/64 + 2 aligned chunks; dst rows are distinct
@@ -130,8 +131,11 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
         L.plan_g0 = take((size_t) L.max_rows * 4);
         L.plan_desc = take((size_t) L.max_chunks * 4);
     }
+    // last of the per-batch sections: gns_sample_blocks_static keeps this one elsewhere on large graphs
+    L.table = take((size_t) n * 4);
     // shared: the cache and everything that is a pure function of (graph, cache)
     L.shared_begin = off;
+    if (L.shared_begin > GNS_STATIC_SCRATCH_BYTES && L.table <= GNS_STATIC_SCRATCH_BYTES) L.static_table = take((size_t) n * 4);
     if (uses_cache) {
         L.draw_keys = take((size_t) L.draw_hash_cap * 4);
         L.draw_vals = take((size_t) L.draw_hash_cap * 4);
@@ -148,8 +152,7 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     }
     if (uses_cache && cfg->flag_mode == GNS_FLAGS_PER_CACHE) {
         if (g->num_entries >= (int64_t) 1 << 32) GNS_BAD("GNS_FLAGS_PER_CACHE counts cached entries in 32 bits: num_entries must be < 2^32");
-        L.chunk_tiles = (g->num_entries / 64 + 1 + kTile - 1) / kTile;
-        L.sums_chunks = take((size_t) (L.chunk_tiles + 1) * 4);
+        L.s_tile_shift = induced_tile_shift(g->num_entries);
     }
     // The cache block: everything a cache draw writes and the mini-batches read.  There are two copies
     // (generations): a draw fills the one that is not in use, so it can run while batches that were
@@ -181,11 +184,12 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     L.cache_nodes = take((size_t) (C > 0 ? C : 1) * 4);
     L.cache_feat = take((size_t) (C > 0 ? C : 1) * (size_t) (g->feat_dim > 0 ? g->feat_dim : 1) * 4);
     if (uses_cache) {
-        L.edge_flags = take((size_t) (g->num_entries / 64 + 1) * 8);
+        if (cfg->flag_mode == GNS_FLAGS_PER_BATCH) L.edge_flags = take((size_t) (g->num_entries / 64 + 1) * 8);
         L.node_pc = take((size_t) n * 4);
         if (cfg->flag_mode == GNS_FLAGS_PER_CACHE) {
-            L.srec = take((size_t) (g->num_entries / 64 + 2) * 16);
+            L.srec = take((size_t) (g->num_entries / 64 + 1) * 16);
             L.s_nodes = take((size_t) g->num_entries * 4);
+            L.s_count = take((size_t) ((g->num_entries >> L.s_tile_shift) + 1) * 4);
         }
     }
     L.cache_block_bytes = off - L.cache_block_begin;
@@ -214,14 +218,16 @@ gns_status enqueue_batch(const Group& g, const BeginDyn& d, hipStream_t s)
 {
     gns_ctx* c = g.ctx[0];
     const int nl = c->config.num_layers;
-    hipError_t e = launch_batch_begin(g, d, s);
+    // the first layer's sampler enters the seeds itself where nothing runs in front of it
+    const bool fused = first_layer_enters_seeds(c->config);
+    hipError_t e = fused ? hipSuccess : launch_batch_begin(g, d, s);
     if (e != hipSuccess) return ctx_fail(c, GNS_EHIP, "batch begin", e);
     // the batch's kernels read the seeds from the context's own copy (made by the first kernel), so
     // the captured launch sequence does not depend on where the caller keeps them
     for (int i = 0; i < nl; ++i) {
         {
             StageTimer t(c, GNS_STAGE_SAMPLE + i, s);
-            e = launch_sample_layer(g, i, s);
+            e = i == 0 && fused ? launch_first_layer(g, d, s) : launch_sample_layer(g, i, s);
         }
         if (e != hipSuccess) return ctx_fail(c, GNS_EHIP, "sample layer", e);
         {
@@ -234,8 +240,22 @@ gns_status enqueue_batch(const Group& g, const BeginDyn& d, hipStream_t s)
     return GNS_OK;
 }
 
-// The first kernel's per-call arguments: seeds, Philox keys, batch ids, and for every batch which hash map
-// it uses and which copy of the cache structures it reads (the current one).
+hipError_t next_stamps(const Group& g, hipStream_t s)
+{
+    for (int b = 0; b < g.count; ++b) {
+        gns_ctx* c = g.ctx[b];
+        if (c->stamp == c->lay.max_stamp) {
+            const hipError_t e = launch_fill_u32(ws_ptr_table(c), (size_t) c->graph.num_nodes, 0u, s);
+            if (e != hipSuccess) return e;
+            c->stamp = 0;
+        }
+        c->stamp += 1;
+    }
+    return hipSuccess;
+}
+
+// The first kernel's per-call arguments: seeds, Philox keys, batch ids, and for every batch which stamp its node table
+// entries carry and which copy of the cache structures it reads (the current one).
 void fill_begin_dyn(const Group& g, const uint64_t* seeds, const int32_t* const* seeds_dev, const int32_t* num_seeds,
                     BeginDyn* out)
 {
@@ -247,7 +267,7 @@ void fill_begin_dyn(const Group& g, const uint64_t* seeds, const int32_t* const*
         out->key0[b] = (uint32_t) seeds[b];
         out->key1[b] = (uint32_t) (seeds[b] >> 32);
         out->batch_id[b] = c->batch_id + 1;
-        out->parity[b] = c->hash_parity;
+        out->stamp[b] = c->stamp;
         out->cache_gen[b] = active_gen(c);
     }
 }
@@ -288,6 +308,16 @@ static hipError_t events_create(gns_ctx* c)
             e = hipEventCreateWithFlags(&c->gen_event[g][i], hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ready_event[0], hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ready_event[1], hipEventDisableTiming);
+    return e;
+}
+
+// The address under which kernels write the context's pinned host mirror.
+static hipError_t host_mirror_setup(gns_ctx* c)
+{
+    memset(c->h_state, 0, sizeof(DeviceState));
+    void* p = nullptr;
+    const hipError_t e = hipHostGetDevicePointer(&p, c->h_state, 0);
+    c->h_state_dev = static_cast<DeviceState*>(p);
     return e;
 }
 
@@ -350,21 +380,10 @@ static gns_status launch_batch_graph(const Group& grp, const BeginDyn& dyn, hipS
         if (e != hipSuccess) { graph_release(g); return ctx_fail(c, GNS_EHIP, "end capture", e); }
         e = hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0);
         if (e != hipSuccess) { graph_release(g); return ctx_fail(c, GNS_EHIP, "graph instantiate", e); }
-        // find the first kernel's node
-        size_t count = 0;
-        e = hipGraphGetNodes(g.graph, nullptr, &count);
-        if (e != hipSuccess || count == 0 || count > 256) { graph_release(g); return ctx_fail(c, GNS_EHIP, "graph nodes", e); }
-        hipGraphNode_t nodes[256];
-        e = hipGraphGetNodes(g.graph, nodes, &count);
-        if (e != hipSuccess) { graph_release(g); return ctx_fail(c, GNS_EHIP, "graph nodes", e); }
-        for (size_t i = 0; i < count && !g.first; ++i) {
-            hipGraphNodeType type;
-            if (hipGraphNodeGetType(nodes[i], &type) != hipSuccess || type != hipGraphNodeTypeKernel) continue;
-            hipKernelNodeParams kp;
-            if (hipGraphKernelNodeGetParams(nodes[i], &kp) != hipSuccess) continue;
-            if (kp.func == batch_first_kernel()) g.first = nodes[i];
-        }
-        if (!g.first) { graph_release(g); return ctx_fail(c, GNS_EHIP, "first kernel node not found in the captured graph"); }
+        // the sequence is a chain: its one root is the first kernel, whose arguments change from replay to replay
+        size_t count = 1;
+        e = hipGraphGetRootNodes(g.graph, &g.first, &count);
+        if (e != hipSuccess || count != 1) { graph_release(g); return ctx_fail(c, GNS_EHIP, "first kernel of the captured graph", e); }
         g.count = grp.count;
         for (int b = 0; b < grp.count; ++b) {
             g.ctx[b] = grp.ctx[b];
@@ -373,9 +392,8 @@ static gns_status launch_batch_graph(const Group& grp, const BeginDyn& dyn, hipS
         // the first kernel's fixed argument block: the same for every replay of this graph
         static_assert(sizeof(LayerArgs) <= sizeof(g.args.fixed), "BeginArgsHost::fixed too small");
         static_assert(sizeof(BeginDyn) <= sizeof(g.args.dyn), "BeginArgsHost::dyn too small");
-        LayerArgs* fixed = reinterpret_cast<LayerArgs*>(g.args.fixed);
-        fill_group_args(grp, fixed);
-        fill_finish_template(c, 0, &fixed->f);
+        fill_first_args(grp, reinterpret_cast<LayerArgs*>(g.args.fixed));
+        g.args.rows_per_wave = rows_per_sum(grp, 0) / (kBlock / kWave);
         g.valid = true;
         hit = &g;
     }
@@ -388,6 +406,7 @@ static gns_status launch_batch_graph(const Group& grp, const BeginDyn& dyn, hipS
     memcpy(g.args.dyn, &dyn, sizeof(dyn));
     g.arg_ptrs[0] = g.args.fixed;
     g.arg_ptrs[1] = g.args.dyn;
+    g.arg_ptrs[2] = &g.args.rows_per_wave;
     kp.kernelParams = g.arg_ptrs;
     kp.extra = nullptr;
     e = hipGraphExecKernelNodeSetParams(g.exec, g.first, &kp);
@@ -398,8 +417,8 @@ static gns_status launch_batch_graph(const Group& grp, const BeginDyn& dyn, hipS
 }
 
 namespace gns {
-// What a context's per-batch scratch must hold before its first mini-batch: zeroed device state, an empty
-// frontier mark bitmap, two empty hash maps.  Enqueue only.
+// What a context's per-batch scratch must hold before its first mini-batch: zeroed device state and tile
+// sums, empty mark bitmaps, a node table without stamps.  Enqueue only.
 hipError_t init_batch_scratch(gns_ctx* c, hipStream_t s)
 {
     const Layout& L = c->lay;
@@ -407,8 +426,10 @@ hipError_t init_batch_scratch(gns_ctx* c, hipStream_t s)
     if (e == hipSuccess) e = launch_fill_u64(ws_ptr<unsigned long long>(c, L.mark_bitmap), (size_t) L.words, 0ull, s);
     if (e == hipSuccess && L.summary_words > 0)
         e = launch_fill_u64(ws_ptr<unsigned long long>(c, L.mark_summary), (size_t) L.summary_words, 0ull, s);
-    for (int par = 0; par < 2 && e == hipSuccess; ++par)
-        e = launch_fill_u64(ws_ptr<unsigned long long>(c, L.hash_slots[par]), (size_t) L.hash_cap, ~0ull, s);
+    if (e == hipSuccess) e = launch_fill_u64(ws_ptr<unsigned long long>(c, L.seed_mark), (size_t) L.words, 0ull, s);
+    if (e == hipSuccess) e = launch_fill_u64(ws_ptr<unsigned long long>(c, L.tile_sums), (size_t) L.mark_tiles, 0ull, s);
+    if (e == hipSuccess) e = launch_fill_u32(ws_ptr_table(c), (size_t) c->graph.num_nodes, 0u, s);
+    c->stamp = 0;
     return e;
 }
 
@@ -433,7 +454,7 @@ gns_status make_child(gns_ctx* root, void* workspace, bool with_capture_stream, 
     c->err[0] = 0;
     c->bg = nullptr;
     c->graph_clock = 0;
-    c->hash_parity = 0;
+    c->stamp = 0;
     c->batch_id = 0;
     c->bad_reported = 0;
     c->cap_stream = nullptr;
@@ -452,6 +473,7 @@ gns_status make_child(gns_ctx* root, void* workspace, bool with_capture_stream, 
         e = hipHostMalloc(reinterpret_cast<void**>(&c->h_state), sizeof(DeviceState), hipHostMallocDefault);
         if (e != hipSuccess) c->h_state = nullptr;
     }
+    if (e == hipSuccess) e = host_mirror_setup(c);
     if (e == hipSuccess) e = events_create(c);
     if (e != hipSuccess) {
         free(c->bg);
@@ -541,8 +563,11 @@ gns_status gns_create(gns_ctx** out_ctx, const gns_graph* graph, const gns_confi
     c->lds_bitmap_limit = prop.sharedMemPerBlock >= kLdsBitmapBytes + 1024 ? kLdsBitmapBytes : 0;
     e = hipHostMalloc(reinterpret_cast<void**>(&c->h_state), sizeof(DeviceState), hipHostMallocDefault);
     if (e != hipSuccess) { c->h_state = nullptr; return bail(GNS_EHIP, "hipHostMalloc", e); }
+    e = host_mirror_setup(c);
+    if (e != hipSuccess) return bail(GNS_EHIP, "hipHostGetDevicePointer", e);
     e = events_create(c);
     if (e != hipSuccess) return bail(GNS_EHIP, "hipEventCreate", e);
+    c->union_spins = getenv("GNS_UNION_SPINS") ? atoi(getenv("GNS_UNION_SPINS")) : 256;
     c->family[0] = c;
     c->family_count = 1;
     if (!getenv("GNS_NO_GRAPH")) {
@@ -835,6 +860,8 @@ gns_status gns_sample_blocks_group(gns_ctx* const* ctxs, int32_t count, const ui
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     st = group_before_cache_readers(ctxs, count, s);
     if (st != GNS_OK) return st;
+    const hipError_t es = next_stamps(g, s);
+    if (es != hipSuccess) return ctx_fail(lead, GNS_EHIP, "node table", es);
     BeginDyn dyn;
     fill_begin_dyn(g, seeds, seeds_dev, num_seeds, &dyn);
     if (lead->prof_mask == 0 && lead->cap_stream) st = launch_batch_graph(g, dyn, s);
@@ -843,7 +870,6 @@ gns_status gns_sample_blocks_group(gns_ctx* const* ctxs, int32_t count, const ui
     const int nl = lead->config.num_layers;
     for (int b = 0; b < count; ++b) {
         ctxs[b]->batch_id += 1;
-        ctxs[b]->hash_parity ^= 1;             // this batch has left the other map empty
         for (int i = 0; i < nl; ++i) {
             blocks[b][i].num_dst = GNS_DEVICE_COUNTS(i);
             blocks[b][i].num_src = -1;
@@ -860,10 +886,8 @@ gns_status gns_sample_blocks_group_wait(gns_ctx* const* ctxs, int32_t count, gns
     gns_ctx* lead = ctxs[0];
     if (!blocks) return ctx_fail(lead, GNS_EINVAL, "null blocks");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    hipError_t e = hipSuccess;
-    for (int b = 0; b < count && e == hipSuccess; ++b)
-        e = hipMemcpyAsync(ctxs[b]->h_state, ctxs[b]->d_state, sizeof(DeviceState), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    // the last kernel of every sequence has written the counts to the pinned host mirror
+    const hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) return ctx_fail(lead, GNS_EHIP, "sample_blocks wait", e);
     st = GNS_OK;
     for (int b = 0; b < count; ++b) {

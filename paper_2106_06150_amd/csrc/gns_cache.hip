@@ -481,7 +481,6 @@ gns_status run_sample_cache(gns_ctx* c, uint64_t seed, uint64_t epoch, bool wait
         GNS_HIP_TRY(hipGetLastError(), "coarse bitmap launch");
     }
     if (c->config.flag_mode == GNS_FLAGS_PER_CACHE) {
-        GNS_HIP_TRY(launch_flag_all_entries(c, gen, s), "flag all entries");
         GNS_HIP_TRY(launch_build_induced(c, gen, s), "induced subgraph");
     }
     if (c->graph.feat_dim > 0) {

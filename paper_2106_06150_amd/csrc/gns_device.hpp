@@ -62,43 +62,10 @@ struct alignas(16) RowExtent {
     int64_t start, end;
 };
 
-// ---------------------------------------------------------------------------
-// Open-addressing hash map node id -> local id, one 64-bit slot per entry
-// (low word = key, high word = value), linear probing, load factor <= 1/2.
-constexpr uint64_t kEmptySlot = 0xFFFFFFFFFFFFFFFFull;
-
+// First slot of a key in a table of 2^(32 - shift) slots.
 __device__ __forceinline__ uint32_t hash_start(uint32_t key, uint32_t shift)
 {
     return (key * 0x9E3779B1u) >> shift;    // shift = 32 - log2(capacity)
-}
-
-// returns the slot the entry went into, or -1 if the key was already present (or the table is full)
-__device__ __forceinline__ int64_t hash_insert(unsigned long long* slots, uint32_t mask, uint32_t shift,
-                                               uint32_t key, uint32_t val)
-{
-    const unsigned long long entry = ((unsigned long long) val << 32) | key;
-    uint32_t h = hash_start(key, shift);
-    for (uint32_t probe = 0; probe <= mask; ++probe) {
-        const unsigned long long old = atomicCAS(&slots[h], (unsigned long long) kEmptySlot, entry);
-        if (old == kEmptySlot) return (int64_t) h;
-        if ((uint32_t) old == key) return -1;
-        h = (h + 1) & mask;
-    }
-    return -1;
-}
-
-// local id of `key`, or -1 if absent
-__device__ __forceinline__ int32_t hash_lookup(const unsigned long long* slots, uint32_t mask, uint32_t shift,
-                                               uint32_t key)
-{
-    uint32_t h = hash_start(key, shift);
-    for (uint32_t probe = 0; probe <= mask; ++probe) {
-        const unsigned long long s = slots[h];
-        if ((uint32_t) s == key && s != kEmptySlot) return (int32_t) (s >> 32);
-        if (s == kEmptySlot) return -1;
-        h = (h + 1) & mask;
-    }
-    return -1;
 }
 
 // ---------------------------------------------------------------------------

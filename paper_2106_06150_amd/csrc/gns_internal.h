@@ -16,7 +16,6 @@ struct DeviceState {
     int32_t num_edges[GNS_MAX_LAYERS];
     uint32_t key0, key1;                  // Philox key of the current batch (lo32(seed), hi32(seed))
     uint32_t bad_seed;                    // id of the last batch that had a seed out of range or repeated
-    int32_t map_nodes[2];                 // entries of each of the two hash maps (what its next clear has to undo)
     int32_t hub_count;                    // entries of the batch's hub-row list (reset by the batch's last kernel)
     int32_t chunk_distinct;               // cache draw: first occurrences found in the current chunk
     int32_t chunk_limit;                  //   how many of them enter the cache
@@ -24,7 +23,8 @@ struct DeviceState {
     int32_t draw_distinct;                //   nodes in the cache before the current chunk
     int32_t draw_done_chunk;              //   index of the chunk that completed the cache, -1 while incomplete
     int32_t plan_chunks;                  // CACHE_ONLY sampler: aligned chunks in the current work list
-    int32_t hash_parity;                  // which of the two hash maps the current batch uses (set by its first kernel)
+    uint32_t stamp;                       // what the current batch's entries of the node table carry (set by its first kernel)
+    uint32_t batch_id;                    // id of the current batch (set by its first kernel)
     int32_t cache_gen;                    // which copy of the cache structures it reads (set by its first kernel)
     unsigned long long cut_draw;          // cache draw: stream index of the draw that completed the cache
     unsigned long long walk_total;        // random-walk probability: sum of the weights
@@ -53,21 +53,24 @@ struct Layout {
     size_t seed_copy;         // [max_seeds] the batch's seeds, copied by its first kernel
     size_t hub_rows;          // [max nodes of a batch] rows whose CSR segment spans more than kHubChunks chunks
     size_t row_ext;           // [max nodes of a batch] CSR extent of every node of the batch's list (append-only)
-    size_t slot_list[2];      // [max nodes of a batch] per hash map: the slot each of the batch's nodes went into
-    size_t hash_slots[2];     // consecutive batches alternate: each one leaves the other map empty for the next
+    size_t seed_mark;         // bitmap of the batch's seeds (first layer sampled by the lane kernel)
+    size_t table;             // [n] node table: local id of every node of the batch, stamped (the last per-batch section)
+    int table_shift;          // bits of a local id in a table entry
+    uint32_t max_stamp;
+    size_t static_table;      // node table of gns_sample_blocks_static where the library's array cannot hold it (shared; 0: none)
+    bool lists_hubs;          // some layer gives hub rows a wave of their own
     // per-layer sampler scratch (fixed stride fanout)
     size_t s_nbr[2], s_w[2], s_cnt[2];     // double-buffered by layer parity
     // CACHE_ONLY sampler: per-row chunk counts, chunk work list, CSR-aligned membership flags
     size_t plan_cnt, plan_g0, plan_desc, edge_flags;
-    // GNS_FLAGS_PER_CACHE: the induced subgraph S of Section 3.3 in compact form.  s_nodes lists, in CSR order,
-    // the entries that point into the cache; srec[g] = {flags of chunk g, number of such entries before chunk g},
-    // so a row's cached neighbors are s_nodes[P(start) .. P(end)) with P(e) = off[e >> 6] + popcount(flags below e).
-    size_t srec, s_nodes, sums_chunks;
+    // GNS_FLAGS_PER_CACHE: the induced subgraph S of Section 3.3 in compact form (see gns_induced.hip).
+    size_t srec, s_nodes;
+    size_t s_count;
+    int s_tile_shift;
 
-    int64_t chunk_tiles;
     int64_t max_chunks;
     // scan partials
-    size_t sums_rows, sums_words, sums_marks, sums_plan;
+    size_t sums_rows, sums_words, tile_sums, sums_plan;
     size_t state;
     size_t shared_begin;      // sections at or past this offset are shared with forked contexts
     size_t cache_block_begin; // first of the two copies of what a cache draw writes (bitmap ... 1/p^C table)
@@ -82,7 +85,6 @@ struct Layout {
     int64_t draw_chunk;       // stream draws processed per round of the cache draw
     int64_t draw_tiles;
     uint32_t draw_hash_cap;   // power of two
-    uint32_t hash_cap;        // power of two
     int64_t max_rows;         // worst-case dst rows of any layer
     int64_t max_edges;        // worst-case edges of any layer
     int64_t rows[GNS_MAX_LAYERS + 1];
@@ -97,10 +99,11 @@ namespace gns {
 constexpr int kReaderStreams = 4;
 struct Group;       // gns_kernels.hpp: the mini-batches one launch sequence serves
 struct BeginDyn;    //   the first kernel's per-replay arguments
-// Opaque host-side storage for the first kernel's two argument blocks (LayerArgs, BeginDyn).
+// Opaque host-side storage for the first kernel's arguments (LayerArgs, BeginDyn).
 struct BeginArgsHost {
     alignas(8) unsigned char fixed[3072];
     alignas(8) unsigned char dyn[768];
+    int rows_per_wave;                   // k_sample_first's third argument
 };
 // One captured launch sequence of a group of mini-batches, kept by the group's first context.
 struct BatchGraph {
@@ -114,7 +117,7 @@ struct BatchGraph {
     gns_ctx* ctx[GNS_MAX_GROUP];
     gns_block blocks[GNS_MAX_GROUP][GNS_MAX_LAYERS];
     BeginArgsHost args;              // the first kernel's arguments (the node's parameter list points here)
-    void* arg_ptrs[2];
+    void* arg_ptrs[3];
 };
 constexpr int kGraphsPerContext = 2;
 struct ProfileRecord {
@@ -131,7 +134,8 @@ struct gns_ctx {
     char* shared_ws;                 // base for the shared sections (the root context's workspace)
     gns_ctx* root;                   // owner of the cache; this for a context made by gns_create
     gns::DeviceState* d_state;       // device
-    gns::DeviceState* h_state;       // pinned host mirror
+    gns::DeviceState* h_state;       // pinned host mirror, written by the last kernel of every mini-batch and by cache draws
+    gns::DeviceState* h_state_dev;   //   its address for kernels
     bool uses_cache;
     bool cache_valid;
     int cache_gen;                   // root only: which copy of the cache block the mini-batches read
@@ -166,7 +170,8 @@ struct gns_ctx {
     hipStream_t cap_stream;          // used for capture only, never for execution
     gns::BatchGraph* bg;             // [kGraphsPerContext] captured launch sequences (least recently used is replaced)
     uint64_t graph_clock;
-    int hash_parity;                 // which hash map the next mini-batch uses
+    uint32_t stamp;                  // of the last mini-batch enqueued on this context, 1 .. lay.max_stamp (0: none yet)
+    int union_spins;                 // how often the union step polls another tile's sum before it counts that tile itself
     uint32_t batch_id;               // id of the last mini-batch enqueued on this context (from 1)
     uint32_t bad_reported;           // DeviceState::bad_seed as of the last report to the caller
     gns_ctx* static_child;           // root only: the context of gns_sample_blocks_static (scratch in the library's array)
@@ -186,6 +191,9 @@ static inline T* ws_ptr(const gns_ctx* c, size_t off)
 {
     return reinterpret_cast<T*>((off >= c->lay.shared_begin ? c->shared_ws : c->ws) + off);
 }
+
+// The node table of a context (see Layout::static_table for the one place where it is not part of the scratch).
+static inline uint32_t* ws_ptr_table(const gns_ctx* c) { return reinterpret_cast<uint32_t*>(c->ws + c->lay.table); }
 
 // A section of the cache block in the given generation (off is the section's offset in generation 0).
 template <typename T>
@@ -216,6 +224,8 @@ static inline hipError_t before_cache_readers(gns_ctx* c, hipStream_t s)
 gns_status ctx_fail(gns_ctx* c, gns_status st, const char* what, hipError_t e = hipSuccess);
 // gns_api.hip
 gns_status enqueue_batch(const Group& g, const BeginDyn& d, hipStream_t s);
+// takes the next stamp of every context of the group (enqueues the clearing of a node table whose stamps have run out)
+hipError_t next_stamps(const Group& g, hipStream_t s);
 void fill_begin_dyn(const Group& g, const uint64_t* seeds, const int32_t* const* seeds_dev, const int32_t* num_seeds,
                     BeginDyn* out);
 gns_status check_batch_args(gns_ctx* c, const int32_t* seeds_dev, int32_t num_seeds, const gns_block* blocks);
@@ -262,16 +272,15 @@ gns_status retire_cache(gns_ctx* c);
 gns_status finish_pending_draw(gns_ctx* c);
 
 // gns_induced.hip
+int induced_tile_shift(int64_t num_entries);
 hipError_t launch_build_induced(gns_ctx* c, int cache_gen, hipStream_t s);
 
 // gns_sampler.hip
 // the previous layer's relabel shares this layer's first launch
 hipError_t launch_sample_layer(const Group& g, int layer_index, hipStream_t s);
-hipError_t launch_flag_all_entries(gns_ctx* c, int cache_gen, hipStream_t s);
 
 // gns_frontier.hip
 hipError_t launch_batch_begin(const Group& g, const BeginDyn& d, hipStream_t s);
-const void* batch_first_kernel();
 hipError_t launch_relabel(const Group& g, int layer_index, hipStream_t s);
 hipError_t launch_finish_layer(const Group& g, int layer_index, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v, hipStream_t s);

@@ -17,8 +17,22 @@ constexpr int kMaxGroup = GNS_MAX_GROUP;
 // One record per aligned 64-entry chunk of the CSR entry array (GNS_FLAGS_PER_CACHE).
 struct alignas(16) ChunkRec {
     uint64_t flags;            // bit e & 63: entry e points into the cache
-    uint32_t before;           // number of such entries in all earlier chunks
+    uint32_t before;           // place in s_nodes of the first of them
     uint32_t pad;
+};
+
+// Which node has which local id in the current mini-batch: one 32-bit entry per node of the graph, the batch's stamp in
+// the upper bits and the local id in the lower `shift` ones.  An entry of another batch carries another stamp, so
+// nothing is cleared between batches (the host clears the table when the stamps run out), a node is entered with a
+// plain store and found with one read.
+struct NodeTable {
+    uint32_t* entry;           // [n]
+    uint32_t stamp;
+    int shift;
+
+    __device__ __forceinline__ uint32_t make(uint32_t local) const { return (stamp << shift) | local; }
+    __device__ __forceinline__ bool current(uint32_t e) const { return (e >> shift) == stamp; }
+    __device__ __forceinline__ uint32_t local(uint32_t e) const { return e & ((1u << shift) - 1u); }
 };
 
 struct SampleArgs {
@@ -28,24 +42,21 @@ struct SampleArgs {
     int fanout;
     int wmode;
     int policy;                // GNS_CACHE_ONLY or GNS_CACHE_FIRST for the select kernel
-    int64_t num_nodes;
-    const void* indptr;
     const int32_t* indices;
     const int32_t* dst_nodes;
-    const RowExtent* row_ext;  // CSR extent of every dst row's node (written when the node joined the batch)
+    RowExtent* row_ext;        // CSR extent of every dst row's node (written when the node joined the batch)
     const float* node_inv_pc;  // 1 / p^C_u for the nodes of the cache
     const int32_t* hub_rows;   // rows of the batch whose CSR segment spans more than kHubChunks chunks
     const uint64_t* cache_bitmap;
-    const int32_t* cache_prefix;
-    int64_t cache_size;
     int32_t* s_nbr;
     float* s_w;
     int32_t* s_cnt;
+    int32_t* sums_rows;        // sampled neighbors of the rows of every block of the sampler
     int32_t* row_eligible;
+    int32_t* src_nodes;        // the layer's src list begins with its dst nodes
     uint64_t* mark;
     uint64_t* mark_summary;    // one bit per word of mark, or null (small graphs)
-    const unsigned long long* slots;   // batch hash map node -> local id (holds this layer's dst nodes)
-    uint32_t hmask, hshift;
+    NodeTable tab;             // holds this layer's dst nodes
     // CACHE_ONLY: per-batch plan and the CSR-aligned membership flags
     int64_t num_entries;
     int32_t* plan_cnt;         // [rows] aligned 64-entry chunks touched by each dst row
@@ -59,23 +70,28 @@ struct SampleArgs {
     int coarse_shift;
     const ChunkRec* srec;      // induced subgraph (GNS_FLAGS_PER_CACHE): chunk records and the cached entries' node ids
     const int32_t* s_nodes;
+    const int32_t* s_count;    // cached entries of every tile of 2^s_tile_shift entries
+    int s_tile_shift;
 };
 
 struct FinishArgs {
     DeviceState* st;
     int layer_index;
     int fanout;
-    const int32_t* dst_nodes;      // [R]
+    double inv_fanout;
+    int unit_weights;              // UNIFORM layers: every weight is 1 and s_w is not used
     const int32_t* s_nbr;          // [R x fanout]
     const float* s_w;              // [R x fanout]
     const int32_t* s_cnt;          // [R]
+    const int32_t* sums_rows;      // sampled neighbors of every rows_per_sum consecutive rows
+    int32_t rows_per_sum;          //   (a power of two up to kTile)
     uint64_t* mark;                // [words]
     uint64_t* mark_summary;        // [ceil(words / 64)] or null: bit w & 63 of word w >> 6 says mark[w] != 0
+    int marks_seeds;               // first layer sampled in the launch that enters the seeds: it marks them like any node,
+    const uint64_t* seed_mark;     //   and this bitmap of the seeds tells them apart (null otherwise)
     int64_t words;
-    unsigned long long* slots;
-    uint32_t hmask, hshift;
-    int32_t* sums_rows;            // [row_tiles + 1]
-    int32_t* sums_marks;           // [mark_tiles + 1]
+    NodeTable tab;
+    unsigned long long* tile_sums; // [mark_tiles] (tag, new nodes of the tile), see union_offset
     int32_t row_tiles_max;         // grid split point: blocks [0, row_tiles_max) work on rows
     int32_t mark_tiles;            // tiles of mark_tile_words bitmap words
     int32_t mark_tile_words;
@@ -83,28 +99,26 @@ struct FinishArgs {
     int32_t* indices;
     float* weights;
     int32_t* src_nodes;
-    int64_t max_slots;             // worst-case rows * fanout of this layer
-    RowExtent* row_ext;            // [nodes of the batch] phase 3 appends the new nodes' CSR extents
+    RowExtent* row_ext;            // [nodes of the batch] the union step appends the new nodes' CSR extents
     const void* g_indptr;          // the graph's offsets
     int g_i64;
-    int32_t* hub_rows;             // phase 3 appends the new nodes that are hubs
-    uint32_t* slot_list;           // phase 3 records the hash slot of every new node (for the sparse clear)
-    int parity;                    // which of the two hash maps this batch uses
-    unsigned long long* other_slots;       // the other hash map and its slot list (emptied by the batch's last kernel)
-    const uint32_t* other_slot_list;
+    int32_t* hub_rows;             // the union step appends the new nodes that are hubs
     int64_t num_nodes;
 };
 
 // Byte offsets of the sections of a context's per-batch scratch (the same for every context of a family).
 struct WsOffsets {
-    uint64_t state, mark, mark_summary, seed_copy, row_ext, hub_rows;
-    uint64_t slot_list[2], hash_slots[2];
+    uint64_t state, mark, mark_summary, seed_mark, seed_copy, row_ext, hub_rows;
+    uint64_t table;
     uint64_t s_nbr[2], s_w[2], s_cnt[2];
     uint64_t plan_cnt, plan_g0, plan_desc;
-    uint64_t sums_rows, sums_marks, sums_plan;
+    uint64_t sums_rows, tile_sums, sums_plan;
     uint64_t cache_block_bytes;    // distance between the two copies of what a cache draw writes
     int32_t uses_cache;
     int32_t has_summary;
+    int32_t table_shift;
+    int32_t lists_hubs;            // some layer gives hub rows a wave of their own
+    int32_t marks_seeds;           // the first layer's launch fills the seed bitmap
 };
 
 struct BlockPtrs {
@@ -118,8 +132,8 @@ struct BlockPtrs {
 // What differs between the mini-batches of a group.
 struct BatchSlot {
     char* ws;                  // the batch's context: its per-batch scratch
+    DeviceState* host;         //   and its pinned host mirror
     const int32_t* dst;        // dst nodes of the layer being sampled / finished
-    const int32_t* prev_dst;   // dst nodes of the layer before it
     BlockPtrs cur, prev;       // block buffers of that layer and of the one before it
 };
 
@@ -136,7 +150,7 @@ struct BeginDyn {
     int32_t num_seeds[kMaxGroup];
     uint32_t key0[kMaxGroup], key1[kMaxGroup];
     uint32_t batch_id[kMaxGroup];
-    int32_t parity[kMaxGroup];     // which hash map the batch uses
+    uint32_t stamp[kMaxGroup];     // what the batch's entries of the node table carry
     int32_t cache_gen[kMaxGroup];  // which copy of the cache structures it reads
 };
 
@@ -148,44 +162,60 @@ __device__ __forceinline__ DeviceState* bind_state(const LayerArgs& g, int b)
     return at<DeviceState>(g.b[b].ws, g.off.state);
 }
 
-// The sampler's arguments for batch b of the group.  The hash-map parity and the cache generation were
-// left in the batch's device state by its first kernel.
-__device__ __forceinline__ SampleArgs bind_sample(const LayerArgs& g, int b)
+__device__ __forceinline__ NodeTable bind_table(const LayerArgs& g, int b, uint32_t stamp)
+{
+    NodeTable t;
+    t.entry = at<uint32_t>(g.b[b].ws, g.off.table);
+    t.stamp = stamp;
+    t.shift = g.off.table_shift;
+    return t;
+}
+
+// The sampler's arguments for batch b of the group, given the batch's stamp and cache generation (left in its device
+// state by its first kernel, which has them as arguments).
+__device__ __forceinline__ SampleArgs bind_sample(const LayerArgs& g, int b, uint32_t stamp, int cache_gen)
 {
     SampleArgs a = g.s;
     const BatchSlot& q = g.b[b];
     char* ws = q.ws;
     a.st = at<DeviceState>(ws, g.off.state);
-    const int parity = a.st->hash_parity;
-    const uint64_t gen_shift = a.st->cache_gen ? g.off.cache_block_bytes : 0;
+    const uint64_t gen_shift = cache_gen ? g.off.cache_block_bytes : 0;
     const int par = g.s.layer_index & 1;             // sampler scratch is double-buffered by layer parity
     a.dst_nodes = q.dst;
     a.row_ext = at<RowExtent>(ws, g.off.row_ext);
-    a.hub_rows = g.off.uses_cache ? at<int32_t>(ws, g.off.hub_rows) : nullptr;
+    a.hub_rows = g.off.lists_hubs ? at<int32_t>(ws, g.off.hub_rows) : nullptr;
     a.s_nbr = at<int32_t>(ws, g.off.s_nbr[par]);
     a.s_w = at<float>(ws, g.off.s_w[par]);
     a.s_cnt = at<int32_t>(ws, g.off.s_cnt[par]);
+    a.sums_rows = at<int32_t>(ws, g.off.sums_rows);
     a.row_eligible = q.cur.row_eligible;
+    a.src_nodes = q.cur.src_nodes;
     a.mark = at<uint64_t>(ws, g.off.mark);
     a.mark_summary = g.off.has_summary ? at<uint64_t>(ws, g.off.mark_summary) : nullptr;
-    a.slots = at<unsigned long long>(ws, g.off.hash_slots[parity]);
+    a.tab = bind_table(g, b, stamp);
     a.plan_cnt = at<int32_t>(ws, g.off.plan_cnt);
     a.plan_g0 = at<int32_t>(ws, g.off.plan_g0);
     a.plan_sums = at<int32_t>(ws, g.off.sums_plan);
     a.plan_desc = at<int32_t>(ws, g.off.plan_desc);
     if (g.off.uses_cache) {
-        a.node_inv_pc = reinterpret_cast<const float*>(reinterpret_cast<const char*>(g.s.node_inv_pc) + gen_shift);
-        a.cache_bitmap = reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(g.s.cache_bitmap) + gen_shift);
-        a.cache_prefix = reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(g.s.cache_prefix) + gen_shift);
-        a.flags = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(g.s.flags) + gen_shift);
-        if (g.s.coarse_bitmap)
-            a.coarse_bitmap = reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(g.s.coarse_bitmap) + gen_shift);
-        if (g.s.srec) {
-            a.srec = reinterpret_cast<const ChunkRec*>(reinterpret_cast<const char*>(g.s.srec) + gen_shift);
-            a.s_nodes = reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(g.s.s_nodes) + gen_shift);
-        }
+        auto shifted = [&](auto* ptr) {
+            return ptr ? reinterpret_cast<decltype(ptr)>(reinterpret_cast<uintptr_t>(ptr) + gen_shift) : ptr;
+        };
+        a.node_inv_pc = shifted(g.s.node_inv_pc);
+        a.cache_bitmap = shifted(g.s.cache_bitmap);
+        a.flags = shifted(g.s.flags);
+        a.coarse_bitmap = shifted(g.s.coarse_bitmap);
+        a.srec = shifted(g.s.srec);
+        a.s_nodes = shifted(g.s.s_nodes);
+        a.s_count = shifted(g.s.s_count);
     }
     return a;
+}
+
+__device__ __forceinline__ SampleArgs bind_sample(const LayerArgs& g, int b)
+{
+    const DeviceState* st = bind_state(g, b);
+    return bind_sample(g, b, st->stamp, st->cache_gen);
 }
 
 // The union / relabel arguments of batch b for the layer the template describes: the launch's own layer
@@ -196,48 +226,61 @@ __device__ __forceinline__ FinishArgs bind_finish(const LayerArgs& g, int b, boo
     const BatchSlot& q = g.b[b];
     char* ws = q.ws;
     a.st = at<DeviceState>(ws, g.off.state);
-    const int parity = a.st->hash_parity;
     const int par = g.f.layer_index & 1;
     const BlockPtrs& blk = own_layer ? q.cur : q.prev;
-    a.dst_nodes = own_layer ? q.dst : q.prev_dst;
     a.s_nbr = at<int32_t>(ws, g.off.s_nbr[par]);
     a.s_w = at<float>(ws, g.off.s_w[par]);
     a.s_cnt = at<int32_t>(ws, g.off.s_cnt[par]);
+    a.sums_rows = at<int32_t>(ws, g.off.sums_rows);
     a.mark = at<uint64_t>(ws, g.off.mark);
     a.mark_summary = g.off.has_summary ? at<uint64_t>(ws, g.off.mark_summary) : nullptr;
-    a.slots = at<unsigned long long>(ws, g.off.hash_slots[parity]);
-    a.sums_rows = at<int32_t>(ws, g.off.sums_rows);
-    a.sums_marks = at<int32_t>(ws, g.off.sums_marks);
+    a.seed_mark = g.f.marks_seeds ? at<uint64_t>(ws, g.off.seed_mark) : nullptr;
+    a.tab = bind_table(g, b, a.st->stamp);
+    a.tile_sums = at<unsigned long long>(ws, g.off.tile_sums);
     a.indptr = blk.indptr;
     a.indices = blk.indices;
     a.weights = blk.weights;
     a.src_nodes = blk.src_nodes;
     a.row_ext = at<RowExtent>(ws, g.off.row_ext);
-    a.hub_rows = g.off.uses_cache ? at<int32_t>(ws, g.off.hub_rows) : nullptr;
-    a.slot_list = at<uint32_t>(ws, g.off.slot_list[parity]);
-    a.parity = parity;
-    a.other_slots = at<unsigned long long>(ws, g.off.hash_slots[parity ^ 1]);
-    a.other_slot_list = at<uint32_t>(ws, g.off.slot_list[parity ^ 1]);
+    a.hub_rows = g.off.lists_hubs ? at<int32_t>(ws, g.off.hub_rows) : nullptr;
     return a;
 }
 
-// Relabel: every sampled edge of a finished layer gets its neighbor's local id (from the scratch slot if
-// the sampler already found one, else from the batch's hash map) and is compacted to its CSR position.  `block` of `nblocks` blocks of kBlock threads.
-// It only needs that layer's phase 3, so it shares a launch with the next layer's first kernel.
-__device__ __forceinline__ void relabel_body(const FinishArgs& a, int64_t block, int64_t nblocks)
+// Relabel: every sampled edge of a finished layer gets its neighbor's local id (from the scratch slot if the sampler
+// already found one, else from the node table) and is compacted to its CSR position.  `block` of `nblocks` blocks of
+// kBlock threads, kRelabelUnroll slots per thread in flight.  It only needs that layer's union step, so it shares a
+// launch with the next layer's first kernel.
+constexpr int kRelabelUnroll = 4;
+
+__device__ __forceinline__ void relabel_body(const FinishArgs& a, int32_t block, int32_t nblocks)
 {
     const int32_t R = a.st->num_dst[a.layer_index];
-    const int64_t limit = (int64_t) R * a.fanout;
-    int64_t t = block * kBlock + threadIdx.x;
-    const int64_t stride = nblocks * kBlock;
-    for (; t < limit && t < a.max_slots; t += stride) {
-        const int32_t row = (int32_t) (t / a.fanout);
-        const int32_t s = (int32_t) (t - (int64_t) row * a.fanout);
-        if (s < a.s_cnt[row]) {
-            const int32_t u = a.s_nbr[t];          // -(local id + 1) if the sampler already knew it, else the global id
-            const int32_t o = a.indptr[row] + s;
-            a.indices[o] = u < 0 ? -1 - u : hash_lookup(a.slots, a.hmask, a.hshift, (uint32_t) u);
-            a.weights[o] = a.s_w[t];
+    const int32_t limit = R * a.fanout;                            // below 2^31: checked when the workspace is sized
+    const int32_t step = nblocks * kBlock;
+    for (int64_t t0 = (int64_t) block * kBlock + threadIdx.x; t0 < limit; t0 += (int64_t) step * kRelabelUnroll) {
+        int32_t u[kRelabelUnroll], o[kRelabelUnroll];
+        float w[kRelabelUnroll];
+        bool ok[kRelabelUnroll];
+#pragma unroll
+        for (int i = 0; i < kRelabelUnroll; ++i) {
+            const int64_t t = t0 + (int64_t) i * step;
+            const int32_t q = t < limit ? (int32_t) t : limit - 1;
+            const int32_t row = (int32_t) (((double) q + 0.5) * a.inv_fanout);          // q / fanout: exact below 2^31
+            const int32_t s = q - row * a.fanout;
+            const int32_t cnt = a.s_cnt[row];
+            u[i] = a.s_nbr[q];                        // -(local id + 1) if the sampler already knew it, else the global id
+            w[i] = a.unit_weights ? 1.0f : a.s_w[q];
+            o[i] = a.indptr[row] + s;
+            ok[i] = t < limit && s < cnt;
+        }
+#pragma unroll
+        for (int i = 0; i < kRelabelUnroll; ++i) {
+            const bool search = ok[i] && u[i] >= 0;
+            const uint32_t e = a.tab.entry[search ? u[i] : 0];
+            if (ok[i]) {
+                a.indices[o[i]] = search ? (int32_t) a.tab.local(e) : -1 - u[i];
+                a.weights[o[i]] = w[i];
+            }
         }
     }
 }
@@ -265,6 +308,48 @@ __device__ __forceinline__ void append_hub_rows(DeviceState* st, int32_t* hub_ro
     if (is_hub && hub_rows) hub_rows[base + __popcll(m & ((1ull << lane) - 1ull))] = row;
 }
 
+// The batch's scalars, published for its later kernels; one thread of the batch's first kernel.
+__device__ __forceinline__ void begin_state(const LayerArgs& g, const BeginDyn& d, int b)
+{
+    DeviceState* st = bind_state(g, b);
+    st->num_dst[0] = d.num_seeds[b];
+    for (int l = 0; l < GNS_MAX_LAYERS; ++l) { st->num_edges[l] = 0; st->num_dst[l + 1] = 0; }
+    st->key0 = d.key0[b];
+    st->key1 = d.key1[b];
+    st->stamp = d.stamp[b];
+    st->batch_id = d.batch_id[b];
+    st->cache_gen = d.cache_gen[b];
+}
+
+// Seed q of the batch, node u: the CSR extent of its row (empty for an id out of range).
+__device__ __forceinline__ RowExtent seed_extent(const LayerArgs& g, int32_t u)
+{
+    RowExtent ext = {0, 0};
+    if (u >= 0 && (int64_t) u < g.f.num_nodes) {
+        ext.start = load_off_rt(g.f.g_indptr, g.f.g_i64, u);
+        ext.end = load_off_rt(g.f.g_indptr, g.f.g_i64, (int64_t) u + 1);
+    }
+    return ext;
+}
+
+// Seed q enters the batch: its id copied, its extent recorded, its local id entered in the node table; with `mark` also
+// its bit in the seed bitmap, for a first layer that is sampled in the same launch.
+__device__ __forceinline__ void enter_seed(const LayerArgs& g, const BeginDyn& d, int b, const NodeTable& tab, int32_t q, int32_t u,
+                                           const RowExtent& ext, bool mark)
+{
+    char* ws = g.b[b].ws;
+    bool bad = true;
+    if (u >= 0 && (int64_t) u < g.f.num_nodes) {
+        if (mark) atomicOr(at<unsigned long long>(ws, g.off.seed_mark) + (u >> 6), 1ull << (u & 63));
+        bad = tab.current(atomicExch(&tab.entry[u], tab.make((uint32_t) q)));         // a repeated seed
+    }
+    at<int32_t>(ws, g.off.seed_copy)[q] = u;
+    at<RowExtent>(ws, g.off.row_ext)[q] = ext;
+    append_hub_rows(bind_state(g, b), g.off.lists_hubs ? at<int32_t>(ws, g.off.hub_rows) : nullptr,
+                    is_hub_extent(ext.start, ext.end), q);
+    if (bad) bind_state(g, b)->bad_seed = d.batch_id[b];
+}
+
 // ---------------------------------------------------------------------------
 // Host side: a group of mini-batches and the argument block of one of its launches.
 struct Group {
@@ -279,7 +364,17 @@ void fill_group_args(const Group& g, LayerArgs* out);
 void set_group_layer(const Group& g, int layer_index, LayerArgs* out);
 // The templates for one layer (sampler side: own layer; finish side: `finish_layer`).
 void fill_sample_template(gns_ctx* c, int layer_index, SampleArgs* out);
-void fill_finish_template(gns_ctx* c, int finish_layer, FinishArgs* out);
+void fill_finish_template(const Group& g, int finish_layer, FinishArgs* out);
+// The fixed arguments of the group's first kernel.
+void fill_first_args(const Group& g, LayerArgs* out);
 int relabel_grid(const gns_ctx* c, int layer_index);
+// Whether a layer is sampled without a plan or flag pass in front: UNIFORM, or from the induced subgraph.
+bool direct_layer(const gns_config& config, int layer_index);
+// Whether the first layer's sampler is also the batch's first kernel (k_batch_begin runs in front of the others).
+bool first_layer_enters_seeds(const gns_config& config);
+// Rows whose sampled neighbors the layer's sampler sums up (0: it does not; k_row_sums does, over kBlock rows).
+int rows_per_sum(const Group& g, int layer_index);
+// The batch's first launch when the first layer is direct: seeds and sampling in one.
+hipError_t launch_first_layer(const Group& g, const BeginDyn& d, hipStream_t s);
 
 }  // namespace gns

@@ -15,12 +15,13 @@
 // integer arithmetic, so the sample does not depend on scheduling.
 //
 // Output per row r (fixed stride k): s_nbr[r*k + i] (the neighbor's local id as -(id+1) if it has
-// one, else its global id), s_w[r*k + i] for
-// i < s_cnt[r], row_eligible[r]; every emitted id that has no local id yet
-// (it is not a dst node of this layer) also sets its bit in the node-indexed
-// mark bitmap that the frontier stage turns into the src list.
+// one, else its global id), s_w[r*k + i] for i < s_cnt[r] (UNIFORM layers: no weights, they are 1),
+// row_eligible[r], the dst node as the r-th src node, and the sum of s_cnt over the rows of a block;
+// every emitted id that has no local id yet (it is not a dst node of this layer) also sets its bit in
+// the node-indexed mark bitmap that the frontier stage turns into the src list.
 #include <string.h>
 #include <stdlib.h>
+#include <type_traits>
 #include "gns_kernels.hpp"
 
 namespace gns {
@@ -77,181 +78,374 @@ __device__ __forceinline__ void mark_node(const SampleArgs& a, uint32_t u)
 
 __device__ __forceinline__ int32_t mark_if_new(const SampleArgs& a, uint32_t u)
 {
-    const int32_t local = hash_lookup(a.slots, a.hmask, a.hshift, u);
-    if (local >= 0) return -1 - local;
+    const uint32_t e = a.tab.entry[u];
+    if (a.tab.current(e)) return -1 - (int32_t) a.tab.local(e);
     mark_node(a, u);
     return (int32_t) u;
 }
 
 // ---------------------------------------------------------------------------
-// UNIFORM: G lanes per row, rows assigned round-robin to groups.
-template <int G>
-__global__ void __launch_bounds__(kBlock) k_sample_uniform(LayerArgs g, int relabel_blocks)
-{
-    // the last relabel_blocks blocks finish the previous layer's block instead (see relabel_body); they are
-    // dispatched after this layer's rows, whose dependent loads set the length of the launch
-    const int64_t nblocks = (int64_t) gridDim.x - relabel_blocks;
-    if ((int64_t) blockIdx.x >= nblocks) {
-        relabel_body(bind_finish(g, (int) blockIdx.y, false), (int64_t) blockIdx.x - nblocks, relabel_blocks);
-        return;
-    }
-    const SampleArgs a = bind_sample(g, (int) blockIdx.y);
-    const int64_t block = (int64_t) blockIdx.x;
-    const int32_t R = a.st->num_dst[a.layer_index];
-    const int k = a.fanout;
-    constexpr int kRowsPerWave = kWave / G;
-    // The loop bounds live in scalar registers (readfirstlane) so that the whole wave
-    // provably iterates together: the draw below exchanges data between lanes.
-    const int64_t wave_global = block * (kBlock / kWave) +
-                                __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
-    const int64_t num_waves = nblocks * (kBlock / kWave);
-    for (int64_t row0 = wave_global * kRowsPerWave; row0 < R; row0 += num_waves * kRowsPerWave) {
-        const int lane = opaque_lane_id();
-        const int s = lane & (G - 1);
-        const int64_t row = row0 + (lane / G);
-        const bool live = row < R;
-        int64_t start = 0;
-        uint32_t m = 0;
-        uint32_t v = 0;
-        if (live) {
-            const RowExtent ext = a.row_ext[row];
-            v = (uint32_t) a.dst_nodes[row];
-            start = ext.start;
-            m = (uint32_t) (ext.end - ext.start);
-        }
-        uint32_t val;
-        int pos;
-        // run the draw with a safe size in every lane, then keep it only where it applies
-        floyd_in_group<G>(m > (uint32_t) k ? m : (uint32_t) k + 1u, k, k, a.st->key0, a.st->key1, a.layer_number, v, s, &val, &pos);
-        const int cnt = (m > (uint32_t) k) ? k : (int) m;
-        if (m <= (uint32_t) k) { val = (uint32_t) s; pos = s; }
-        if (live && s < cnt) {
-            const int32_t u = a.indices[start + val];
-            a.s_w[row * k + pos] = 1.0f;
-            a.s_nbr[row * k + pos] = mark_if_new(a, (uint32_t) u);
-        }
-        if (live && s == 0) {
-            a.s_cnt[row] = cnt;
-            a.row_eligible[row] = (int32_t) m;
-        }
-    }
-}
+// What a row's entries are drawn from: its CSR segment (UNIFORM), its cached neighbors in the induced subgraph
+// (CACHE_ONLY), or those first and then the rest of its CSR segment (CACHE_FIRST).
+enum { kListRow = 0, kListCached = 1, kListCachedFirst = 2 };
 
-// ---------------------------------------------------------------------------
-// One dst row per lane (fan-outs up to 16).  The list a row draws from is either its CSR segment (UNIFORM)
-// or, with the induced subgraph S of GNS_FLAGS_PER_CACHE, its cached neighbors s_nodes[P(start) .. P(end))
-// (CACHE_ONLY): in both cases a contiguous list of m ids of which min(k, m) ranks are chosen, so a lane
-// needs the row's extent, the k drawn entries and nothing else of the row.  Every lane runs Floyd's draw
-// for its own row with the loops over the k slots unrolled (the chosen ranks stay in registers); the
-// loads of all k entries, their weights and their hash slots are issued together.  A wave handles 64
-// rows at once and consecutive lanes read consecutive rows' extents and ids.
 __device__ __forceinline__ uint64_t bits_below(int64_t e)
 {
     return (1ull << (e & 63)) - 1ull;
 }
 
-template <int KMAX, bool kInduced>
-__global__ void __launch_bounds__(kBlock) k_sample_lane(LayerArgs g, int relabel_blocks)
+// The cached neighbors of one row in the induced subgraph: `count` of them, the first `here` from s_nodes[first] on (all
+// of them unless the row crosses a tile), the others from the offsets of tiles tile + 1, tile + 2, ... on.
+struct CachedList {
+    uint32_t first, here, count, tile;
+};
+
+__device__ __forceinline__ CachedList cached_list(const SampleArgs& a, const RowExtent& ext)
 {
-    const int64_t nblocks = (int64_t) gridDim.x - relabel_blocks;
-    if ((int64_t) blockIdx.x >= nblocks) {
-        relabel_body(bind_finish(g, (int) blockIdx.y, false), (int64_t) blockIdx.x - nblocks, relabel_blocks);
+    CachedList r;
+    const bool some = ext.end > ext.start;
+    const int64_t start = some ? ext.start : 0, last = some ? ext.end - 1 : 0;
+    const ChunkRec rs = a.srec[start >> 6];
+    const ChunkRec re = a.srec[last >> 6];
+    const uint32_t stop = re.before + (uint32_t) __popcll(re.flags & (bits_below(last) * 2 + 1));
+    r.first = rs.before + (uint32_t) __popcll(rs.flags & bits_below(start));
+    r.tile = (uint32_t) (start >> a.s_tile_shift);
+    r.here = r.count = some ? stop - r.first : 0u;
+    const uint32_t last_tile = (uint32_t) (last >> a.s_tile_shift);
+    if (r.tile != last_tile) {                       // rare: tiles are much longer than rows
+        r.here = r.count = (r.tile << a.s_tile_shift) + (uint32_t) a.s_count[r.tile] - r.first;
+        for (uint32_t t = r.tile + 1; t < last_tile; ++t) r.count += (uint32_t) a.s_count[t];
+        r.count += stop - (last_tile << a.s_tile_shift);
+    }
+    return r;
+}
+
+// Place in s_nodes of the row's cached neighbor of rank `rank`, here <= rank < count.
+__device__ __forceinline__ int64_t later_tile(const SampleArgs& a, const CachedList& r, uint32_t rank)
+{
+    uint32_t left = rank - r.here, t = r.tile + 1;
+    for (;; ++t) {
+        const uint32_t n = (uint32_t) a.s_count[t];
+        if (left < n) return (int64_t) (t << a.s_tile_shift) + left;
+        left -= n;
+    }
+}
+
+// CSR entry of the row [start, end) that is the `rank`-th among those not in the cache (rank is below their number).
+__device__ __forceinline__ int64_t uncached_entry(const SampleArgs& a, const RowExtent& ext, uint32_t rank)
+{
+    const int64_t first = ext.start >> 6, last = (ext.end - 1) >> 6;
+    for (int64_t c = first;; ++c) {
+        uint64_t open = ~a.srec[c].flags;
+        if (c == first) open &= ~bits_below(ext.start);
+        if (c == last) open &= bits_below(ext.end - 1) * 2 + 1;
+        const uint32_t n = (uint32_t) __popcll(open);
+        if (rank < n || c == last) return (c << 6) + select_bit64(open, (int) rank);
+        rank -= n;
+    }
+}
+
+// Section 3.4: coefficient p^C_u * k / min(k, N_C(v)), weight = 1 / coefficient (fp32 from the 1/p^C table on); the factor
+// of 1/p^C for a row of m cached neighbors of which cnt are drawn.
+__device__ __forceinline__ float cached_scale(const SampleArgs& a, uint32_t m, int cnt)
+{
+    return a.wmode == GNS_W_UNBIASED ? (float) m / (float) (cnt > 0 ? cnt : 1) : (float) cnt / (float) a.fanout;
+}
+
+// Fill neighbors: weight 1 (a node-wise sample), or the inverse inclusion probability of a uniform subset of the
+// uncached neighbors in the unbiased mode.
+__device__ __forceinline__ float fill_weight(const SampleArgs& a, uint32_t others, int fill)
+{
+    return a.wmode == GNS_W_UNBIASED ? (float) others / (float) (fill > 0 ? fill : 1) : 1.0f;
+}
+
+// ---------------------------------------------------------------------------
+// Direct layers with fan-outs up to 16.  A wave takes W rows (W a power of two up to 64) in two stages:
+//   draw   one row per lane: extent, chunk records, Floyd's draw for the whole row (the loops over the slots are
+//          unrolled, the chosen ranks stay in registers); the Philox blocks of the W rows are spread over all lanes;
+//   fetch  one drawn entry per lane: the W * k (row, slot) pairs are dealt to the lanes, kFetch at a time with
+//          their reads in flight together: entry -> node table and 1/p^C -> mark, scratch.
+// The stages have opposite needs.  The draw is instruction-bound (a Philox block is forty quarter-rate multiplies), and
+// with a slot per lane every lane of a row repeats it; the fetch is a chain of scattered reads, and with a row per lane
+// half of the slots a lane holds sit in branches that wait for one another.  W is chosen by the launch: 64 where there
+// are rows enough to fill the chip, fewer for the small layers next to the seeds, whose launches are as long as that chain.
+// Groups of four on the graph of 1 M nodes: 9.9 / 27 / 44 us for the three layers (entering the seeds included), where a
+// lane group per row on the upper and a row per lane on the input layer took 15.7 / 28 / 55; the input layer is now bound by
+// the lines its records and drawn entries pull in (1.5 M L2 misses), no longer by instructions.
+// kFirst: also the batch's first kernel.  No sampled node has a local id yet as far as that launch can know, so every one
+// is marked, and the union step takes the seeds out again (seed bitmap).
+constexpr int kFetch = 5;
+
+template <int K>
+struct WaveRows {
+    static constexpr int kSlots = (K + 3) / 4 * 4;
+    uint32_t slot[kWave][kSlots];                // Philox words, then the chosen ranks (top bit: of the fill; ~0: none)
+    int64_t start[kWave], end[kWave];            // CSR extent
+    uint32_t first[kWave], here[kWave], tile[kWave];     // CachedList
+    int32_t count[kWave];                        // entries drawn from the list, and in all, << 8
+    float scale[kWave], fill_w[kWave];
+};
+
+template <int K, int kList, bool kFirst>
+__device__ __forceinline__ void sample_wave_rows(const LayerArgs& g, const BeginDyn* d, const SampleArgs& a, int b, int32_t row0,
+                                                 int W, int32_t R, uint32_t key0, uint32_t key1, WaveRows<K>& w, int32_t& sum)
+{
+    const int k = a.fanout;                         // <= K
+    const int lane = opaque_lane_id();
+    const bool live = lane < W && row0 + lane < R;
+    const int32_t row = row0 + lane < R && lane < W ? row0 + lane : R - 1;
+    // ---- draw
+    RowExtent ext;
+    int32_t vi;
+    if (kFirst) {
+        vi = d->seeds[b][row];
+        ext = seed_extent(g, vi);
+        if (live) enter_seed(g, *d, b, a.tab, row, vi, ext, true);
+    } else {
+        ext = a.row_ext[row];
+        vi = a.dst_nodes[row];
+    }
+    const int blocks = (k + 3) >> 2;
+    for (int t = lane; t < kWave * blocks; t += kWave) {
+        // task t: block t / W of row t % W (tasks past the last repeat nothing of use; the shuffle wants every lane)
+        const int r = t & (W - 1), c = t >> __builtin_ctz((unsigned) W);
+        if (!__any(c < blocks)) break;
+        const uint32_t v = (uint32_t) __shfl(vi, r, kWave);
+        if (c < blocks) {
+            const Philox4 p = philox4x32_10(v, (uint32_t) c, a.layer_number, kTagNeighbor, key0, key1);
+            *reinterpret_cast<uint4*>(&w.slot[r][4 * c]) = make_uint4(p.w[0], p.w[1], p.w[2], p.w[3]);
+        }
+    }
+    const uint32_t deg = (uint32_t) (ext.end - ext.start);
+    CachedList cached = {0u, 0u, 0u, 0u};
+    if (kList != kListRow) cached = cached_list(a, ext);
+    const uint32_t m = kList == kListRow ? deg : cached.count;
+    const int cnt = m > (uint32_t) k ? k : (int) m;           // entries drawn from the list
+    const uint32_t others = deg - m, room = (uint32_t) (k - cnt);
+    const int fill = kList != kListCachedFirst ? 0 : others > room ? (int) room : (int) others;
+    const int total = cnt + fill;
+    __builtin_amdgcn_wave_barrier();
+    if (lane < W) {
+        uint32_t word[WaveRows<K>::kSlots];
+#pragma unroll
+        for (int c = 0; c < WaveRows<K>::kSlots / 4; ++c) {
+            const uint4 q = *reinterpret_cast<const uint4*>(&w.slot[lane][4 * c]);
+            word[4 * c] = q.x; word[4 * c + 1] = q.y; word[4 * c + 2] = q.z; word[4 * c + 3] = q.w;
+        }
+        // List ranks, then (kListCachedFirst) ranks among the other neighbors with the top bit set.  A row with no more
+        // entries than slots takes them all.
+        const bool draw = m > (uint32_t) k, draw_fill = kList == kListCachedFirst && others > room;
+        uint32_t chosen[WaveRows<K>::kSlots];
+#pragma unroll
+        for (int s = 0; s < WaveRows<K>::kSlots; ++s) {
+            const uint32_t j = m - (uint32_t) k + (uint32_t) s;
+            const uint32_t t = __umulhi(word[s], j + 1u);
+            bool dup = false;
+#pragma unroll
+            for (int q = 0; q < s; ++q) dup = dup || chosen[q] == t;
+            uint32_t c = draw ? (dup ? j : t) : (uint32_t) s;
+            if (kList == kListCachedFirst) {
+                // slot cnt + i draws fill entry i: a Floyd draw of `room` out of `others`
+                const uint32_t i = (uint32_t) (s - cnt);
+                const uint32_t fj = others - room + i;
+                const uint32_t ft = __umulhi(word[s], fj + 1u) | 0x80000000u;
+                bool fdup = false;
+#pragma unroll
+                for (int q = 0; q < s; ++q) fdup = fdup || chosen[q] == ft;
+                if (s >= cnt) c = draw_fill ? (fdup ? fj | 0x80000000u : ft) : i | 0x80000000u;
+            }
+            chosen[s] = s < total ? c : 0xFFFFFFFFu;
+        }
+#pragma unroll
+        for (int c = 0; c < WaveRows<K>::kSlots / 4; ++c)
+            *reinterpret_cast<uint4*>(&w.slot[lane][4 * c]) = make_uint4(chosen[4 * c], chosen[4 * c + 1], chosen[4 * c + 2], chosen[4 * c + 3]);
+        w.start[lane] = ext.start;
+        if (kList == kListCachedFirst) { w.end[lane] = ext.end; w.fill_w[lane] = fill_weight(a, others, fill); }
+        if (kList != kListRow) {
+            w.first[lane] = cached.first; w.here[lane] = cached.here; w.tile[lane] = cached.tile;
+            w.scale[lane] = cached_scale(a, m, cnt);
+        }
+        w.count[lane] = live ? cnt | total << 8 : 0;
+    }
+    if (live) {
+        a.s_cnt[row] = total;
+        a.row_eligible[row] = (int32_t) m;
+        a.src_nodes[row] = vi;
+        sum += total;
+    }
+    __builtin_amdgcn_wave_barrier();
+
+    // ---- fetch
+    const int items = W * k;
+    const uint32_t inv_k = 65535u / (uint32_t) k + 1u;          // j / k = j * inv_k >> 16, exact for j < 4096
+    for (int j0 = 0; j0 < items; j0 += kWave * kFetch) {
+        int r[kFetch], pos[kFetch];
+        bool mine[kFetch], is_fill[kFetch];
+        int64_t place[kFetch];
+#pragma unroll
+        for (int i = 0; i < kFetch; ++i) {
+            const int j = j0 + i * kWave + lane;
+            const int q = j < items ? j : 0;
+            r[i] = (int) ((uint32_t) q * inv_k >> 16);
+            const int s = q - r[i] * k;
+            const int counts = w.count[r[i]];
+            mine[i] = j < items && s < counts >> 8;
+            is_fill[i] = kList == kListCachedFirst && s >= (counts & 255);
+            const uint32_t rank = w.slot[r[i]][s];
+            int p = 0;
+#pragma unroll
+            for (int c = 0; c < WaveRows<K>::kSlots / 4; ++c) {
+                const uint4 o = *reinterpret_cast<const uint4*>(&w.slot[r[i]][4 * c]);
+                p += (o.x < rank ? 1 : 0) + (o.y < rank ? 1 : 0) + (o.z < rank ? 1 : 0) + (o.w < rank ? 1 : 0);
+            }
+            pos[i] = p;
+            place[i] = 0;
+            if (kList == kListRow) {
+                if (mine[i]) place[i] = w.start[r[i]] + (int64_t) rank;
+            } else if (mine[i]) {
+                place[i] = (int64_t) (w.first[r[i]] + rank);
+                if (is_fill[i]) {
+                    place[i] = uncached_entry(a, RowExtent{w.start[r[i]], w.end[r[i]]}, rank & 0x7FFFFFFFu);
+                } else if (rank >= w.here[r[i]]) {              // rare: the row crosses a tile
+                    place[i] = later_tile(a, CachedList{w.first[r[i]], w.here[r[i]], 0u, w.tile[r[i]]}, rank);
+                }
+            }
+        }
+        uint32_t u[kFetch], e[kFetch];
+        float inv_pc[kFetch];
+#pragma unroll
+        for (int i = 0; i < kFetch; ++i) u[i] = (uint32_t) (kList == kListRow || is_fill[i] ? a.indices : a.s_nodes)[place[i]];
+#pragma unroll
+        for (int i = 0; i < kFetch; ++i) {
+            if (!mine[i]) u[i] = 0u;
+            e[i] = kFirst ? 0u : a.tab.entry[u[i]];
+            inv_pc[i] = kList == kListRow ? 1.0f : a.node_inv_pc[u[i]];
+        }
+#pragma unroll
+        for (int i = 0; i < kFetch; ++i) {
+            if (!mine[i]) continue;
+            int32_t out = (int32_t) u[i];
+            if (!kFirst && a.tab.current(e[i])) out = -1 - (int32_t) a.tab.local(e[i]);
+            else mark_node(a, u[i]);
+            const int64_t at = (int64_t) (row0 + r[i]) * k + pos[i];
+            a.s_nbr[at] = out;
+            if (kList != kListRow) a.s_w[at] = is_fill[i] ? w.fill_w[r[i]] : inv_pc[i] * w.scale[r[i]];
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Blocks of four waves: rows block * 4 * W .. of the batch's layer, whose sampled neighbors are summed for the union step.
+template <int K, int kList, bool kFirst>
+__device__ __forceinline__ void sample_block_rows(const LayerArgs& g, const BeginDyn* d, const SampleArgs& a, int b, int32_t block,
+                                                  int W, int32_t R, uint32_t key0, uint32_t key1, WaveRows<K>* w, int32_t* smem)
+{
+    const int wave = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
+    const int32_t row0 = (block * (kBlock / kWave) + wave) * W;
+    int32_t sum = 0;
+    if (row0 < R) sample_wave_rows<K, kList, kFirst>(g, d, a, b, row0, W, R, key0, key1, w[wave], sum);
+    sum = block_sum(sum, smem);
+    if (threadIdx.x == 0) a.sums_rows[block] = sum;
+}
+
+template <int K, int kList>
+__global__ void __launch_bounds__(kBlock) k_sample_rows(LayerArgs g, int W, int relabel_blocks)
+{
+    // the last relabel_blocks blocks finish the previous layer's block instead (see relabel_body); they are
+    // dispatched after this layer's rows, whose dependent loads set the length of the launch
+    __shared__ int32_t smem[kBlock / kWave + 1];
+    __shared__ WaveRows<K> rows[kBlock / kWave];
+    const int32_t nblocks = (int32_t) gridDim.x - relabel_blocks;
+    if ((int32_t) blockIdx.x >= nblocks) {
+        relabel_body(bind_finish(g, (int) blockIdx.y, false), (int32_t) blockIdx.x - nblocks, relabel_blocks);
         return;
     }
     const SampleArgs a = bind_sample(g, (int) blockIdx.y);
     const int32_t R = a.st->num_dst[a.layer_index];
-    const int k = a.fanout;                         // <= KMAX
+    for (int32_t block = (int32_t) blockIdx.x; (int64_t) block * (kBlock / kWave) * W < R; block += nblocks)
+        sample_block_rows<K, kList, false>(g, nullptr, a, (int) blockIdx.y, block, W, R, a.st->key0, a.st->key1, rows, smem);
+}
+
+// The first layer of a mini-batch, in the launch that enters its seeds.
+template <int K, int kList>
+__global__ void __launch_bounds__(kBlock) k_sample_first(LayerArgs g, BeginDyn d, int W)
+{
+    __shared__ int32_t smem[kBlock / kWave + 1];
+    __shared__ WaveRows<K> rows[kBlock / kWave];
+    const int b = (int) blockIdx.y;
+    const int32_t R = d.num_seeds[b];
+    if (blockIdx.x == 0 && threadIdx.x == 0) begin_state(g, d, b);
+    if ((int64_t) blockIdx.x * (kBlock / kWave) * W >= R) return;
+    const SampleArgs a = bind_sample(g, b, d.stamp[b], d.cache_gen[b]);
+    sample_block_rows<K, kList, true>(g, &d, a, b, (int32_t) blockIdx.x, W, R, d.key0[b], d.key1[b], rows, smem);
+}
+
+// ---------------------------------------------------------------------------
+// Direct layers with fan-outs above 16: a wave per row, one slot per lane.
+template <int kList>
+__global__ void __launch_bounds__(kBlock) k_sample_wide(LayerArgs g, int relabel_blocks)
+{
+    __shared__ int32_t smem[kBlock / kWave + 1];
+    const int32_t nblocks = (int32_t) gridDim.x - relabel_blocks;
+    if ((int32_t) blockIdx.x >= nblocks) {
+        relabel_body(bind_finish(g, (int) blockIdx.y, false), (int32_t) blockIdx.x - nblocks, relabel_blocks);
+        return;
+    }
+    const SampleArgs a = bind_sample(g, (int) blockIdx.y);
+    const int32_t R = a.st->num_dst[a.layer_index];
     const uint32_t key0 = a.st->key0, key1 = a.st->key1;
-    const int32_t* list = kInduced ? a.s_nodes : a.indices;
-    for (int64_t row = (int64_t) blockIdx.x * kBlock + threadIdx.x; row < R; row += nblocks * kBlock) {
+    constexpr int kRows = kBlock / kWave;
+    for (int32_t block = (int32_t) blockIdx.x; (int64_t) block * kRows < R; block += nblocks) {
+        const int k = a.fanout;
+        const int s = opaque_lane_id();
+        const int32_t my_row = block * kRows + (int32_t) (threadIdx.x >> 6);
+        const bool live = my_row < R;
+        const int32_t row = live ? my_row : R - 1;
         const RowExtent ext = a.row_ext[row];
-        const uint32_t v = (uint32_t) a.dst_nodes[row];
-        int64_t base = ext.start;
-        uint32_t m = (uint32_t) (ext.end - ext.start);
-        if (kInduced) {
-            m = 0;
-            if (ext.end > ext.start) {
-                const ChunkRec rs = a.srec[ext.start >> 6];
-                const ChunkRec re = a.srec[ext.end >> 6];
-                const uint32_t p0 = rs.before + (uint32_t) __popcll(rs.flags & bits_below(ext.start));
-                const uint32_t p1 = re.before + (uint32_t) __popcll(re.flags & bits_below(ext.end));
-                base = (int64_t) p0;
-                m = p1 - p0;
-            }
+        const int32_t vi = a.dst_nodes[row];
+        const uint32_t v = (uint32_t) vi, deg = (uint32_t) (ext.end - ext.start);
+        CachedList cached = {0u, 0u, 0u, 0u};
+        if (kList != kListRow) cached = cached_list(a, ext);
+        const uint32_t m = kList == kListRow ? deg : cached.count;
+        const int cnt = m > (uint32_t) k ? k : (int) m;           // entries drawn from the list
+        const uint32_t others = deg - m, room = (uint32_t) (k - cnt);
+        const int fill = kList != kListCachedFirst ? 0 : others > room ? (int) room : (int) others;
+        // run the draw with a safe size in every lane, then keep it only where it applies
+        uint32_t val;
+        int pos;
+        floyd_in_group<kWave>(m > (uint32_t) k ? m : (uint32_t) k + 1u, k, k, key0, key1, a.layer_number, v, s, &val, &pos);
+        if (m <= (uint32_t) k) { val = (uint32_t) s; pos = s; }
+        const bool is_fill = kList == kListCachedFirst && s >= cnt;
+        if (kList == kListCachedFirst && __any(fill > 0)) {
+            // the shortfall: slots cnt, cnt + 1, ... of the row draw from its entries outside the cache; lane i draws the
+            // i-th of them, lane cnt + i emits it
+            uint32_t fval;
+            int fpos;
+            floyd_in_group<kWave>(others > room ? others : room + 1u, (int) room, k, key0, key1, a.layer_number, v, s, &fval, &fpos, cnt);
+            if (others <= room) { fval = (uint32_t) s; fpos = s; }
+            const int from = s >= cnt ? s - cnt : 0;
+            const uint32_t f = (uint32_t) __shfl((int) fval, from, kWave);
+            const int fp = __shfl(fpos, from, kWave);
+            if (is_fill) { val = f; pos = cnt + fp; }
         }
-        const int cnt = m > (uint32_t) k ? k : (int) m;
-        uint32_t chosen[KMAX];
-#pragma unroll
-        for (int s = 0; s < KMAX; ++s) chosen[s] = s < cnt ? (uint32_t) s : 0xFFFFFFFFu;     // m <= k: take all
-        if (m > (uint32_t) k) {
-            // slot s of (layer, node) is word s & 3 of the Philox block with counter word s >> 2
-            uint32_t word[KMAX];
-#pragma unroll
-            for (int c = 0; c < KMAX / 4; ++c) {
-                if (4 * c < k) {
-                    const Philox4 r = philox4x32_10(v, (uint32_t) c, a.layer_number, kTagNeighbor, key0, key1);
-                    word[4 * c] = r.w[0]; word[4 * c + 1] = r.w[1]; word[4 * c + 2] = r.w[2]; word[4 * c + 3] = r.w[3];
-                } else {
-                    word[4 * c] = word[4 * c + 1] = word[4 * c + 2] = word[4 * c + 3] = 0u;
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < KMAX; ++s) {
-                if (s < k) {
-                    const uint32_t j = m - (uint32_t) k + (uint32_t) s;
-                    const uint32_t t = __umulhi(word[s], j + 1u);
-                    bool dup = false;
-#pragma unroll
-                    for (int q = 0; q < s; ++q) dup = dup || chosen[q] == t;
-                    chosen[s] = dup ? j : t;
-                }
-            }
+        if (live && s < cnt + fill) {
+            int64_t place;
+            if (is_fill)                  place = uncached_entry(a, ext, val);
+            else if (kList == kListRow)   place = ext.start + val;
+            else if (val >= cached.here)  place = later_tile(a, cached, val);
+            else                          place = (int64_t) cached.first + val;
+            const uint32_t u = (uint32_t) (kList == kListRow || is_fill ? a.indices : a.s_nodes)[place];
+            const int64_t at = (int64_t) row * k + pos;
+            if (kList != kListRow) a.s_w[at] = is_fill ? fill_weight(a, others, fill) : a.node_inv_pc[u] * cached_scale(a, m, cnt);
+            a.s_nbr[at] = mark_if_new(a, u);
         }
-        // entries of the chosen ranks, all in flight together
-        uint32_t u[KMAX];
-#pragma unroll
-        for (int s = 0; s < KMAX; ++s) u[s] = s < cnt ? (uint32_t) list[base + (int64_t) chosen[s]] : 0u;
-        float wgt[KMAX];
-        unsigned long long first[KMAX];
-#pragma unroll
-        for (int s = 0; s < KMAX; ++s) {
-            wgt[s] = 1.0f;
-            first[s] = kEmptySlot;
-            if (s < cnt) {
-                if (kInduced) wgt[s] = a.node_inv_pc[u[s]];
-                first[s] = a.slots[hash_start(u[s], a.hshift)];
-            }
+        if (live && s == 0) {
+            a.s_cnt[row] = cnt + fill;
+            a.row_eligible[row] = (int32_t) m;
+            a.src_nodes[row] = vi;
         }
-        // Section 3.4: coefficient p^C_u * k / min(k, N_C(v)), weight = 1 / coefficient (fp32 from the table on)
-        const float scale = !kInduced ? 1.0f
-                          : (a.wmode == GNS_W_UNBIASED) ? ((float) m / (float) (cnt > 0 ? cnt : 1))
-                                                        : ((float) cnt / (float) k);
-#pragma unroll
-        for (int s = 0; s < KMAX; ++s) {
-            if (s < cnt) {
-                int pos = 0;
-#pragma unroll
-                for (int q = 0; q < KMAX; ++q) pos += chosen[q] < chosen[s] ? 1 : 0;
-                // local id if the node has one already (first probe in hand), else mark it as a new src node
-                int32_t out;
-                const unsigned long long f = first[s];
-                if ((uint32_t) f == u[s] && f != kEmptySlot) {
-                    out = -1 - (int32_t) (f >> 32);
-                } else {
-                    const int32_t local = f == kEmptySlot ? -1 : hash_lookup(a.slots, a.hmask, a.hshift, u[s]);
-                    if (local >= 0) {
-                        out = -1 - local;
-                    } else {
-                        mark_node(a, u[s]);
-                        out = (int32_t) u[s];
-                    }
-                }
-                a.s_nbr[row * k + pos] = out;
-                a.s_w[row * k + pos] = kInduced ? wgt[s] * scale : 1.0f;
-            }
-        }
-        a.s_cnt[row] = cnt;
-        a.row_eligible[row] = (int32_t) m;
+        const int32_t sum = block_sum(live && s == 0 ? cnt + fill : 0, smem);
+        if (threadIdx.x == 0) a.sums_rows[block] = sum;
     }
 }
 
@@ -284,7 +478,7 @@ __global__ void __launch_bounds__(kBlock) k_plan_count(LayerArgs g, int relabel_
     __shared__ int32_t smem[kBlock / kWave + 1];
     const int64_t ntiles = (int64_t) gridDim.x - relabel_blocks;
     if ((int64_t) blockIdx.x >= ntiles) {
-        relabel_body(bind_finish(g, (int) blockIdx.y, false), (int64_t) blockIdx.x - ntiles, relabel_blocks);
+        relabel_body(bind_finish(g, (int) blockIdx.y, false), (int32_t) ((int64_t) blockIdx.x - ntiles), relabel_blocks);
         return;
     }
     const SampleArgs a = bind_sample(g, (int) blockIdx.y);
@@ -393,7 +587,7 @@ __device__ __forceinline__ void flag_chunk_set(const SampleArgs& a, const uint32
 // 16 bytes).  Every wave takes an equal, contiguous share of the work list.
 // One work list: every wave takes an equal, contiguous share of its Q chunks.
 template <int kMode>
-__device__ __forceinline__ void flag_work_list(const SampleArgs& a, const uint32_t* lds32, int64_t Q, int use_plan)
+__device__ __forceinline__ void flag_work_list(const SampleArgs& a, const uint32_t* lds32, int64_t Q)
 {
     if (Q <= 0 || a.num_entries <= 0) return;
     const int waves_per_block = (int) (blockDim.x >> 6);
@@ -411,7 +605,7 @@ __device__ __forceinline__ void flag_work_list(const SampleArgs& a, const uint32
         // Lane l holds the chunk id of work-list entry c0 + l; lanes past the share repeat its last
         // entry (their result is not stored), so that every unrolled set is made of valid chunks.
         const int64_t q = c0 + (lane < here ? lane : here - 1);
-        const int32_t my_chunk = use_plan ? a.plan_desc[q] : (int32_t) q;
+        const int32_t my_chunk = a.plan_desc[q];
         const bool careful = last_is_partial && __ballot((int64_t) my_chunk == last_chunk) != 0ull;
         uint32_t lo = 0, hi = 0;
         for (int sub = 0; sub < here; sub += kFlagUnroll) {                            // scalar bounds
@@ -423,14 +617,13 @@ __device__ __forceinline__ void flag_work_list(const SampleArgs& a, const uint32
 }
 
 // kMode 1 / 2: the cache bitmap / its coarse companion is first copied into dynamic LDS (rounded up to
-// 16 bytes).  count > 0: the work lists of the group's `count` mini-batches, one after the other (they read
-// the same cache, so the bitmap is staged once); count == 0: every aligned chunk of the CSR entry array,
-// with the template's own cache pointers (the pass a cache draw runs over the whole graph).
+// 16 bytes).  The work lists of the group's `count` mini-batches are taken one after the other (they read
+// the same cache, so the bitmap is staged once).
 template <int kMode>
-__global__ void k_flag_chunks(LayerArgs g, int count, int64_t all_chunks)
+__global__ void k_flag_chunks(LayerArgs g, int count)
 {
     extern __shared__ uint4 lds_bitmap16[];
-    SampleArgs a = count > 0 ? bind_sample(g, 0) : g.s;
+    SampleArgs a = bind_sample(g, 0);
     if (kMode == 1 || kMode == 2) {
         const uint4* src = reinterpret_cast<const uint4*>(kMode == 1 ? a.cache_bitmap : a.coarse_bitmap);
         const int64_t n16 = ((kMode == 1 ? a.bitmap_words : a.coarse_words) + 1) / 2;
@@ -451,10 +644,9 @@ __global__ void k_flag_chunks(LayerArgs g, int count, int64_t all_chunks)
         __syncthreads();
     }
     const uint32_t* lds32 = reinterpret_cast<const uint32_t*>(lds_bitmap16);
-    if (count == 0) { flag_work_list<kMode>(a, lds32, all_chunks, 0); return; }
     for (int b = 0; b < count; ++b) {
         if (b > 0) a = bind_sample(g, b);
-        flag_work_list<kMode>(a, lds32, (int64_t) a.st->plan_chunks, 1);
+        flag_work_list<kMode>(a, lds32, (int64_t) a.st->plan_chunks);
     }
 }
 
@@ -637,21 +829,18 @@ __device__ __forceinline__ void select_row(const SampleArgs& a, int64_t row, boo
     if (live && s == 0) {
         a.s_cnt[row] = total;
         a.row_eligible[row] = (int32_t) m;
+        a.src_nodes[row] = vi;
     }
 }
 
 // G lanes per dst row, one flag word per lane and step.  Hub rows (listed when their nodes joined
 // the batch) would keep the rest of their wave waiting, so for G < 64 the row blocks skip them
 // and hub_blocks further blocks give each of them a whole wave (64 * kHubWords words per step).
-// Block order: hub blocks, row blocks, relabel blocks of the previous layer.
+// Block order: hub blocks, row blocks.
 template <int G>
-__global__ void __launch_bounds__(kBlock) k_select_rows(LayerArgs g, int relabel_blocks, int hub_blocks)
+__global__ void __launch_bounds__(kBlock) k_select_rows(LayerArgs g, int hub_blocks)
 {
-    const int64_t own_blocks = (int64_t) gridDim.x - relabel_blocks;
-    if ((int64_t) blockIdx.x >= own_blocks) {
-        relabel_body(bind_finish(g, (int) blockIdx.y, false), (int64_t) blockIdx.x - own_blocks, relabel_blocks);
-        return;
-    }
+    const int64_t own_blocks = (int64_t) gridDim.x;
     const SampleArgs a = bind_sample(g, (int) blockIdx.y);
     const int wave_in_block = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
     if ((int) blockIdx.x < hub_blocks) {
@@ -690,9 +879,9 @@ __global__ void __launch_bounds__(kBlock) k_select_rows(LayerArgs g, int relabel
     }
 }
 
-// The cache pointers of the template are those of generation `cache_gen`; kernels that serve mini-batches
-// shift them to the generation each batch reads.
-static void fill_sample_template_gen(gns_ctx* c, int layer_index, int cache_gen, SampleArgs* out)
+// The cache pointers of the template are those of generation 0; the kernels shift them to the generation each
+// batch reads.
+void fill_sample_template(gns_ctx* c, int layer_index, SampleArgs* out)
 {
     const Layout& L = c->lay;
     SampleArgs& a = *out;
@@ -702,18 +891,12 @@ static void fill_sample_template_gen(gns_ctx* c, int layer_index, int cache_gen,
     a.fanout = c->config.fanout[layer_index];
     a.wmode = c->config.wmode;
     a.policy = c->config.policy[layer_index];
-    a.num_nodes = c->graph.num_nodes;
-    a.indptr = c->graph.indptr;
     a.indices = c->graph.indices;
-    const int gen = cache_gen;
+    const int gen = 0;
     a.node_inv_pc = c->uses_cache ? cache_ptr<float>(c, L.node_pc, gen) : nullptr;
     a.cache_bitmap = cache_ptr<uint64_t>(c, L.cache_bitmap, gen);
-    a.cache_prefix = cache_ptr<int32_t>(c, L.cache_prefix, gen);
-    a.cache_size = c->config.cache_size;
-    a.hmask = L.hash_cap - 1;
-    a.hshift = 32u - (uint32_t) __builtin_ctz(L.hash_cap);
     a.num_entries = c->graph.num_entries;
-    a.flags = c->uses_cache ? cache_ptr<uint64_t>(c, L.edge_flags, gen) : nullptr;
+    a.flags = c->uses_cache && c->config.flag_mode == GNS_FLAGS_PER_BATCH ? cache_ptr<uint64_t>(c, L.edge_flags, gen) : nullptr;
     a.bitmap_words = L.words;
     a.coarse_bitmap = L.coarse_shift ? cache_ptr<uint64_t>(c, L.coarse_bitmap, gen) : nullptr;
     a.coarse_words = L.coarse_words;
@@ -721,25 +904,22 @@ static void fill_sample_template_gen(gns_ctx* c, int layer_index, int cache_gen,
     const bool induced = c->uses_cache && c->config.flag_mode == GNS_FLAGS_PER_CACHE;
     a.srec = induced ? cache_ptr<ChunkRec>(c, L.srec, gen) : nullptr;
     a.s_nodes = induced ? cache_ptr<int32_t>(c, L.s_nodes, gen) : nullptr;
+    a.s_count = induced ? cache_ptr<int32_t>(c, L.s_count, gen) : nullptr;
+    a.s_tile_shift = L.s_tile_shift;
 }
 
-void fill_sample_template(gns_ctx* c, int layer_index, SampleArgs* out)
-{
-    fill_sample_template_gen(c, layer_index, 0, out);
-}
-
-static void launch_flag_kernel(gns_ctx* c, const LayerArgs& a, int count, int64_t all_chunks, hipStream_t s)
+static void launch_flag_kernel(gns_ctx* c, const LayerArgs& a, int count, hipStream_t s)
 {
     const size_t lds_bytes = (size_t) ((c->lay.words + 1) / 2) * 16;
     const size_t coarse_bytes = (size_t) ((c->lay.coarse_words + 1) / 2) * 16;
     if (lds_bytes <= c->lds_bitmap_limit)
-        hipLaunchKernelGGL((k_flag_chunks<1>), dim3((unsigned) c->num_cus), dim3(1024), lds_bytes, s, a, count, all_chunks);
+        hipLaunchKernelGGL((k_flag_chunks<1>), dim3((unsigned) c->num_cus), dim3(1024), lds_bytes, s, a, count);
     else if (c->lay.coarse_shift > 0 && coarse_bytes <= c->lds_bitmap_limit)
-        hipLaunchKernelGGL((k_flag_chunks<2>), dim3((unsigned) c->num_cus), dim3(1024), coarse_bytes, s, a, count, all_chunks);
+        hipLaunchKernelGGL((k_flag_chunks<2>), dim3((unsigned) c->num_cus), dim3(1024), coarse_bytes, s, a, count);
     else if (c->lay.coarse_shift > 0 && !getenv("GNS_NO_COARSE_L2"))
     {
         const int per_cu = getenv("GNS_FLAG_BLOCKS_PER_CU") ? atoi(getenv("GNS_FLAG_BLOCKS_PER_CU")) : 2;
-        hipLaunchKernelGGL((k_flag_chunks<3>), dim3((unsigned) (c->num_cus * per_cu)), dim3(kBlock), 0, s, a, count, all_chunks);
+        hipLaunchKernelGGL((k_flag_chunks<3>), dim3((unsigned) (c->num_cus * per_cu)), dim3(kBlock), 0, s, a, count);
     }
     else
     {
@@ -747,19 +927,82 @@ static void launch_flag_kernel(gns_ctx* c, const LayerArgs& a, int count, int64_
         // memory system gives scattered reads; a grid that filled the chip would keep the kernels of other
         // streams out for the whole pass
         const int per_cu = getenv("GNS_FLAG_BLOCKS_PER_CU") ? atoi(getenv("GNS_FLAG_BLOCKS_PER_CU")) : 2;
-        hipLaunchKernelGGL((k_flag_chunks<0>), dim3((unsigned) (c->num_cus * per_cu)), dim3(kBlock), 0, s, a, count, all_chunks);
+        hipLaunchKernelGGL((k_flag_chunks<0>), dim3((unsigned) (c->num_cus * per_cu)), dim3(kBlock), 0, s, a, count);
     }
 }
 
-// GNS_FLAGS_PER_CACHE: one pass over every aligned chunk of the CSR entry array, for the copy of the cache
-// structures a draw is filling.
-hipError_t launch_flag_all_entries(gns_ctx* c, int cache_gen, hipStream_t s)
+bool direct_layer(const gns_config& config, int layer_index)
 {
+    return config.policy[layer_index] == GNS_UNIFORM || config.flag_mode == GNS_FLAGS_PER_CACHE;
+}
+
+bool first_layer_enters_seeds(const gns_config& config)
+{
+    return direct_layer(config, 0) && config.fanout[0] <= 16;
+}
+
+// Rows per wave of the two-stage sampler: as many as leave sixteen waves for every CU at the layer's worst-case number of
+// rows (real batches have a third of that and more), a power of two between 4 and 64.  Layers of 4 x 12,600 rows, fan-out
+// 10: 37 us with 64 rows per wave, 27 us with 16.
+static int wave_rows(const Group& g, int layer_index)
+{
+    const gns_ctx* c = g.ctx[0];
+    const int64_t rows = c->lay.rows[layer_index] * g.count;
+    int W = 4;
+    while (W < kWave && (int64_t) W * c->num_cus * 16 < rows) W *= 2;
+    return W;
+}
+
+int rows_per_sum(const Group& g, int layer_index)
+{
+    const gns_ctx* c = g.ctx[0];
+    if (!direct_layer(c->config, layer_index)) return 0;
+    return kBlock / kWave * (c->config.fanout[layer_index] <= 16 ? wave_rows(g, layer_index) : 1);
+}
+
+// f(kList): calls it with the kind of list a direct layer draws from as a compile-time constant.
+template <typename F>
+static void with_list(const gns_ctx* c, int layer_index, F&& f)
+{
+    const int policy = c->config.policy[layer_index];
+    if (policy == GNS_UNIFORM)         f(std::integral_constant<int, kListRow>());
+    else if (policy == GNS_CACHE_ONLY) f(std::integral_constant<int, kListCached>());
+    else                               f(std::integral_constant<int, kListCachedFirst>());
+}
+
+// f(K): the smallest unroll length that holds the fan-out.
+template <typename F>
+static void with_unroll(int fanout, F&& f)
+{
+    if (fanout <= 5)       f(std::integral_constant<int, 5>());
+    else if (fanout <= 10) f(std::integral_constant<int, 10>());
+    else                   f(std::integral_constant<int, 16>());
+}
+
+hipError_t launch_first_layer(const Group& g, const BeginDyn& d, hipStream_t s)
+{
+    gns_ctx* c = g.ctx[0];
     LayerArgs a;
-    memset(&a, 0, sizeof(a));
-    fill_sample_template_gen(c, 0, cache_gen, &a.s);
-    launch_flag_kernel(c, a, 0, (c->graph.num_entries + 63) / 64, s);
+    fill_first_args(g, &a);
+    // the grid is sized for the largest batch: the same launch serves every replay
+    const int rows_per_block = rows_per_sum(g, 0);
+    const dim3 grid((unsigned) ((c->config.max_seeds + rows_per_block - 1) / rows_per_block), (unsigned) g.count);
+    with_unroll(a.s.fanout, [&](auto K) {
+        with_list(c, 0, [&](auto kList) {
+            hipLaunchKernelGGL((k_sample_first<decltype(K)::value, decltype(kList)::value>), grid, dim3(kBlock), 0, s, a, d,
+                               rows_per_block / (kBlock / kWave));
+        });
+    });
     return hipGetLastError();
+}
+
+// The fixed argument block of a group's first launch (k_batch_begin or k_sample_first).
+void fill_first_args(const Group& g, LayerArgs* out)
+{
+    fill_group_args(g, out);
+    set_group_layer(g, 0, out);
+    fill_sample_template(g.ctx[0], 0, &out->s);
+    fill_finish_template(g, 0, &out->f);
 }
 
 // One layer's sampler launches for a group of mini-batches.  The previous layer's relabel rides in front
@@ -775,13 +1018,36 @@ hipError_t launch_sample_layer(const Group& g, int layer_index, hipStream_t s)
     fill_sample_template(c, layer_index, &a.s);
     int rl = 0;
     if (layer_index > 0) {
-        fill_finish_template(c, layer_index - 1, &a.f);
+        fill_finish_template(g, layer_index - 1, &a.f);
         rl = relabel_grid(c, layer_index - 1);
     }
     const unsigned gy = (unsigned) g.count;
 
     const int64_t rows_max = L.rows[layer_index];
-    const int G = (a.s.fanout <= 8) ? 8 : (a.s.fanout <= 16) ? 16 : 64;
+    const dim3 tb(kBlock);
+    const int policy = c->config.policy[layer_index];
+    if (direct_layer(c->config, layer_index)) {
+        StageTimer t(c, GNS_STAGE_SELECT, s, policy == GNS_CACHE_ONLY);
+        const int rows_per_block = rows_per_sum(g, layer_index);
+        // sized for the worst case; batches are much smaller, so from four blocks per CU on a block takes several turns
+        int64_t blocks = (rows_max + rows_per_block - 1) / rows_per_block;
+        const bool narrow = a.s.fanout <= 16;
+        const int64_t cap = (int64_t) c->num_cus * (narrow ? 4 : 16);
+        if (blocks > cap) blocks = cap;
+        const dim3 grid((unsigned) (blocks + rl), gy);
+        with_list(c, layer_index, [&](auto kList) {
+            if (!narrow) {
+                hipLaunchKernelGGL((k_sample_wide<decltype(kList)::value>), grid, tb, 0, s, a, rl);
+                return;
+            }
+            with_unroll(a.s.fanout, [&](auto K) {
+                hipLaunchKernelGGL((k_sample_rows<decltype(K)::value, decltype(kList)::value>), grid, tb, 0, s, a,
+                                   rows_per_block / (kBlock / kWave), rl);
+            });
+        });
+        return hipGetLastError();
+    }
+    const int G = a.s.fanout <= 8 ? 8 : a.s.fanout <= 16 ? 16 : 64;
     const int64_t rows_per_block = kBlock / G;
     int64_t row_blocks = (rows_max + rows_per_block - 1) / rows_per_block;
     // One step of rows per wave where that fits: rows differ a lot in cost, and with more blocks
@@ -789,61 +1055,26 @@ hipError_t launch_sample_layer(const Group& g, int layer_index, hipStream_t s)
     const int64_t cap = (int64_t) c->num_cus * 64;
     if (row_blocks > cap) row_blocks = cap;
     if (row_blocks < 1) row_blocks = 1;
-    const dim3 tb(kBlock);
 
-#define GNS_LAUNCH_BY_G(KERNEL, RL, ...)                                                         \
-    do {                                                                                         \
-        if (G == 8)       hipLaunchKernelGGL((KERNEL<8>), rb, tb, 0, s, a, (RL), ##__VA_ARGS__);  \
-        else if (G == 16) hipLaunchKernelGGL((KERNEL<16>), rb, tb, 0, s, a, (RL), ##__VA_ARGS__); \
-        else              hipLaunchKernelGGL((KERNEL<64>), rb, tb, 0, s, a, (RL), ##__VA_ARGS__); \
-    } while (0)
-
-    // fan-outs up to 16: one row per lane, for UNIFORM layers and for CACHE_ONLY layers that have the induced subgraph
-    const int policy = c->config.policy[layer_index];
-    const bool induced = policy == GNS_CACHE_ONLY && c->config.flag_mode == GNS_FLAGS_PER_CACHE;
-    // (one row per lane needs many rows to fill the chip: 64 rows make one wave)
-    const int64_t lane_rows_min = getenv("GNS_LANE_ROWS_MIN") ? atoll(getenv("GNS_LANE_ROWS_MIN")) : 262144;
-    const bool enough_rows = induced || rows_max * g.count >= lane_rows_min;
-    if (a.s.fanout <= 16 && (policy == GNS_UNIFORM || induced) && enough_rows && !getenv("GNS_NO_LANE_SAMPLER")) {
-        StageTimer t(c, GNS_STAGE_SELECT, s, induced);
-        int64_t lane_blocks = (rows_max + kBlock - 1) / kBlock;
-        if (lane_blocks > cap) lane_blocks = cap;
-        const dim3 lb((unsigned) (lane_blocks + rl), gy);
-        if (induced) {
-            if (a.s.fanout <= 8) hipLaunchKernelGGL((k_sample_lane<8, true>), lb, tb, 0, s, a, rl);
-            else                 hipLaunchKernelGGL((k_sample_lane<16, true>), lb, tb, 0, s, a, rl);
-        } else {
-            if (a.s.fanout <= 8) hipLaunchKernelGGL((k_sample_lane<8, false>), lb, tb, 0, s, a, rl);
-            else                 hipLaunchKernelGGL((k_sample_lane<16, false>), lb, tb, 0, s, a, rl);
-        }
-        return hipGetLastError();
+    // CACHE_ONLY and CACHE_FIRST without the induced subgraph: plan -> flag -> select
+    {
+        StageTimer t(c, GNS_STAGE_PLAN, s);
+        const unsigned plan_blocks = (unsigned) ((rows_max + kPlanTile - 1) / kPlanTile);
+        hipLaunchKernelGGL(k_plan_count, dim3(plan_blocks + (unsigned) rl, gy), tb, 0, s, a, rl);
+        hipLaunchKernelGGL(k_plan_expand, dim3(plan_blocks, gy), tb, 0, s, a);
     }
-
-    if (policy == GNS_UNIFORM) {
-        const dim3 rb((unsigned) (row_blocks + rl), gy);
-        GNS_LAUNCH_BY_G(k_sample_uniform, rl);
-        return hipGetLastError();
-    }
-
-    // CACHE_ONLY: (plan -> flag ->) select
-    if (c->config.flag_mode == GNS_FLAGS_PER_BATCH) {
-        {
-            StageTimer t(c, GNS_STAGE_PLAN, s);
-            const unsigned plan_blocks = (unsigned) ((rows_max + kPlanTile - 1) / kPlanTile);
-            hipLaunchKernelGGL(k_plan_count, dim3(plan_blocks + (unsigned) rl, gy), tb, 0, s, a, rl);
-            hipLaunchKernelGGL(k_plan_expand, dim3(plan_blocks, gy), tb, 0, s, a);
-        }
-        rl = 0;                          // done with the plan kernel
+    {
         StageTimer t(c, GNS_STAGE_FLAG, s);
-        launch_flag_kernel(c, a, g.count, 0, s);
+        launch_flag_kernel(c, a, g.count, s);
     }
     StageTimer t(c, GNS_STAGE_SELECT, s);
     // hub rows get dedicated waves (the count lives on the device; the waves stride over the list)
     const int hub_blocks = (G < 64) ? (int) (rows_max / (kBlock / kWave) < (int64_t) c->num_cus * 2
                                                  ? rows_max / (kBlock / kWave) + 1 : (int64_t) c->num_cus * 2) : 0;
-    const dim3 rb((unsigned) (row_blocks + rl + hub_blocks), gy);
-    GNS_LAUNCH_BY_G(k_select_rows, rl, hub_blocks);
-#undef GNS_LAUNCH_BY_G
+    const dim3 rb((unsigned) (row_blocks + hub_blocks), gy);
+    if (G == 8)       hipLaunchKernelGGL(k_select_rows<8>, rb, tb, 0, s, a, hub_blocks);
+    else if (G == 16) hipLaunchKernelGGL(k_select_rows<16>, rb, tb, 0, s, a, hub_blocks);
+    else              hipLaunchKernelGGL(k_select_rows<64>, rb, tb, 0, s, a, hub_blocks);
     return hipGetLastError();
 }
 

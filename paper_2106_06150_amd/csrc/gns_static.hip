@@ -1,7 +1,7 @@
 // gns_sample_blocks_static: gns_sample_blocks for callers that cannot allocate device memory (code under
 // HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).  The per-batch scratch that a
 // context otherwise keeps in the workspace the caller allocated -- device counters, the frontier mark
-// bitmap, the batch hash map, row extents, hub list, sampler scratch, scan partials -- lives in one fixed
+// bitmaps, the node table, row extents, hub list, sampler scratch, scan partials -- lives in one fixed
 // array of the library instead.  The kernels are the ones gns_sample_blocks launches; they are handed the
 // array's device address where they are otherwise handed the workspace.
 #include <stdio.h>
@@ -44,10 +44,14 @@ gns_status static_scratch_setup(gns_ctx* root)
         }
         g_scratch_ptr[dev] = ptr;
     }
-    if (root->lay.shared_begin > kStaticScratchBytes) return GNS_OK;   // too big: the entry point says so
+    // too big even without the node table: the entry point says so
+    if (root->lay.shared_begin > kStaticScratchBytes && !root->lay.static_table) return GNS_OK;
     gns_ctx* child = nullptr;
     const gns_status st = make_child(root, g_scratch_ptr[dev], false, &child);   // eager launches, no capture
     if (st != GNS_OK) return st;
+    // a node table that does not fit the array lies in the root context's workspace (offsets are relative to the array)
+    if (root->lay.static_table)
+        child->lay.table = (size_t) (root->ws + root->lay.static_table - static_cast<char*>(g_scratch_ptr[dev]));
     root->static_child = child;
     return GNS_OK;
 }
@@ -82,7 +86,6 @@ extern "C" gns_status gns_sample_blocks_static(gns_ctx* ctx, uint64_t seed, cons
     // The array keeps whatever the last call on this GPU left (possibly of another context with another
     // layout): everything that must start clean is cleared here, with fill kernels on the caller's stream.
     if (st == GNS_OK) {
-        c->hash_parity = 0;
         c->batch_id = 0;
         c->bad_reported = 0;
         const hipError_t e = init_batch_scratch(c, s);
@@ -95,13 +98,13 @@ extern "C" gns_status gns_sample_blocks_static(gns_ctx* ctx, uint64_t seed, cons
         g.ctx[0] = c;
         g.blocks[0] = blocks;
         BeginDyn dyn;
+        c->stamp = 1;                     // the table has just been cleared
         fill_begin_dyn(g, &seed, &seeds_dev, &num_seeds, &dyn);
         st = enqueue_batch(g, dyn, s);
     }
     if (st == GNS_OK) {
         c->batch_id = 1;
-        hipError_t e = hipMemcpyAsync(c->h_state, c->d_state, sizeof(DeviceState), hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        const hipError_t e = hipStreamSynchronize(s);
         if (e != hipSuccess) st = ctx_fail(c, GNS_EHIP, "gns_sample_blocks_static wait", e);
     }
     if (st == GNS_OK) {

@@ -1191,3 +1191,34 @@ def test_directed_adjacency():
                 full_parity(gns, cache_seed=14, epoch=trial, batch_seed=15 + trial, seeds=seeds)
         finally:
             gns.close()
+
+
+@pytest.mark.parametrize("spins", ["0", "256"])
+@pytest.mark.parametrize("fanouts,policies,flag_mode", [((16, 11, 1), (U, CF, C), 1), ((6, 10, 5), (CF, U, C), 1), ((17, 16), (U, C), 1),
+                                                        ((20, 40), (CF, C), 1), ((5, 15), (CF, CF), 0)])
+def test_sampler_unrolls_and_counts_taken_from_the_bitmap(spins, fanouts, policies, flag_mode, monkeypatch):
+    """Fan-outs at the edges of the two-stage sampler's unroll lengths and above them; union blocks that do not wait
+    for one another's counts (no polls at all) and that do."""
+    monkeypatch.setenv("GNS_UNION_SPINS", spins)
+    ip, ix = _small(n=30000, avg=14, seed=29, hub=40)
+    gns = GpuGns(ip, ix, _feat(ip.numel() - 1, 4), fanouts=fanouts, policies=policies, cache_size=900, max_seeds=300, flag_mode=flag_mode)
+    try:
+        for trial, count in enumerate((300, 1, 67)):
+            full_parity(gns, cache_seed=8, epoch=trial, batch_seed=50 + trial, seeds=synth.uniform_seed_batch(30000, count, 20 + trial))
+    finally:
+        gns.close()
+
+
+def test_node_table_is_cleared_when_its_stamps_run_out():
+    """Mini-batches are told apart in the node table by a stamp of few bits: more mini-batches than stamps."""
+    ip, ix = random_symmetric_csr(300000, 6, np.random.default_rng(3))
+    ip, ix = torch.from_numpy(ip), torch.from_numpy(ix)
+    gns = GpuGns(ip, ix, None, fanouts=(20, 16), policies=(U, U), cache_size=0, max_seeds=2000)
+    try:
+        seeds = synth.uniform_seed_batch(300000, 40, 5).cuda()
+        for b in range(8300):                              # 19 bits of local id leave 13 for the stamp
+            B.gns_sample_blocks_async(gns.ctx, b, seeds, gns.blocks.array)
+        B.gns_sample_blocks_wait(gns.ctx, gns.blocks.array)
+        full_parity(gns, cache_seed=0, epoch=0, batch_seed=9, seeds=seeds.cpu())
+    finally:
+        gns.close()
