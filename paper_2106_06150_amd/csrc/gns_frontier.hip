@@ -196,6 +196,8 @@ __device__ __forceinline__ int32_t union_offset(const FinishArgs& a, uint32_t ta
         }
         if ((uint32_t) (x >> 32) != tag) {
             const uint32_t counted = count_tile(a, t);
+            // the marks have been read before the tag is looked at once more: had they begun to go, it would be out
+            asm volatile("s_waitcnt vmcnt(0)" ::"v"(counted) : "memory");
             x = __hip_atomic_load(&a.tile_sums[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if ((uint32_t) (x >> 32) != tag) x = counted;
         }
