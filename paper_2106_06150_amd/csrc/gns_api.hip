@@ -314,7 +314,8 @@ static hipError_t events_create(gns_ctx* c)
 // The address under which kernels write the context's pinned host mirror.
 static hipError_t host_mirror_setup(gns_ctx* c)
 {
-    memset(c->h_state, 0, sizeof(DeviceState));
+    memset(c->h_state, 0, 2 * sizeof(DeviceState));
+    c->h_draw = c->h_state + 1;
     void* p = nullptr;
     const hipError_t e = hipHostGetDevicePointer(&p, c->h_state, 0);
     c->h_state_dev = static_cast<DeviceState*>(p);
@@ -470,7 +471,7 @@ gns_status make_child(gns_ctx* root, void* workspace, bool with_capture_stream, 
         if (e == hipSuccess && !c->bg) e = hipErrorOutOfMemory;
     }
     if (e == hipSuccess) {
-        e = hipHostMalloc(reinterpret_cast<void**>(&c->h_state), sizeof(DeviceState), hipHostMallocDefault);
+        e = hipHostMalloc(reinterpret_cast<void**>(&c->h_state), 2 * sizeof(DeviceState), hipHostMallocDefault);
         if (e != hipSuccess) c->h_state = nullptr;
     }
     if (e == hipSuccess) e = host_mirror_setup(c);
@@ -561,7 +562,7 @@ gns_status gns_create(gns_ctx** out_ctx, const gns_graph* graph, const gns_confi
     c->num_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     // the flag kernel may keep the whole cache bitmap in LDS (one 1024-thread block per CU)
     c->lds_bitmap_limit = prop.sharedMemPerBlock >= kLdsBitmapBytes + 1024 ? kLdsBitmapBytes : 0;
-    e = hipHostMalloc(reinterpret_cast<void**>(&c->h_state), sizeof(DeviceState), hipHostMallocDefault);
+    e = hipHostMalloc(reinterpret_cast<void**>(&c->h_state), 2 * sizeof(DeviceState), hipHostMallocDefault);
     if (e != hipSuccess) { c->h_state = nullptr; return bail(GNS_EHIP, "hipHostMalloc", e); }
     e = host_mirror_setup(c);
     if (e != hipSuccess) return bail(GNS_EHIP, "hipHostGetDevicePointer", e);

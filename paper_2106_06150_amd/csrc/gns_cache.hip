@@ -369,10 +369,10 @@ gns_status finish_pending_draw(gns_ctx* c)
 {
     const int gen = c->pending ? c->pending_gen : c->cache_gen;
     GNS_HIP_TRY(hipEventSynchronize(c->ready_event[gen]), "cache draw wait");
-    GNS_HIP_TRY(hipMemcpy(c->h_state, c->d_state, sizeof(DeviceState), hipMemcpyDeviceToHost), "cache readback");
-    if (c->h_state->draw_done_chunk < 0)
+    GNS_HIP_TRY(hipMemcpy(c->h_draw, c->d_state, sizeof(DeviceState), hipMemcpyDeviceToHost), "cache readback");
+    if (c->h_draw->draw_done_chunk < 0)
         return fail(c, GNS_ECAPACITY, "cache draw: the stream did not yield cache_size distinct nodes within the chunks an asynchronous draw enqueues", hipSuccess);
-    c->cache_draws = (int64_t) c->h_state->cut_draw + 1;
+    c->cache_draws = (int64_t) c->h_draw->cut_draw + 1;
     return GNS_OK;
 }
 
@@ -449,9 +449,9 @@ gns_status run_sample_cache(gns_ctx* c, uint64_t seed, uint64_t epoch, bool wait
         hipLaunchKernelGGL(k_cache_commit, dim3((unsigned) a.tiles), dim3(kBlock), 0, s, a);
         GNS_HIP_TRY(hipGetLastError(), "cache draw launch");
         if (wait_for_it) {
-            GNS_HIP_TRY(hipMemcpyAsync(c->h_state, c->d_state, sizeof(DeviceState), hipMemcpyDeviceToHost, s), "cache draw readback");
+            GNS_HIP_TRY(hipMemcpyAsync(c->h_draw, c->d_state, sizeof(DeviceState), hipMemcpyDeviceToHost, s), "cache draw readback");
             GNS_HIP_TRY(hipStreamSynchronize(s), "cache draw sync");
-            if (c->h_state->draw_done_chunk >= 0) break;
+            if (c->h_draw->draw_done_chunk >= 0) break;
         }
     }
 

@@ -134,8 +134,10 @@ struct gns_ctx {
     char* shared_ws;                 // base for the shared sections (the root context's workspace)
     gns_ctx* root;                   // owner of the cache; this for a context made by gns_create
     gns::DeviceState* d_state;       // device
-    gns::DeviceState* h_state;       // pinned host mirror, written by the last kernel of every mini-batch and by cache draws
+    gns::DeviceState* h_state;       // pinned host mirror, written by the last kernel of every mini-batch
     gns::DeviceState* h_state_dev;   //   its address for kernels
+    gns::DeviceState* h_draw;        // pinned: where cache draws and the walk probability read their outcome back (mini-batches
+                                     //   of this context may be in flight meanwhile, so not the mirror they write)
     bool uses_cache;
     bool cache_valid;
     int cache_gen;                   // root only: which copy of the cache block the mini-batches read

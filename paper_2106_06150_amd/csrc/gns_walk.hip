@@ -364,15 +364,15 @@ gns_status run_walk_probability(gns_ctx* c, const int32_t* train_nodes, int64_t 
     hipLaunchKernelGGL(k_walk_scan_phase2, dim3(1), dim3(kBlock), 0, s, tile_sums, tile_nz, tiles, c->d_state);
     hipLaunchKernelGGL(k_walk_scan_phase3, dim3((unsigned) tiles), dim3(kBlock), 0, s, cur, n, tile_sums, prefix, c->d_state);
     e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(c->h_state, c->d_state, sizeof(DeviceState), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(c->h_draw, c->d_state, sizeof(DeviceState), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return ctx_fail(c, GNS_EHIP, "walk probability", e);
-    if (c->h_state->walk_error == 1) return ctx_fail(c, GNS_EINVAL, "a training node id lies outside [0, num_nodes)");
-    if (c->h_state->walk_error) return ctx_fail(c, GNS_ECAPACITY, "the walk probability does not fit in 62 bits: lower scale_log2");
-    if (c->h_state->walk_total == 0) return ctx_fail(c, GNS_EINVAL, "the walk probability is zero everywhere");
+    if (c->h_draw->walk_error == 1) return ctx_fail(c, GNS_EINVAL, "a training node id lies outside [0, num_nodes)");
+    if (c->h_draw->walk_error) return ctx_fail(c, GNS_ECAPACITY, "the walk probability does not fit in 62 bits: lower scale_log2");
+    if (c->h_draw->walk_total == 0) return ctx_fail(c, GNS_EINVAL, "the walk probability is zero everywhere");
     root->prob_weights = cur;
-    root->prob_total = c->h_state->walk_total;
-    root->prob_support = c->h_state->walk_support;
+    root->prob_total = c->h_draw->walk_total;
+    root->prob_support = c->h_draw->walk_support;
     root->prob_valid = true;
     return GNS_OK;
 }
