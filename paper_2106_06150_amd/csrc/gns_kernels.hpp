@@ -144,7 +144,7 @@ struct LayerArgs {
     BatchSlot b[kMaxGroup];
 };
 
-// What changes from one replay of a group's launch sequence to the next (arguments of the first kernel).
+// What the first kernel publishes for the others: the group's seeds, keys, ids.
 struct BeginDyn {
     const int32_t* seeds[kMaxGroup];
     int32_t num_seeds[kMaxGroup];

@@ -556,6 +556,30 @@ def test_bad_seed_in_an_earlier_batch_is_still_reported():
         gns.close()
 
 
+def test_a_stream_that_is_being_captured_is_refused():
+    """Stamps and batch ids are arguments of the launches, so a mini-batch cannot be replayed: the call says so, enqueues
+    nothing, and the context goes on as before."""
+    ip, ix = _small(n=2000)
+    gns = GpuGns(ip, ix, None, fanouts=(4, 3), policies=(U, U), cache_size=0, max_seeds=48)
+    try:
+        seeds = synth.uniform_seed_batch(ip.numel() - 1, 48, 70).cuda()
+        x = torch.zeros(64, device="cuda")
+        stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(stream):
+            graph.capture_begin()
+            x.add_(1.0)
+            with pytest.raises(B.GnsError) as e:
+                B.gns_sample_blocks_async(gns.ctx, 4, seeds, gns.blocks.array, stream)
+            graph.capture_end()
+        assert e.value.status == B.GNS_EHIP
+        B.gns_sample_blocks(gns.ctx, 4, seeds, gns.blocks.array)
+        ref = oracle.sample_blocks(ip.numpy(), ix.numpy(), None, 0, 4, seeds.cpu().numpy(), [4, 3], [U, U])
+        compare_blocks([gns.blocks.views(i) for i in range(2)], ref)
+    finally:
+        gns.close()
+
+
 def test_walk_probability_recomputed_while_batches_are_in_flight():
     """gns_cache_walk_probability invalidates the cache; mini-batches enqueued before it (on another stream,
     not yet waited for) keep the cache they were enqueued with, and the draw that follows fills the other
