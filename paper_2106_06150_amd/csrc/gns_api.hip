@@ -57,7 +57,6 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     const int64_t n = g->num_nodes;
     const int64_t C = uses_cache ? cfg->cache_size : 0;
     L.words = (n + 63) / 64;
-    L.word_tiles = (L.words + kTile - 1) / kTile;
     L.mark_tile_words = kMarkTileMin;
     // about a hundred tiles per mini-batch (measured best on the 1 M-, 2.4 M- and 111 M-node graphs: more tiles mean
     // more blocks that each add up the tile sums before them, fewer mean more new nodes per thread, one after the other)
@@ -90,10 +89,14 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     for (int i = 0; i < cfg->num_layers; ++i)
         if (!direct_layer(*cfg, i)) L.lists_hubs = true;
 
-    L.draw_chunk = C;
+    // the refusal of a draw that needs too many stream draws counts in these
+    L.draw_unit = C;
+    if (L.draw_unit < 65536) L.draw_unit = 65536;
+    if (L.draw_unit > (int64_t) 1 << 22) L.draw_unit = (int64_t) 1 << 22;
+    L.draw_chunk = first_draws(C);
     if (L.draw_chunk < 65536) L.draw_chunk = 65536;
     if (L.draw_chunk > (int64_t) 1 << 22) L.draw_chunk = (int64_t) 1 << 22;
-    L.draw_tiles = (L.draw_chunk + kTile - 1) / kTile;
+    L.draw_tiles = (L.draw_chunk + kDrawTile - 1) / kDrawTile;
     L.draw_hash_cap = pow2_at_least(2 * (uint64_t) (C + L.draw_chunk));
 
     size_t off = 0;
@@ -119,8 +122,7 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
         L.s_cnt[par] = take((size_t) L.max_rows * 4);
     }
     L.sums_rows = take((size_t) (L.max_rows / (kBlock / kWave) + 1) * 4);
-    const int64_t word_or_draw_tiles = L.word_tiles > L.draw_tiles ? L.word_tiles : L.draw_tiles;
-    L.sums_words = take((size_t) (word_or_draw_tiles + 1) * 4);
+    L.info = take(16);
     L.tile_sums = take((size_t) L.mark_tiles * 8);
     L.sums_plan = take((size_t) (L.max_rows / kBlock + 2) * 4);
     if (uses_cache) {
@@ -137,10 +139,12 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     L.shared_begin = off;
     if (L.shared_begin > GNS_STATIC_SCRATCH_BYTES && L.table <= GNS_STATIC_SCRATCH_BYTES) L.static_table = take((size_t) n * 4);
     if (uses_cache) {
-        L.draw_keys = take((size_t) L.draw_hash_cap * 4);
-        L.draw_vals = take((size_t) L.draw_hash_cap * 4);
-        L.draw_node = take((size_t) L.draw_chunk * 4);
+        L.draw_table = take((size_t) L.draw_hash_cap * 8);
         L.draw_slot = take((size_t) L.draw_chunk * 4);
+        L.draw_sums = take((size_t) L.draw_tiles * 8);
+        L.index_tiles = (L.words + kBlock - 1) / kBlock;
+        L.index_sums = take((size_t) L.index_tiles * 8);
+        if (cfg->cache_probability != GNS_PROB_WALK) L.entry_rows = take((size_t) (g->num_entries / 64 + 1) * 4);
         if (cfg->cache_probability == GNS_PROB_WALK) {
             L.walk_a = take((size_t) n * 8);
             L.walk_b = take((size_t) n * 8);
@@ -473,8 +477,12 @@ gns_status gns_create(gns_ctx** out_ctx, const gns_graph* graph, const gns_confi
     // zero the state, the mark bitmap and the cache bitmap; validate the graph
     e = init_batch_scratch(c, s);
     if (e == hipSuccess) e = launch_fill_u64(cache_ptr<unsigned long long>(c, L.cache_bitmap, 0), (size_t) L.words, 0ull, s);
+    if (e == hipSuccess && c->uses_cache) {
+        e = launch_fill_u64(ws_ptr<unsigned long long>(c, L.draw_sums), (size_t) L.draw_tiles, 0ull, s);
+        if (e == hipSuccess) e = launch_fill_u64(ws_ptr<unsigned long long>(c, L.index_sums), (size_t) L.index_tiles, 0ull, s);
+    }
     if (e != hipSuccess) return bail(GNS_EHIP, "workspace init", e);
-    int32_t* d_info = ws_ptr<int32_t>(c, L.sums_words);   // scratch, 4 ints
+    int32_t* d_info = ws_ptr<int32_t>(c, L.info);
     e = launch_count_nonzero_rows(c, s, d_info);
     if (e != hipSuccess) return bail(GNS_EHIP, "graph validation launch", e);
     int32_t info[4] = {0, 0, 0, 0};
@@ -736,6 +744,10 @@ gns_status gns_sample_blocks_group(gns_ctx* const* ctxs, int32_t count, const ui
         g.blocks[b] = blocks[b];
     }
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    // Stamp, batch id and cache copy are arguments of the launches: a replay of them would sample into the wrong ones.
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (s && hipStreamIsCapturing(s, &capturing) == hipSuccess && capturing != hipStreamCaptureStatusNone)
+        return ctx_fail(lead, GNS_EHIP, "mini-batches cannot be captured", hipErrorStreamCaptureUnsupported);
     st = group_before_cache_readers(ctxs, count, s);
     if (st != GNS_OK) return st;
     const hipError_t es = next_stamps(g, s);
@@ -744,10 +756,6 @@ gns_status gns_sample_blocks_group(gns_ctx* const* ctxs, int32_t count, const ui
     fill_begin_dyn(g, seeds, seeds_dev, num_seeds, &dyn);
     st = enqueue_batch(g, dyn, s);
     if (st != GNS_OK) return st;
-    // Stamp, batch id and cache copy are arguments of the launches: a replay of them would sample into the wrong ones.
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    if (s && hipStreamIsCapturing(s, &capturing) == hipSuccess && capturing != hipStreamCaptureStatusNone)
-        return ctx_fail(lead, GNS_EHIP, "mini-batches cannot be captured", hipErrorStreamCaptureUnsupported);
     const int nl = lead->config.num_layers;
     for (int b = 0; b < count; ++b) {
         ctxs[b]->batch_id += 1;

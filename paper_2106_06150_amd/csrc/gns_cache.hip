@@ -8,9 +8,16 @@
 // smallest stream index at which it appeared (atomicMin), which makes "draw j
 // is the first occurrence of its node" a pure function of the stream and
 // independent of thread order.  First occurrences are counted with a prefix
-// scan; the chunk in which the count reaches |C| is cut at exactly that draw.
+// sum over the blocks of one launch; the chunk in which the count reaches |C|
+// is cut at exactly that draw.
+//
+// On graphs of a million nodes a draw is a chain of small launches, so there are few: clear, then two per chunk (draw,
+// commit), then the index with the 1/p^C table; and the host looks at the outcome once, at the end, not per chunk.
+// A draw of 10 K of 1 M nodes with the mini-batch behind it: 247 us, where a launch per phase, a read-back per chunk of 64 K
+// draws and searches over all offsets took 295; 400 K of 40 M nodes: 1779 us, before 1992.
 #include "gns_internal.h"
 #include "gns_device.hpp"
+#include <string.h>
 
 namespace gns {
 
@@ -26,7 +33,7 @@ struct ValidateOut {
 
 template <typename OffT>
 __global__ void __launch_bounds__(kBlock) k_validate_graph(const void* indptr, const int32_t* indices, int64_t n,
-                                                           int64_t nnz, ValidateOut* out)
+                                                           int64_t nnz, int32_t* entry_rows, ValidateOut* out)
 {
     __shared__ int32_t smem[kBlock / kWave + 1];
     int32_t nonzero = 0;
@@ -34,6 +41,8 @@ __global__ void __launch_bounds__(kBlock) k_validate_graph(const void* indptr, c
         const int64_t b = load_off<OffT>(indptr, v), e = load_off<OffT>(indptr, v + 1);
         if (b < 0 || e < b || e > nnz || (v == 0 && b != 0) || (v == n - 1 && e != nnz)) { out->bad_offsets = 1; continue; }
         if (e > b) ++nonzero;
+        if (entry_rows)
+            for (int64_t i = (b + 63) >> 6; (i << 6) < e; ++i) entry_rows[i] = (int32_t) v;
         int32_t prev = -1;
         for (int64_t q = b; q < e; ++q) {
             const int32_t u = indices[q];
@@ -54,32 +63,35 @@ hipError_t launch_count_nonzero_rows(gns_ctx* c, hipStream_t s, int32_t* d_out)
     hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t*>(d_out), 4, 0u, s);
     if (e != hipSuccess) return e;
     ValidateOut* out = reinterpret_cast<ValidateOut*>(d_out);
+    int32_t* entry_rows = c->lay.entry_rows ? ws_ptr<int32_t>(c, c->lay.entry_rows) : nullptr;
     if (c->graph.indptr_is_i64)
         hipLaunchKernelGGL((k_validate_graph<int64_t>), dim3((unsigned) blocks), dim3(kBlock), 0, s, c->graph.indptr,
-                           c->graph.indices, n, c->graph.num_entries, out);
+                           c->graph.indices, n, c->graph.num_entries, entry_rows, out);
     else
         hipLaunchKernelGGL((k_validate_graph<int32_t>), dim3((unsigned) blocks), dim3(kBlock), 0, s, c->graph.indptr,
-                           c->graph.indices, n, c->graph.num_entries, out);
+                           c->graph.indices, n, c->graph.num_entries, entry_rows, out);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
 struct DrawArgs {
     DeviceState* st;
+    DeviceState* host;         // pinned: draw_done_chunk and cut_draw are left here too
     const void* indptr;
     int64_t n;
     uint64_t nnz;
+    const int32_t* entry_rows; // row that owns entry 64 * i, or null
     uint32_t key0, key1, epoch;
     uint64_t j0;               // stream index of the chunk's first draw
     int32_t count;             // draws in this chunk
-    uint32_t* keys;            // draw hash: node ids (0xFFFFFFFF = empty)
-    uint32_t* first;           // draw hash: smallest stream index seen for the node
+    unsigned long long* table; // draw hash: node in the upper half, smallest stream index seen for it below (~0 = empty)
     uint32_t hmask, hshift;
-    int32_t* draw_node;        // [chunk]
     int32_t* draw_slot;        // [chunk] slot of the node in the draw hash
-    int32_t* sums;             // [tiles + 1]
-    int32_t tiles;
+    unsigned long long* sums;  // [tiles] (tag, first occurrences of the tile), see sum_before
+    uint32_t tag;
+    int32_t spins;
     uint64_t* cache_bitmap;
+    int64_t words;
     int64_t cache_size;
     int32_t chunk_index;       // chunks of one draw are numbered from 0
 };
@@ -92,22 +104,23 @@ __device__ __forceinline__ bool chunk_stands_down(const DrawArgs& a)
     return done >= 0 && done < a.chunk_index;
 }
 
-__global__ void k_cache_draw_reset(DeviceState* st)
+// What a draw begins with: an empty bitmap, an empty hash, nothing drawn.
+__global__ void __launch_bounds__(kBlock) k_cache_clear(DrawArgs a)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        st->draw_distinct = 0;
-        st->draw_done_chunk = -1;
-        st->chunk_distinct = 0;
-        st->chunk_limit = 0;
-        st->chunk_final = 0;
+    const int64_t t = (int64_t) blockIdx.x * kBlock + threadIdx.x, stride = (int64_t) gridDim.x * kBlock;
+    if (t == 0) {
+        a.st->draw_distinct[0] = 0;
+        a.st->draw_done_chunk = -1;
+        __hip_atomic_store(&a.host->draw_done_chunk, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
+    for (int64_t i = t; i < a.words; i += stride) a.cache_bitmap[i] = 0ull;
+    for (int64_t i = t; i <= (int64_t) a.hmask; i += stride) a.table[i] = ~0ull;
 }
 
-// the unique row i with indptr[i] <= e < indptr[i+1]
+// the unique row i in [lo, hi) with indptr[i] <= e < indptr[i+1]
 template <typename OffT>
-__device__ __forceinline__ int64_t owner_row(const void* indptr, int64_t n, int64_t e)
+__device__ __forceinline__ int64_t owner_row(const void* indptr, int64_t lo, int64_t hi, int64_t e)
 {
-    int64_t lo = 0, hi = n;
     while (hi - lo > 1) {
         const int64_t mid = lo + ((hi - lo) >> 1);
         if (load_off<OffT>(indptr, mid) <= e) lo = mid; else hi = mid;
@@ -115,6 +128,8 @@ __device__ __forceinline__ int64_t owner_row(const void* indptr, int64_t n, int6
     return lo;
 }
 
+// Bound by the chain of reads that finds an entry's row: over the whole of the offsets 20 reads on a graph of 1 M nodes and
+// 26 on one of 40 M, the last dozen of them to memory.  The table of every 64th entry's row leaves the few rows in between.
 template <typename OffT>
 __global__ void __launch_bounds__(kBlock) k_cache_draw(DrawArgs a)
 {
@@ -124,143 +139,125 @@ __global__ void __launch_bounds__(kBlock) k_cache_draw(DrawArgs a)
     const Philox4 r = philox4x32_10((uint32_t) j, (uint32_t) (j >> 32), a.epoch, kTagCache, a.key0, a.key1);
     const uint64_t r64 = ((uint64_t) r.w[1] << 32) | (uint64_t) r.w[0];
     const uint64_t e = __umul64hi(r64, a.nnz);                      // uniform CSR entry
-    const uint32_t node = (uint32_t) owner_row<OffT>(a.indptr, a.n, (int64_t) e);
+    int64_t lo = 0, hi = a.n;
+    if (a.entry_rows) {
+        const uint64_t i = e >> 6, last = (a.nnz - 1) >> 6;
+        lo = a.entry_rows[i];
+        if (i < last) hi = (int64_t) a.entry_rows[i + 1] + 1;
+    }
+    const uint32_t node = (uint32_t) owner_row<OffT>(a.indptr, lo, hi, (int64_t) e);
+    const unsigned long long mine = ((unsigned long long) node << 32) | (uint32_t) j;
     uint32_t h = hash_start(node, a.hshift);
     for (uint32_t probe = 0; probe <= a.hmask; ++probe) {
-        const uint32_t old = atomicCAS(&a.keys[h], 0xFFFFFFFFu, node);
-        if (old == 0xFFFFFFFFu || old == node) break;
+        const unsigned long long old = atomicCAS(&a.table[h], ~0ull, mine);
+        if (old == ~0ull) break;
+        if ((uint32_t) (old >> 32) == node) {
+            if (old > mine) atomicMin(&a.table[h], mine);
+            break;
+        }
         h = (h + 1) & a.hmask;
     }
-    atomicMin(&a.first[h], (uint32_t) j);
-    a.draw_node[t] = (int32_t) node;
     a.draw_slot[t] = (int32_t) h;
 }
 
-__device__ __forceinline__ int32_t is_first_occurrence(const DrawArgs& a, int32_t t)
-{
-    if (t >= a.count) return 0;
-    return a.first[a.draw_slot[t]] == (uint32_t) (a.j0 + (uint64_t) t) ? 1 : 0;
-}
-
-__global__ void __launch_bounds__(kBlock) k_cache_flags_phase1(DrawArgs a)
-{
-    __shared__ int32_t smem[kBlock / kWave + 1];
-    if (chunk_stands_down(a)) return;
-    const int32_t base = (int32_t) blockIdx.x * kTile;
-    int32_t sum = 0;
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) sum += is_first_occurrence(a, base + i * kBlock + (int32_t) threadIdx.x);
-    sum = block_sum(sum, smem);
-    if (threadIdx.x == 0) a.sums[blockIdx.x] = sum;
-}
-
-__global__ void __launch_bounds__(kBlock) k_cache_flags_phase2(DrawArgs a)
-{
-    __shared__ int32_t smem[kBlock / kWave + 1];
-    if (chunk_stands_down(a)) return;
-    int32_t carry = 0;
-    for (int32_t base = 0; base < a.tiles; base += kBlock) {
-        const int32_t i = base + (int32_t) threadIdx.x;
-        const int32_t v = (i < a.tiles) ? a.sums[i] : 0;
-        int32_t total;
-        const int32_t ex = block_exclusive_scan(v, smem, &total);
-        if (i < a.tiles) a.sums[i] = carry + ex;
-        carry += total;
-    }
-    if (threadIdx.x == 0) {
-        // how many of this chunk's first occurrences the cache still takes, and whether that completes it
-        const int64_t need = a.cache_size - (int64_t) a.st->draw_distinct;
-        const int32_t limit = (int32_t) ((int64_t) carry < need ? (int64_t) carry : need);
-        const int32_t final = (int64_t) carry >= need ? 1 : 0;
-        a.st->chunk_distinct = carry;
-        a.st->chunk_limit = limit;
-        a.st->chunk_final = final;
-        a.st->draw_distinct += limit;
-        if (final) a.st->draw_done_chunk = a.chunk_index;
-    }
-}
-
+// The draws of a chunk that are the first of their node, counted in stream order, enter the cache until it is full.
 __global__ void __launch_bounds__(kBlock) k_cache_commit(DrawArgs a)
 {
     __shared__ int32_t smem[kBlock / kWave + 1];
+    constexpr int kPer = kDrawTile / kBlock;
     if (chunk_stands_down(a)) return;
-    const int32_t limit = a.st->chunk_limit, is_final = a.st->chunk_final;
-    const int32_t base = (int32_t) blockIdx.x * kTile;
-    const int32_t t0 = base + (int32_t) threadIdx.x * kItems;
-    int32_t f[kItems];
+    const int32_t tile = (int32_t) blockIdx.x;
+    const int32_t t0 = tile * kDrawTile + (int32_t) threadIdx.x * kPer;
+    // node of draw t if it is the node's first, else -1
+    auto first_of = [&](int32_t t) -> int32_t {
+        if (t >= a.count) return -1;
+        const unsigned long long x = a.table[a.draw_slot[t]];
+        return (uint32_t) x == (uint32_t) (a.j0 + (uint64_t) t) ? (int32_t) (x >> 32) : -1;
+    };
+    int32_t node[kPer];
     int32_t sum = 0;
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) { f[i] = is_first_occurrence(a, t0 + i); sum += f[i]; }
+    for (int i = 0; i < kPer; ++i) { node[i] = first_of(t0 + i); sum += node[i] >= 0 ? 1 : 0; }
     int32_t total;
-    int32_t g = a.sums[blockIdx.x] + block_exclusive_scan(sum, smem, &total);
+    const int32_t off = block_exclusive_scan(sum, smem, &total);
+    if (threadIdx.x == 0) publish_sum(a.sums, tile, a.tag, (uint32_t) total);
+    const int32_t before = sum_before(a.sums, a.tag, tile, a.spins, smem, [&](int32_t t) {
+        uint32_t c = 0;
+        for (int32_t q = t * kDrawTile; q < (t + 1) * kDrawTile; ++q) c += first_of(q) >= 0 ? 1u : 0u;
+        return c;
+    });
+    // how many more the cache takes; this chunk's blocks read one of the two counts, its last block writes the other
+    const int64_t have = (int64_t) a.st->draw_distinct[a.chunk_index & 1];
+    const int64_t need = a.cache_size - have;
+    int64_t g = (int64_t) before + off;
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        if (f[i]) {
-            if (g < limit) {
-                const uint32_t node = (uint32_t) a.draw_node[t0 + i];
-                atomicOr(reinterpret_cast<unsigned long long*>(&a.cache_bitmap[node >> 6]), 1ull << (node & 63u));
-                if (is_final && g == limit - 1) a.st->cut_draw = a.j0 + (uint64_t) (t0 + i);
+    for (int i = 0; i < kPer; ++i) {
+        if (node[i] < 0) continue;
+        if (g < need) {
+            atomicOr(reinterpret_cast<unsigned long long*>(&a.cache_bitmap[node[i] >> 6]), 1ull << (node[i] & 63));
+            if (g == need - 1) {
+                a.st->cut_draw = a.j0 + (uint64_t) (t0 + i);
+                __hip_atomic_store(&a.host->cut_draw, (unsigned long long) (a.j0 + (uint64_t) (t0 + i)), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_SYSTEM);
             }
-            ++g;
+        }
+        ++g;
+    }
+    if (tile == (int32_t) gridDim.x - 1 && threadIdx.x == 0) {
+        const int64_t all = (int64_t) before + total;
+        a.st->draw_distinct[(a.chunk_index + 1) & 1] = (int32_t) (have + (all < need ? all : need));
+        if (all >= need) {
+            a.st->draw_done_chunk = a.chunk_index;
+            __hip_atomic_store(&a.host->draw_done_chunk, a.chunk_index, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
 }
 
 // ---------------------------------------------------------------------------
-// Rank index and ascending node list from the finished bitmap.
+// From the finished bitmap: the rank index, the ascending node list, and Section 3.4 for every node of the cache:
+// p_u = deg(u)/nnz, p^C_u = 1 - (1 - p_u)^|C| (expm1/log1p keep a tiny p_u exact), stored as 1/p^C_u in fp32.  The table
+// is indexed by node id; entries of nodes outside the current cache are stale and never read.
 struct IndexArgs {
     const uint64_t* bitmap;
     int64_t words;
-    int32_t* sums;
-    int32_t tiles;
+    unsigned long long* sums;  // [tiles] (tag, nodes of the tile), see sum_before
+    uint32_t tag;
+    int32_t spins;
     int32_t* word_prefix;
     int32_t* cache_nodes;
+    int64_t cache_size;
+    const void* prob_prefix;
+    int64_t prob_total;
+    float* node_inv_pc;
 };
 
-__global__ void __launch_bounds__(kBlock) k_cache_index_phase1(IndexArgs a)
+// A tile is kPer words per thread.  Latency-bound: one word per thread and many blocks while their number stays small
+// enough for every block to add up the sums of the others, then the nodes of the tile over all threads.
+template <typename OffT, int kPer>
+__global__ void __launch_bounds__(kBlock) k_cache_index(IndexArgs a)
 {
     __shared__ int32_t smem[kBlock / kWave + 1];
-    const int64_t base = (int64_t) blockIdx.x * kTile;
+    const int32_t tile = (int32_t) blockIdx.x;
+    const int64_t w0 = ((int64_t) tile * kBlock + threadIdx.x) * kPer;
+    uint64_t word[kPer];
     int32_t sum = 0;
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        const int64_t w = base + (int64_t) i * kBlock + threadIdx.x;
-        if (w < a.words) sum += __popcll(a.bitmap[w]);
-    }
-    sum = block_sum(sum, smem);
-    if (threadIdx.x == 0) a.sums[blockIdx.x] = sum;
-}
-
-__global__ void __launch_bounds__(kBlock) k_cache_index_phase2(IndexArgs a)
-{
-    __shared__ int32_t smem[kBlock / kWave + 1];
-    int32_t carry = 0;
-    for (int32_t base = 0; base < a.tiles; base += kBlock) {
-        const int32_t i = base + (int32_t) threadIdx.x;
-        const int32_t v = (i < a.tiles) ? a.sums[i] : 0;
-        int32_t total;
-        const int32_t ex = block_exclusive_scan(v, smem, &total);
-        if (i < a.tiles) a.sums[i] = carry + ex;
-        carry += total;
-    }
-}
-
-__global__ void __launch_bounds__(kBlock) k_cache_index_phase3(IndexArgs a)
-{
-    __shared__ int32_t smem[kBlock / kWave + 1];
-    const int64_t base = (int64_t) blockIdx.x * kTile;
-    const int64_t w0 = base + (int64_t) threadIdx.x * kItems;
-    uint64_t word[kItems];
-    int32_t sum = 0;
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) {
+    for (int i = 0; i < kPer; ++i) {
         word[i] = (w0 + i < a.words) ? a.bitmap[w0 + i] : 0ull;
         sum += __popcll(word[i]);
     }
     int32_t total;
-    int32_t pos = a.sums[blockIdx.x] + block_exclusive_scan(sum, smem, &total);
+    const int32_t off = block_exclusive_scan(sum, smem, &total);
+    if (threadIdx.x == 0) publish_sum(a.sums, tile, a.tag, (uint32_t) total);
+    const int32_t before = sum_before(a.sums, a.tag, tile, a.spins, smem, [&](int32_t t) {
+        uint32_t c = 0;
+        const int64_t first = (int64_t) t * kBlock * kPer;
+        for (int64_t w = first; w < first + kBlock * kPer && w < a.words; ++w) c += (uint32_t) __popcll(a.bitmap[w]);
+        return c;
+    });
+    int32_t pos = before + off;
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) {
+    for (int i = 0; i < kPer; ++i) {
         if (w0 + i < a.words) {
             a.word_prefix[w0 + i] = pos;
             uint64_t rest = word[i];
@@ -271,22 +268,23 @@ __global__ void __launch_bounds__(kBlock) k_cache_index_phase3(IndexArgs a)
             }
         }
     }
+    __syncthreads();                                     // the tile's part of the list is read back by other threads
+    for (int32_t i = (int32_t) threadIdx.x; i < total; i += kBlock) {
+        const int32_t u = a.cache_nodes[before + i];
+        const int64_t deg = load_off<OffT>(a.prob_prefix, (int64_t) u + 1) - load_off<OffT>(a.prob_prefix, u);
+        const double p = (double) deg / (double) a.prob_total;
+        const double pc = (p >= 1.0) ? 1.0 : -expm1((double) a.cache_size * log1p(-p));
+        a.node_inv_pc[u] = (float) (1.0 / pc);
+    }
 }
 
-// Section 3.4 for every node of the cache: p_u = deg(u)/nnz, p^C_u = 1 - (1 - p_u)^|C|
-// (expm1/log1p keep a tiny p_u exact), stored as 1/p^C_u in fp32.  The table is indexed by node id; entries of nodes
-// outside the current cache are stale and never read.
 template <typename OffT>
-__global__ void __launch_bounds__(kBlock) k_cache_pc(const int32_t* cache_nodes, int64_t C, const void* indptr,
-                                                     int64_t nnz, float* node_inv_pc)
+static void launch_cache_index(const IndexArgs& a, hipStream_t s)
 {
-    const int64_t i = (int64_t) blockIdx.x * kBlock + threadIdx.x;
-    if (i >= C) return;
-    const int32_t u = cache_nodes[i];
-    const int64_t deg = load_off<OffT>(indptr, (int64_t) u + 1) - load_off<OffT>(indptr, u);
-    const double p = (double) deg / (double) nnz;
-    const double pc = (p >= 1.0) ? 1.0 : -expm1((double) C * log1p(-p));
-    node_inv_pc[u] = (float) (1.0 / pc);
+    auto grid = [&](int per) { return dim3((unsigned) ((a.words + (int64_t) kBlock * per - 1) / ((int64_t) kBlock * per))); };
+    if (a.words <= 1024 * kBlock / 4)      hipLaunchKernelGGL((k_cache_index<OffT, 1>), grid(1), dim3(kBlock), 0, s, a);
+    else if (a.words <= 1024 * kBlock * 4) hipLaunchKernelGGL((k_cache_index<OffT, 4>), grid(4), dim3(kBlock), 0, s, a);
+    else                                   hipLaunchKernelGGL((k_cache_index<OffT, 16>), grid(16), dim3(kBlock), 0, s, a);
 }
 
 // Coarse companion of the cache bitmap: bit g of the result is set iff some node of
@@ -324,7 +322,7 @@ static gns_status fail(gns_ctx* c, gns_status st, const char* what, hipError_t e
         if (e__ != hipSuccess) return fail(c, GNS_EHIP, what, e__);    \
     } while (0)
 
-constexpr int kAsyncChunks = 8;     // chunks an asynchronous draw enqueues (a typical cache needs one or two)
+constexpr int kAsyncUnits = 8;      // draws an asynchronous draw enqueues, in Layout::draw_unit (a typical cache needs one or two)
 
 // Records, on the stream every context of the family last used, the end of what may still read the copy
 // of the cache block that stops being current now.
@@ -369,10 +367,33 @@ gns_status finish_pending_draw(gns_ctx* c)
 {
     const int gen = c->pending ? c->pending_gen : c->cache_gen;
     GNS_HIP_TRY(hipEventSynchronize(c->ready_event[gen]), "cache draw wait");
-    GNS_HIP_TRY(hipMemcpy(c->h_draw, c->d_state, sizeof(DeviceState), hipMemcpyDeviceToHost), "cache readback");
     if (c->h_draw->draw_done_chunk < 0)
         return fail(c, GNS_ECAPACITY, "cache draw: the stream did not yield cache_size distinct nodes within the chunks an asynchronous draw enqueues", hipSuccess);
     c->cache_draws = (int64_t) c->h_draw->cut_draw + 1;
+    return GNS_OK;
+}
+
+// Everything a finished bitmap determines: index, weights, coarse bitmap, induced subgraph, the cached rows' features.
+static gns_status fill_cache(gns_ctx* c, int gen, const IndexArgs& x, bool i64, hipStream_t s)
+{
+    const Layout& L = c->lay;
+    if (i64) launch_cache_index<int64_t>(x, s);
+    else     launch_cache_index<int32_t>(x, s);
+    GNS_HIP_TRY(hipGetLastError(), "cache index launch");
+    if (L.coarse_shift > 0) {
+        const unsigned cb = (unsigned) ((L.coarse_words + kBlock / kWave - 1) / (kBlock / kWave));
+        hipLaunchKernelGGL(k_cache_coarse, dim3(cb), dim3(kBlock), 0, s, x.bitmap, (int64_t) L.words, (int) L.coarse_shift,
+                           cache_ptr<uint64_t>(c, L.coarse_bitmap, gen), (int64_t) L.coarse_words);
+        GNS_HIP_TRY(hipGetLastError(), "coarse bitmap launch");
+    }
+    if (c->config.flag_mode == GNS_FLAGS_PER_CACHE) GNS_HIP_TRY(launch_build_induced(c, gen, s), "induced subgraph");
+    if (c->graph.feat_dim > 0) {
+        // fill the device table of cached feature rows (slot order) straight from the full store
+        const int32_t* fill_nodes = x.cache_nodes;
+        const int32_t fill_count = (int32_t) x.cache_size;
+        float* fill_out = cache_ptr<float>(c, L.cache_feat, gen);
+        GNS_HIP_TRY(launch_gather(&c, 1, &fill_nodes, &fill_count, &fill_out, -1, s), "cache feature fill");
+    }
     return GNS_OK;
 }
 
@@ -393,110 +414,104 @@ gns_status run_sample_cache(gns_ctx* c, uint64_t seed, uint64_t epoch, bool wait
             GNS_HIP_TRY(hipStreamWaitEvent(s, m->gen_event[gen][i], 0), "wait for the readers of the old cache");
         m->gen_event_used[gen] = 0;
     }
-    hipLaunchKernelGGL(k_cache_draw_reset, dim3(1), dim3(kWave), 0, s, c->d_state);
-    GNS_HIP_TRY(launch_fill_u64(reinterpret_cast<unsigned long long*>(bitmap), (size_t) L.words, 0ull, s), "clear cache bitmap");
-    GNS_HIP_TRY(launch_fill_u32(ws_ptr<uint32_t>(c, L.draw_keys), L.draw_hash_cap, 0xFFFFFFFFu, s), "clear draw keys");
-    GNS_HIP_TRY(launch_fill_u32(ws_ptr<uint32_t>(c, L.draw_vals), L.draw_hash_cap, 0xFFFFFFFFu, s), "clear draw vals");
-
     // The draw picks a uniform integer below the total mass and takes the node whose prefix interval
     // holds it: the CSR offsets for Eq. (1), the prefix of the walk weights for the other probability.
     const bool walk = c->config.cache_probability == GNS_PROB_WALK;
     const void* prob_prefix = walk ? static_cast<const void*>(ws_ptr<int64_t>(c, L.prob_prefix)) : c->graph.indptr;
     const uint64_t prob_total = walk ? (uint64_t) c->prob_total : (uint64_t) c->graph.num_entries;
+    const bool i64 = walk || c->graph.indptr_is_i64 != 0;
+    auto next_tag = [&]() { return ++c->draw_tag ? c->draw_tag : ++c->draw_tag; };
     DrawArgs a;
+    memset(&a, 0, sizeof(a));
     a.st = c->d_state;
+    a.host = c->h_state_dev + 1;                        // h_draw, as kernels see it
     a.indptr = prob_prefix;
     a.n = c->graph.num_nodes;
     a.nnz = prob_total;
+    a.entry_rows = walk ? nullptr : ws_ptr<int32_t>(c, L.entry_rows);
     a.key0 = (uint32_t) seed;
     a.key1 = (uint32_t) (seed >> 32);
     a.epoch = (uint32_t) epoch;
-    a.keys = ws_ptr<uint32_t>(c, L.draw_keys);
-    a.first = ws_ptr<uint32_t>(c, L.draw_vals);
+    a.table = ws_ptr<unsigned long long>(c, L.draw_table);
     a.hmask = L.draw_hash_cap - 1;
     a.hshift = 32u - (uint32_t) __builtin_ctz(L.draw_hash_cap);
-    a.draw_node = ws_ptr<int32_t>(c, L.draw_node);
     a.draw_slot = ws_ptr<int32_t>(c, L.draw_slot);
-    a.sums = ws_ptr<int32_t>(c, L.sums_words);      // sized for max(word tiles, draw tiles)
+    a.sums = ws_ptr<unsigned long long>(c, L.draw_sums);
+    a.spins = c->union_spins;
     a.cache_bitmap = bitmap;
+    a.words = L.words;
     a.cache_size = C;
+    {
+        int64_t blocks = ((int64_t) L.draw_hash_cap + kBlock * 4 - 1) / (kBlock * 4);
+        if (blocks > (int64_t) c->num_cus * 8) blocks = (int64_t) c->num_cus * 8;
+        hipLaunchKernelGGL(k_cache_clear, dim3((unsigned) blocks), dim3(kBlock), 0, s, a);
+        GNS_HIP_TRY(hipGetLastError(), "cache draw clear");
+    }
 
     // The draw hash holds every distinct node seen so far: fewer than |C| before the final
     // chunk plus at most one chunk's worth, which is what it was sized for.  Stream indices
     // are kept in 32 bits; a cache that needs more draws than the limit is refused.  How many of a
     // chunk's first occurrences enter the cache, and whether they complete it, is decided on the device
-    // (k_cache_flags_phase2); the host only needs to know when to stop enqueuing chunks.
-    uint64_t draw_limit = 256ull * (uint64_t) C + 64ull * (uint64_t) L.draw_chunk;
+    // (k_cache_commit); the host only needs to know when to stop enqueuing chunks.
+    uint64_t draw_limit = 256ull * (uint64_t) C + 64ull * (uint64_t) L.draw_unit;
     if (draw_limit > 0xFFFFFFFFull) draw_limit = 0xFFFFFFFFull;
-    const bool i64 = walk || c->graph.indptr_is_i64 != 0;
-    const int64_t count = L.draw_chunk;
-    a.count = (int32_t) count;
-    a.tiles = (int32_t) ((count + kTile - 1) / kTile);
-    const unsigned draw_blocks = (unsigned) ((count + kBlock - 1) / kBlock);
-    for (int chunk = 0;; ++chunk) {
-        const uint64_t j0 = (uint64_t) chunk * (uint64_t) count;
-        if (j0 + (uint64_t) count > draw_limit) {
-            if (!wait_for_it) break;
-            return fail(c, GNS_ECAPACITY, "cache draw: the stream did not yield cache_size distinct nodes within the draw limit (cache_size too close to the number of nodes with neighbors)", hipSuccess);
-        }
-        if (!wait_for_it && chunk >= kAsyncChunks) break;
-        a.j0 = j0;
-        a.chunk_index = chunk;
-        if (i64) hipLaunchKernelGGL((k_cache_draw<int64_t>), dim3(draw_blocks), dim3(kBlock), 0, s, a);
-        else     hipLaunchKernelGGL((k_cache_draw<int32_t>), dim3(draw_blocks), dim3(kBlock), 0, s, a);
-        hipLaunchKernelGGL(k_cache_flags_phase1, dim3((unsigned) a.tiles), dim3(kBlock), 0, s, a);
-        hipLaunchKernelGGL(k_cache_flags_phase2, dim3(1), dim3(kBlock), 0, s, a);
-        hipLaunchKernelGGL(k_cache_commit, dim3((unsigned) a.tiles), dim3(kBlock), 0, s, a);
-        GNS_HIP_TRY(hipGetLastError(), "cache draw launch");
-        if (wait_for_it) {
-            GNS_HIP_TRY(hipMemcpyAsync(c->h_draw, c->d_state, sizeof(DeviceState), hipMemcpyDeviceToHost, s), "cache draw readback");
-            GNS_HIP_TRY(hipStreamSynchronize(s), "cache draw sync");
-            if (c->h_draw->draw_done_chunk >= 0) break;
-        }
-    }
-
+    draw_limit -= draw_limit % (uint64_t) L.draw_unit;
+    const uint64_t ahead = (uint64_t) kAsyncUnits * (uint64_t) L.draw_unit;
+    const uint64_t stop = wait_for_it || draw_limit < ahead ? draw_limit : ahead;
+    uint64_t drawn = 0;
+    auto enqueue_chunk = [&]() -> hipError_t {
+        uint64_t count = (uint64_t) (drawn == 0 && first_draws(C) < L.draw_chunk ? first_draws(C) : L.draw_chunk);
+        if (count > stop - drawn) count = stop - drawn;
+        a.j0 = drawn;
+        a.count = (int32_t) count;
+        a.tag = next_tag();
+        const dim3 draws((unsigned) ((count + kBlock - 1) / kBlock)), tiles((unsigned) ((count + kDrawTile - 1) / kDrawTile));
+        if (i64) hipLaunchKernelGGL((k_cache_draw<int64_t>), draws, dim3(kBlock), 0, s, a);
+        else     hipLaunchKernelGGL((k_cache_draw<int32_t>), draws, dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL(k_cache_commit, tiles, dim3(kBlock), 0, s, a);
+        drawn += count;
+        a.chunk_index += 1;
+        return hipGetLastError();
+    };
+    // A draw that is waited for enqueues two chunks and what follows them, and looks at the outcome then; a cache that is
+    // still incomplete (a stream that repeats itself a lot) gets its further chunks one by one and the rest once more.
+    while (drawn < stop && (!wait_for_it || a.chunk_index < 2)) GNS_HIP_TRY(enqueue_chunk(), "cache draw launch");
     IndexArgs x;
+    memset(&x, 0, sizeof(x));
     x.bitmap = bitmap;
     x.words = L.words;
-    x.sums = ws_ptr<int32_t>(c, L.sums_words);
-    x.tiles = (int32_t) L.word_tiles;
+    x.sums = ws_ptr<unsigned long long>(c, L.index_sums);
+    x.tag = next_tag();
+    x.spins = c->union_spins;
     x.word_prefix = cache_ptr<int32_t>(c, L.cache_prefix, gen);
     x.cache_nodes = cache_ptr<int32_t>(c, L.cache_nodes, gen);
-    hipLaunchKernelGGL(k_cache_index_phase1, dim3((unsigned) x.tiles), dim3(kBlock), 0, s, x);
-    hipLaunchKernelGGL(k_cache_index_phase2, dim3(1), dim3(kBlock), 0, s, x);
-    hipLaunchKernelGGL(k_cache_index_phase3, dim3((unsigned) x.tiles), dim3(kBlock), 0, s, x);
-    GNS_HIP_TRY(hipGetLastError(), "cache index launch");
-
-    {
-        const unsigned pc_blocks = (unsigned) ((C + kBlock - 1) / kBlock);
-        float* node_pc = cache_ptr<float>(c, L.node_pc, gen);
-        if (i64) hipLaunchKernelGGL((k_cache_pc<int64_t>), dim3(pc_blocks), dim3(kBlock), 0, s, x.cache_nodes, C, prob_prefix, (int64_t) prob_total, node_pc);
-        else     hipLaunchKernelGGL((k_cache_pc<int32_t>), dim3(pc_blocks), dim3(kBlock), 0, s, x.cache_nodes, C, prob_prefix, (int64_t) prob_total, node_pc);
-        GNS_HIP_TRY(hipGetLastError(), "cache weight table launch");
-    }
-    if (L.coarse_shift > 0) {
-        const unsigned cb = (unsigned) ((L.coarse_words + kBlock / kWave - 1) / (kBlock / kWave));
-        hipLaunchKernelGGL(k_cache_coarse, dim3(cb), dim3(kBlock), 0, s, bitmap, (int64_t) L.words, (int) L.coarse_shift,
-                           cache_ptr<uint64_t>(c, L.coarse_bitmap, gen), (int64_t) L.coarse_words);
-        GNS_HIP_TRY(hipGetLastError(), "coarse bitmap launch");
-    }
-    if (c->config.flag_mode == GNS_FLAGS_PER_CACHE) {
-        GNS_HIP_TRY(launch_build_induced(c, gen, s), "induced subgraph");
-    }
-    if (c->graph.feat_dim > 0) {
-        // fill the device table of cached feature rows (slot order) straight from the full store
-        const int32_t* fill_nodes = x.cache_nodes;
-        const int32_t fill_count = (int32_t) C;
-        float* fill_out = cache_ptr<float>(c, L.cache_feat, gen);
-        GNS_HIP_TRY(launch_gather(&c, 1, &fill_nodes, &fill_count, &fill_out, -1, s), "cache feature fill");
+    x.cache_size = C;
+    x.prob_prefix = prob_prefix;
+    x.prob_total = (int64_t) prob_total;
+    x.node_inv_pc = cache_ptr<float>(c, L.node_pc, gen);
+    gns_status st = fill_cache(c, gen, x, i64, s);
+    if (st != GNS_OK) return st;
+    if (wait_for_it) {
+        GNS_HIP_TRY(hipStreamSynchronize(s), "cache draw sync");
+        if (c->h_draw->draw_done_chunk < 0) {
+            while (c->h_draw->draw_done_chunk < 0) {
+                if (drawn >= stop)
+                    return fail(c, GNS_ECAPACITY, "cache draw: the stream did not yield cache_size distinct nodes within the draw limit (cache_size too close to the number of nodes with neighbors)", hipSuccess);
+                GNS_HIP_TRY(enqueue_chunk(), "cache draw launch");
+                GNS_HIP_TRY(hipStreamSynchronize(s), "cache draw sync");
+            }
+            x.tag = next_tag();
+            st = fill_cache(c, gen, x, i64, s);
+            if (st != GNS_OK) return st;
+            GNS_HIP_TRY(hipStreamSynchronize(s), "cache draw sync");
+        }
     }
     GNS_HIP_TRY(hipEventRecord(c->ready_event[gen], s), "event record");
     c->pending = true;
     c->pending_gen = gen;
     c->cache_draws = -1;                           // read back on demand
     if (!wait_for_it) return GNS_OK;
-    const gns_status st = finish_pending_draw(c);
-    if (st != GNS_OK) { c->pending = false; return st; }
+    c->cache_draws = (int64_t) c->h_draw->cut_draw + 1;
     return activate_cache(c);
 }
 

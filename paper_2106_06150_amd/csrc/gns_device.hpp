@@ -139,6 +139,40 @@ __device__ __forceinline__ int32_t block_sum(int32_t v, int32_t* smem)
     return sum;
 }
 
+// A tile's sum travels to the blocks of later tiles of the same launch as one 64-bit word: the launch's tag above, the
+// sum below, so relaxed accesses suffice and nothing is reset between launches.
+__device__ __forceinline__ void publish_sum(unsigned long long* tile_sums, int32_t tile, uint32_t tag, uint32_t sum)
+{
+    __hip_atomic_store(&tile_sums[tile], ((unsigned long long) tag << 32) | sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Sum of the tiles before `tile`, by the whole block.  A sum that does not arrive within `spins` polls is taken from
+// count(tile), which works it out from the tile's data, so no block ever depends on another one being scheduled.
+template <typename Count>
+__device__ __forceinline__ int32_t sum_before(unsigned long long* tile_sums, uint32_t tag, int32_t tile, int spins, int32_t* smem,
+                                              Count&& count)
+{
+    uint32_t v = 0;
+    for (int32_t t = (int32_t) threadIdx.x; t < tile; t += kBlock) {
+        unsigned long long x = 0;
+        int i = 0;
+        for (;; ++i) {
+            x = __hip_atomic_load(&tile_sums[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((uint32_t) (x >> 32) == tag || i >= spins) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        if ((uint32_t) (x >> 32) != tag) {
+            const uint32_t counted = count(t);
+            // the data has been read before the tag is looked at once more: had it begun to change, the tag would be out
+            asm volatile("s_waitcnt vmcnt(0)" ::"v"(counted) : "memory");
+            x = __hip_atomic_load(&tile_sums[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((uint32_t) (x >> 32) != tag) x = counted;
+        }
+        v += (uint32_t) x;
+    }
+    return block_sum((int32_t) v, smem);
+}
+
 // index of the n-th (0-based) set bit of a 64-bit mask that has more than n bits set
 __device__ __forceinline__ int select_bit64(uint64_t mask, int n)
 {

@@ -179,33 +179,6 @@ __device__ __forceinline__ uint32_t count_tile(const FinishArgs& a, int32_t tile
     return n;
 }
 
-// New nodes of the tiles before `tile`: every tile's block publishes its own count with the layer's tag in one
-// 64-bit word (so relaxed accesses suffice and nothing is reset between launches), and every block adds up the words of
-// the tiles before it.  A count that does not arrive within `spins` polls is taken from the bitmap itself -- a tile's
-// marks are cleared only after its count is out -- so no block ever depends on another one being scheduled.
-__device__ __forceinline__ int32_t union_offset(const FinishArgs& a, uint32_t tag, int32_t tile, int spins, int32_t* smem)
-{
-    uint32_t v = 0;
-    for (int32_t t = (int32_t) threadIdx.x; t < tile; t += kBlock) {
-        unsigned long long x = 0;
-        int i = 0;
-        for (;; ++i) {
-            x = __hip_atomic_load(&a.tile_sums[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((uint32_t) (x >> 32) == tag || i >= spins) break;
-            __builtin_amdgcn_s_sleep(1);
-        }
-        if ((uint32_t) (x >> 32) != tag) {
-            const uint32_t counted = count_tile(a, t);
-            // the marks have been read before the tag is looked at once more: had they begun to go, it would be out
-            asm volatile("s_waitcnt vmcnt(0)" ::"v"(counted) : "memory");
-            x = __hip_atomic_load(&a.tile_sums[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((uint32_t) (x >> 32) != tag) x = counted;
-        }
-        v += (uint32_t) x;
-    }
-    return block_sum((int32_t) v, smem);
-}
-
 // The union step of one layer.  Latency-bound: every block is a chain of a few dependent reads (tile words -> counts of
 // other tiles -> offsets of the new nodes), so it is one launch (two, with the tile counts in a launch of their own,
 // cost another 4.6 us each, three times per mini-batch), the tiles are small, and new nodes are spread over threads.
@@ -267,14 +240,12 @@ __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
         int32_t total, total_nz;
         const int32_t off = block_exclusive_scan(cnt, smem, &total);        // marks before this thread's words
         const uint32_t tag = a.st->batch_id * GNS_MAX_LAYERS + (uint32_t) a.layer_index;
-        if (threadIdx.x == 0)
-            __hip_atomic_store(&a.tile_sums[tile], ((unsigned long long) tag << 32) | (uint32_t) total, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) publish_sum(a.tile_sums, tile, tag, (uint32_t) total);
         const bool last = tile == a.mark_tiles - 1;
         int32_t before = 0;
-        if (total > 0 || last) before = union_offset(a, tag, tile, spins, smem);
+        if (total > 0 || last) before = sum_before(a.tile_sums, tag, tile, spins, smem, [&](int32_t t) { return count_tile(a, t); });
         if (last && threadIdx.x == 0) a.st->num_dst[a.layer_index + 1] = R + before + total;
-        // The count is out (its store is older than the reads that union_offset waited for, or than the barriers of the
+        // The count is out (its store is older than the reads that sum_before waited for, or than the barriers of the
         // scan below): from here on the marks may go.
         const int32_t widx = block_exclusive_scan(nz, smem, &total_nz);     // marked words before this thread's words
         __builtin_amdgcn_s_waitcnt(0);

@@ -17,10 +17,7 @@ struct DeviceState {
     uint32_t key0, key1;                  // Philox key of the current batch (lo32(seed), hi32(seed))
     uint32_t bad_seed;                    // id of the last batch that had a seed out of range or repeated
     int32_t hub_count;                    // entries of the batch's hub-row list (reset by the batch's last kernel)
-    int32_t chunk_distinct;               // cache draw: first occurrences found in the current chunk
-    int32_t chunk_limit;                  //   how many of them enter the cache
-    int32_t chunk_final;                  //   1 if they complete it
-    int32_t draw_distinct;                //   nodes in the cache before the current chunk
+    int32_t draw_distinct[2];             // cache draw: nodes in the cache before a chunk (by the chunk's parity)
     int32_t draw_done_chunk;              //   index of the chunk that completed the cache, -1 while incomplete
     int32_t plan_chunks;                  // CACHE_ONLY sampler: aligned chunks in the current work list
     uint32_t stamp;                       // what the current batch's entries of the node table carry (set by its first kernel)
@@ -45,7 +42,8 @@ struct Layout {
     size_t walk_a, walk_b, prob_prefix, walk_tiles, walk_tiles_nz;
     size_t node_pc;           // [n] floats: 1 / p^C_u (Section 3.4), filled for the nodes of the current cache
     // cache-draw scratch
-    size_t draw_keys, draw_vals, draw_node, draw_slot;
+    size_t draw_table, draw_slot, draw_sums, index_sums;
+    size_t entry_rows;        // row that owns entry 64 * i of the CSR entry array (Eq. (1) draws; filled by gns_create)
     // frontier structures
     size_t mark_bitmap;
     size_t mark_summary;      // one bit per word of the mark bitmap: "this word has a mark" (large graphs only)
@@ -70,7 +68,8 @@ struct Layout {
 
     int64_t max_chunks;
     // scan partials
-    size_t sums_rows, sums_words, tile_sums, sums_plan;
+    size_t sums_rows, tile_sums, sums_plan;
+    size_t info;              // outcome of the graph validation
     size_t state;
     size_t shared_begin;      // sections at or past this offset are shared with forked contexts
     size_t cache_block_begin; // first of the two copies of what a cache draw writes (bitmap ... 1/p^C table)
@@ -78,12 +77,13 @@ struct Layout {
     size_t total;
     // sizes
     int64_t words;            // ceil(n / 64)
-    int64_t word_tiles;       // ceil(words / kTile)
     int32_t mark_tile_words;  // bitmap words per frontier tile (kMarkTileMin .. kMarkTileMax, a power of two)
     int64_t mark_tiles;       // ceil(words / mark_tile_words)
     int64_t row_tiles;        // ceil(max rows / kTile)
-    int64_t draw_chunk;       // stream draws processed per round of the cache draw
+    int64_t draw_chunk;       // largest number of stream draws processed at a time
+    int64_t draw_unit;        // the draw's limits count the stream in pieces of this many draws
     int64_t draw_tiles;
+    int64_t index_tiles;
     uint32_t draw_hash_cap;   // power of two
     int64_t max_rows;         // worst-case dst rows of any layer
     int64_t max_edges;        // worst-case edges of any layer
@@ -115,7 +115,7 @@ struct gns_ctx {
     gns::DeviceState* d_state;       // device
     gns::DeviceState* h_state;       // pinned host mirror, written by the last kernel of every mini-batch
     gns::DeviceState* h_state_dev;   //   its address for kernels
-    gns::DeviceState* h_draw;        // pinned: where cache draws and the walk probability read their outcome back (mini-batches
+    gns::DeviceState* h_draw;        // pinned: where cache draws and the walk probability leave their outcome (mini-batches
                                      //   of this context may be in flight meanwhile, so not the mirror they write)
     bool uses_cache;
     bool cache_valid;
@@ -128,7 +128,7 @@ struct gns_ctx {
     hipStream_t reader_streams[gns::kReaderStreams];   // where this context enqueued readers of the cache block
     int reader_stream_count;         //   since the last draw became current
     bool had_cache;                  // root only: some draw has been made current (cache_gen is meaningful)
-    int64_t refresh_count;           // root only
+    uint32_t draw_tag;               // root only: of the last launch of a draw that passes sums between its blocks
     // root only: a draw enqueued by gns_sample_cache_async and not yet made current
     bool pending;
     int pending_gen;
@@ -239,9 +239,14 @@ gns_status run_walk_probability(gns_ctx* c, const int32_t* train_nodes, int64_t 
                                 hipStream_t s);
 
 // gns_cache.hip
+// validates the graph and fills Layout::entry_rows
 hipError_t launch_count_nonzero_rows(gns_ctx* c, hipStream_t s, int32_t* d_out);
 // wait_for_it: run the chunk loop with a read-back per chunk and synchronise (exact error reporting); otherwise
 // enqueue a fixed number of chunks (later ones stand down once the cache is complete) and return.
+// Draws of the first chunk of a cache draw: half as many again as the cache has nodes, which completes a cache of one
+// percent of the nodes on most graphs; further chunks are Layout::draw_chunk long.
+constexpr int32_t kDrawTile = 1024;
+constexpr int64_t first_draws(int64_t cache_size) { return cache_size + cache_size / 2 + 2048; }
 gns_status run_sample_cache(gns_ctx* c, uint64_t seed, uint64_t epoch, bool wait_for_it, hipStream_t s);
 gns_status activate_cache(gns_ctx* c);
 gns_status retire_cache(gns_ctx* c);

@@ -91,7 +91,7 @@ struct FinishArgs {
     const uint64_t* seed_mark;     //   and this bitmap of the seeds tells them apart (null otherwise)
     int64_t words;
     NodeTable tab;
-    unsigned long long* tile_sums; // [mark_tiles] (tag, new nodes of the tile), see union_offset
+    unsigned long long* tile_sums; // [mark_tiles] (tag, new nodes of the tile), see sum_before
     int32_t row_tiles_max;         // grid split point: blocks [0, row_tiles_max) work on rows
     int32_t mark_tiles;            // tiles of mark_tile_words bitmap words
     int32_t mark_tile_words;

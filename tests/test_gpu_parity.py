@@ -1246,3 +1246,26 @@ def test_node_table_is_cleared_when_its_stamps_run_out():
         full_parity(gns, cache_seed=0, epoch=0, batch_seed=9, seeds=seeds.cpu())
     finally:
         gns.close()
+
+
+@pytest.mark.parametrize("spins", ["256", "0"])
+@pytest.mark.parametrize("n,avg,csize", [(70, 3, 1), (64, 4, 40), (5000, 2, 1365), (40000, 6, 1366), (40000, 6, 39000), (300000, 4, 30000)])
+def test_cache_draw_chunks_and_counts_taken_from_the_data(spins, n, avg, csize, monkeypatch):
+    """Caches that the first chunk of the stream completes and that need several (most of the nodes cached), chunks at
+    the edges of a tile of draws, rows found between two entries of the table; blocks that do not wait for one another's
+    counts and that do.  Waited for and enqueued."""
+    monkeypatch.setenv("GNS_UNION_SPINS", spins)
+    ip, ix = _small(n=n, avg=avg, seed=n + csize)
+    csize = min(csize, int((ip[1:] > ip[:-1]).sum()))
+    gns = GpuGns(ip, ix, None, fanouts=(2,), policies=(C,), cache_size=csize, max_seeds=8)
+    try:
+        for epoch in range(3):
+            compare_cache(gns.sample_cache(12, epoch), oracle.sample_cache(ip.numpy(), 12, epoch, csize))
+        ref = oracle.sample_cache(ip.numpy(), 12, 3, csize)
+        if ref[2] <= 8 * 65536:                            # what an enqueued draw takes from the stream
+            B.gns_sample_cache_async(gns.ctx, 12, 3)
+            B.gns_activate_cache(gns.ctx)
+            _, _, _, draws = B.gns_cache_view(gns.ctx)
+            assert draws == ref[2]
+    finally:
+        gns.close()
