@@ -130,21 +130,15 @@ hipError_t launch_batch_begin(const Group& g, const BeginDyn& d, hipStream_t s)
     return hipGetLastError();
 }
 
-// Words first .. first + per - 1 of a tile that starts at word `base` (per <= kPerMax consecutive words of one
-// thread; they never straddle a summary word because per divides 64 and first is a multiple of per).  With a
-// summary only the words it reports as marked are read; the reads are issued together, behind one read of
-// the summary word.
+// Words first .. first + per - 1 of a tile that starts at word `base` (per <= kPerMax consecutive words of one thread).
 template <int kPerMax>
 __device__ __forceinline__ void load_marks(const FinishArgs& a, int64_t base, int first, int per, int T, uint64_t* word)
 {
-    uint64_t has = ~0ull;
     const int64_t w0 = base + first;
-    if (a.mark_summary && first < T && w0 < a.words) has = a.mark_summary[w0 >> 6] >> (w0 & 63);
 #pragma unroll
     for (int i = 0; i < kPerMax; ++i) {
         const int64_t w = w0 + i;
-        const bool live = i < per && first + i < T && w < a.words && ((has >> i) & 1ull);
-        word[i] = live ? a.mark[w] : 0ull;
+        word[i] = i < per && first + i < T && w < a.words ? a.mark[w] : 0ull;
     }
 }
 
@@ -179,9 +173,120 @@ __device__ __forceinline__ uint32_t count_tile(const FinishArgs& a, int32_t tile
     return n;
 }
 
+// The node of bit `bit` of bitmap word `word` joins the batch's list at place `pos`.
+__device__ __forceinline__ void emit_new_node(const FinishArgs& a, int32_t pos, int64_t word, int bit)
+{
+    const uint32_t node = (uint32_t) (word * 64 + bit);
+    RowExtent ext;
+    ext.start = load_off_rt(a.g_indptr, a.g_i64, node);
+    ext.end = load_off_rt(a.g_indptr, a.g_i64, (int64_t) node + 1);
+    a.src_nodes[pos] = (int32_t) node;
+    a.tab.entry[node] = a.tab.make((uint32_t) pos);
+    a.row_ext[pos] = ext;
+    append_hub_rows(a.st, a.hub_rows, is_hub_extent(ext.start, ext.end), pos);
+}
+
+// The bitmap side of the union step on graphs whose bitmap has a summary.  A tile has far more words than marks there, so
+// the marked words are enumerated from the tile's summary words (bit q of them is found by a search over their counts in
+// LDS) and read one per thread and turn, kMarkCap at a time: one read of the summary and one of the marks in the chain,
+// where a thread that looked at 32 words of its own in turn made the layer 21 to 29 us long (groups of four on 40 M nodes;
+// 15 to 28 us now, bound by the scattered reads and writes per new node, and the same for tiles of 2048 to 8192 words).  Most tiles take one pass; others read their words once more when the ids are written.
+__device__ __forceinline__ void union_sparse_tile(const FinishArgs& a, int32_t tile, int32_t R, int spins, int32_t* smem,
+                                                  uint64_t* s_word, int32_t* s_widx, int32_t* s_off)
+{
+    __shared__ uint64_t s_sum[kMarkTileMax / 64];
+    __shared__ int32_t s_pre[kMarkTileMax / 64];
+    constexpr int kPer = kMarkCap / kBlock;
+    const int T = a.mark_tile_words, S = T / 64;
+    const int64_t base = (int64_t) tile * T;
+    const int tid = (int) threadIdx.x;
+    // the tile's summary words and the number of marked words before each
+    const bool has = tid < S && base / 64 + tid < (a.words + 63) / 64;
+    const uint64_t mine = has ? a.mark_summary[base / 64 + tid] : 0ull;
+    int32_t words;
+    const int32_t words_before = block_exclusive_scan(__popcll(mine), smem, &words);
+    if (tid < S) { s_sum[tid] = mine; s_pre[tid] = words_before; }
+    __syncthreads();
+    // marked words p0 .. p0 + kMarkCap - 1 into LDS, four consecutive ones per thread; returns the new nodes among them
+    int32_t widx[kPer];
+    auto load_pass = [&](int32_t p0, int32_t before) -> int32_t {
+        uint64_t w[kPer];
+        int32_t cnt = 0;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int32_t q = p0 + tid * kPer + i;
+            widx[i] = -1;
+            if (q < words) {
+                int lo = 0, hi = S;                          // last summary word with no more than q marked words before it
+                while (hi - lo > 1) {
+                    const int mid = (lo + hi) >> 1;
+                    if (s_pre[mid] <= q) lo = mid; else hi = mid;
+                }
+                widx[i] = lo * 64 + select_bit64(s_sum[lo], q - s_pre[lo]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) w[i] = widx[i] >= 0 ? a.mark[base + widx[i]] : 0ull;
+        if (a.seed_mark) {                                   // a marked seed is no new node
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) w[i] &= widx[i] >= 0 ? ~a.seed_mark[base + widx[i]] : 0ull;
+        }
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) cnt += __popcll(w[i]);
+        int32_t total;
+        int32_t off = before + block_exclusive_scan(cnt, smem, &total);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int k = tid * kPer + i;
+            s_word[k] = w[i];
+            s_widx[k] = widx[i];
+            s_off[k] = off;                                  // words without new nodes share the offset of the next one
+            off += __popcll(w[i]);
+        }
+        return total;
+    };
+    int32_t total = 0;
+    for (int32_t p0 = 0; p0 < words; p0 += kMarkCap) total += load_pass(p0, total);
+    const uint32_t tag = a.st->batch_id * GNS_MAX_LAYERS + (uint32_t) a.layer_index;
+    if (tid == 0) publish_sum(a.tile_sums, tile, tag, (uint32_t) total);
+    const bool last = tile == a.mark_tiles - 1;
+    int32_t before = 0;
+    if (total > 0 || last)
+        before = sum_before(a.tile_sums, tag, tile, spins, smem, [&](int32_t t) { return count_tile(a, t); });
+    if (last && tid == 0) a.st->num_dst[a.layer_index + 1] = R + before + total;
+    // the count is out: from here on the marks may go
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (has && mine) a.mark_summary[base / 64 + tid] = 0ull;
+    int32_t node_lo = 0;
+    for (int32_t p0 = 0; p0 < words; p0 += kMarkCap) {
+        int32_t in_pass = total;
+        if (words > kMarkCap) {
+            __syncthreads();                                 // the pass before is still being read
+            in_pass = load_pass(p0, node_lo);
+            __syncthreads();
+        }
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+            if (widx[i] >= 0) a.mark[base + widx[i]] = 0ull;                 // ready for the next layer
+        const int32_t here = words - p0 < kMarkCap ? words - p0 : kMarkCap;
+        // one thread per new node: its word (the last one whose offset is <= j), then its bit
+        for (int32_t j = node_lo + tid; j < node_lo + in_pass; j += kBlock) {
+            int32_t lo = 0, hi = here;
+            while (hi - lo > 1) {
+                const int32_t mid = (lo + hi) >> 1;
+                if (s_off[mid] <= j) lo = mid; else hi = mid;
+            }
+            emit_new_node(a, R + before + j, base + s_widx[lo], select_bit64(s_word[lo], j - s_off[lo]));
+        }
+        node_lo += in_pass;
+    }
+}
+
 // The union step of one layer.  Latency-bound: every block is a chain of a few dependent reads (tile words -> counts of
 // other tiles -> offsets of the new nodes), so it is one launch (two, with the tile counts in a launch of their own,
 // cost another 4.6 us each, three times per mini-batch), the tiles are small, and new nodes are spread over threads.
+// kPerMax: words of a tile per thread at most; 0: the bitmap has a summary (union_sparse_tile).
 template <int kPerMax>
 __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
 {
@@ -217,6 +322,8 @@ __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
             if (r0 + i < R) a.indptr[r0 + i] = off;
             off += c[i];
         }
+    } else if constexpr (kPerMax == 0) {
+        union_sparse_tile(a, (int32_t) blockIdx.x - a.row_tiles_max, R, spins, smem, s_word, s_widx, s_off);
     } else {
         const int32_t tile = (int32_t) blockIdx.x - a.row_tiles_max;
         const int T = a.mark_tile_words;
@@ -253,10 +360,6 @@ __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
 #pragma unroll
         for (int i = 0; i < kPerMax; ++i)
             if (marked & (1u << i)) a.mark[base + first + i] = 0ull;         // ready for the next layer
-        // every thread has read its summary words: clear them (a tile is a whole number of summary words)
-        if (a.mark_summary)
-            for (int i = (int) threadIdx.x; i < T / 64; i += kBlock)
-                if (base / 64 + i < (a.words + 63) / 64) a.mark_summary[base / 64 + i] = 0ull;
         if (total == 0) return;
         // The marked words go through LDS in order, kMarkCap at a time (most tiles need one pass).
         for (int32_t p0 = 0; p0 < total_nz; p0 += kMarkCap) {
@@ -284,16 +387,7 @@ __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
                     const int32_t mid = (lo + hi) >> 1;
                     if (s_off[mid] <= j) lo = mid; else hi = mid;
                 }
-                const int bit = select_bit64(s_word[lo], j - s_off[lo]);
-                const uint32_t node = (uint32_t) ((base + s_widx[lo]) * 64 + bit);
-                const int32_t pos = R + before + j;
-                RowExtent ext;
-                ext.start = load_off_rt(a.g_indptr, a.g_i64, node);
-                ext.end = load_off_rt(a.g_indptr, a.g_i64, (int64_t) node + 1);
-                a.src_nodes[pos] = (int32_t) node;
-                a.tab.entry[node] = a.tab.make((uint32_t) pos);
-                a.row_ext[pos] = ext;
-                append_hub_rows(a.st, a.hub_rows, is_hub_extent(ext.start, ext.end), pos);
+                emit_new_node(a, R + before + j, base + s_widx[lo], select_bit64(s_word[lo], j - s_off[lo]));
             }
             __syncthreads();
         }
@@ -342,9 +436,10 @@ hipError_t launch_finish_layer(const Group& g, int layer_index, hipStream_t s)
         hipLaunchKernelGGL(k_row_sums, dim3((unsigned) ((c->lay.rows[layer_index] + kBlock - 1) / kBlock), (unsigned) g.count),
                            dim3(kBlock), 0, s, a);
     const dim3 grid((unsigned) (a.f.row_tiles_max + a.f.mark_tiles), (unsigned) g.count);
-    // words of a tile per thread: the kernel's loops over them are unrolled for 1, 4 or 32
+    // by summary, or by words of a tile per thread: the kernel's loops over them are unrolled for 1, 4 or 32
     const int per = a.f.mark_tile_words / kBlock, spins = c->union_spins;
-    if (per <= 1)      hipLaunchKernelGGL(k_union<1>, grid, dim3(kBlock), 0, s, a, spins);
+    if (a.off.has_summary) hipLaunchKernelGGL(k_union<0>, grid, dim3(kBlock), 0, s, a, spins);
+    else if (per <= 1) hipLaunchKernelGGL(k_union<1>, grid, dim3(kBlock), 0, s, a, spins);
     else if (per <= 4) hipLaunchKernelGGL(k_union<4>, grid, dim3(kBlock), 0, s, a, spins);
     else               hipLaunchKernelGGL((k_union<kMarkTileMax / kBlock>), grid, dim3(kBlock), 0, s, a, spins);
     return hipGetLastError();
