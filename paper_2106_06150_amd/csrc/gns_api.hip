@@ -124,13 +124,13 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     L.sums_rows = take((size_t) (L.max_rows / (kBlock / kWave) + 1) * 4);
     L.info = take(16);
     L.tile_sums = take((size_t) L.mark_tiles * 8);
-    L.sums_plan = take((size_t) (L.max_rows / kBlock + 2) * 4);
+    L.row_sums = take((size_t) L.row_tiles * 8);
+    L.plan_tiles = (L.max_rows + kBlock - 1) / kBlock;
+    L.plan_sums = take((size_t) L.plan_tiles * 8);
     if (uses_cache) {
         // a dst row of deg entries touches at most deg/64 + 2 aligned chunks; dst rows are distinct
         L.max_chunks = g->num_entries / 64 + 2 * L.max_rows + 64;
         if (L.max_chunks >= (int64_t) 1 << 31) GNS_BAD("graph too large for 32-bit chunk ids");
-        L.plan_cnt = take((size_t) L.max_rows * 4);
-        L.plan_g0 = take((size_t) L.max_rows * 4);
         L.plan_desc = take((size_t) L.max_chunks * 4);
     }
     // last of the per-batch sections: gns_sample_blocks_static keeps this one elsewhere on large graphs
@@ -348,6 +348,8 @@ hipError_t init_batch_scratch(gns_ctx* c, hipStream_t s)
         e = launch_fill_u64(ws_ptr<unsigned long long>(c, L.mark_summary), (size_t) L.summary_words, 0ull, s);
     if (e == hipSuccess) e = launch_fill_u64(ws_ptr<unsigned long long>(c, L.seed_mark), (size_t) L.words, 0ull, s);
     if (e == hipSuccess) e = launch_fill_u64(ws_ptr<unsigned long long>(c, L.tile_sums), (size_t) L.mark_tiles, 0ull, s);
+    if (e == hipSuccess) e = launch_fill_u64(ws_ptr<unsigned long long>(c, L.row_sums), (size_t) L.row_tiles, 0ull, s);
+    if (e == hipSuccess) e = launch_fill_u64(ws_ptr<unsigned long long>(c, L.plan_sums), (size_t) L.plan_tiles, 0ull, s);
     if (e == hipSuccess) e = launch_fill_u32(ws_ptr_table(c), (size_t) c->graph.num_nodes, 0u, s);
     c->stamp = 0;
     return e;

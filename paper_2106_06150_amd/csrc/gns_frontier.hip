@@ -86,8 +86,8 @@ void fill_group_args(const Group& g, LayerArgs* out)
     o.table = L.table;
     o.table_shift = L.table_shift;
     for (int p = 0; p < 2; ++p) { o.s_nbr[p] = L.s_nbr[p]; o.s_w[p] = L.s_w[p]; o.s_cnt[p] = L.s_cnt[p]; }
-    o.plan_cnt = L.plan_cnt; o.plan_g0 = L.plan_g0; o.plan_desc = L.plan_desc;
-    o.sums_rows = L.sums_rows; o.tile_sums = L.tile_sums; o.sums_plan = L.sums_plan;
+    o.plan_desc = L.plan_desc;
+    o.sums_rows = L.sums_rows; o.tile_sums = L.tile_sums; o.row_sums = L.row_sums; o.plan_sums = L.plan_sums;
     o.cache_block_bytes = L.cache_block_bytes;
     o.uses_cache = c->uses_cache ? 1 : 0;
     o.lists_hubs = L.lists_hubs ? 1 : 0;
@@ -149,18 +149,6 @@ __device__ __forceinline__ int32_t block_sum_array(const int32_t* vals, int32_t 
 #pragma unroll 4
     for (int32_t t = (int32_t) threadIdx.x; t < count; t += kBlock) v += vals[t];
     return block_sum(v, smem);
-}
-
-// The row counts' sums over blocks of kBlock rows, for the sampler that does not leave them.
-__global__ void __launch_bounds__(kBlock) k_row_sums(LayerArgs g)
-{
-    __shared__ int32_t smem[kBlock / kWave + 1];
-    const FinishArgs a = bind_finish(g, (int) blockIdx.y, true);
-    const int32_t R = a.st->num_dst[a.layer_index];
-    const int64_t r = (int64_t) blockIdx.x * kBlock + threadIdx.x;
-    if ((int64_t) blockIdx.x * kBlock >= R) return;
-    const int32_t sum = block_sum(r < R ? a.s_cnt[r] : 0, smem);
-    if (threadIdx.x == 0) const_cast<int32_t*>(a.sums_rows)[blockIdx.x] = sum;
 }
 
 // New nodes of one bitmap tile, counted from the bitmap by one thread.
@@ -247,7 +235,7 @@ __device__ __forceinline__ void union_sparse_tile(const FinishArgs& a, int32_t t
     };
     int32_t total = 0;
     for (int32_t p0 = 0; p0 < words; p0 += kMarkCap) total += load_pass(p0, total);
-    const uint32_t tag = a.st->batch_id * GNS_MAX_LAYERS + (uint32_t) a.layer_index;
+    const uint32_t tag = launch_tag(a.st, a.layer_index);
     if (tid == 0) publish_sum(a.tile_sums, tile, tag, (uint32_t) total);
     const bool last = tile == a.mark_tiles - 1;
     int32_t before = 0;
@@ -310,9 +298,20 @@ __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
             if (r0 + i >= R) c[i] = 0;
             sum += c[i];
         }
-        const int32_t before = block_sum_array(a.sums_rows, (int32_t) blockIdx.x * (kTile / a.rows_per_sum), smem);
-        int32_t total;
-        int32_t off = before + block_exclusive_scan(sum, smem, &total);
+        int32_t total, before;
+        int32_t off = block_exclusive_scan(sum, smem, &total);
+        if (a.rows_per_sum) {
+            before = block_sum_array(a.sums_rows, (int32_t) blockIdx.x * (kTile / a.rows_per_sum), smem);
+        } else {
+            const uint32_t tag = launch_tag(a.st, a.layer_index);
+            if (threadIdx.x == 0) publish_sum(a.row_sums, (int32_t) blockIdx.x, tag, (uint32_t) total);
+            before = sum_before(a.row_sums, tag, (int32_t) blockIdx.x, spins, smem, [&](int32_t t) {
+                uint32_t n = 0;
+                for (int32_t r = t * kTile; r < (t + 1) * kTile; ++r) n += (uint32_t) a.s_cnt[r];      // a full tile: one follows
+                return n;
+            });
+        }
+        off += before;
         if (base + kTile >= R && threadIdx.x == 0) {
             a.st->num_edges[a.layer_index] = before + total;
             a.indptr[R] = before + total;
@@ -346,7 +345,7 @@ __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
         }
         int32_t total, total_nz;
         const int32_t off = block_exclusive_scan(cnt, smem, &total);        // marks before this thread's words
-        const uint32_t tag = a.st->batch_id * GNS_MAX_LAYERS + (uint32_t) a.layer_index;
+        const uint32_t tag = launch_tag(a.st, a.layer_index);
         if (threadIdx.x == 0) publish_sum(a.tile_sums, tile, tag, (uint32_t) total);
         const bool last = tile == a.mark_tiles - 1;
         int32_t before = 0;
@@ -404,7 +403,7 @@ void fill_finish_template(const Group& g, int layer_index, FinishArgs* out)
     a.fanout = c->config.fanout[layer_index];
     a.words = L.words;
     a.marks_seeds = layer_index == 0 && first_layer_enters_seeds(c->config) ? 1 : 0;
-    a.rows_per_sum = rows_per_sum(g, layer_index) ? rows_per_sum(g, layer_index) : kBlock;
+    a.rows_per_sum = rows_per_sum(g, layer_index);
     a.inv_fanout = 1.0 / (double) a.fanout;
     a.unit_weights = c->config.policy[layer_index] == GNS_UNIFORM ? 1 : 0;
     a.row_tiles_max = (int32_t) ((L.rows[layer_index] + kTile - 1) / kTile);
@@ -432,9 +431,6 @@ hipError_t launch_finish_layer(const Group& g, int layer_index, hipStream_t s)
     fill_group_args(g, &a);
     set_group_layer(g, layer_index, &a);
     fill_finish_template(g, layer_index, &a.f);
-    if (rows_per_sum(g, layer_index) == 0)
-        hipLaunchKernelGGL(k_row_sums, dim3((unsigned) ((c->lay.rows[layer_index] + kBlock - 1) / kBlock), (unsigned) g.count),
-                           dim3(kBlock), 0, s, a);
     const dim3 grid((unsigned) (a.f.row_tiles_max + a.f.mark_tiles), (unsigned) g.count);
     // by summary, or by words of a tile per thread: the kernel's loops over them are unrolled for 1, 4 or 32
     const int per = a.f.mark_tile_words / kBlock, spins = c->union_spins;

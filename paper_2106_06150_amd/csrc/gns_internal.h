@@ -59,8 +59,8 @@ struct Layout {
     bool lists_hubs;          // some layer gives hub rows a wave of their own
     // per-layer sampler scratch (fixed stride fanout)
     size_t s_nbr[2], s_w[2], s_cnt[2];     // double-buffered by layer parity
-    // CACHE_ONLY sampler: per-row chunk counts, chunk work list, CSR-aligned membership flags
-    size_t plan_cnt, plan_g0, plan_desc, edge_flags;
+    // CACHE_ONLY sampler: chunk work list, CSR-aligned membership flags
+    size_t plan_desc, edge_flags;
     // GNS_FLAGS_PER_CACHE: the induced subgraph S of Section 3.3 in compact form (see gns_induced.hip).
     size_t srec, s_nodes;
     size_t s_count;
@@ -68,7 +68,7 @@ struct Layout {
 
     int64_t max_chunks;
     // scan partials
-    size_t sums_rows, tile_sums, sums_plan;
+    size_t sums_rows, tile_sums, row_sums, plan_sums;
     size_t info;              // outcome of the graph validation
     size_t state;
     size_t shared_begin;      // sections at or past this offset are shared with forked contexts
@@ -80,6 +80,7 @@ struct Layout {
     int32_t mark_tile_words;  // bitmap words per frontier tile (kMarkTileMin .. kMarkTileMax, a power of two)
     int64_t mark_tiles;       // ceil(words / mark_tile_words)
     int64_t row_tiles;        // ceil(max rows / kTile)
+    int64_t plan_tiles;       // ceil(max rows / kBlock)
     int64_t draw_chunk;       // largest number of stream draws processed at a time
     int64_t draw_unit;        // the draw's limits count the stream in pieces of this many draws
     int64_t draw_tiles;

@@ -59,9 +59,7 @@ struct SampleArgs {
     NodeTable tab;             // holds this layer's dst nodes
     // CACHE_ONLY: per-batch plan and the CSR-aligned membership flags
     int64_t num_entries;
-    int32_t* plan_cnt;         // [rows] aligned 64-entry chunks touched by each dst row
-    int32_t* plan_g0;          // [rows] id of the first of them
-    int32_t* plan_sums;        // [row tiles + 1]
+    unsigned long long* plan_sums;   // [row tiles] (tag, chunks of the tile), see sum_before
     int32_t* plan_desc;        // [chunks] ids of the aligned chunks to flag
     uint64_t* flags;           // [ceil(nnz / 64)] bit e & 63 of word e >> 6: entry e points into the cache
     int64_t bitmap_words;
@@ -84,7 +82,8 @@ struct FinishArgs {
     const float* s_w;              // [R x fanout]
     const int32_t* s_cnt;          // [R]
     const int32_t* sums_rows;      // sampled neighbors of every rows_per_sum consecutive rows
-    int32_t rows_per_sum;          //   (a power of two up to kTile)
+    int32_t rows_per_sum;          //   (a power of two up to kTile; 0: the sampler does not leave them)
+    unsigned long long* row_sums;  // [row tiles] (tag, sampled neighbors of the tile's rows) for those
     uint64_t* mark;                // [words]
     uint64_t* mark_summary;        // [ceil(words / 64)] or null: bit w & 63 of word w >> 6 says mark[w] != 0
     int marks_seeds;               // first layer sampled in the launch that enters the seeds: it marks them like any node,
@@ -111,8 +110,8 @@ struct WsOffsets {
     uint64_t state, mark, mark_summary, seed_mark, seed_copy, row_ext, hub_rows;
     uint64_t table;
     uint64_t s_nbr[2], s_w[2], s_cnt[2];
-    uint64_t plan_cnt, plan_g0, plan_desc;
-    uint64_t sums_rows, tile_sums, sums_plan;
+    uint64_t plan_desc;
+    uint64_t sums_rows, tile_sums, row_sums, plan_sums;
     uint64_t cache_block_bytes;    // distance between the two copies of what a cache draw writes
     int32_t uses_cache;
     int32_t has_summary;
@@ -154,6 +153,12 @@ struct BeginDyn {
     int32_t cache_gen[kMaxGroup];  // which copy of the cache structures it reads
 };
 
+// What the words by which the blocks of a launch pass sums on carry (see sum_before): one value per mini-batch and layer.
+__device__ __forceinline__ uint32_t launch_tag(const DeviceState* st, int layer_index)
+{
+    return st->batch_id * GNS_MAX_LAYERS + (uint32_t) layer_index;
+}
+
 template <typename T>
 __device__ __forceinline__ T* at(char* base, uint64_t off) { return reinterpret_cast<T*>(base + off); }
 
@@ -193,9 +198,7 @@ __device__ __forceinline__ SampleArgs bind_sample(const LayerArgs& g, int b, uin
     a.mark = at<uint64_t>(ws, g.off.mark);
     a.mark_summary = g.off.has_summary ? at<uint64_t>(ws, g.off.mark_summary) : nullptr;
     a.tab = bind_table(g, b, stamp);
-    a.plan_cnt = at<int32_t>(ws, g.off.plan_cnt);
-    a.plan_g0 = at<int32_t>(ws, g.off.plan_g0);
-    a.plan_sums = at<int32_t>(ws, g.off.sums_plan);
+    a.plan_sums = at<unsigned long long>(ws, g.off.plan_sums);
     a.plan_desc = at<int32_t>(ws, g.off.plan_desc);
     if (g.off.uses_cache) {
         auto shifted = [&](auto* ptr) {
@@ -237,6 +240,7 @@ __device__ __forceinline__ FinishArgs bind_finish(const LayerArgs& g, int b, boo
     a.seed_mark = g.f.marks_seeds ? at<uint64_t>(ws, g.off.seed_mark) : nullptr;
     a.tab = bind_table(g, b, a.st->stamp);
     a.tile_sums = at<unsigned long long>(ws, g.off.tile_sums);
+    a.row_sums = at<unsigned long long>(ws, g.off.row_sums);
     a.indptr = blk.indptr;
     a.indices = blk.indices;
     a.weights = blk.weights;
@@ -372,7 +376,7 @@ int relabel_grid(const gns_ctx* c, int layer_index);
 bool direct_layer(const gns_config& config, int layer_index);
 // Whether the first layer's sampler is also the batch's first kernel (k_batch_begin runs in front of the others).
 bool first_layer_enters_seeds(const gns_config& config);
-// Rows whose sampled neighbors the layer's sampler sums up (0: it does not; k_row_sums does, over kBlock rows).
+// Rows whose sampled neighbors the layer's sampler sums up (0: it does not, the union step's blocks do).
 int rows_per_sum(const Group& g, int layer_index);
 // The batch's first launch when the first layer is direct: seeds and sampling in one.
 hipError_t launch_first_layer(const Group& g, const BeginDyn& d, hipStream_t s);

@@ -455,7 +455,7 @@ __global__ void __launch_bounds__(kBlock) k_sample_wide(LayerArgs g, int relabel
 // The CSR entry array is cut into aligned chunks of 64 entries; flags[g] holds, for chunk g,
 // one bit per entry: "this neighbor is in the cache".
 //   plan     per dst row, the aligned chunks its segment touches; prefix sum; the chunk ids
-//            are written out as a flat work list (k_plan_count, k_plan_expand)
+//            are written out as a flat work list (k_plan)
 //   flag     one wave step = a few chunks of the list: coalesced 256-byte index loads, one
 //            cache-bitmap test per entry, a ballot per chunk stored as one 64-bit word.  Every
 //            chunk costs the same, so the stream is balanced whatever the degree skew
@@ -473,52 +473,41 @@ __device__ __forceinline__ int32_t chunks_touched(int64_t start, int64_t end)
 // Plan tiles are kPlanTile rows (one row per thread): many small blocks keep the expansion parallel.
 constexpr int kPlanTile = kBlock;
 
-__global__ void __launch_bounds__(kBlock) k_plan_count(LayerArgs g, int relabel_blocks)
+// One launch: a tile's block passes its number of chunks on to the blocks of later tiles (sum_before), as the union step's
+// blocks do with the rows' samples.  Two launches fewer: a mini-batch with a scan of its rows 189 -> 185 us.
+__global__ void __launch_bounds__(kBlock) k_plan(LayerArgs g, int relabel_blocks, int spins)
 {
     __shared__ int32_t smem[kBlock / kWave + 1];
-    const int64_t ntiles = (int64_t) gridDim.x - relabel_blocks;
-    if ((int64_t) blockIdx.x >= ntiles) {
-        relabel_body(bind_finish(g, (int) blockIdx.y, false), (int32_t) ((int64_t) blockIdx.x - ntiles), relabel_blocks);
+    __shared__ int32_t s_off[kPlanTile + 1];
+    __shared__ int32_t s_g0[kPlanTile];
+    const int32_t ntiles = (int32_t) gridDim.x - relabel_blocks;
+    const int32_t tile = (int32_t) blockIdx.x;
+    if (tile >= ntiles) {
+        relabel_body(bind_finish(g, (int) blockIdx.y, false), tile - ntiles, relabel_blocks);
         return;
     }
     const SampleArgs a = bind_sample(g, (int) blockIdx.y);
-    const int64_t tile = (int64_t) blockIdx.x;
     const int32_t R = a.st->num_dst[a.layer_index];
-    const int64_t r = tile * kPlanTile + threadIdx.x;
-    if (tile * kPlanTile >= R) return;
-    int32_t c = 0;
-    if (r < R) {
-        const RowExtent ext = a.row_ext[r];
-        const int64_t start = ext.start, end = ext.end;
-        c = chunks_touched(start, end);
-        a.plan_cnt[r] = c;
-        a.plan_g0[r] = (int32_t) (start >> 6);
-    }
-    const int32_t sum = block_sum(c, smem);
-    if (threadIdx.x == 0) a.plan_sums[tile] = sum;
-}
-
-__global__ void __launch_bounds__(kBlock) k_plan_expand(LayerArgs g)
-{
-    __shared__ int32_t smem[kBlock / kWave + 1];
-    const SampleArgs a = bind_sample(g, (int) blockIdx.y);
-    __shared__ int32_t s_off[kPlanTile + 1];
-    __shared__ int32_t s_g0[kPlanTile];
-    const int32_t R = a.st->num_dst[a.layer_index];
-    const int64_t base = (int64_t) blockIdx.x * kPlanTile;
-    if (base >= R) return;
-    // chunks of all earlier tiles
-    int32_t before = 0;
-    for (int32_t t = (int32_t) threadIdx.x; t < (int32_t) blockIdx.x; t += kBlock) before += a.plan_sums[t];
-    before = block_sum(before, smem);
-    const int64_t r = base + threadIdx.x;
-    const int32_t c = (r < R) ? a.plan_cnt[r] : 0;
-    s_g0[threadIdx.x] = (r < R) ? a.plan_g0[r] : 0;
+    if (tile >= (R + kPlanTile - 1) / kPlanTile) return;
+    const int32_t r = tile * kPlanTile + (int32_t) threadIdx.x;
+    RowExtent ext = {0, 0};
+    if (r < R) ext = a.row_ext[r];
+    s_g0[threadIdx.x] = (int32_t) (ext.start >> 6);
     int32_t total;
-    s_off[threadIdx.x] = block_exclusive_scan(c, smem, &total);
-    if (threadIdx.x == 0) s_off[kPlanTile] = total;
-    const int32_t last_tile = (R - 1) / kPlanTile;
-    if ((int32_t) blockIdx.x == last_tile && threadIdx.x == 0) a.st->plan_chunks = before + total;
+    s_off[threadIdx.x] = block_exclusive_scan(chunks_touched(ext.start, ext.end), smem, &total);
+    const uint32_t tag = launch_tag(a.st, a.layer_index);
+    if (threadIdx.x == 0) {
+        s_off[kPlanTile] = total;
+        publish_sum(a.plan_sums, tile, tag, (uint32_t) total);
+    }
+    // chunks of all earlier tiles
+    const int32_t before = sum_before(a.plan_sums, tag, tile, spins, smem, [&](int32_t t) {
+        uint32_t n = 0;
+        for (int32_t q = t * kPlanTile; q < (t + 1) * kPlanTile; ++q)            // a full tile: one follows
+            n += (uint32_t) chunks_touched(a.row_ext[q].start, a.row_ext[q].end);
+        return n;
+    });
+    if (tile == (R - 1) / kPlanTile && threadIdx.x == 0) a.st->plan_chunks = before + total;
     __syncthreads();
     // one thread per work-list entry: its row is the last one whose offset is <= j
     for (int32_t j = (int32_t) threadIdx.x; j < total; j += kBlock) {
@@ -1060,8 +1049,7 @@ hipError_t launch_sample_layer(const Group& g, int layer_index, hipStream_t s)
     {
         StageTimer t(c, GNS_STAGE_PLAN, s);
         const unsigned plan_blocks = (unsigned) ((rows_max + kPlanTile - 1) / kPlanTile);
-        hipLaunchKernelGGL(k_plan_count, dim3(plan_blocks + (unsigned) rl, gy), tb, 0, s, a, rl);
-        hipLaunchKernelGGL(k_plan_expand, dim3(plan_blocks, gy), tb, 0, s, a);
+        hipLaunchKernelGGL(k_plan, dim3(plan_blocks + (unsigned) rl, gy), tb, 0, s, a, rl, c->union_spins);
     }
     {
         StageTimer t(c, GNS_STAGE_FLAG, s);
