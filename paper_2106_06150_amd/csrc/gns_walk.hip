@@ -44,8 +44,9 @@ __device__ __forceinline__ unsigned long long sat_add(unsigned long long a, unsi
 //      kNarrow every entry fits 32 bits
 //      kWide   64 bits
 // The last step writes 64 bits (the vector the caller sees).
-// 1 M nodes, 40 M entries, scale 24, fan-outs 15/10/5: 87 + 240 + 225 us for the three steps (the two narrow ones at
-// 174 G reads/s, the rate the L2s take scattered requests); one row per 16 lanes on 64-bit vectors took 3 x 490 us.
+// 1 M nodes, 40 M entries, scale 24, fan-outs 15/10/5: 68 + 229 + 227 us for the three steps (the two narrow ones at
+// 177 G requests/s, what the L2s take of scattered ones: 92 % of them hit); one row per 16 lanes on 64-bit vectors took
+// 3 x 490 us, the first step with its rows' sums taken chunk by chunk and no reads ahead 78.
 enum { kBits = 0, kNarrow = 1, kWide = 2 };
 
 struct WalkStepArgs {
@@ -116,7 +117,54 @@ __global__ void __launch_bounds__(kLds ? 1024 : kBlock) k_walk_step(WalkStepArgs
         const int64_t first = load_off<OffT>(a.indptr, r0);
         unsigned long long carry = 0, carry_hi = 0;          // sums of the list's entries so far (kWide: and of their upper halves)
         unsigned long long at_b = 0, at_b_hi = 0;            // the same up to my_b
-        for (int64_t c0 = first & ~(int64_t) 15; c0 < end; c0 += kWave * kUnroll) {
+        const int64_t window0 = first & ~(int64_t) 15;
+        if constexpr (kIn == kBits) {
+            // The next window's ids are on their way while this one's are tested.  The chunks' ballots stay in lanes
+            // 0 .. kUnroll - 1, where a row's beginning is looked up once per window.
+            constexpr int kWindow = kWave * kUnroll;
+            auto rel_to = [&](int64_t c0, int64_t p) { return (int) (p < c0 ? 0 : p - c0 < 2 * kWindow ? p - c0 : 2 * kWindow); };
+            auto load = [&](int64_t c0, int32_t (&dst)[kUnroll]) {
+                const int32_t* ids = a.indices + c0;
+                const int from = rel_to(c0, first), to = rel_to(c0, end);
+                if (from == 0 && to >= kWindow) {
+#pragma unroll
+                    for (int t = 0; t < kUnroll; ++t) dst[t] = ids[t * kWave + lane];
+                } else {
+#pragma unroll
+                    for (int t = 0; t < kUnroll; ++t) {      // (a run of empty rows has from == to: the entry before them)
+                        const int q = t * kWave + lane, at = q < from ? from : q;
+                        dst[t] = ids[at < to ? at : to - 1];
+                    }
+                }
+            };
+            int32_t j[kUnroll], ahead[kUnroll];
+#pragma unroll
+            for (int t = 0; t < kUnroll; ++t) j[t] = ahead[t] = 0;
+            if (window0 < end) load(window0, j);
+            for (int64_t c0 = window0; c0 < end; c0 += kWindow) {
+                if (c0 + kWindow < end) load(c0 + kWindow, ahead);
+                const int from = rel_to(c0, first), to = rel_to(c0, end), rel_b = rel_to(c0, my_b);
+                uint64_t mine = 0;
+#pragma unroll
+                for (int t = 0; t < kUnroll; ++t) {
+                    const int q = t * kWave + lane;
+                    const uint32_t w = kLds ? lds_bits[(uint32_t) j[t] >> 5] : bits[(uint32_t) j[t] >> 5];
+                    const uint64_t m = __ballot(q >= from && q < to && ((w >> (j[t] & 31)) & 1u));
+                    if (lane == t) mine = m;
+                }
+                const int32_t incl = wave_inclusive_scan(__popcll(mine));
+                const int at_word = rel_b >> 6 < kUnroll ? rel_b >> 6 : kUnroll;       // lane kUnroll: nothing, behind all others
+                const uint32_t lo = (uint32_t) __shfl((int) (uint32_t) mine, at_word, kWave);
+                const uint32_t hi = (uint32_t) __shfl((int) (uint32_t) (mine >> 32), at_word, kWave);
+                const int32_t before = __shfl(incl - __popcll(mine), at_word, kWave);
+                const uint64_t m = (((uint64_t) hi << 32) | lo) & ((1ull << (rel_b & 63)) - 1ull);
+                if (rel_b >= 1 && rel_b <= kWindow) at_b = carry + (unsigned long long) (before + __popcll(m));
+                carry += (unsigned long long) (uint32_t) __builtin_amdgcn_readlane(incl, kWave - 1);
+#pragma unroll
+                for (int t = 0; t < kUnroll; ++t) j[t] = ahead[t];
+            }
+        }
+        for (int64_t c0 = window0; kIn != kBits && c0 < end; c0 += kWave * kUnroll) {
             // positions relative to c0 in 32 bits: 64-bit arithmetic per entry would cost as much as the reads
             auto rel = [&](int64_t p) { return (int) (p < c0 ? 0 : p - c0 < 2 * kWave * kUnroll ? p - c0 : 2 * kWave * kUnroll); };
             const int rel_first = rel(first), rel_end = rel(end), rel_b = rel(my_b);
@@ -134,21 +182,15 @@ __global__ void __launch_bounds__(kLds ? 1024 : kBlock) k_walk_step(WalkStepArgs
             for (int t = 0; t < kUnroll; ++t) {
                 const int x = rel_b - t * kWave;                 // entries of this chunk before my_b
                 const bool here = x >= 1 && x <= kWave;
-                if (kIn == kBits) {
-                    const uint64_t m = __ballot(v[t] != 0ull);
-                    if (here) at_b = carry + (unsigned long long) __popcll(x == kWave ? m : m & ((1ull << x) - 1ull));
-                    carry += (unsigned long long) __popcll(m);
-                } else {
-                    const unsigned long long incl = wave_inclusive_scan64(v[t]);
-                    const unsigned long long got = __shfl(incl, here ? x - 1 : 0, kWave);
-                    if (here) at_b = carry + got;
-                    carry += last_lane64(incl);
-                    if (kIn == kWide) {
-                        const unsigned long long incl_hi = wave_inclusive_scan64(v[t] >> 32);
-                        const unsigned long long got_hi = __shfl(incl_hi, here ? x - 1 : 0, kWave);
-                        if (here) at_b_hi = carry_hi + got_hi;
-                        carry_hi += last_lane64(incl_hi);
-                    }
+                const unsigned long long incl = wave_inclusive_scan64(v[t]);
+                const unsigned long long got = __shfl(incl, here ? x - 1 : 0, kWave);
+                if (here) at_b = carry + got;
+                carry += last_lane64(incl);
+                if (kIn == kWide) {
+                    const unsigned long long incl_hi = wave_inclusive_scan64(v[t] >> 32);
+                    const unsigned long long got_hi = __shfl(incl_hi, here ? x - 1 : 0, kWave);
+                    if (here) at_b_hi = carry_hi + got_hi;
+                    carry_hi += last_lane64(incl_hi);
                 }
             }
         }

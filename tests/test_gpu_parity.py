@@ -380,6 +380,27 @@ def test_walk_probability_vector_widths(n, scale):
         gns.close()
 
 
+@pytest.mark.parametrize("n,degrees", [(3000, (0,)), (3000, (0, 0, 0, 7)), (3000, (1023, 1, 0)), (70000, (0, 1024, 0, 2049, 5, 0))])
+def test_walk_windows_and_runs_of_empty_rows(n, degrees):
+    """The first step's windows of 1024 entries: rows that end, begin and span where a window does, windows that begin
+    inside the row before, runs of nothing but empty rows, in the middle and behind the last entry."""
+    rng = np.random.default_rng(n + len(degrees))
+    deg = np.zeros(n, dtype=np.int64)
+    deg[500:700] = [degrees[i % len(degrees)] for i in range(200)]
+    deg[[3, 64, 1200]] = (17, 1024, 33)
+    ip = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    ix = np.concatenate([np.sort(rng.choice(n, d, replace=False)) for d in deg if d]).astype(np.int32)
+    ip, ix = torch.from_numpy(ip), torch.from_numpy(ix)
+    gns = GpuGns(ip, ix, None, fanouts=(3, 2), policies=(U, C), cache_size=2, max_seeds=8, cache_probability=B.GNS_PROB_WALK)
+    try:
+        train = torch.arange(1, n, 3, dtype=torch.int32)
+        w, pre, _, _ = gns.walk_probability(train, 20)
+        w_ref, pre_ref = oracle.walk_weights(ip.numpy(), ix.numpy(), train.numpy(), [3, 2], scale_log2=20)
+        assert np.array_equal(w, w_ref) and np.array_equal(pre, pre_ref)
+    finally:
+        gns.close()
+
+
 def test_cache_nearly_all_nodes():
     # the cache takes every node that has a neighbor: the stream must run until the rarest node shows up
     ip, ix = _small(n=300, avg=6)
