@@ -1,9 +1,10 @@
 // The update step of one layer (paper Algorithm 1, h_u = g(W . (h_u, h_N(u))), GraphSAGE form of
 // Section 2.1), forward only:  out = g([h_self | h_neigh] . W + bias).  This is the one dense
-// contraction of the path, so it runs on the matrix cores: fp32 products, fp32 accumulate.
+// contraction of the path, so it runs on the matrix cores, with the precision of fp32 products and fp32 sums.
 //
-// Two kernels: k_sage_rows keeps a slab of the weights in LDS and streams rows past it (from a few thousand rows on);
-// k_sage_split cuts k into four for everything the first has no rows or no LDS for.
+// Three kernels: k_sage_rows keeps a slab of the weights in LDS and streams rows past it (from a few thousand rows on);
+// k_sage_terms does the same with the factors in bf16 terms on the faster matrix cores (large products);
+// k_sage_split cuts k into four for everything the others have no rows or no LDS for.
 #include "gns_internal.h"
 #include "gns_device.hpp"
 
@@ -165,6 +166,162 @@ __global__ void __launch_bounds__(kRowsBlock) k_sage_rows(DenseArgs a)
     }
 }
 
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// Eight consecutive k of one row or column as three bf16 terms each: x = hi + mid + lo exactly (8 + 8 + 8 bits, every term
+// what is left of x cut after its top 16 bits; below 2^-110 the last terms leave the normal range).
+struct SplitFrag { uint32_t term[3][4]; };
+
+__device__ __forceinline__ SplitFrag split8(const float4& x0, const float4& x1)
+{
+    const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+    uint32_t t[3][8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        float r = x[i];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            t[q][i] = __float_as_uint(r) & 0xFFFF0000u;
+            if (q < 2) r -= __uint_as_float(t[q][i]);
+        }
+    }
+    SplitFrag f;
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f.term[q][i] = __builtin_amdgcn_perm(t[q][2 * i + 1], t[q][2 * i], 0x07060302u);   // upper halves
+    return f;
+}
+
+__device__ __forceinline__ bf16x8 as_bf16(const uint32_t (&t)[4])
+{
+    const uint4 v = make_uint4(t[0], t[1], t[2], t[3]);
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+constexpr int terms_block(int slab) { return slab == 64 ? 768 : 1024; }        // three or four waves per SIMD
+constexpr int kTermsTile = 32;
+
+// k_sage_terms: the products on the bf16 matrix cores, at no less than fp32's precision.  Both factors are split into three
+// bf16 terms, which hold every bit of an fp32; of the nine products of terms the six largest are taken (the others are
+// below 2^-24 of the product together).  The products of the leading terms and the rest have an accumulator each, so the
+// large sum is rounded once per 16 k and the rest, at 2^-8 of its size, adds next to nothing.  Error against 64 bits (2-norm,
+// normal inputs): 8.0e-8 at K = 256, 1.0e-7 at K = 512, 6e-8 at K = 56 to 72; k_sage_rows 2.0e-7, 2.9e-7, 9 to 10e-8 (one
+// accumulator for all six products: 1.7e-7, 2.5e-7, and at small K no better than fp32).
+// Layout as in k_sage_rows: one block per CU holds a slab of kSlab columns of W in LDS, in terms, and its waves walk tiles
+// of 32 rows, splitting the rows as they come in.  32x32x16 products: lane l holds k 8 * (l / 32) .. + 7 of the step, of row
+// l % 32 and of column l % 32 of a group; a fragment of W is one 16-byte read of LDS.  Per step and group of 32 columns a
+// wave multiplies for 192 cycles and reads 3 KB of LDS, half of what LDS delivers to four SIMDs in that time.
+// 85,000 rows, K = 256, 256 columns: 79 us, of which the products at the matrix cores' rate are 30 (k_sage_rows: 109);
+// 12,600 rows, K = 512: 38 us (43); 200,000 rows, K = 128: 115 us (138).  What is left is a wave's chain of splitting, LDS
+// reads and products with three waves per SIMD to hide it (two: 85 us), and the rows, read once per slab.
+// A result that is not finite (an infinity or NaN among its inputs, or an overflow) is computed once more with plain fp32
+// products: the terms of an infinity do not add up to it.
+template <int kSlab>
+__global__ void __launch_bounds__(terms_block(kSlab)) k_sage_terms(DenseArgs a)
+{
+    constexpr int kGroups = kSlab / 32, kTermsBlock = terms_block(kSlab);
+    constexpr int kDepth = 2;                     // steps of activations in flight
+    extern __shared__ uint4 s_terms[];            // [step][term][half of the step][column]: eight k each
+    const int32_t K = a.f1 + a.f2, steps = (K + 15) / 16;
+    const int32_t q = (int32_t) blockIdx.x / 8, xcd = (int32_t) blockIdx.x % 8;      // as in k_sage_rows
+    const int32_t n0 = q % a.n_blocks * kSlab;
+    const int32_t strip = q / a.n_blocks * 8 + xcd;
+    const int32_t rows = a.rows_dev ? *a.rows_dev : a.rows;
+    for (int32_t i = (int32_t) threadIdx.x; i < steps * 2 * kSlab; i += kTermsBlock) {
+        const int32_t c = i % kSlab, k0 = i / kSlab * 8, col = n0 + c;
+        float x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = k0 + u < K && col < a.hdim ? a.w[(int64_t) (k0 + u) * a.hdim + col] : 0.f;
+        const SplitFrag f = split8(make_float4(x[0], x[1], x[2], x[3]), make_float4(x[4], x[5], x[6], x[7]));
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+            s_terms[(((k0 >> 4) * 3 + t) * 2 + ((k0 >> 3) & 1)) * kSlab + c] = make_uint4(f.term[t][0], f.term[t][1], f.term[t][2], f.term[t][3]);
+    }
+    __syncthreads();
+    const int wave = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
+    const int lane = (int) threadIdx.x & 63, kh = lane >> 5, l32 = lane & 31;
+    float bias[kGroups];
+#pragma unroll
+    for (int h = 0; h < kGroups; ++h) {
+        const int32_t col = n0 + h * 32 + l32;
+        bias[h] = a.bias && col < a.hdim ? a.bias[col] : 0.f;
+    }
+    const int32_t tiles = (rows + kTermsTile - 1) / kTermsTile;
+    for (int32_t tile = wave * a.m_blocks + strip; tile < tiles; tile += a.m_blocks * (kTermsBlock / kWave)) {
+        const int64_t r0 = (int64_t) tile * kTermsTile;
+        const int64_t r = r0 + l32 < rows ? r0 + l32 : rows - 1;          // read, never stored
+        const float* row1 = a.a1 + r * a.f1;
+        const float* row2 = a.a2 + r * a.f2 - a.f1;
+        float4 x[kDepth][2];
+        // k of the step past K read the row's first ones again; their weights in LDS are zero, so only a row with a value
+        // that is not finite notices, and that one is computed once more
+        auto fetch = [&](int d, int32_t step) {
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int32_t at = step * 16 + 8 * kh + 4 * e, k = at < K ? at : 0;
+                x[d][e] = *reinterpret_cast<const float4*>((k < a.f1 ? row1 : row2) + k);
+            }
+        };
+        floatx16 acc[kGroups], rest[kGroups];
+#pragma unroll
+        for (int h = 0; h < kGroups; ++h)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[h][v] = rest[h][v] = 0.f;
+        auto multiply = [&](const float4& x0, const float4& x1, int32_t step) {
+            const SplitFrag f = split8(x0, x1);
+            const bf16x8 hi = as_bf16(f.term[0]), mid = as_bf16(f.term[1]), lo = as_bf16(f.term[2]);
+#pragma unroll
+            for (int h = 0; h < kGroups; ++h) {
+                const uint4* p = s_terms + (step * 6 + kh) * kSlab + h * 32 + l32;
+                const bf16x8 whi = __builtin_bit_cast(bf16x8, p[0]);
+                const bf16x8 wmid = __builtin_bit_cast(bf16x8, p[2 * kSlab]);
+                const bf16x8 wlo = __builtin_bit_cast(bf16x8, p[4 * kSlab]);
+                rest[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo, whi, rest[h], 0, 0, 0);
+                rest[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, wlo, rest[h], 0, 0, 0);
+                rest[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mid, wmid, rest[h], 0, 0, 0);
+                rest[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(mid, whi, rest[h], 0, 0, 0);
+                rest[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, wmid, rest[h], 0, 0, 0);
+                acc[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, whi, acc[h], 0, 0, 0);
+            }
+        };
+        // steps past the last re-read it, so that no read of the loop sits in a branch
+        auto clamped = [&](int32_t step) { return step < steps ? step : steps - 1; };
+#pragma unroll
+        for (int d = 0; d < kDepth; ++d) fetch(d, clamped(d));
+        int32_t s = 0;
+        for (; s + kDepth <= steps; s += kDepth) {
+#pragma unroll
+            for (int d = 0; d < kDepth; ++d) {
+                const float4 x0 = x[d][0], x1 = x[d][1];
+                fetch(d, clamped(s + d + kDepth));
+                multiply(x0, x1, s + d);
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < kDepth; ++d)
+            if (s + d < steps) multiply(x[d][0], x[d][1], s + d);
+#pragma unroll
+        for (int h = 0; h < kGroups; ++h) {
+            const int32_t col = n0 + h * 32 + l32;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int64_t row = r0 + 8 * (v >> 2) + 4 * kh + (v & 3);
+                if (row >= rows || col >= a.hdim) continue;
+                float y = acc[h][v] + rest[h][v];
+                if (!(fabsf(y) < __builtin_inff())) {
+                    y = 0.f;
+                    for (int32_t k = 0; k < K; ++k)
+                        y = fmaf(k < a.f1 ? a.a1[row * a.f1 + k] : a.a2[row * a.f2 + k - a.f1], a.w[(int64_t) k * a.hdim + col], y);
+                }
+                y += bias[h];
+                if (a.relu) y = fmaxf(y, 0.f);
+                a.out[row * a.hdim + col] = y;
+            }
+        }
+    }
+}
+
 // k_sage_split: a block of four waves owns 32 rows x 32 * NT columns and cuts k in four (the waves' sums meet in LDS), so
 // that a thousand rows still occupy every CU and no wave's chain of products is long.  32x32x2 products, k in steps of
 // 32: A comes in as whole 128-byte lines (eight lanes per row) and is turned through a piece of LDS of the wave's own;
@@ -305,6 +462,15 @@ static void launch_rows(const gns_ctx* c, DenseArgs a, hipStream_t s)
     hipLaunchKernelGGL(k_sage_rows<kSlab>, dim3((unsigned) (a.m_blocks * a.n_blocks)), dim3(kRowsBlock), lds, s, a);
 }
 
+template <int kSlab>
+static void launch_terms(const gns_ctx* c, DenseArgs a, hipStream_t s)
+{
+    a.n_blocks = (a.hdim + kSlab - 1) / kSlab;
+    a.m_blocks = c->num_cus / 8 / a.n_blocks * 8;              // strips of rows
+    const size_t lds = (size_t) ((a.f1 + a.f2 + 15) / 16 * 16) * kSlab * 6;
+    hipLaunchKernelGGL(k_sage_terms<kSlab>, dim3((unsigned) (a.m_blocks * a.n_blocks)), dim3(terms_block(kSlab)), lds, s, a);
+}
+
 template <int NT>
 static void launch_split(DenseArgs a, hipStream_t s)
 {
@@ -333,6 +499,18 @@ hipError_t launch_sage_dense(gns_ctx* c, const float* h_self, int32_t f1, const 
     // num_cus * 4 tiles; below three quarters of that, and where no slab fits, the split kernel is ahead (256 columns,
     // K = 512: 13.0 against 8.2 us at 1024 rows, 14.4 against 15.8 us at 4000).
     const int32_t K = f1 + f2;
+    // k_sage_terms where its slab of at least 32 columns fits LDS (K up to 848) and every SIMD gets two tiles of 32 x 32 and
+    // more; with fewer, and for narrow outputs, which leave its splitting of the rows little to be spread over, the fp32
+    // products are as fast or faster (256 columns: 7000 rows, K = 256, 15.0 against 14.6 us, 12,600 rows, K = 512, 38 against
+    // 43; 40,000 rows, K = 512, 32 columns: 22.1 against 20.8 us; 20,000 rows, K = 128, 64 columns: 10.0 against 9.6).
+    int32_t terms = 64;
+    while (terms >= 32 && (size_t) ((K + 15) / 16 * 16) * 6 * terms > c->lds_bitmap_limit) terms /= 2;
+    if (K > 0 && hdim > 64 && terms >= 32 && (hdim + terms - 1) / terms <= c->num_cus / 8 &&
+        ((int64_t) rows + 31) / 32 * ((hdim + 31) / 32) >= (int64_t) c->num_cus * 8) {
+        if (terms == 64) launch_terms<64>(c, a, s);
+        else             launch_terms<32>(c, a, s);
+        return hipGetLastError();
+    }
     const size_t k_bytes = (size_t) ((K + 15) / 16 * 16) * 4;
     const int32_t want = hdim > 64 ? 128 : hdim > 32 ? 64 : 32;
     int32_t slab = want;

@@ -933,6 +933,41 @@ def test_sage_dense_slabs_and_split(rows, f1, f2, hdim):
     test_sage_dense_update_step(rows, f1, f2, hdim, rows % 2 == 0, True)
 
 
+@pytest.mark.parametrize("rows,f1,f2,hdim", [(16_385, 64, 68, 128), (9_400, 36, 220, 200), (8_193, 400, 448, 256), (8_200, 400, 452, 256),
+                                             (21_900, 208, 208, 96), (22_000, 212, 208, 68), (16_400, 4, 4, 128)])
+def test_sage_dense_in_bf16_terms(rows, f1, f2, hdim):
+    """Slabs of 64 and 32 columns in terms and the first K beyond them; rows, k and columns past the last.  The bound is that
+    of the fp32 products: a product of terms is exact in the accumulator's 24 bits, the three that are left out are below
+    3 * 2^-25 of |a||w|, and there are fewer additions."""
+    test_sage_dense_update_step(rows, f1, f2, hdim, rows % 2 == 0, True)
+
+
+def test_sage_dense_infinities_nan_and_the_largest_values():
+    """Values whose bf16 terms do not add up to them, and the largest finite ones: as plain products have it."""
+    rows, f, hdim = 16_500, 64, 128
+    gns = GpuGns(*_small(n=600), None, fanouts=(2,), policies=(U,), cache_size=0, max_seeds=8)
+    try:
+        g = torch.Generator().manual_seed(4)
+        a = torch.randn((rows, 2 * f), generator=g)
+        w = torch.randn((2 * f, hdim), generator=g) / 16
+        w[3, 5], w[70, 90] = 0.0, float("inf")
+        a[17, 2], a[40, 100], a[41, 3], a[90, 70] = float("inf"), -float("inf"), float("inf"), 0.0
+        a[300, 7], a[16_499, 127] = float("nan"), 3.0e38
+        out = torch.full((rows, hdim), 7.0, device=gns.device)
+        B.gns_sage_dense(gns.ctx, a[:, :f].contiguous().cuda(), a[:, f:].contiguous().cuda(), w.cuda(), None, False, out, rows)
+        ref = (a.double() @ w.double()).float()
+        out = out.cpu()
+        assert torch.equal(torch.isnan(out), torch.isnan(ref))
+        inf = torch.isinf(ref)
+        assert torch.equal(out[inf], ref[inf]) and not torch.isinf(out[~inf]).any()
+        ok = torch.isfinite(ref)
+        scale = torch.where(torch.isfinite(a), a, 0.0).double().abs() @ torch.where(torch.isfinite(w), w, 0.0).double().abs()
+        err = (out.double() - ref.double()).abs()
+        assert bool((err[ok] <= (2 * f + 3) * 2.0 ** -24 * scale[ok]).all())
+    finally:
+        gns.close()
+
+
 def _group_setup(gns, count):
     """count contexts (the created one and forks) with their own block buffers, feature buffers and a GroupCall."""
     ctxs, keep = [gns.ctx], []
