@@ -174,10 +174,11 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     L.coarse_bitmap = 0;
     if (uses_cache && (size_t) L.words * 8 > kLdsBitmapBytes) {
         int sh = 1;
-        while (sh <= 9 && (size_t) (((n >> sh) + 63) / 64 + 1) * 8 > kLdsBitmapBytes) ++sh;
-        // Too big for LDS even at one bit per 512 ids (more than 650 M nodes): the coarse bitmap then stays in global
-        // memory at one bit per 16 ids, where it spares most entries the read of the exact bitmap.
-        if (sh > 9) {
+        while (sh <= 6 && (size_t) (((n >> sh) + 63) / 64 + 1) * 8 > kLdsBitmapBytes) ++sh;
+        // Beyond one bit per 64 ids (more than 81 M nodes) most entries would pass: the coarse bitmap then stays in global
+        // memory, in every L2, at one bit per 16 ids
+        // (111 M nodes, 1.6 G entries: a draw takes 20.9 ms so, 26.1 ms with one bit per 128 ids in LDS).
+        if (sh > 6) {
             sh = 4;
             if (const char* e = getenv("GNS_COARSE_SHIFT")) { const int v = atoi(e); if (v >= 1 && v <= 6) sh = v; }
         }
