@@ -16,7 +16,7 @@ Passes over the same workload:
   A  the timed region of the contract: K steps, repeated --repeats times back to
      back (each window bracketed by a device synchronisation); `value` is K over
      the median window.  Warm-up runs at least --warmup steps and always a whole
-     number of cache periods, so that every launch sequence has been captured and
+     number of cache periods, so that every launch sequence has run and
      both copies of the cache structures have been drawn before the first window.
   C  the same windows without the aggregation: the sampler + gather pipeline alone
      (`roofline.sampler_gather`).

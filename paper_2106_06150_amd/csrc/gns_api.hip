@@ -166,7 +166,7 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     L.cache_prefix = take((size_t) L.words * 4);
     // A cache bitmap too big for LDS gets a coarse companion that does fit: one bit per 2^shift ids.  With a cache of
     // about 1 % of the nodes it answers "not cached" without leaving the CU for most entries while the groups are small,
-    // and for a good part of them up to groups of a few hundred; what passes costs one request to the exact bitmap, and
+    // and for a good part of them up to groups of a few dozen; what passes costs one request to the exact bitmap, and
     // the rate of those requests bounds the pass.  (40 M nodes, 400 M entries: one bit per 32 ids in LDS passes half of
     // the entries, 1.33 ms; one bit per 16 ids in L2, a request for every entry and for 46 % of them a second, 2.67 ms.)
     L.coarse_shift = 0;
@@ -177,7 +177,7 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
         while (sh <= 6 && (size_t) (((n >> sh) + 63) / 64 + 1) * 8 > kLdsBitmapBytes) ++sh;
         // Beyond one bit per 64 ids (more than 81 M nodes) most entries would pass: the coarse bitmap then stays in global
         // memory, in every L2, at one bit per 16 ids
-        // (111 M nodes, 1.6 G entries: a draw takes 20.9 ms so, 26.1 ms with one bit per 128 ids in LDS).
+        // (111 M nodes, 1.6 G entries: a draw takes 10.7 ms so, 16.0 ms with one bit per 128 ids in LDS).
         if (sh > 6) {
             sh = 4;
             if (const char* e = getenv("GNS_COARSE_SHIFT")) { const int v = atoi(e); if (v >= 1 && v <= 6) sh = v; }

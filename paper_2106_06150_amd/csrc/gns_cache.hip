@@ -406,8 +406,10 @@ gns_status run_sample_cache(gns_ctx* c, uint64_t seed, uint64_t epoch, bool wait
     // the device may not have reached all of it yet if the host runs far ahead, so the draw waits for them.
     const int gen = c->had_cache ? (c->cache_gen ^ 1) : 0;
     uint64_t* bitmap = cache_ptr<uint64_t>(c, L.cache_bitmap, gen);
-    if (c->pending)                                  // a draw that was never made current: this one replaces it
-        GNS_HIP_TRY(hipStreamWaitEvent(s, c->ready_event[c->pending_gen], 0), "wait for the replaced draw");
+    // Draws share their hash and their outcome, so one begins when the one before has ended, also on another stream: the
+    // one that is to be made current still (this one replaces it), or the one that is.
+    if (c->pending || c->had_cache)
+        GNS_HIP_TRY(hipStreamWaitEvent(s, c->ready_event[c->pending ? c->pending_gen : c->cache_gen], 0), "wait for the draw before");
     for (int i = 0; i < c->family_count; ++i) {
         gns_ctx* m = c->family[i];
         for (int i = 0; i < m->gen_event_used[gen]; ++i)

@@ -8,9 +8,8 @@
 
 namespace gns {
 
-// Device-resident scalars the kernels of one call communicate through.  The
-// whole struct is copied to a pinned host mirror when a call has to report
-// counts.
+// Device-resident scalars the kernels of one call communicate through.  What a
+// call reports to the host goes into the same fields of a pinned struct.
 struct DeviceState {
     int32_t num_dst[GNS_MAX_LAYERS + 1];  // rows of layer index i (num_dst[i+1] = num_src of layer i)
     int32_t num_edges[GNS_MAX_LAYERS];

@@ -406,7 +406,11 @@ gns_status run_walk_probability(gns_ctx* c, const int32_t* train_nodes, int64_t 
     hipLaunchKernelGGL(k_walk_scan_phase2, dim3(1), dim3(kBlock), 0, s, tile_sums, tile_nz, tiles, c->d_state);
     hipLaunchKernelGGL(k_walk_scan_phase3, dim3((unsigned) tiles), dim3(kBlock), 0, s, cur, n, tile_sums, prefix, c->d_state);
     e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(c->h_draw, c->d_state, sizeof(DeviceState), hipMemcpyDeviceToHost, s);
+    // only the walk's own fields (walk_total, walk_support, walk_error): a draw in flight leaves its outcome beside them
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(&c->h_draw->walk_total, &c->d_state->walk_total,
+                           offsetof(DeviceState, walk_error) + sizeof(int32_t) - offsetof(DeviceState, walk_total),
+                           hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return ctx_fail(c, GNS_EHIP, "walk probability", e);
     if (c->h_draw->walk_error == 1) return ctx_fail(c, GNS_EINVAL, "a training node id lies outside [0, num_nodes)");
