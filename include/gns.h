@@ -25,9 +25,10 @@
  *    device memory the kernels touch is the caller's (or, for
  *    gns_sample_blocks_static, the library's fixed scratch array).  What the
  *    library itself allocates is host-side or runtime state: gns_create and
- *    gns_fork allocate a small pinned host mirror of the device counters and
- *    HIP events; gns_profile_begin creates HIP events.  Everything is released
- *    by gns_destroy.
+ *    gns_fork allocate a small pinned host mirror of the device counters, HIP
+ *    events and a capture stream; the first mini-batch with a new set of block
+ *    buffers instantiates a HIP graph of its launch sequence; gns_profile_begin
+ *    creates HIP events.  Everything is released by gns_destroy.
  *  - All device work is enqueued on the hipStream_t passed as `hip_stream`
  *    (NULL = the default stream).  Calls that must report counts to the host
  *    (gns_sample_cache, gns_sample_blocks) synchronise that stream before
@@ -54,6 +55,8 @@
  *      GNS_UNION_SPINS=<n>  how often a block of the union step polls for another
  *        block's count before it counts that part of the bitmap itself
  *        (default 256)
+ *      GNS_NO_GRAPH=1  enqueue a mini-batch's kernels one by one instead of
+ *        replaying a captured HIP graph
  */
 #ifndef GNS_H_
 #define GNS_H_
@@ -173,7 +176,11 @@ gns_status gns_block_capacity(const gns_graph* graph, const gns_config* config, 
  * gns_workspace_bytes bytes, 256-byte aligned, borrowed until gns_destroy.
  * Validates the arguments (GNS_EINVAL), e.g. cache_size must not exceed the
  * number of nodes with at least one neighbor when a cache policy is used.
- * Initialises the workspace on `hip_stream` and synchronises it. */
+ * Initialises the workspace on `hip_stream` and synchronises it.
+ * A mini-batch of ten launches or more (two layers or more that scan their rows: GNS_FLAGS_PER_BATCH) is captured
+ * into a HIP graph on first use (per set of block buffers) and replayed afterwards, whatever the cache generation;
+ * with the environment variable GNS_NO_GRAPH set when the context is created (forks inherit it) its kernels are
+ * launched one by one like those of shorter ones. */
 gns_status gns_create(gns_ctx** out_ctx, const gns_graph* graph, const gns_config* config,
                       void* workspace, size_t workspace_bytes, void* hip_stream);
 
@@ -310,8 +317,8 @@ gns_status gns_aggregate_group(gns_ctx* const* ctxs, int32_t count, const gns_bl
  * loaded on, instead of in the context's workspace.  Same arguments, same results, same errors
  * as gns_sample_blocks; ctx may be the context made by gns_create or any of its forks (the
  * graph, config and current cache are theirs).  The call allocates nothing: no hipMalloc, no
- * host allocation (the kernels are enqueued on hip_stream, which is synchronised before the call
- * returns).  GNS_ECAPACITY if the per-batch scratch of this graph
+ * host allocation, no HIP graph (the kernels are launched one by one on hip_stream, which is
+ * synchronised before the call returns).  GNS_ECAPACITY if the per-batch scratch of this graph
  * and config (what gns_fork_workspace_bytes reports, without the 4 bytes per node of the node table, which
  * large graphs keep in the context's workspace) exceeds the array: nothing is launched.
  * All calls on one GPU share that GPU's array, whatever their context: it is re-initialised at

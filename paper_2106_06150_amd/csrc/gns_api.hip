@@ -216,10 +216,9 @@ gns_status ctx_fail(gns_ctx* c, gns_status st, const char* what, hipError_t e)
 
 using namespace gns;
 
+// Every launch of one mini-batch, in order, on stream s (also the body that is captured).
 namespace gns {
-// Every launch of one group of mini-batches, in order, on stream s.  They are enqueued one by one: replaying them as a
-// captured graph, which spared the host six launches while there were eleven, starts later and costs more between kernels
-// than seven direct launches (one mini-batch of one seed 67 us replayed, 54 us so; a group of four on 1 M nodes 274 and 269).
+// Every launch of one group of mini-batches, in order, on stream s (also the body that is captured).
 gns_status enqueue_batch(const Group& g, const BeginDyn& d, hipStream_t s)
 {
     gns_ctx* c = g.ctx[0];
@@ -228,7 +227,8 @@ gns_status enqueue_batch(const Group& g, const BeginDyn& d, hipStream_t s)
     const bool fused = first_layer_enters_seeds(c->config);
     hipError_t e = fused ? hipSuccess : launch_batch_begin(g, d, s);
     if (e != hipSuccess) return ctx_fail(c, GNS_EHIP, "batch begin", e);
-    // the later kernels read the seeds from the context's own copy (made by the first kernel)
+    // the batch's kernels read the seeds from the context's own copy (made by the first kernel), so
+    // the captured launch sequence does not depend on where the caller keeps them
     for (int i = 0; i < nl; ++i) {
         {
             StageTimer t(c, GNS_STAGE_SAMPLE + i, s);
@@ -337,6 +337,102 @@ static void events_destroy(gns_ctx* c)
     }
 }
 
+static void graph_release(BatchGraph& g)
+{
+    if (g.exec) (void) hipGraphExecDestroy(g.exec);
+    if (g.graph) (void) hipGraphDestroy(g.graph);
+    g.exec = nullptr;
+    g.graph = nullptr;
+    g.first = nullptr;
+    g.valid = false;
+}
+
+// Whether a mini-batch's launches are replayed as a captured graph: from ten launches on (two or more layers that scan their
+// rows).  Starting a graph and setting its first node's arguments costs the host as much as a handful of launches, and
+// small kernels follow one another with longer gaps in it: seven launches take 54 us directly and 67 replayed (one seed),
+// 269 and 274 for a group of four on 1 M nodes, nine (a scan of the input layer) 189 and 196.  Fourteen launches on each
+// of two streams leave the device waiting for the host: 147 us directly, 107 replayed (batches of 100 on 300 K nodes).
+static bool replayed(const gns_config& config)
+{
+    int launches = first_layer_enters_seeds(config) ? 1 : 2;                  // the last relabel, k_batch_begin
+    for (int i = 0; i < config.num_layers; ++i) launches += direct_layer(config, i) ? 2 : 4;
+    return launches > 9;
+}
+
+// A group's launch sequence does not depend on the data (grids are sized for the worst case; counts, stamps and the
+// cache generation stay on the device), so it is captured once per set of contexts and caller block buffers and replayed
+// with hipGraphLaunch; only the first kernel's arguments (seeds pointers, seeds, seed counts, batch ids, stamps, cache
+// generation) change between replays.  The graphs are kept by the group's first context.
+static gns_status launch_batch_graph(const Group& grp, const BeginDyn& dyn, hipStream_t s)
+{
+    gns_ctx* c = grp.ctx[0];
+    const int nl = c->config.num_layers;
+    BatchGraph* hit = nullptr;
+    BatchGraph* victim = &c->bg[0];
+    for (int k = 0; k < kGraphsPerContext; ++k) {
+        BatchGraph& g = c->bg[k];
+        if (!g.valid) { victim = &g; continue; }
+        bool same = g.count == grp.count;
+        for (int b = 0; same && b < grp.count; ++b) {
+            same = g.ctx[b] == grp.ctx[b];
+            for (int i = 0; same && i < nl; ++i) {
+                const gns_block& x = g.blocks[b][i];
+                const gns_block& y = grp.blocks[b][i];
+                same = x.indptr == y.indptr && x.indices == y.indices && x.src_nodes == y.src_nodes &&
+                       x.row_eligible == y.row_eligible && x.weights == y.weights;
+            }
+        }
+        if (same) { hit = &g; break; }
+        if (victim->valid && g.last_use < victim->last_use) victim = &g;
+    }
+    hipError_t e;
+    if (!hit) {
+        BatchGraph& g = *victim;
+        graph_release(g);
+        e = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeRelaxed);
+        if (e != hipSuccess) return ctx_fail(c, GNS_EHIP, "begin capture", e);
+        const gns_status st = enqueue_batch(grp, dyn, c->cap_stream);
+        e = hipStreamEndCapture(c->cap_stream, &g.graph);
+        if (st != GNS_OK) { graph_release(g); return st; }
+        if (e != hipSuccess) { graph_release(g); return ctx_fail(c, GNS_EHIP, "end capture", e); }
+        e = hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0);
+        if (e != hipSuccess) { graph_release(g); return ctx_fail(c, GNS_EHIP, "graph instantiate", e); }
+        // the sequence is a chain: its one root is the first kernel, whose arguments change from replay to replay
+        size_t count = 1;
+        e = hipGraphGetRootNodes(g.graph, &g.first, &count);
+        if (e != hipSuccess || count != 1) { graph_release(g); return ctx_fail(c, GNS_EHIP, "first kernel of the captured graph", e); }
+        g.count = grp.count;
+        for (int b = 0; b < grp.count; ++b) {
+            g.ctx[b] = grp.ctx[b];
+            for (int i = 0; i < nl; ++i) g.blocks[b][i] = grp.blocks[b][i];
+        }
+        // the first kernel's fixed argument block: the same for every replay of this graph
+        static_assert(sizeof(LayerArgs) <= sizeof(g.args.fixed), "BeginArgsHost::fixed too small");
+        static_assert(sizeof(BeginDyn) <= sizeof(g.args.dyn), "BeginArgsHost::dyn too small");
+        fill_first_args(grp, reinterpret_cast<LayerArgs*>(g.args.fixed));
+        g.args.rows_per_wave = rows_per_sum(grp, 0) / (kBlock / kWave);
+        g.valid = true;
+        hit = &g;
+    }
+    BatchGraph& g = *hit;
+    g.last_use = ++c->graph_clock;
+    // new scalars for this group of batches
+    hipKernelNodeParams kp;
+    e = hipGraphKernelNodeGetParams(g.first, &kp);
+    if (e != hipSuccess) return ctx_fail(c, GNS_EHIP, "get first kernel params", e);
+    memcpy(g.args.dyn, &dyn, sizeof(dyn));
+    g.arg_ptrs[0] = g.args.fixed;
+    g.arg_ptrs[1] = g.args.dyn;
+    g.arg_ptrs[2] = &g.args.rows_per_wave;
+    kp.kernelParams = g.arg_ptrs;
+    kp.extra = nullptr;
+    e = hipGraphExecKernelNodeSetParams(g.exec, g.first, &kp);
+    if (e != hipSuccess) return ctx_fail(c, GNS_EHIP, "set first kernel params", e);
+    e = hipGraphLaunch(g.exec, s);
+    if (e != hipSuccess) return ctx_fail(c, GNS_EHIP, "graph launch", e);
+    return GNS_OK;
+}
+
 namespace gns {
 // What a context's per-batch scratch must hold before its first mini-batch: zeroed device state and tile
 // sums, empty mark bitmaps, a node table without stamps.  Enqueue only.
@@ -358,7 +454,7 @@ hipError_t init_batch_scratch(gns_ctx* c, hipStream_t s)
 
 // A context that shares root's graph, config and cache and keeps its per-batch scratch at `workspace`
 // (not initialised here).  Joins root's family.
-gns_status make_child(gns_ctx* root, void* workspace, gns_ctx** out)
+gns_status make_child(gns_ctx* root, void* workspace, bool with_capture_stream, gns_ctx** out)
 {
     *out = nullptr;
     if (root->family_count >= (int) (sizeof(root->family) / sizeof(root->family[0])))
@@ -375,19 +471,33 @@ gns_status make_child(gns_ctx* root, void* workspace, gns_ctx** out)
     c->prof_capacity = c->prof_count = 0;
     c->prof_mask = 0;
     c->err[0] = 0;
+    c->bg = nullptr;
+    c->graph_clock = 0;
     c->stamp = 0;
     c->batch_id = 0;
     c->bad_reported = 0;
+    c->cap_stream = nullptr;
     c->family_count = 0;
     c->static_child = nullptr;
     memset(c->gen_event, 0, sizeof(c->gen_event));
     c->ready_event[0] = c->ready_event[1] = nullptr;
-    hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&c->h_state), 2 * sizeof(DeviceState), hipHostMallocDefault);
-    if (e != hipSuccess) c->h_state = nullptr;
+    hipError_t e = hipSuccess;
+    if (with_capture_stream) {
+        e = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking);
+        if (e != hipSuccess) c->cap_stream = nullptr;
+        c->bg = static_cast<BatchGraph*>(calloc(kGraphsPerContext, sizeof(BatchGraph)));
+        if (e == hipSuccess && !c->bg) e = hipErrorOutOfMemory;
+    }
+    if (e == hipSuccess) {
+        e = hipHostMalloc(reinterpret_cast<void**>(&c->h_state), 2 * sizeof(DeviceState), hipHostMallocDefault);
+        if (e != hipSuccess) c->h_state = nullptr;
+    }
     if (e == hipSuccess) e = host_mirror_setup(c);
     if (e == hipSuccess) e = events_create(c);
     if (e != hipSuccess) {
+        free(c->bg);
         if (c->h_state) (void) hipHostFree(c->h_state);
+        if (c->cap_stream) (void) hipStreamDestroy(c->cap_stream);
         events_destroy(c);
         delete c;
         return ctx_fail(root, GNS_EHIP, "child context", e);
@@ -454,6 +564,8 @@ gns_status gns_create(gns_ctx** out_ctx, const gns_graph* graph, const gns_confi
         if (e != hipSuccess) snprintf(g_create_err, sizeof(g_create_err), "%s: %s", what, hipGetErrorString(e));
         else snprintf(g_create_err, sizeof(g_create_err), "%s", what);
         if (c->h_state) (void) hipHostFree(c->h_state);
+        if (c->cap_stream) (void) hipStreamDestroy(c->cap_stream);
+        free(c->bg);
         events_destroy(c);
         delete c;
         return st;
@@ -477,6 +589,13 @@ gns_status gns_create(gns_ctx** out_ctx, const gns_graph* graph, const gns_confi
     c->union_spins = getenv("GNS_UNION_SPINS") ? atoi(getenv("GNS_UNION_SPINS")) : 256;
     c->family[0] = c;
     c->family_count = 1;
+    if (!getenv("GNS_NO_GRAPH")) {
+        e = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking);
+        if (e != hipSuccess) { c->cap_stream = nullptr; return bail(GNS_EHIP, "hipStreamCreate", e); }
+        c->bg = static_cast<BatchGraph*>(calloc(kGraphsPerContext, sizeof(BatchGraph)));
+        if (!c->bg) return bail(GNS_ENOMEM, "host allocation failed", hipSuccess);
+    }
+
     // zero the state, the mark bitmap and the cache bitmap; validate the graph
     e = init_batch_scratch(c, s);
     if (e == hipSuccess) e = launch_fill_u64(cache_ptr<unsigned long long>(c, L.cache_bitmap, 0), (size_t) L.words, 0ull, s);
@@ -588,7 +707,7 @@ gns_status gns_fork(gns_ctx* parent, void* workspace, size_t workspace_bytes, vo
         return ctx_fail(parent, GNS_EINVAL, "workspace must be a 256-byte aligned device pointer");
     if (workspace_bytes < root->lay.shared_begin) return ctx_fail(parent, GNS_ECAPACITY, "fork workspace too small");
     gns_ctx* c = nullptr;
-    const gns_status st = make_child(root, workspace, &c);
+    const gns_status st = make_child(root, workspace, root->cap_stream != nullptr, &c);
     if (st != GNS_OK) { snprintf(parent->err, sizeof(parent->err), "%s", root->err); return st; }
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     hipError_t e = init_batch_scratch(c, s);
@@ -606,6 +725,21 @@ gns_status gns_destroy(gns_ctx* ctx)
     if (!ctx) return GNS_OK;
     if (ctx->static_child) { (void) gns_destroy(ctx->static_child); ctx->static_child = nullptr; }
     profile_release(ctx);
+    // captured launch sequences that name this context: its own, and those of groups it was a member of
+    gns_ctx* fam_root = ctx->root;
+    for (int i = 0; i < fam_root->family_count; ++i) {
+        gns_ctx* m = fam_root->family[i];
+        if (!m->bg) continue;
+        for (int k = 0; k < kGraphsPerContext; ++k) {
+            BatchGraph& g = m->bg[k];
+            bool names = m == ctx;
+            for (int b = 0; !names && b < g.count; ++b) names = g.ctx[b] == ctx;
+            if (names) graph_release(g);
+        }
+    }
+    free(ctx->bg);
+    ctx->bg = nullptr;
+    if (ctx->cap_stream) (void) hipStreamDestroy(ctx->cap_stream);
     if (ctx->h_state) (void) hipHostFree(ctx->h_state);
     events_destroy(ctx);
     if (ctx->root != ctx) {                               // a fork leaves its family
@@ -757,7 +891,8 @@ gns_status gns_sample_blocks_group(gns_ctx* const* ctxs, int32_t count, const ui
     if (es != hipSuccess) return ctx_fail(lead, GNS_EHIP, "node table", es);
     BeginDyn dyn;
     fill_begin_dyn(g, seeds, seeds_dev, num_seeds, &dyn);
-    st = enqueue_batch(g, dyn, s);
+    if (lead->prof_mask == 0 && lead->cap_stream && replayed(lead->config)) st = launch_batch_graph(g, dyn, s);
+    else                                                                     st = enqueue_batch(g, dyn, s);
     if (st != GNS_OK) return st;
     const int nl = lead->config.num_layers;
     for (int b = 0; b < count; ++b) {

@@ -124,7 +124,7 @@ hipError_t launch_batch_begin(const Group& g, const BeginDyn& d, hipStream_t s)
     gns_ctx* c = g.ctx[0];
     LayerArgs a;
     fill_first_args(g, &a);
-    // sized for the largest batch the context accepts
+    // the grid is sized for the largest batch: the same launch serves every replay
     const unsigned grid = (unsigned) ((c->config.max_seeds + kBlock - 1) / kBlock);
     hipLaunchKernelGGL(k_batch_begin, dim3(grid, (unsigned) g.count), dim3(kBlock), 0, s, a, d);
     return hipGetLastError();

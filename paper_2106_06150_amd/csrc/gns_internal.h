@@ -98,7 +98,28 @@ namespace gns {
 // draw after next waits for).
 constexpr int kReaderStreams = 4;
 struct Group;       // gns_kernels.hpp: the mini-batches one launch sequence serves
-struct BeginDyn;    //   the first kernel's per-batch arguments
+struct BeginDyn;    //   the first kernel's per-replay arguments
+// Opaque host-side storage for the first kernel's arguments (LayerArgs, BeginDyn).
+struct BeginArgsHost {
+    alignas(8) unsigned char fixed[3072];
+    alignas(8) unsigned char dyn[768];
+    int rows_per_wave;                   // k_sample_first's third argument
+};
+// One captured launch sequence of a group of mini-batches, kept by the group's first context.
+struct BatchGraph {
+    hipGraph_t graph;
+    hipGraphExec_t exec;
+    hipGraphNode_t first;            // the k_batch_begin node
+    bool valid;
+    uint64_t last_use;
+    // capture key: the contexts of the group and the caller's block buffers
+    int count;
+    gns_ctx* ctx[GNS_MAX_GROUP];
+    gns_block blocks[GNS_MAX_GROUP][GNS_MAX_LAYERS];
+    BeginArgsHost args;              // the first kernel's arguments (the node's parameter list points here)
+    void* arg_ptrs[3];
+};
+constexpr int kGraphsPerContext = 2;
 struct ProfileRecord {
     int32_t stage;
     hipEvent_t start, stop;
@@ -146,6 +167,11 @@ struct gns_ctx {
     int64_t nonzero_degree_nodes;
     int num_cus;
     size_t lds_bitmap_limit;         // largest cache bitmap (bytes) the flag kernel stages in LDS
+    // The launch sequence of one mini-batch, captured once per (seeds pointer, block buffers) and
+    // replayed; only the first kernel's arguments (seed, number of seeds) change between replays.
+    hipStream_t cap_stream;          // used for capture only, never for execution
+    gns::BatchGraph* bg;             // [kGraphsPerContext] captured launch sequences (least recently used is replaced)
+    uint64_t graph_clock;
     uint32_t stamp;                  // of the last mini-batch enqueued on this context, 1 .. lay.max_stamp (0: none yet)
     int union_spins;                 // how often the union step polls another tile's sum before it counts that tile itself
     uint32_t batch_id;               // id of the last mini-batch enqueued on this context (from 1)
@@ -206,7 +232,7 @@ void fill_begin_dyn(const Group& g, const uint64_t* seeds, const int32_t* const*
                     BeginDyn* out);
 gns_status check_batch_args(gns_ctx* c, const int32_t* seeds_dev, int32_t num_seeds, const gns_block* blocks);
 hipError_t init_batch_scratch(gns_ctx* c, hipStream_t s);
-gns_status make_child(gns_ctx* root, void* workspace, gns_ctx** out);
+gns_status make_child(gns_ctx* root, void* workspace, bool with_capture_stream, gns_ctx** out);
 // gns_static.hip
 gns_status static_scratch_setup(gns_ctx* root);
 bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char* err, size_t errlen);

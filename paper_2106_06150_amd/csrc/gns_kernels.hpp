@@ -143,7 +143,7 @@ struct LayerArgs {
     BatchSlot b[kMaxGroup];
 };
 
-// What the first kernel publishes for the others: the group's seeds, keys, ids.
+// What changes from one replay of a group's launch sequence to the next (arguments of the first kernel).
 struct BeginDyn {
     const int32_t* seeds[kMaxGroup];
     int32_t num_seeds[kMaxGroup];

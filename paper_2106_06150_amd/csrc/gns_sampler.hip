@@ -973,7 +973,7 @@ hipError_t launch_first_layer(const Group& g, const BeginDyn& d, hipStream_t s)
     gns_ctx* c = g.ctx[0];
     LayerArgs a;
     fill_first_args(g, &a);
-    // sized for the largest batch the context accepts
+    // the grid is sized for the largest batch: the same launch serves every replay
     const int rows_per_block = rows_per_sum(g, 0);
     const dim3 grid((unsigned) ((c->config.max_seeds + rows_per_block - 1) / rows_per_block), (unsigned) g.count);
     with_unroll(a.s.fanout, [&](auto K) {

@@ -47,7 +47,7 @@ gns_status static_scratch_setup(gns_ctx* root)
     // too big even without the node table: the entry point says so
     if (root->lay.shared_begin > kStaticScratchBytes && !root->lay.static_table) return GNS_OK;
     gns_ctx* child = nullptr;
-    const gns_status st = make_child(root, g_scratch_ptr[dev], &child);
+    const gns_status st = make_child(root, g_scratch_ptr[dev], false, &child);   // eager launches, no capture
     if (st != GNS_OK) return st;
     // a node table that does not fit the array lies in the root context's workspace (offsets are relative to the array)
     if (root->lay.static_table)
