@@ -4,6 +4,8 @@ capacities, argument validation) behave as documented.  No GPU work here."""
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import pytest
 
@@ -103,3 +105,22 @@ def test_product_path_does_not_touch_the_oracle():
             if f.endswith((".py", ".hip", ".h", ".hpp")):
                 text = open(os.path.join(dirpath, f)).read()
                 assert "oracle" not in text.lower() or f == "synth.py", f
+
+
+def test_kernels_do_not_spill_their_staging_to_scratch_memory(tmp_path):
+    """A kernel with scratch memory starts microseconds later, which is what a short launch takes.  Only the flag pass on
+    graphs whose bitmap does not fit LDS (1024 threads with a chunk set and its coarse words in registers) has a few bytes."""
+    objdump, readelf = (os.path.join("/opt/rocm/llvm/bin", t) for t in ("llvm-objdump", "llvm-readelf"))
+    if not (os.path.exists(objdump) and os.path.exists(readelf)):
+        pytest.skip("no ROCm binary tools")
+    lib = shutil.copy(LIB, tmp_path / "libgns.so")
+    subprocess.run([objdump, "--offloading", lib], cwd=tmp_path, check=True, capture_output=True)
+    scratch = {}
+    for part in tmp_path.glob("*gfx950*"):
+        notes = subprocess.run([readelf, "--notes", str(part)], check=True, capture_output=True, text=True).stdout
+        for name, size in re.findall(r"\.name: +(_Z\w*gns\w+)\s.*?\.private_segment_fixed_size: +(\d+)", notes, re.S):
+            scratch[name] = int(size)
+    assert len(scratch) > 100, len(scratch)
+    allowed = {n: s for n, s in scratch.items() if re.search(r"k_flag_chunksILi[23]E", n)}
+    assert all(s <= 16 for s in allowed.values()), allowed
+    assert not {n: s for n, s in scratch.items() if s and n not in allowed}
