@@ -177,7 +177,8 @@ gns_status gns_block_capacity(const gns_graph* graph, const gns_config* config, 
  * Validates the arguments (GNS_EINVAL), e.g. cache_size must not exceed the
  * number of nodes with at least one neighbor when a cache policy is used.
  * Initialises the workspace on `hip_stream` and synchronises it.
- * A mini-batch of ten launches or more (two layers or more that scan their rows: GNS_FLAGS_PER_BATCH) is captured
+ * A mini-batch of ten launches or more (two layers or more that scan their rows: GNS_FLAGS_PER_BATCH), and one of eight
+ * or nine whose predecessor in the context's family went to another stream, is captured
  * into a HIP graph on first use (per set of block buffers) and replayed afterwards, whatever the cache generation;
  * with the environment variable GNS_NO_GRAPH set when the context is created (forks inherit it) its kernels are
  * launched one by one like those of shorter ones. */

@@ -347,16 +347,19 @@ static void graph_release(BatchGraph& g)
     g.valid = false;
 }
 
-// Whether a mini-batch's launches are replayed as a captured graph: from ten launches on (two or more layers that scan their
-// rows).  Starting a graph and setting its first node's arguments costs the host as much as a handful of launches, and
-// small kernels follow one another with longer gaps in it: seven launches take 54 us directly and 67 replayed (one seed),
-// 269 and 274 for a group of four on 1 M nodes, nine (a scan of the input layer) 189 and 196.  Fourteen launches on each
-// of two streams leave the device waiting for the host: 147 us directly, 107 replayed (batches of 100 on 300 K nodes).
-static bool replayed(const gns_config& config)
+// Whether a mini-batch's launches are replayed as a captured graph.  Starting a graph and setting its first node's
+// arguments costs the host as much as a handful of launches, and small kernels follow one another with longer gaps in it:
+// on one stream seven launches take 54 us directly and 67 replayed (one seed), nine 85 and 90 (a group of two, batches of
+// 100 on 300 K nodes).  With sequences side by side on several streams one host thread enqueues them all and the device
+// waits for it: two sequences of nine launches take 98 us directly and 84 replayed, of fourteen 138 and 124, of seven 81 and
+// 82, of five 77 and 82 (two sequences of groups of two: nine 98 and 101, seven 84 and 85).  So from eight launches on where
+// the family's sequences come on different streams, else from ten on, where replaying halves the host's time (fourteen on
+// one stream: the host 116 us directly, 60 replayed; the device 131 and 136).
+static bool replayed(const gns_config& config, bool side_by_side)
 {
     int launches = first_layer_enters_seeds(config) ? 1 : 2;                  // the last relabel, k_batch_begin
     for (int i = 0; i < config.num_layers; ++i) launches += direct_layer(config, i) ? 2 : 4;
-    return launches > 9;
+    return launches > (side_by_side ? 7 : 9);
 }
 
 // A group's launch sequence does not depend on the data (grids are sized for the worst case; counts, stamps and the
@@ -891,8 +894,12 @@ gns_status gns_sample_blocks_group(gns_ctx* const* ctxs, int32_t count, const ui
     if (es != hipSuccess) return ctx_fail(lead, GNS_EHIP, "node table", es);
     BeginDyn dyn;
     fill_begin_dyn(g, seeds, seeds_dev, num_seeds, &dyn);
-    if (lead->prof_mask == 0 && lead->cap_stream && replayed(lead->config)) st = launch_batch_graph(g, dyn, s);
-    else                                                                     st = enqueue_batch(g, dyn, s);
+    gns_ctx* root = lead->root;
+    const bool side_by_side = root->has_sampled && root->last_sampled_on != s;
+    root->has_sampled = true;
+    root->last_sampled_on = s;
+    if (lead->prof_mask == 0 && lead->cap_stream && replayed(lead->config, side_by_side)) st = launch_batch_graph(g, dyn, s);
+    else                                                                                   st = enqueue_batch(g, dyn, s);
     if (st != GNS_OK) return st;
     const int nl = lead->config.num_layers;
     for (int b = 0; b < count; ++b) {

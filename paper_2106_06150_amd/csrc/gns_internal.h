@@ -156,6 +156,8 @@ struct gns_ctx {
     hipEvent_t ready_event[2];       // recorded behind the draw that filled the copy
     uint64_t cache_version;          // bumped when a copy becomes current
     uint64_t seen_version;           // per context: the version its stream has been made to wait for
+    bool has_sampled;                // root only: whether some context of the family has enqueued mini-batches yet, and
+    hipStream_t last_sampled_on;     //   the stream of the last ones
     gns_ctx* family[64];             // root only: the root itself and its live forks
     int family_count;
     int64_t cache_draws;

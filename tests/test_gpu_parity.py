@@ -237,6 +237,37 @@ def test_graph_replays_and_eager_launches_agree_with_the_oracle():
         gns.close()
 
 
+@pytest.mark.parametrize("fanouts,policies,flag_mode", [((6, 4, 3), (U, U, C), 0), ((5, 4), (C, U), 0), ((4, 3, 3, 2), (U, U, U, C), 1)])
+def test_replays_on_alternating_streams_between_direct_launches(fanouts, policies, flag_mode):
+    """Sequences of nine, eight and nine launches are replayed where the family's sequences alternate between streams and
+    launched directly where they do not: two contexts on two streams, then both on one, then on two again, nothing waited for
+    within a round, every mini-batch against the oracle."""
+    ip, ix = _small(n=4000, avg=16, seed=43)
+    n = ip.numel() - 1
+    csize, bs = 300, 70
+    gns = GpuGns(ip, ix, None, fanouts=fanouts, policies=policies, cache_size=csize, max_seeds=bs, flag_mode=flag_mode)
+    ctxs, keep, bufs, _ = _group_setup(gns, 2)
+    calls = [B.GroupCall([c], [b.array]) for c, b in zip(ctxs, bufs)]
+    try:
+        streams = [torch.cuda.Stream() for _ in range(2)]
+        cache = None
+        for rnd, spread in enumerate((True, True, False, False, True, True)):
+            if rnd % 2 == 0:
+                B.gns_sample_cache(gns.ctx, 6, rnd)
+                cache = oracle.sample_cache(ip.numpy(), 6, rnd, csize)
+            seeds = [synth.uniform_seed_batch(n, bs - 9 * ((rnd + i) % 4), 10 * rnd + i).cuda() for i in range(2)]
+            for i, call in enumerate(calls):
+                call.sample([100 * rnd + i], [seeds[i]], streams[i if spread else 0])
+            for i, call in enumerate(calls):
+                call.wait(streams[i if spread else 0])
+                ref = oracle.sample_blocks(ip.numpy(), ix.numpy(), cache[1], csize, 100 * rnd + i, seeds[i].cpu().numpy(),
+                                           list(fanouts), list(policies))
+                compare_blocks([bufs[i].views(j) for j in range(len(fanouts))], ref)
+    finally:
+        B.gns_destroy(ctxs[1])
+        gns.close()
+
+
 def test_error_paths():
     ip, ix = _small(n=500)
     n = ip.numel() - 1
