@@ -357,8 +357,9 @@ gns_status gns_aggregate(gns_ctx* ctx, const gns_block* block, const float* x_sr
  * nodes' own rows: the first num_dst rows of what gns_gather_features wrote), h_neigh_dev
  * fp32[num_rows x f2] (what gns_aggregate wrote), w_dev fp32[(f1 + f2) x hdim] row-major, bias_dev
  * fp32[hdim] or NULL, out_dev fp32[num_rows x hdim]; all row-major device buffers, 16-byte aligned,
- * f1, f2 and hdim multiples of 4 (GNS_EINVAL otherwise).  fp32 matrix-core arithmetic with fp32
- * accumulation; the order of the additions is the kernel's own.  num_rows may be
+ * f1, f2 and hdim multiples of 4 (GNS_EINVAL otherwise).  Matrix-core products of fp32's
+ * precision or better (large ones from factors in three bf16 terms) with fp32 accumulation; the order of the additions
+ * is the kernel's own.  num_rows may be
  * GNS_DEVICE_COUNTS(i): the dst rows of layer index i of the last gns_sample_blocks(_async), read on
  * the device (buffers must then hold that layer's cap_dst rows).  Enqueue only. */
 gns_status gns_sage_dense(gns_ctx* ctx, const float* h_self_dev, int32_t f1, const float* h_neigh_dev, int32_t f2,

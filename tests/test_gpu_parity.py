@@ -964,18 +964,80 @@ def test_sage_dense_slabs_and_split(rows, f1, f2, hdim):
     test_sage_dense_update_step(rows, f1, f2, hdim, rows % 2 == 0, True)
 
 
-@pytest.mark.parametrize("rows,f1,f2,hdim", [(16_385, 64, 68, 128), (9_400, 36, 220, 200), (8_193, 400, 448, 256), (8_200, 400, 452, 256),
-                                             (21_900, 208, 208, 96), (22_000, 212, 208, 68), (16_400, 4, 4, 128)])
+@pytest.mark.parametrize("rows,f1,f2,hdim", [(24_577, 32, 32, 128), (24_600, 64, 80, 100), (24_608, 160, 192, 128), (24_577, 176, 192, 128),
+                                             (12_290, 336, 336, 256), (12_290, 336, 352, 256), (65_601, 20, 44, 128), (65_537, 100, 100, 128),
+                                             (87_400, 36, 220, 96), (65_537, 24, 36, 128)])
 def test_sage_dense_in_bf16_terms(rows, f1, f2, hdim):
-    """Slabs of 64 and 32 columns in terms and the first K beyond them; rows, k and columns past the last.  The bound is that
-    of the fp32 products: a product of terms is exact in the accumulator's 24 bits, the three that are left out are below
-    3 * 2^-25 of |a||w|, and there are fewer additions."""
+    """Slabs of 64 and 32 columns in terms and the first K beyond them; widths that are multiples of 16 and that are not; odd
+    numbers of steps; rows, k and columns past the last.  The bound is that of the fp32 products: a product of terms is exact
+    in the accumulator's 24 bits, the two that are left out are below 2^-24 of |a||w|, and there are fewer additions."""
     test_sage_dense_update_step(rows, f1, f2, hdim, rows % 2 == 0, True)
+
+
+def _one_pattern(bits):
+    value = torch.tensor([bits], dtype=torch.int32).view(torch.float32).item()
+    return lambda shape, g: (torch.randint(0, 2, shape, generator=g, device="cuda") * 2 - 1).float() * value
+
+
+def _normal(shape, g):
+    return torch.randn(shape, generator=g, device="cuda")
+
+
+@pytest.mark.parametrize("f", [32, 128, 256])
+@pytest.mark.parametrize("rows_of,weights_of", [
+    (_normal, _normal), (_one_pattern(0x3F80FFFF),) * 2, (_one_pattern(0x3F808040),) * 2, (_one_pattern(0x3F807EC0),) * 2,
+    (lambda s, g: _normal(s, g) * 1e-36, _normal), (_normal, lambda s, g: _normal(s, g) * 1e-37),
+    (lambda s, g: _normal(s, g) * 1e-18, lambda s, g: _normal(s, g) * 1e-18), (lambda s, g: _normal(s, g) * 1e20, _normal),
+    (lambda s, g: _normal(s, g) * torch.exp2(torch.randint(-60, 60, s, generator=g, device="cuda").float()), _normal),
+])
+def test_sage_dense_in_bf16_terms_is_no_further_from_64_bits_than_fp32_products(rows_of, weights_of, f):
+    """A large product against 64 bits, and the same rows in two calls, each too small for the terms and therefore in fp32
+    products: factors whose bits are cut badly, all of one sign of error; very small and very large ones; rows whose values
+    span 36 decades."""
+    rows, hdim = 24_576, 128
+    g = torch.Generator(device="cuda").manual_seed(f)
+    hs, hn, w = rows_of((rows, f), g), rows_of((rows, f), g), weights_of((2 * f, hdim), g)
+    gns = GpuGns(*_small(n=600), None, fanouts=(2,), policies=(U,), cache_size=0, max_seeds=8)
+    try:
+        whole, parts = (torch.full((rows, hdim), 7.0, device="cuda") for _ in range(2))
+        B.gns_sage_dense(gns.ctx, hs, hn, w, None, False, whole, rows)
+        for lo in (0, rows // 2):
+            part = slice(lo, lo + rows // 2)
+            B.gns_sage_dense(gns.ctx, hs[part], hn[part], w, None, False, parts[part], rows // 2)
+        a = torch.cat([hs, hn], dim=1).double()
+        ref = a @ w.double()
+        err_terms, err_fp32 = (((o.double() - ref).norm() / ref.norm()).item() for o in (whole, parts))
+        assert 0 < err_terms <= err_fp32 < 1e-6, (err_terms, err_fp32)
+        assert bool(((whole.double() - ref).abs() <= (2 * f + 3) * 2.0 ** -24 * (a.abs() @ w.double().abs())).all())
+    finally:
+        gns.close()
+
+
+@pytest.mark.parametrize("count", [1, 31, 32, 33, 100])
+def test_sage_dense_in_bf16_terms_with_few_rows_counted_on_the_device(count):
+    """The kernel is chosen by the largest number of rows there may be; the number there is may be less than a tile."""
+    ip, ix = _small(n=30_000, avg=4)
+    F, H = 32, 100
+    gns = GpuGns(ip, ix, None, fanouts=(2,), policies=(U,), cache_size=0, max_seeds=25_000)
+    try:
+        B.gns_sample_blocks(gns.ctx, 5, synth.uniform_seed_batch(30_000, count, 3).cuda(), gns.blocks.array)
+        g = torch.Generator(device="cuda").manual_seed(count)
+        hs, hn = _normal((25_000, F), g), _normal((25_000, F), g)
+        w, bias = _normal((2 * F, H), g), _normal((H,), g)
+        out = torch.full((25_000, H), 7.0, device="cuda")
+        B.gns_sage_dense(gns.ctx, hs, hn, w, bias, True, out, -1)
+        a = torch.cat([hs, hn], dim=1)[:count].double()
+        ref = (a @ w.double() + bias.double()).clamp_min(0)
+        scale = a.abs() @ w.double().abs() + bias.double().abs()
+        assert bool(((out[:count].double() - ref).abs() <= (2 * F + 3) * 2.0 ** -24 * scale).all())
+        assert bool((out[count:] == 7.0).all())
+    finally:
+        gns.close()
 
 
 def test_sage_dense_infinities_nan_and_the_largest_values():
     """Values whose bf16 terms do not add up to them, and the largest finite ones: as plain products have it."""
-    rows, f, hdim = 16_500, 64, 128
+    rows, f, hdim = 24_600, 64, 128
     gns = GpuGns(*_small(n=600), None, fanouts=(2,), policies=(U,), cache_size=0, max_seeds=8)
     try:
         g = torch.Generator().manual_seed(4)
@@ -983,7 +1045,7 @@ def test_sage_dense_infinities_nan_and_the_largest_values():
         w = torch.randn((2 * f, hdim), generator=g) / 16
         w[3, 5], w[70, 90] = 0.0, float("inf")
         a[17, 2], a[40, 100], a[41, 3], a[90, 70] = float("inf"), -float("inf"), float("inf"), 0.0
-        a[300, 7], a[16_499, 127] = float("nan"), 3.0e38
+        a[300, 7], a[24_599, 127] = float("nan"), 3.0e38
         out = torch.full((rows, hdim), 7.0, device=gns.device)
         B.gns_sage_dense(gns.ctx, a[:, :f].contiguous().cuda(), a[:, f:].contiguous().cuda(), w.cuda(), None, False, out, rows)
         ref = (a.double() @ w.double()).float()
