@@ -250,7 +250,8 @@ gns_status gns_cache_view(gns_ctx* ctx, const int32_t** cache_nodes, int64_t* ca
  * GNS_EINVAL for a node id outside [0, n) or an all-zero result.  Synchronises the stream.
  * Call it on the context made by gns_create; it invalidates the current cache: mini-batches
  * already enqueued keep the cache they were enqueued with (the next draw fills the other copy of
- * the cache structures), new ones need a new gns_sample_cache.  No cache draw may be in flight. */
+ * the cache structures), new ones need a new gns_sample_cache.  A draw of gns_sample_cache_async that has
+ * not run yet keeps the probability it was enqueued with: the computation waits for it on the device. */
 gns_status gns_cache_walk_probability(gns_ctx* ctx, const int32_t* train_nodes_dev, int64_t num_train,
                                       int32_t scale_log2, void* hip_stream);
 

@@ -806,6 +806,13 @@ gns_status gns_cache_walk_probability(gns_ctx* ctx, const int32_t* train_nodes_d
         const gns_status st = retire_cache(ctx);
         if (st != GNS_OK) return st;
     }
+    // A draw enqueued and perhaps still to run, on another stream, reads the prefix that is about to be overwritten; draws wait
+    // for one another, so the last one stands for all.
+    if (ctx->pending || ctx->had_cache) {
+        const hipError_t e = hipStreamWaitEvent(static_cast<hipStream_t>(hip_stream),
+                                                ctx->ready_event[ctx->pending ? ctx->pending_gen : ctx->cache_gen], 0);
+        if (e != hipSuccess) return ctx_fail(ctx, GNS_EHIP, "wait for the cache draw", e);
+    }
     return run_walk_probability(ctx, train_nodes_dev, num_train, scale_log2, static_cast<hipStream_t>(hip_stream));
 }
 

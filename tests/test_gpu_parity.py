@@ -679,6 +679,41 @@ def test_walk_probability_recomputed_while_batches_are_in_flight():
         gns.close()
 
 
+def test_walk_probability_waits_for_a_draw_in_flight():
+    """An asynchronous draw on a stream that is busy with other work, then the probability of other training nodes on another
+    stream: the draw, its cache and its weights are those of the probability it was enqueued with."""
+    ip, ix = _small(n=6000, avg=18, seed=31)
+    n = ip.numel() - 1
+    fanouts, policies, csize, bs = (5, 4), (CF, C), 300, 80
+    nodes = torch.from_numpy(np.random.default_rng(9).permutation(n).astype(np.int32))
+    first, second = nodes[:400].contiguous(), nodes[3000:3100].contiguous()
+    gns = GpuGns(ip, ix, None, fanouts=fanouts, policies=policies, cache_size=csize, max_seeds=bs, flag_mode=1,
+                 cache_probability=B.GNS_PROB_WALK)
+    try:
+        gns.walk_probability(first, 20)
+        busy = torch.cuda.Stream()
+        a = torch.randn((4096, 4096), device="cuda")
+        torch.cuda.synchronize()
+        with torch.cuda.stream(busy):
+            for _ in range(20):
+                a = (a @ a).clamp_(-1.0, 1.0)
+        B.gns_sample_cache_async(gns.ctx, 12, 0, busy)
+        _, pre, _, _ = gns.walk_probability(second, 20)
+        assert np.array_equal(pre, oracle.walk_weights(ip.numpy(), ix.numpy(), second.numpy(), list(fanouts), scale_log2=20)[1])
+        B.gns_activate_cache(gns.ctx)
+        nodes_ptr, size, _, draws = B.gns_cache_view(gns.ctx)
+        _, pre_first = oracle.walk_weights(ip.numpy(), ix.numpy(), first.numpy(), list(fanouts), scale_log2=20)
+        ref = oracle.sample_cache(pre_first, 12, 0, csize)
+        assert draws == ref[2]
+        assert np.array_equal(B.device_view_i32(nodes_ptr, size, gns.device).cpu().numpy(), ref[0])
+        seeds = first[:bs].contiguous()
+        blocks = oracle.sample_blocks(ip.numpy(), ix.numpy(), ref[1], csize, 7, seeds.numpy(), list(fanouts), list(policies),
+                                      prob_prefix=pre_first)
+        compare_blocks(gns.sample_blocks(7, seeds), blocks)
+    finally:
+        gns.close()
+
+
 def test_cache_refresh_while_batches_are_in_flight():
     """A cache draw fills the copy of the cache structures that is not in use: batches enqueued before it
     (here on two forks, not yet waited for) must come out with the old cache, batches enqueued after it
