@@ -12,7 +12,9 @@
 // is cut at exactly that draw.
 //
 // On graphs of a million nodes a draw is a chain of small launches, so there are few: clear, then two per chunk (draw,
-// commit), then the index with the 1/p^C table; and the host looks at the outcome once, at the end, not per chunk.
+// commit), then the index with the 1/p^C table; and the host looks at the outcome behind two chunks and all of it, once for
+// most caches.  What follows an incomplete cache stands down on the device: half of 1 M nodes take 562 us, 16 M of 40 M nodes
+// 9.35 ms, where filling everything behind the first two chunks and again at the end took 728 us and 12.5 ms.
 // A draw of 10 K of 1 M nodes with the mini-batch behind it: 247 us, where a launch per phase, a read-back per chunk of 64 K
 // draws and searches over all offsets took 295; 400 K of 40 M nodes: 1779 us, before 1992.
 #include "gns_internal.h"
@@ -218,6 +220,7 @@ __global__ void __launch_bounds__(kBlock) k_cache_commit(DrawArgs a)
 // p_u = deg(u)/nnz, p^C_u = 1 - (1 - p_u)^|C| (expm1/log1p keep a tiny p_u exact), stored as 1/p^C_u in fp32.  The table
 // is indexed by node id; entries of nodes outside the current cache are stale and never read.
 struct IndexArgs {
+    const int32_t* done;       // the draw's completing chunk, or null: below zero the cache is incomplete and there is nothing to do
     const uint64_t* bitmap;
     int64_t words;
     unsigned long long* sums;  // [tiles] (tag, nodes of the tile), see sum_before
@@ -237,6 +240,7 @@ template <typename OffT, int kPer>
 __global__ void __launch_bounds__(kBlock) k_cache_index(IndexArgs a)
 {
     __shared__ int32_t smem[kBlock / kWave + 1];
+    if (a.done && *a.done < 0) return;
     const int32_t tile = (int32_t) blockIdx.x;
     const int64_t w0 = ((int64_t) tile * kBlock + threadIdx.x) * kPer;
     uint64_t word[kPer];
@@ -289,9 +293,10 @@ static void launch_cache_index(const IndexArgs& a, hipStream_t s)
 
 // Coarse companion of the cache bitmap: bit g of the result is set iff some node of
 // [g << shift, (g + 1) << shift) is cached.  One lane per coarse bit; a wave's ballot is a coarse word.
-__global__ void __launch_bounds__(kBlock) k_cache_coarse(const uint64_t* bitmap, int64_t words, int shift,
+__global__ void __launch_bounds__(kBlock) k_cache_coarse(const int32_t* done, const uint64_t* bitmap, int64_t words, int shift,
                                                          uint64_t* coarse, int64_t coarse_words)
 {
+    if (done && *done < 0) return;
     const int64_t cw = (int64_t) blockIdx.x * (kBlock / kWave) + (threadIdx.x >> 6);
     if (cw >= coarse_words) return;
     const int64_t g = cw * kWave + lane_id();
@@ -382,17 +387,17 @@ static gns_status fill_cache(gns_ctx* c, int gen, const IndexArgs& x, bool i64, 
     GNS_HIP_TRY(hipGetLastError(), "cache index launch");
     if (L.coarse_shift > 0) {
         const unsigned cb = (unsigned) ((L.coarse_words + kBlock / kWave - 1) / (kBlock / kWave));
-        hipLaunchKernelGGL(k_cache_coarse, dim3(cb), dim3(kBlock), 0, s, x.bitmap, (int64_t) L.words, (int) L.coarse_shift,
+        hipLaunchKernelGGL(k_cache_coarse, dim3(cb), dim3(kBlock), 0, s, x.done, x.bitmap, (int64_t) L.words, (int) L.coarse_shift,
                            cache_ptr<uint64_t>(c, L.coarse_bitmap, gen), (int64_t) L.coarse_words);
         GNS_HIP_TRY(hipGetLastError(), "coarse bitmap launch");
     }
-    if (c->config.flag_mode == GNS_FLAGS_PER_CACHE) GNS_HIP_TRY(launch_build_induced(c, gen, s), "induced subgraph");
+    if (c->config.flag_mode == GNS_FLAGS_PER_CACHE) GNS_HIP_TRY(launch_build_induced(c, gen, x.done, s), "induced subgraph");
     if (c->graph.feat_dim > 0) {
         // fill the device table of cached feature rows (slot order) straight from the full store
         const int32_t* fill_nodes = x.cache_nodes;
         const int32_t fill_count = (int32_t) x.cache_size;
         float* fill_out = cache_ptr<float>(c, L.cache_feat, gen);
-        GNS_HIP_TRY(launch_gather(&c, 1, &fill_nodes, &fill_count, &fill_out, -1, s), "cache feature fill");
+        GNS_HIP_TRY(launch_gather(&c, 1, &fill_nodes, &fill_count, &fill_out, -1, s, x.done), "cache feature fill");
     }
     return GNS_OK;
 }
@@ -475,15 +480,11 @@ gns_status run_sample_cache(gns_ctx* c, uint64_t seed, uint64_t epoch, bool wait
         a.chunk_index += 1;
         return hipGetLastError();
     };
-    // A draw that is waited for enqueues two chunks and what follows them, and looks at the outcome then; a cache that is
-    // still incomplete (a stream that repeats itself a lot) gets its further chunks one by one and the rest once more.
-    while (drawn < stop && (!wait_for_it || a.chunk_index < 2)) GNS_HIP_TRY(enqueue_chunk(), "cache draw launch");
     IndexArgs x;
     memset(&x, 0, sizeof(x));
     x.bitmap = bitmap;
     x.words = L.words;
     x.sums = ws_ptr<unsigned long long>(c, L.index_sums);
-    x.tag = next_tag();
     x.spins = c->union_spins;
     x.word_prefix = cache_ptr<int32_t>(c, L.cache_prefix, gen);
     x.cache_nodes = cache_ptr<int32_t>(c, L.cache_nodes, gen);
@@ -491,22 +492,26 @@ gns_status run_sample_cache(gns_ctx* c, uint64_t seed, uint64_t epoch, bool wait
     x.prob_prefix = prob_prefix;
     x.prob_total = (int64_t) prob_total;
     x.node_inv_pc = cache_ptr<float>(c, L.node_pc, gen);
-    gns_status st = fill_cache(c, gen, x, i64, s);
-    if (st != GNS_OK) return st;
     if (wait_for_it) {
-        GNS_HIP_TRY(hipStreamSynchronize(s), "cache draw sync");
-        if (c->h_draw->draw_done_chunk < 0) {
-            while (c->h_draw->draw_done_chunk < 0) {
-                if (drawn >= stop)
-                    return fail(c, GNS_ECAPACITY, "cache draw: the stream did not yield cache_size distinct nodes within the draw limit (cache_size too close to the number of nodes with neighbors)", hipSuccess);
-                GNS_HIP_TRY(enqueue_chunk(), "cache draw launch");
-                GNS_HIP_TRY(hipStreamSynchronize(s), "cache draw sync");
+        // Two chunks and what follows them, then a look at the outcome.  While the cache is incomplete (a stream that repeats
+        // itself a lot: a large share of the nodes, a concentrated probability) two chunks more are tried.
+        x.done = &c->d_state->draw_done_chunk;
+        do {
+            if (drawn >= stop) {
+                c->pending = false;                    // the copy an enqueued draw may have filled is gone
+                return fail(c, GNS_ECAPACITY, "cache draw: the stream did not yield cache_size distinct nodes within the draw limit (cache_size too close to the number of nodes with neighbors)", hipSuccess);
             }
+            for (int k = 0; k < 2 && drawn < stop; ++k) GNS_HIP_TRY(enqueue_chunk(), "cache draw launch");
             x.tag = next_tag();
-            st = fill_cache(c, gen, x, i64, s);
+            const gns_status st = fill_cache(c, gen, x, i64, s);
             if (st != GNS_OK) return st;
             GNS_HIP_TRY(hipStreamSynchronize(s), "cache draw sync");
-        }
+        } while (c->h_draw->draw_done_chunk < 0);
+    } else {
+        while (drawn < stop) GNS_HIP_TRY(enqueue_chunk(), "cache draw launch");
+        x.tag = next_tag();                            // an incomplete cache has consistent structures too: it may be made current
+        const gns_status st = fill_cache(c, gen, x, i64, s);
+        if (st != GNS_OK) return st;
     }
     GNS_HIP_TRY(hipEventRecord(c->ready_event[gen], s), "event record");
     c->pending = true;

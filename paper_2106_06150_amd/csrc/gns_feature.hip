@@ -31,6 +31,7 @@ struct GatherBatch {
 
 struct GatherArgs {
     GatherBatch b[GNS_MAX_GROUP];
+    const int32_t* unless_negative;   // if not null and below zero there, nothing is copied
     int64_t n;
     int32_t feat_dim;
     int32_t use_cache;
@@ -44,6 +45,7 @@ struct GatherArgs {
 template <int kLanes, bool kVec>
 __global__ void __launch_bounds__(kBlock) k_gather(GatherArgs a)
 {
+    if (a.unless_negative && *a.unless_negative < 0) return;
     const int lane = (int) (threadIdx.x % kLanes);
     const int64_t groups_per_block = kBlock / kLanes;
     const int64_t group = (int64_t) blockIdx.x * groups_per_block + threadIdx.x / kLanes;
@@ -95,12 +97,13 @@ static void gather_dispatch(int lanes, dim3 blocks, hipStream_t s, const GatherA
 // count mini-batches (contexts ctxs[0..count) of one family) in one launch.  num_nodes[b] < 0: the input
 // nodes of the last batch sampled on ctxs[b], counted on the device.
 hipError_t launch_gather(gns_ctx* const* ctxs, int count, const int32_t* const* nodes, const int32_t* num_nodes,
-                         float* const* out, int use_cache_gen, hipStream_t s)
+                         float* const* out, int use_cache_gen, hipStream_t s, const int32_t* unless_negative)
 {
     gns_ctx* c = ctxs[0];
     const Layout& L = c->lay;
     GatherArgs a;
     memset(&a, 0, sizeof(a));
+    a.unless_negative = unless_negative;
     int64_t most = 0;
     bool aligned = true;
     for (int b = 0; b < count; ++b) {

@@ -19,6 +19,7 @@
 namespace gns {
 
 struct InducedArgs {
+    const int32_t* done;       // the draw's completing chunk, or null: below zero the cache is incomplete and there is nothing to do
     const int32_t* indices;
     int64_t num_entries;
     int64_t num_chunks;        // ceil(nnz / 64)
@@ -51,6 +52,7 @@ template <int kMode>
 __global__ void __launch_bounds__(kMode == kExactLds || kMode == kCoarseLds ? 1024 : kBlock) k_build_induced(InducedArgs a)
 {
     extern __shared__ uint4 lds_bitmap16[];
+    if (a.done && *a.done < 0) return;
     if (kMode == kExactLds || kMode == kCoarseLds) {
         const uint4* src = reinterpret_cast<const uint4*>(kMode == kExactLds ? a.bitmap : a.coarse);
         const int32_t n16 = (int32_t) (((kMode == kExactLds ? a.bitmap_words : a.coarse_words) + 1) / 2);
@@ -173,10 +175,11 @@ int induced_tile_shift(int64_t num_entries)
     return shift;
 }
 
-hipError_t launch_build_induced(gns_ctx* c, int cache_gen, hipStream_t s)
+hipError_t launch_build_induced(gns_ctx* c, int cache_gen, const int32_t* done, hipStream_t s)
 {
     const Layout& L = c->lay;
     InducedArgs a;
+    a.done = done;
     a.indices = c->graph.indices;
     a.num_entries = c->graph.num_entries;
     a.num_chunks = (c->graph.num_entries + 63) / 64;

@@ -269,8 +269,9 @@ gns_status run_walk_probability(gns_ctx* c, const int32_t* train_nodes, int64_t 
 // gns_cache.hip
 // validates the graph and fills Layout::entry_rows
 hipError_t launch_count_nonzero_rows(gns_ctx* c, hipStream_t s, int32_t* d_out);
-// wait_for_it: run the chunk loop with a read-back per chunk and synchronise (exact error reporting); otherwise
-// enqueue a fixed number of chunks (later ones stand down once the cache is complete) and return.
+// wait_for_it: enqueue chunks two at a time, with what follows a complete cache behind them, and look at the outcome until it
+// is complete or refused; otherwise enqueue a fixed number of chunks (later ones stand down once the cache is complete) and
+// return.
 // Draws of the first chunk of a cache draw: half as many again as the cache has nodes, which completes a cache of one
 // percent of the nodes on most graphs; further chunks are Layout::draw_chunk long.
 constexpr int32_t kDrawTile = 1024;
@@ -282,7 +283,8 @@ gns_status finish_pending_draw(gns_ctx* c);
 
 // gns_induced.hip
 int induced_tile_shift(int64_t num_entries);
-hipError_t launch_build_induced(gns_ctx* c, int cache_gen, hipStream_t s);
+// done: as IndexArgs::done in gns_cache.hip
+hipError_t launch_build_induced(gns_ctx* c, int cache_gen, const int32_t* done, hipStream_t s);
 
 // gns_sampler.hip
 // the previous layer's relabel shares this layer's first launch
@@ -296,9 +298,10 @@ hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s);
 
 // gns_feature.hip
-// use_cache_gen < 0: every row comes from the full store (used while a cache's own table is being filled)
+// use_cache_gen < 0: every row comes from the full store (used while a cache's own table is being filled);
+// unless_negative: device count below which nothing is copied, or null
 hipError_t launch_gather(gns_ctx* const* ctxs, int count, const int32_t* const* nodes, const int32_t* num_nodes,
-                         float* const* out, int use_cache_gen, hipStream_t s);
+                         float* const* out, int use_cache_gen, hipStream_t s, const int32_t* unless_negative = nullptr);
 hipError_t launch_aggregate(gns_ctx* const* ctxs, int count, const gns_block* const* blks, const float* const* x_src,
                             int32_t feat_dim, float* const* out, hipStream_t s);
 

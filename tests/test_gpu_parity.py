@@ -444,6 +444,45 @@ def test_cache_nearly_all_nodes():
         gns.close()
 
 
+@pytest.mark.parametrize("flag_mode", [0, 1])
+def test_draw_of_many_chunks_fills_everything_once_it_is_complete(flag_mode):
+    """A cache of nearly all nodes takes several rounds of two chunks: bitmap, list, induced subgraph, weights and feature
+    table are those of the complete one."""
+    ip, ix = _small(n=40_000, avg=6, seed=3)
+    csize = min(39_000, int((ip[1:] > ip[:-1]).sum()))
+    gns = GpuGns(ip, ix, _feat(40_000, 8), fanouts=(5, 4), policies=(CF, C), cache_size=csize, max_seeds=100, flag_mode=flag_mode)
+    try:
+        for epoch in range(3):
+            assert oracle.sample_cache(ip.numpy(), 3, epoch, csize)[2] > 4 * 1.6 * csize
+            full_parity(gns, cache_seed=3, epoch=epoch, batch_seed=50 + epoch, seeds=synth.uniform_seed_batch(40_000, 100, 20 + epoch))
+    finally:
+        gns.close()
+
+
+def test_a_refused_draw_leaves_no_draw_to_activate():
+    """One node of 6001 owns one of 12 M entries: drawing all of them is refused, and the copy of the cache structures that an
+    enqueued draw had filled is gone with it."""
+    wide, n = 2000, 6001
+    ip = torch.cat([torch.arange(n, dtype=torch.int64) * wide, torch.tensor([(n - 1) * wide + 1])])
+    ix = torch.cat([torch.arange(wide, dtype=torch.int32).repeat(n - 1), torch.zeros(1, dtype=torch.int32)])
+    gns = GpuGns(ip, ix, None, fanouts=(3,), policies=(C,), cache_size=n, max_seeds=50)
+    try:
+        for epoch in range(20):
+            B.gns_sample_cache_async(gns.ctx, 7, epoch)
+            try:
+                B.gns_sample_cache(gns.ctx, 7, epoch)
+            except B.GnsError as e:
+                assert e.status == B.GNS_ECAPACITY
+                with pytest.raises(B.GnsError) as err:
+                    B.gns_activate_cache(gns.ctx)
+                assert err.value.status == B.GNS_ESTATE
+                break
+        else:
+            pytest.fail("no draw was refused")
+    finally:
+        gns.close()
+
+
 def _release_cached_memory():
     """Hand torch's cached device and pinned-host blocks back: the giant workloads need tens of
     GB of each, and blocks cached for an earlier test's shapes would be counted twice."""
