@@ -178,7 +178,8 @@ constexpr int kFetch = 5;
 
 template <int K>
 struct WaveRows {
-    static constexpr int kSlots = (K + 3) / 4 * 4;
+    static_assert(K % 4 == 0, "whole Philox blocks");
+    static constexpr int kSlots = K;
     uint32_t slot[kWave][kSlots];                // Philox words, then the chosen ranks (top bit: of the fill; ~0: none)
     int64_t start[kWave], end[kWave];            // CSR extent
     uint32_t first[kWave], here[kWave], tile[kWave];     // CachedList
@@ -956,12 +957,14 @@ static void with_list(const gns_ctx* c, int layer_index, F&& f)
     else                               f(std::integral_constant<int, kListCachedFirst>());
 }
 
-// f(K): the smallest unroll length that holds the fan-out.
+// f(K): the smallest unroll length that holds the fan-out.  A Philox block gives four slots, fan-outs below 5 are not worth an
+// instance of their own, and the longest is the kernel's limit (groups of four on 1 M nodes: fan-outs 8, 8, 8 take 216 us
+// with 8 slots and 218 with 12; 12, 12, 5 take 275 with 12 and 277 with 16).
 template <typename F>
 static void with_unroll(int fanout, F&& f)
 {
-    if (fanout <= 5)       f(std::integral_constant<int, 5>());
-    else if (fanout <= 10) f(std::integral_constant<int, 10>());
+    if (fanout <= 8)       f(std::integral_constant<int, 8>());
+    else if (fanout <= 12) f(std::integral_constant<int, 12>());
     else                   f(std::integral_constant<int, 16>());
 }
 

@@ -1442,6 +1442,7 @@ def test_directed_adjacency():
 
 @pytest.mark.parametrize("spins", ["0", "256"])
 @pytest.mark.parametrize("fanouts,policies,flag_mode", [((16, 11, 1), (U, CF, C), 1), ((6, 10, 5), (CF, U, C), 1), ((17, 16), (U, C), 1),
+                                                        ((8, 9, 12), (CF, U, C), 1), ((13, 8), (CF, C), 1),
                                                         ((20, 40), (CF, C), 1), ((5, 15), (CF, CF), 0)])
 def test_sampler_unrolls_and_counts_taken_from_the_bitmap(spins, fanouts, policies, flag_mode, monkeypatch):
     """Fan-outs at the edges of the two-stage sampler's unroll lengths and above them; union blocks that do not wait
