@@ -213,7 +213,7 @@ def test_single_seed_and_repeatability():
 
 
 def test_graph_replays_and_eager_launches_agree_with_the_oracle():
-    """The batch's launch sequence is captured once per hash-map parity and replayed; with stage timing on
+    """The batch's launch sequence (twelve launches) is captured once per set of buffers and replayed; with stage timing on
     it is issued kernel by kernel instead.  Replays, eager runs and replays again, with different seeds and
     batch sizes on the same buffers, all against the oracle."""
     ip, ix = _small(n=4000, avg=18, seed=17)
@@ -226,7 +226,7 @@ def test_graph_replays_and_eager_launches_agree_with_the_oracle():
                 B.gns_profile_begin(gns.ctx, (1 << B.GNS_STAGE_SAMPLE) | (1 << B.GNS_STAGE_GATHER), 64)
             else:
                 B.gns_profile_begin(gns.ctx, 0, 0)
-            for _ in range(5):                                            # both parities, several times over
+            for _ in range(5):
                 seeds = synth.uniform_seed_batch(n, 120 - 11 * (step % 4), 50 + step)
                 full_parity(gns, cache_seed=8, epoch=step // 4, batch_seed=900 + step, seeds=seeds)
                 step += 1
@@ -1164,8 +1164,8 @@ def _check_group_batch(gns, buf, ref, feat, xin, hout, F):
 @pytest.mark.parametrize("count,fanouts,policies", [(8, (6, 4, 3), (U, U, C)), (3, (5, 7), (CF, CF)), (1, (4, 4), (U, C)),
                                                     (5, (20, 3), (U, C))])
 def test_group_of_mini_batches_in_one_launch_sequence(count, fanouts, policies, flag_mode):
-    """gns_*_group: `count` mini-batches of different sizes per launch sequence, several rounds (both hash-map
-    parities, graph replays), a cache refresh in the middle; every batch against the oracle."""
+    """gns_*_group: `count` mini-batches of different sizes per launch sequence, several rounds (direct launches, and graph
+    replays where two layers scan their rows), a cache refresh in the middle; every batch against the oracle."""
     ip, ix = _small(n=5000, avg=16, seed=37)
     n = ip.numel() - 1
     F = 24
@@ -1195,7 +1195,7 @@ def test_group_of_mini_batches_in_one_launch_sequence(count, fanouts, policies, 
                 ref = oracle.sample_blocks(ip.numpy(), ix.numpy(), cache[1], csize, bseeds[b], seeds[b].cpu().numpy(),
                                            list(fanouts), list(policies))
                 _check_group_batch(gns, bufs[b], ref, feat, xin[b], hout[b], F)
-        # a context of the group used on its own in between, then the group again (parities now differ)
+        # a context of the group used on its own in between, then the group again (their stamps now differ)
         solo = synth.uniform_seed_batch(n, 33, 999).cuda()
         B.gns_sample_blocks(ctxs[-1], 31337, solo, bufs[-1].array, st)
         ref = oracle.sample_blocks(ip.numpy(), ix.numpy(), cache[1], csize, 31337, solo.cpu().numpy(), list(fanouts),
@@ -1355,14 +1355,13 @@ def test_mark_bitmap_summary_on_a_small_graph(fanouts, policies, flag_mode, monk
         gns.close()
 
 
-@pytest.mark.parametrize("env", [{"GNS_LANE_ROWS_MIN": "1"}, {"GNS_NO_LANE_SAMPLER": "1"}, {"GNS_NO_GRAPH": "1"}])
-@pytest.mark.parametrize("fanouts,policies,flag_mode", [((15, 10, 5), (U, U, U), 0), ((16, 8), (U, C), 1), ((4, 10, 3), (U, U, C), 1),
-                                                        ((6, 5), (CF, C), 1)])
+@pytest.mark.parametrize("env", [{}, {"GNS_NO_GRAPH": "1"}, {"GNS_MARK_SUMMARY_MIN_WORDS": "1", "GNS_UNION_SPINS": "0"}])
+@pytest.mark.parametrize("fanouts,policies,flag_mode", [((15, 10, 5), (U, U, U), 0), ((16, 8), (U, C), 1), ((4, 17, 3), (U, U, C), 1),
+                                                        ((6, 5), (CF, C), 0), ((15, 10, 5), (CF, CF, C), 0)])
 def test_sampler_kernel_choices_give_the_same_blocks(env, fanouts, policies, flag_mode, monkeypatch):
-    """Which sampler kernel serves a layer is a matter of size: one row per lane for large UNIFORM launches and
-    for CACHE_ONLY on the induced subgraph, a lane group per row otherwise, flag words where there is no induced
-    subgraph; launches replayed from a captured graph or enqueued one by one.  Each choice forced here on a small
-    graph (the switches are the library's testing aids), in groups of three mini-batches, against the oracle."""
+    """Layers by two-stage sampler, by a wave per row (fan-out 17) and by scans of the rows, whose sequences of ten and fourteen
+    launches are replayed from a captured graph or, without it, enqueued one by one; the union step by the bitmap and by its
+    summary, without a poll for another block's count.  In groups of three mini-batches, against the oracle."""
     for k, v in env.items():
         monkeypatch.setenv(k, v)
     ip, ix = _small(n=20000, avg=12, seed=61)
