@@ -390,8 +390,9 @@ def algorithmic_bytes(w, avg, flag_mode):
         # uniform layers: per row dst id, extent, count + eligible; per edge one index read, id + weight written
         "uniform": avg["upper_rows"] * (4 + 16 + 8) + avg["upper_edges"] * (4 + 8),
         # union + relabel, all layers: per row dst copy + offset; per edge scratch read (8), local id + weight
-        # written (8), one hash probe (8); per new node id written, extent (2 offsets read, 16 written), hash slot (8)
-        "frontier": avg["all_rows"] * 8 + avg["all_edges"] * 24 + avg["new_nodes"] * (4 + 2 * off_bytes + 16 + 8),
+        # written (8), one look-up in the node table (4); per new node id written, extent (2 offsets read, 16 written),
+        # table entry (4)
+        "frontier": avg["all_rows"] * 8 + avg["all_edges"] * 20 + avg["new_nodes"] * (4 + 2 * off_bytes + 16 + 4),
         "gather": avg["input_nodes"] * (F * 4 * 2 + 4),
         # every distinct source row read once, every dst row written once, offsets, and index + weight per edge
         "aggregate": avg["read_rows"] * F * 4 + avg["rows"] * (F * 4 + 4) + avg["edges"] * 8,
@@ -465,8 +466,10 @@ def bench_config(torch, B, synth, cfg_id, args, K, W, repeats, with_oracle, feat
     avg = w.shape_stats(b2, min(K, args.shape_batches))
     alg = algorithmic_bytes(w, avg, args.flag_mode)
     F = w.F
-    # the input layer's CACHE_ONLY sampler: one row per lane on the induced subgraph when there is one, else flag words
-    select_kernel = "k_sample_lane" if (args.flag_mode == 1 and w.fanouts[-1] <= 16) else "k_select_rows"
+    # the input layer's CACHE_ONLY sampler: on the induced subgraph when there is one (by unroll length; list 1 is the cached
+    # neighbors), else on flag words
+    slots = next((k_ for k_ in (8, 12, 16) if w.fanouts[-1] <= k_), None)
+    select_kernel = "k_select_rows" if args.flag_mode == 0 else "k_sample_rows<%d,1>" % slots if slots else "k_sample_wide<1>"
     kernel_of = {"flag": "k_flag_chunks", "select": select_kernel, "gather": "k_gather", "aggregate": "k_aggregate"}
     candidates = [s_ for s_ in kernel_of if s_ in launch_us]
     dom = max(candidates, key=lambda s_: launch_us[s_])

@@ -27,7 +27,7 @@
  *    library itself allocates is host-side or runtime state: gns_create and
  *    gns_fork allocate a small pinned host mirror of the device counters, HIP
  *    events and a capture stream; the first mini-batch with a new set of block
- *    buffers instantiates a HIP graph of its launch sequence; gns_profile_begin
+ *    buffers may instantiate a HIP graph of its launch sequence (see gns_create); gns_profile_begin
  *    creates HIP events.  Everything is released by gns_destroy.
  *  - All device work is enqueued on the hipStream_t passed as `hip_stream`
  *    (NULL = the default stream).  Calls that must report counts to the host
@@ -190,6 +190,8 @@ gns_status gns_create(gns_ctx** out_ctx, const gns_graph* graph, const gns_confi
  * given the cache, as the paper's sampling workers are).  The fork owns its per-batch
  * scratch in `workspace` (gns_fork_workspace_bytes(parent) bytes, 256-byte aligned) and
  * reads the cache structures of the context made by gns_create, which must outlive it.
+ * The scratch grows with the graph: the node table takes 4 bytes per node in every context (444 MB at 111 M nodes), the
+ * two bitmaps n / 4 bytes; the rest depends on max_seeds and the fan-outs.
  * gns_sample_cache is called on that original context only (see there for what may be in
  * flight meanwhile).  Destroy forks with gns_destroy. */
 size_t gns_fork_workspace_bytes(const gns_ctx* parent);
@@ -324,7 +326,7 @@ gns_status gns_aggregate_group(gns_ctx* const* ctxs, int32_t count, const gns_bl
  * and config (what gns_fork_workspace_bytes reports, without the 4 bytes per node of the node table, which
  * large graphs keep in the context's workspace) exceeds the array: nothing is launched.
  * All calls on one GPU share that GPU's array, whatever their context: it is re-initialised at
- * the start of every call, and calls that overlap on one GPU race.  gns_gather_features and
+ * the start of every call (the node table too: 4 bytes per node are written), and calls that overlap on one GPU race.  gns_gather_features and
  * gns_aggregate after it take the host counts the call filled in (the device-count
  * placeholders refer to the context's own scratch, which this call does not use). */
 #define GNS_STATIC_SCRATCH_BYTES (128u << 20)
@@ -383,7 +385,7 @@ gns_status gns_sage_dense(gns_ctx* ctx, const float* h_self_dev, int32_t f1, con
 #define GNS_STAGE_FINISH 8
 #define GNS_STAGE_GATHER 16
 #define GNS_STAGE_AGGREGATE 17
-#define GNS_STAGE_PLAN 18   /* CACHE_ONLY, GNS_FLAGS_PER_BATCH: the two work-list kernels          */
+#define GNS_STAGE_PLAN 18   /* CACHE_ONLY, GNS_FLAGS_PER_BATCH: the work-list kernel               */
 #define GNS_STAGE_FLAG 19   /* CACHE_ONLY, GNS_FLAGS_PER_BATCH: the CSR-segment scan (one kernel)  */
 #define GNS_STAGE_SELECT 20 /* CACHE_ONLY: the per-row selection kernel                            */
 #define GNS_STAGE_DENSE 21  /* gns_sage_dense                                                      */

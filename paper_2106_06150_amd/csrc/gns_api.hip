@@ -175,9 +175,10 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     if (uses_cache && (size_t) L.words * 8 > kLdsBitmapBytes) {
         int sh = 1;
         while (sh <= 6 && (size_t) (((n >> sh) + 63) / 64 + 1) * 8 > kLdsBitmapBytes) ++sh;
-        // Beyond one bit per 64 ids (more than 81 M nodes) most entries would pass: the coarse bitmap then stays in global
-        // memory, in every L2, at one bit per 16 ids
-        // (111 M nodes, 1.6 G entries: a draw takes 10.7 ms so, 16.0 ms with one bit per 128 ids in LDS).
+        // Beyond one bit per 64 ids (more than 83 M nodes) most entries would pass: the coarse bitmap then stays in global
+        // memory, in every L2, at one bit per 16 ids.  A refresh with 400 M entries, 1 % cached, in LDS and in L2: 50 M nodes 2.08
+        // and 2.71 ms, 65 M 2.49 and 2.84, 82 M 2.93 and 3.00 (0.5 % cached 2.01 and 2.62); 111 M nodes, 1.6 G entries: a draw
+        // takes 16.0 ms with one bit per 128 ids in LDS, 10.7 from L2.
         if (sh > 6) {
             sh = 4;
             if (const char* e = getenv("GNS_COARSE_SHIFT")) { const int v = atoi(e); if (v >= 1 && v <= 6) sh = v; }

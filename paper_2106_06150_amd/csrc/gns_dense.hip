@@ -224,7 +224,9 @@ constexpr size_t terms_lds(int32_t K, int slab)
 // sum is rounded once per 16 k, not with every k, and the rest, at 2^-8 of its size, adds next to nothing.
 // Error against 64 bits (2-norm), here and of k_sage_rows: normal inputs 4.9e-8 and 1.4e-7 at K = 64, 8.9e-8 and 2.9e-7 at
 // K = 256, 1.3e-7 and 4.1e-7 at K = 512; all factors of one bit pattern that cuts badly (3F808040, 3F807EC0) 3.9e-8 to 4.4e-8
-// and 6.4e-8 to 7.2e-8 at K = 64; log-normal ones of sigma 3 9.4e-8 and 9.7e-8; inputs of 1e-36 as of 1.  Below K = 64 a
+// and 6.4e-8 to 7.2e-8 at K = 64; log-normal ones of sigma 3 9.4e-8 and 9.7e-8; inputs of 1e-36 as of 1.  Where all rows
+// and all weights are of one magnitude each and the product of the two is nearly an fp32 value, a chain has less to round and
+// is the closer one; the terms stay below 5.4e-8 there, one rounding of the result.  Below K = 64 a
 // fp32 chain is too short to lose to (log-normal, K = 32: 7.4e-8 and 6.7e-8).  With six products (mid times lo left out both
 // ways) the bad patterns give 6.9e-8 to 7.5e-8; with eight every figure is that of seven but for those patterns (3.5e-8), and
 // the launch takes 8 % longer.

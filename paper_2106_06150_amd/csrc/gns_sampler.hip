@@ -929,8 +929,9 @@ bool first_layer_enters_seeds(const gns_config& config)
 }
 
 // Rows per wave of the two-stage sampler: as many as leave sixteen waves for every CU at the layer's worst-case number of
-// rows (real batches have a third of that and more), a power of two between 4 and 64.  Layers of 4 x 12,600 rows, fan-out
-// 10: 37 us with 64 rows per wave, 27 us with 16.
+// rows, a power of two between 4 and 64.  That number is all the host knows; input layers have 0.2 (cache first) to 0.5 of it
+// (fan-outs 15, 10 on 1 M nodes), so their launches have fewer waves than that.  Layers of 4 x 12,600 rows, fan-out 10: 37 us
+// with 64 rows per wave, 27 us with 16.
 static int wave_rows(const Group& g, int layer_index)
 {
     const gns_ctx* c = g.ctx[0];
