@@ -161,15 +161,17 @@ __device__ __forceinline__ uint32_t count_tile(const FinishArgs& a, int32_t tile
     return n;
 }
 
-// The node of bit `bit` of bitmap word `word` joins the batch's list at place `pos`.
+// The node of bit `bit` of bitmap word `word` joins the batch's list at place `pos`.  Nodes that join in the last layer are
+// no layer's rows: nothing reads their extents, and on a graph whose offsets fit no L2 the read of one is a trip to memory.
 __device__ __forceinline__ void emit_new_node(const FinishArgs& a, int32_t pos, int64_t word, int bit)
 {
     const uint32_t node = (uint32_t) (word * 64 + bit);
+    a.src_nodes[pos] = (int32_t) node;
+    a.tab.entry[node] = a.tab.make((uint32_t) pos);
+    if (a.last_layer) return;
     RowExtent ext;
     ext.start = load_off_rt(a.g_indptr, a.g_i64, node);
     ext.end = load_off_rt(a.g_indptr, a.g_i64, (int64_t) node + 1);
-    a.src_nodes[pos] = (int32_t) node;
-    a.tab.entry[node] = a.tab.make((uint32_t) pos);
     a.row_ext[pos] = ext;
     append_hub_rows(a.st, a.hub_rows, is_hub_extent(ext.start, ext.end), pos);
 }
@@ -412,6 +414,7 @@ void fill_finish_template(const Group& g, int layer_index, FinishArgs* out)
     a.g_indptr = c->graph.indptr;
     a.g_i64 = c->graph.indptr_is_i64;
     a.num_nodes = c->graph.num_nodes;
+    a.last_layer = layer_index == c->config.num_layers - 1 ? 1 : 0;
 }
 
 int relabel_grid(const gns_ctx* c, int layer_index)

@@ -103,6 +103,7 @@ struct FinishArgs {
     int g_i64;
     int32_t* hub_rows;             // the union step appends the new nodes that are hubs
     int64_t num_nodes;
+    int32_t last_layer;            // its new nodes have no rows to be sampled
 };
 
 // Byte offsets of the sections of a context's per-batch scratch (the same for every context of a family).
