@@ -62,14 +62,14 @@ hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s)
 // A bad seed is reported by stamping the batch id, so no flag needs resetting while other blocks may be setting it.
 __global__ void __launch_bounds__(kBlock) k_batch_begin(LayerArgs g, BeginDyn d)
 {
-    const int b = (int) blockIdx.y;
+    const auto [b, block] = group_block(g.dealt);
     const int32_t num_seeds = d.num_seeds[b];
     const NodeTable tab = bind_table(g, b, d.stamp[b]);
-    const int64_t t = (int64_t) blockIdx.x * blockDim.x + threadIdx.x;
-    if (t == 0) begin_state(g, d, b);
-    for (int64_t q = t; q < num_seeds; q += (int64_t) gridDim.x * blockDim.x) {
+    const int32_t q = block * kBlock + (int32_t) threadIdx.x;
+    if (q == 0) begin_state(g, d, b);
+    if (q < num_seeds) {
         const int32_t u = d.seeds[b][q];
-        enter_seed(g, d, b, tab, (int32_t) q, u, seed_extent(g, u), false);
+        enter_seed(g, d, b, tab, q, u, seed_extent(g, u), false);
     }
 }
 
@@ -78,6 +78,8 @@ void fill_group_args(const Group& g, LayerArgs* out)
     gns_ctx* c = g.ctx[0];
     const Layout& L = c->lay;
     memset(out, 0, sizeof(*out));
+    // no launch has more threads per batch than it has rows, but for a few thousand blocks; a grid has fewer than 2^32
+    out->dealt = L.max_rows * g.count <= (int64_t) 1 << 31 ? g.count : 1;
     WsOffsets& o = out->off;
     o.mark_summary = L.mark_summary;
     o.has_summary = L.summary_words > 0 ? 1 : 0;
@@ -125,8 +127,8 @@ hipError_t launch_batch_begin(const Group& g, const BeginDyn& d, hipStream_t s)
     LayerArgs a;
     fill_first_args(g, &a);
     // the grid is sized for the largest batch: the same launch serves every replay
-    const unsigned grid = (unsigned) ((c->config.max_seeds + kBlock - 1) / kBlock);
-    hipLaunchKernelGGL(k_batch_begin, dim3(grid, (unsigned) g.count), dim3(kBlock), 0, s, a, d);
+    const dim3 grid = group_grid(g, a, ((int64_t) c->config.max_seeds + kBlock - 1) / kBlock);
+    hipLaunchKernelGGL(k_batch_begin, grid, dim3(kBlock), 0, s, a, d);
     return hipGetLastError();
 }
 
@@ -281,14 +283,16 @@ template <int kPerMax>
 __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
 {
     __shared__ int32_t smem[kBlock / kWave + 1];
-    const FinishArgs a = bind_finish(g, (int) blockIdx.y, true);
+    const auto [b, block] = group_block(g.dealt);
+    if (block >= g.blocks) return;
+    const FinishArgs a = bind_finish(g, b, true);
     // the tile's marked words, kMarkCap at a time: the word, its index in the tile, the number of marks before it
     __shared__ uint64_t s_word[kMarkCap];
     __shared__ int32_t s_widx[kMarkCap];
     __shared__ int32_t s_off[kMarkCap];
     const int32_t R = a.st->num_dst[a.layer_index];
-    if ((int32_t) blockIdx.x < a.row_tiles_max) {
-        const int64_t base = (int64_t) blockIdx.x * kTile;
+    if (block < a.row_tiles_max) {
+        const int64_t base = (int64_t) block * kTile;
         if (base >= R) return;
         // blocked arrangement: thread t owns rows base + t*kItems .. +kItems
         int32_t c[kItems];
@@ -303,11 +307,11 @@ __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
         int32_t total, before;
         int32_t off = block_exclusive_scan(sum, smem, &total);
         if (a.rows_per_sum) {
-            before = block_sum_array(a.sums_rows, (int32_t) blockIdx.x * (kTile / a.rows_per_sum), smem);
+            before = block_sum_array(a.sums_rows, block * (kTile / a.rows_per_sum), smem);
         } else {
             const uint32_t tag = launch_tag(a.st, a.layer_index);
-            if (threadIdx.x == 0) publish_sum(a.row_sums, (int32_t) blockIdx.x, tag, (uint32_t) total);
-            before = sum_before(a.row_sums, tag, (int32_t) blockIdx.x, spins, smem, [&](int32_t t) {
+            if (threadIdx.x == 0) publish_sum(a.row_sums, block, tag, (uint32_t) total);
+            before = sum_before(a.row_sums, tag, block, spins, smem, [&](int32_t t) {
                 uint32_t n = 0;
                 for (int32_t r = t * kTile; r < (t + 1) * kTile; ++r) n += (uint32_t) a.s_cnt[r];      // a full tile: one follows
                 return n;
@@ -324,9 +328,9 @@ __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
             off += c[i];
         }
     } else if constexpr (kPerMax == 0) {
-        union_sparse_tile(a, (int32_t) blockIdx.x - a.row_tiles_max, R, spins, smem, s_word, s_widx, s_off);
+        union_sparse_tile(a, block - a.row_tiles_max, R, spins, smem, s_word, s_widx, s_off);
     } else {
-        const int32_t tile = (int32_t) blockIdx.x - a.row_tiles_max;
+        const int32_t tile = block - a.row_tiles_max;
         const int T = a.mark_tile_words;
         const int64_t base = (int64_t) tile * T;
         // thread t owns words t*per .. t*per+per-1 of the tile (per = 1 for tiles of up to kBlock words)
@@ -434,7 +438,8 @@ hipError_t launch_finish_layer(const Group& g, int layer_index, hipStream_t s)
     fill_group_args(g, &a);
     set_group_layer(g, layer_index, &a);
     fill_finish_template(g, layer_index, &a.f);
-    const dim3 grid((unsigned) (a.f.row_tiles_max + a.f.mark_tiles), (unsigned) g.count);
+    a.blocks = a.f.row_tiles_max + a.f.mark_tiles;
+    const dim3 grid = group_grid(g, a, a.blocks);
     // by summary, or by words of a tile per thread: the kernel's loops over them are unrolled for 1, 4 or 32
     const int per = a.f.mark_tile_words / kBlock, spins = c->union_spins;
     if (a.off.has_summary) hipLaunchKernelGGL(k_union<0>, grid, dim3(kBlock), 0, s, a, spins);
@@ -449,10 +454,12 @@ hipError_t launch_finish_layer(const Group& g, int layer_index, hipStream_t s)
 // gns_sample_blocks_wait finds them.
 __global__ void __launch_bounds__(kBlock) k_relabel_last(LayerArgs g)
 {
-    const FinishArgs a = bind_finish(g, (int) blockIdx.y, true);
-    relabel_body(a, (int32_t) blockIdx.x, (int32_t) gridDim.x);
-    if (blockIdx.x == 0) {
-        const BatchSlot& q = g.b[blockIdx.y];
+    const auto [b, block] = group_block(g.dealt);
+    if (block >= g.blocks) return;
+    const FinishArgs a = bind_finish(g, b, true);
+    relabel_body(a, block, g.blocks);
+    if (block == 0) {
+        const BatchSlot& q = g.b[b];
         const int32_t* seeds = at<int32_t>(q.ws, g.off.seed_copy);
         uint64_t* seed_mark = at<uint64_t>(q.ws, g.off.seed_mark);
         for (int32_t i = (int32_t) threadIdx.x; g.off.marks_seeds && i < a.st->num_dst[0]; i += kBlock)
@@ -473,7 +480,8 @@ hipError_t launch_relabel(const Group& g, int layer_index, hipStream_t s)
     fill_group_args(g, &a);
     set_group_layer(g, layer_index, &a);
     fill_finish_template(g, layer_index, &a.f);
-    hipLaunchKernelGGL(k_relabel_last, dim3((unsigned) relabel_grid(c, layer_index), (unsigned) g.count), dim3(kBlock), 0, s, a);
+    a.blocks = relabel_grid(c, layer_index);
+    hipLaunchKernelGGL(k_relabel_last, group_grid(g, a, a.blocks), dim3(kBlock), 0, s, a);
     return hipGetLastError();
 }
 

@@ -1,8 +1,8 @@
 // Kernel argument blocks and device bodies shared between the sampler and the frontier kernels.
 //
 // One launch serves a *group* of up to kMaxGroup independent mini-batches (mini-batches are independent
-// given the cache: the paper's sampling workers, Section 3.3): blockIdx.y is the batch's index in the
-// group.  A launch's arguments are one LayerArgs: templates of the per-batch argument structs holding
+// given the cache: the paper's sampling workers, Section 3.3): group_block says which of them a block
+// works for.  A launch's arguments are one LayerArgs: templates of the per-batch argument structs holding
 // everything the batches have in common (graph, cache, layer constants), the offsets of the sections of a
 // context's per-batch scratch, and one BatchSlot per batch (where its scratch lies, its block buffers).
 // Every kernel first binds the templates to its own batch.
@@ -141,6 +141,8 @@ struct LayerArgs {
     SampleArgs s;              // template: cache pointers are those of cache generation 0
     FinishArgs f;              // template for the layer the launch finishes or relabels
     WsOffsets off;
+    int32_t dealt;             // see group_block
+    int32_t blocks;            // blocks of the launch per batch (the first launch's kernels need no such bound)
     BatchSlot b[kMaxGroup];
 };
 
@@ -363,6 +365,12 @@ struct Group {
     gns_block* blocks[kMaxGroup];    // each: the caller's array of num_layers blocks
 };
 
+// Grid of a group's launch with `blocks` blocks per batch.
+inline dim3 group_grid(const Group& g, const LayerArgs& a, int64_t blocks)
+{
+    if (a.dealt == 1) return dim3((unsigned) blocks, (unsigned) g.count);
+    return dim3((unsigned) ((blocks + kXcds - 1) / kXcds * kXcds * g.count));
+}
 // Fills the parts of a LayerArgs that do not depend on the layer: offsets and the per-batch scratch bases.
 void fill_group_args(const Group& g, LayerArgs* out);
 // Points the slots at layer `layer_index` (dst lists and block buffers of that layer and the one before).

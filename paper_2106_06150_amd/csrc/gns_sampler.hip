@@ -356,15 +356,17 @@ __global__ void __launch_bounds__(kBlock) k_sample_rows(LayerArgs g, int W, int 
     // dispatched after this layer's rows, whose dependent loads set the length of the launch
     __shared__ int32_t smem[kBlock / kWave + 1];
     __shared__ WaveRows<K> rows[kBlock / kWave];
-    const int32_t nblocks = (int32_t) gridDim.x - relabel_blocks;
-    if ((int32_t) blockIdx.x >= nblocks) {
-        relabel_body(bind_finish(g, (int) blockIdx.y, false), (int32_t) blockIdx.x - nblocks, relabel_blocks);
+    const GroupBlock q = group_block(g.dealt);
+    if (q.block >= g.blocks) return;
+    const int32_t nblocks = g.blocks - relabel_blocks;
+    if (q.block >= nblocks) {
+        relabel_body(bind_finish(g, q.b, false), q.block - nblocks, relabel_blocks);
         return;
     }
-    const SampleArgs a = bind_sample(g, (int) blockIdx.y);
+    const SampleArgs a = bind_sample(g, q.b);
     const int32_t R = a.st->num_dst[a.layer_index];
-    for (int32_t block = (int32_t) blockIdx.x; (int64_t) block * (kBlock / kWave) * W < R; block += nblocks)
-        sample_block_rows<K, kList, false>(g, nullptr, a, (int) blockIdx.y, block, W, R, a.st->key0, a.st->key1, rows, smem);
+    for (int32_t block = q.block; (int64_t) block * (kBlock / kWave) * W < R; block += nblocks)
+        sample_block_rows<K, kList, false>(g, nullptr, a, q.b, block, W, R, a.st->key0, a.st->key1, rows, smem);
 }
 
 // The first layer of a mini-batch, in the launch that enters its seeds.
@@ -373,12 +375,12 @@ __global__ void __launch_bounds__(kBlock) k_sample_first(LayerArgs g, BeginDyn d
 {
     __shared__ int32_t smem[kBlock / kWave + 1];
     __shared__ WaveRows<K> rows[kBlock / kWave];
-    const int b = (int) blockIdx.y;
+    const auto [b, block] = group_block(g.dealt);
     const int32_t R = d.num_seeds[b];
-    if (blockIdx.x == 0 && threadIdx.x == 0) begin_state(g, d, b);
-    if ((int64_t) blockIdx.x * (kBlock / kWave) * W >= R) return;
+    if (block == 0 && threadIdx.x == 0) begin_state(g, d, b);
+    if ((int64_t) block * (kBlock / kWave) * W >= R) return;
     const SampleArgs a = bind_sample(g, b, d.stamp[b], d.cache_gen[b]);
-    sample_block_rows<K, kList, true>(g, &d, a, b, (int32_t) blockIdx.x, W, R, d.key0[b], d.key1[b], rows, smem);
+    sample_block_rows<K, kList, true>(g, &d, a, b, block, W, R, d.key0[b], d.key1[b], rows, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -387,16 +389,18 @@ template <int kList>
 __global__ void __launch_bounds__(kBlock) k_sample_wide(LayerArgs g, int relabel_blocks)
 {
     __shared__ int32_t smem[kBlock / kWave + 1];
-    const int32_t nblocks = (int32_t) gridDim.x - relabel_blocks;
-    if ((int32_t) blockIdx.x >= nblocks) {
-        relabel_body(bind_finish(g, (int) blockIdx.y, false), (int32_t) blockIdx.x - nblocks, relabel_blocks);
+    const GroupBlock q = group_block(g.dealt);
+    if (q.block >= g.blocks) return;
+    const int32_t nblocks = g.blocks - relabel_blocks;
+    if (q.block >= nblocks) {
+        relabel_body(bind_finish(g, q.b, false), q.block - nblocks, relabel_blocks);
         return;
     }
-    const SampleArgs a = bind_sample(g, (int) blockIdx.y);
+    const SampleArgs a = bind_sample(g, q.b);
     const int32_t R = a.st->num_dst[a.layer_index];
     const uint32_t key0 = a.st->key0, key1 = a.st->key1;
     constexpr int kRows = kBlock / kWave;
-    for (int32_t block = (int32_t) blockIdx.x; (int64_t) block * kRows < R; block += nblocks) {
+    for (int32_t block = q.block; (int64_t) block * kRows < R; block += nblocks) {
         const int k = a.fanout;
         const int s = opaque_lane_id();
         const int32_t my_row = block * kRows + (int32_t) (threadIdx.x >> 6);
@@ -481,13 +485,14 @@ __global__ void __launch_bounds__(kBlock) k_plan(LayerArgs g, int relabel_blocks
     __shared__ int32_t smem[kBlock / kWave + 1];
     __shared__ int32_t s_off[kPlanTile + 1];
     __shared__ int32_t s_g0[kPlanTile];
-    const int32_t ntiles = (int32_t) gridDim.x - relabel_blocks;
-    const int32_t tile = (int32_t) blockIdx.x;
+    const auto [b, tile] = group_block(g.dealt);
+    if (tile >= g.blocks) return;
+    const int32_t ntiles = g.blocks - relabel_blocks;
     if (tile >= ntiles) {
-        relabel_body(bind_finish(g, (int) blockIdx.y, false), tile - ntiles, relabel_blocks);
+        relabel_body(bind_finish(g, b, false), tile - ntiles, relabel_blocks);
         return;
     }
-    const SampleArgs a = bind_sample(g, (int) blockIdx.y);
+    const SampleArgs a = bind_sample(g, b);
     const int32_t R = a.st->num_dst[a.layer_index];
     if (tile >= (R + kPlanTile - 1) / kPlanTile) return;
     const int32_t r = tile * kPlanTile + (int32_t) threadIdx.x;
@@ -827,13 +832,14 @@ __device__ __forceinline__ void select_row(const SampleArgs& a, int64_t row, boo
 template <int G>
 __global__ void __launch_bounds__(kBlock) k_select_rows(LayerArgs g, int hub_blocks)
 {
-    const int64_t own_blocks = (int64_t) gridDim.x;
-    const SampleArgs a = bind_sample(g, (int) blockIdx.y);
+    const GroupBlock q = group_block(g.dealt);
+    if (q.block >= g.blocks) return;
+    const SampleArgs a = bind_sample(g, q.b);
     const int wave_in_block = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
-    if ((int) blockIdx.x < hub_blocks) {
+    if (q.block < hub_blocks) {
         const int32_t H = a.st->hub_count;
         const int32_t nhw = hub_blocks * (kBlock / kWave);
-        for (int32_t h = (int32_t) blockIdx.x * (kBlock / kWave) + wave_in_block; h < H; h += nhw) {
+        for (int32_t h = q.block * (kBlock / kWave) + wave_in_block; h < H; h += nhw) {
             const int lane = opaque_lane_id();
             const int32_t row = a.hub_rows[h];
             const RowExtent ext = a.row_ext[row];
@@ -842,8 +848,8 @@ __global__ void __launch_bounds__(kBlock) k_select_rows(LayerArgs g, int hub_blo
         }
         return;
     }
-    const int64_t block = (int64_t) blockIdx.x - hub_blocks;
-    const int64_t nblocks = own_blocks - hub_blocks;
+    const int64_t block = (int64_t) q.block - hub_blocks;
+    const int64_t nblocks = (int64_t) g.blocks - hub_blocks;
     const int32_t R = a.st->num_dst[a.layer_index];
     constexpr int kRowsPerWave = kWave / G;
     const int64_t wave_global = block * (kBlock / kWave) + wave_in_block;
@@ -976,7 +982,7 @@ hipError_t launch_first_layer(const Group& g, const BeginDyn& d, hipStream_t s)
     fill_first_args(g, &a);
     // the grid is sized for the largest batch: the same launch serves every replay
     const int rows_per_block = rows_per_sum(g, 0);
-    const dim3 grid((unsigned) ((c->config.max_seeds + rows_per_block - 1) / rows_per_block), (unsigned) g.count);
+    const dim3 grid = group_grid(g, a, ((int64_t) c->config.max_seeds + rows_per_block - 1) / rows_per_block);
     with_unroll(a.s.fanout, [&](auto K) {
         with_list(c, 0, [&](auto kList) {
             hipLaunchKernelGGL((k_sample_first<decltype(K)::value, decltype(kList)::value>), grid, dim3(kBlock), 0, s, a, d,
@@ -1011,7 +1017,10 @@ hipError_t launch_sample_layer(const Group& g, int layer_index, hipStream_t s)
         fill_finish_template(g, layer_index - 1, &a.f);
         rl = relabel_grid(c, layer_index - 1);
     }
-    const unsigned gy = (unsigned) g.count;
+    auto grid_of = [&](int64_t blocks) {
+        a.blocks = (int32_t) blocks;
+        return group_grid(g, a, blocks);
+    };
 
     const int64_t rows_max = L.rows[layer_index];
     const dim3 tb(kBlock);
@@ -1024,7 +1033,7 @@ hipError_t launch_sample_layer(const Group& g, int layer_index, hipStream_t s)
         const bool narrow = a.s.fanout <= 16;
         const int64_t cap = (int64_t) c->num_cus * (narrow ? 4 : 16);
         if (blocks > cap) blocks = cap;
-        const dim3 grid((unsigned) (blocks + rl), gy);
+        const dim3 grid = grid_of(blocks + rl);
         with_list(c, layer_index, [&](auto kList) {
             if (!narrow) {
                 hipLaunchKernelGGL((k_sample_wide<decltype(kList)::value>), grid, tb, 0, s, a, rl);
@@ -1050,7 +1059,8 @@ hipError_t launch_sample_layer(const Group& g, int layer_index, hipStream_t s)
     {
         StageTimer t(c, GNS_STAGE_PLAN, s);
         const unsigned plan_blocks = (unsigned) ((rows_max + kPlanTile - 1) / kPlanTile);
-        hipLaunchKernelGGL(k_plan, dim3(plan_blocks + (unsigned) rl, gy), tb, 0, s, a, rl, c->union_spins);
+        const dim3 grid = grid_of((int64_t) plan_blocks + rl);
+        hipLaunchKernelGGL(k_plan, grid, tb, 0, s, a, rl, c->union_spins);
     }
     {
         StageTimer t(c, GNS_STAGE_FLAG, s);
@@ -1060,7 +1070,7 @@ hipError_t launch_sample_layer(const Group& g, int layer_index, hipStream_t s)
     // hub rows get dedicated waves (the count lives on the device; the waves stride over the list)
     const int hub_blocks = (G < 64) ? (int) (rows_max / (kBlock / kWave) < (int64_t) c->num_cus * 2
                                                  ? rows_max / (kBlock / kWave) + 1 : (int64_t) c->num_cus * 2) : 0;
-    const dim3 rb((unsigned) (row_blocks + hub_blocks), gy);
+    const dim3 rb = grid_of(row_blocks + hub_blocks);
     if (G == 8)       hipLaunchKernelGGL(k_select_rows<8>, rb, tb, 0, s, a, hub_blocks);
     else if (G == 16) hipLaunchKernelGGL(k_select_rows<16>, rb, tb, 0, s, a, hub_blocks);
     else              hipLaunchKernelGGL(k_select_rows<64>, rb, tb, 0, s, a, hub_blocks);

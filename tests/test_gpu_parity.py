@@ -1492,3 +1492,29 @@ def test_cache_draw_chunks_and_counts_taken_from_the_data(spins, n, avg, csize, 
             assert draws == ref[2]
     finally:
         gns.close()
+
+
+@pytest.mark.parametrize("count", [2, 7, 16])
+@pytest.mark.parametrize("fanouts,policies,flag_mode", [((9, 4), (U, C), 1), ((18, 3), (C, U), 0)])
+def test_group_sizes_that_share_the_xcds_unevenly(count, fanouts, policies, flag_mode):
+    """A group's blocks are dealt to the eight XCDs in turns of eight per batch: sizes that divide the eight, that do not, and
+    the largest, in launches whose number of blocks is no multiple of eight; every batch against the oracle."""
+    ip, ix = _small(n=4000, avg=14, seed=61)
+    csize, bs = 250, 70
+    gns = GpuGns(ip, ix, None, fanouts=fanouts, policies=policies, cache_size=csize, max_seeds=bs, flag_mode=flag_mode)
+    ctxs, keep, bufs, call = _group_setup(gns, count)
+    try:
+        B.gns_sample_cache(gns.ctx, 46, 0)
+        cache = oracle.sample_cache(ip.numpy(), 46, 0, csize)
+        seeds = [synth.uniform_seed_batch(4000, bs - b, 300 + b).cuda() for b in range(count)]
+        for rnd in range(2):
+            call.sample([90 * rnd + b for b in range(count)], seeds)
+            call.wait()
+            for b in range(count):
+                ref = oracle.sample_blocks(ip.numpy(), ix.numpy(), cache[1], csize, 90 * rnd + b, seeds[b].cpu().numpy(),
+                                           list(fanouts), list(policies))
+                compare_blocks([bufs[b].views(j) for j in range(len(fanouts))], ref)
+    finally:
+        for f in ctxs[1:]:
+            B.gns_destroy(f)
+        gns.close()
