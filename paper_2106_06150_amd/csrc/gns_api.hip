@@ -152,6 +152,7 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
             const size_t tiles = (size_t) ((n + kTile - 1) / kTile);
             L.walk_tiles = take((tiles + 1) * 8);
             L.walk_tiles_nz = take((tiles + 1) * 4);
+            L.walk_hot = take(walk_hot_bytes());
         }
     }
     if (uses_cache && cfg->flag_mode == GNS_FLAGS_PER_CACHE) {

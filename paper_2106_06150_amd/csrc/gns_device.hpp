@@ -197,6 +197,21 @@ __device__ __forceinline__ int32_t sum_before(unsigned long long* tile_sums, uin
     return block_sum((int32_t) v, smem);
 }
 
+// Copies n16 16-byte words into LDS by the whole block.  Four reads are in flight, in variables of their own: an array of
+// them ends up in scratch memory, with which a launch that stages 125 KB took 4 us more.
+__device__ __forceinline__ void stage_lds(uint4* lds, const uint4* src, int32_t n16)
+{
+    const int32_t stride = (int32_t) blockDim.x, last = n16 - 1;
+    for (int32_t q = (int32_t) threadIdx.x; q < n16; q += 4 * stride) {
+        const int32_t q1 = q + stride, q2 = q1 + stride, q3 = q2 + stride;
+        const uint4 v0 = src[q], v1 = src[q1 < n16 ? q1 : last], v2 = src[q2 < n16 ? q2 : last], v3 = src[q3 < n16 ? q3 : last];
+        lds[q] = v0;
+        if (q1 < n16) lds[q1] = v1;
+        if (q2 < n16) lds[q2] = v2;
+        if (q3 < n16) lds[q3] = v3;
+    }
+}
+
 // index of the n-th (0-based) set bit of a 64-bit mask that has more than n bits set
 __device__ __forceinline__ int select_bit64(uint64_t mask, int n)
 {

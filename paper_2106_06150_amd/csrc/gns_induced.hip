@@ -54,17 +54,8 @@ __global__ void __launch_bounds__(kMode == kExactLds || kMode == kCoarseLds ? 10
     extern __shared__ uint4 lds_bitmap16[];
     if (a.done && *a.done < 0) return;
     if (kMode == kExactLds || kMode == kCoarseLds) {
-        const uint4* src = reinterpret_cast<const uint4*>(kMode == kExactLds ? a.bitmap : a.coarse);
-        const int32_t n16 = (int32_t) (((kMode == kExactLds ? a.bitmap_words : a.coarse_words) + 1) / 2);
-        const int32_t stride = (int32_t) blockDim.x;
-        for (int32_t i = (int32_t) threadIdx.x; i < n16; i += 4 * stride) {
-            const int32_t i1 = i + stride, i2 = i1 + stride, i3 = i2 + stride, last = n16 - 1;      // four reads in flight
-            const uint4 a0 = src[i], a1 = src[i1 < n16 ? i1 : last], a2 = src[i2 < n16 ? i2 : last], a3 = src[i3 < n16 ? i3 : last];
-            lds_bitmap16[i] = a0;
-            if (i1 < n16) lds_bitmap16[i1] = a1;
-            if (i2 < n16) lds_bitmap16[i2] = a2;
-            if (i3 < n16) lds_bitmap16[i3] = a3;
-        }
+        stage_lds(lds_bitmap16, reinterpret_cast<const uint4*>(kMode == kExactLds ? a.bitmap : a.coarse),
+                  (int32_t) (((kMode == kExactLds ? a.bitmap_words : a.coarse_words) + 1) / 2));
         __syncthreads();
     }
     const uint32_t* lds32 = reinterpret_cast<const uint32_t*>(lds_bitmap16);

@@ -39,6 +39,7 @@ struct Layout {
     int64_t coarse_words;
     // random-walk cache probability (only with GNS_PROB_WALK): two weight vectors, their prefix, scan partials
     size_t walk_a, walk_b, prob_prefix, walk_tiles, walk_tiles_nz;
+    size_t walk_hot;          //   and the hot nodes' table (HotCopy[2])
     size_t node_pc;           // [n] floats: 1 / p^C_u (Section 3.4), filled for the nodes of the current cache
     // cache-draw scratch
     size_t draw_table, draw_slot, draw_sums, index_sums;
@@ -263,6 +264,7 @@ hipError_t launch_sage_dense(gns_ctx* c, const float* h_self, int32_t f1, const 
                              int32_t num_rows, hipStream_t s);
 
 // gns_walk.hip
+size_t walk_hot_bytes();
 gns_status run_walk_probability(gns_ctx* c, const int32_t* train_nodes, int64_t num_train, int32_t scale_log2,
                                 hipStream_t s);
 

@@ -620,19 +620,8 @@ __global__ void k_flag_chunks(LayerArgs g, int count)
     extern __shared__ uint4 lds_bitmap16[];
     SampleArgs a = bind_sample(g, 0);
     if (kMode == 1 || kMode == 2) {
-        const uint4* src = reinterpret_cast<const uint4*>(kMode == 1 ? a.cache_bitmap : a.coarse_bitmap);
-        const int64_t n16 = ((kMode == 1 ? a.bitmap_words : a.coarse_words) + 1) / 2;
-        // Four reads in flight, in variables of their own: an array of them ends up in scratch memory, with which a launch
-        // takes 4 us more (300 K nodes: 12 to 13 us for 8; a mini-batch of 1024 seeds on 1 M nodes 185 us for 176).
-        const int64_t stride = (int64_t) blockDim.x, last = n16 - 1;
-        for (int64_t q = threadIdx.x; q < n16; q += 4 * stride) {
-            const int64_t q1 = q + stride, q2 = q1 + stride, q3 = q2 + stride;
-            const uint4 v0 = src[q], v1 = src[q1 < n16 ? q1 : last], v2 = src[q2 < n16 ? q2 : last], v3 = src[q3 < n16 ? q3 : last];
-            lds_bitmap16[q] = v0;
-            if (q1 < n16) lds_bitmap16[q1] = v1;
-            if (q2 < n16) lds_bitmap16[q2] = v2;
-            if (q3 < n16) lds_bitmap16[q3] = v3;
-        }
+        stage_lds(lds_bitmap16, reinterpret_cast<const uint4*>(kMode == 1 ? a.cache_bitmap : a.coarse_bitmap),
+                  (int32_t) (((kMode == 1 ? a.bitmap_words : a.coarse_words) + 1) / 2));
         __syncthreads();
     }
     const uint32_t* lds32 = reinterpret_cast<const uint32_t*>(lds_bitmap16);

@@ -1518,3 +1518,30 @@ def test_group_sizes_that_share_the_xcds_unevenly(count, fanouts, policies, flag
         for f in ctxs[1:]:
             B.gns_destroy(f)
         gns.close()
+
+
+@pytest.mark.parametrize("offsets", [torch.int32, torch.int64])
+@pytest.mark.parametrize("n", [26_623, 26_625, 53_249, 130_000])
+def test_walk_hot_nodes_in_lds(n, offsets):
+    """Steps on 32-bit values keep the nodes with the longest rows of 26,624 slots in LDS: fewer nodes than slots, one and
+    two more than a multiple of them, several per slot; a graph whose rows say nothing about how often a node is drawn from
+    (directed, hubs among the columns only), rows of thousands of entries that no wave's share can be cut in."""
+    rng = np.random.default_rng(n)
+    cols = np.concatenate([rng.integers(0, n, size=4 * n), rng.integers(0, 50, size=n) * (n // 50)])
+    rows = np.concatenate([rng.integers(0, n, size=4 * n), rng.integers(0, n, size=n)])
+    rows[:9000] = n - 1
+    rows[9000:15000] = 7
+    key = np.unique(rows.astype(np.int64) * n + cols)
+    ip = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(np.bincount(key // n, minlength=n), out=ip[1:])
+    ip, ix = torch.from_numpy(ip), torch.from_numpy((key % n).astype(np.int32))
+    train = torch.from_numpy(rng.choice(n, size=n // 7, replace=False).astype(np.int32))
+    gns = GpuGns(ip.to(offsets), ix, None, fanouts=(7, 3, 2, 2), policies=(U, U, U, C), cache_size=1, max_seeds=1,
+                 cache_probability=B.GNS_PROB_WALK)
+    try:
+        for scale in (10, 22, 33, 40):                 # 32-bit sums, products beyond 32 bits, 64-bit vectors from the second step on
+            w, pre, _, _ = gns.walk_probability(train, scale)
+            w_ref, pre_ref = oracle.walk_weights(ip.numpy(), ix.numpy(), train.numpy(), [7, 3, 2, 2], scale_log2=scale)
+            assert np.array_equal(w, w_ref) and np.array_equal(pre, pre_ref)
+    finally:
+        gns.close()
