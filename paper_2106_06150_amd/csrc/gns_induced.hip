@@ -42,12 +42,102 @@ constexpr int kSStepShift = 10;                          // entries of a step (a
 // global memory (then only entries whose group has a cached node read the exact bitmap).
 enum { kExact = 0, kExactLds = 1, kCoarseLds = 2, kCoarse = 3 };
 
+// Inclusive scan over each row of 16 lanes.
+__device__ __forceinline__ int32_t row_inclusive_scan(int32_t v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // row_shr:1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    return v;
+}
+
+// The entries of the wave's step at e0; what lies past the end of the array repeats its last entry.  No branch for that: a
+// read inside one makes the compiler wait for all reads at its end.
+__device__ __forceinline__ void load_step(const InducedArgs& a, int64_t e0, uint32_t (&dst)[kSChunks])
+{
+    const int64_t at = e0 < a.num_entries ? e0 : a.num_entries - 1, left = a.num_entries - at;
+    const int32_t* src = a.indices + at;                                                   // wave-uniform
+    const uint32_t last = (uint32_t) (left < kSChunks * kWave ? left : kSChunks * kWave) - 1u;
+    const uint32_t lane = (uint32_t) lane_id();
+#pragma unroll
+    for (int i = 0; i < kSChunks; ++i) {
+        const uint32_t q = (uint32_t) (i * kWave) + lane;
+        dst[i] = (uint32_t) src[q < last ? q : last];
+    }
+}
+
+// Membership flags of the step's chunks, the first `left` entries of it (scalars throughout); returns their number.
+template <int kMode>
+__device__ __forceinline__ int32_t test_step(const InducedArgs& a, const uint32_t* lds32, const uint32_t (&u)[kSChunks], int left,
+                                             uint64_t (&f)[kSChunks])
+{
+    const uint32_t* exact32 = reinterpret_cast<const uint32_t*>(a.bitmap);
+    const uint32_t* coarse32 = reinterpret_cast<const uint32_t*>(a.coarse);
+    uint32_t w[kSChunks];
+#pragma unroll
+    for (int i = 0; i < kSChunks; ++i) {
+        if (kMode == kExactLds)       w[i] = lds32[u[i] >> 5];
+        else if (kMode == kCoarseLds) w[i] = lds32[(u[i] >> a.coarse_shift) >> 5];
+        else if (kMode == kCoarse)    w[i] = coarse32[(u[i] >> a.coarse_shift) >> 5];
+        else                          w[i] = exact32[u[i] >> 5];
+    }
+    if (kMode == kCoarseLds || kMode == kCoarse) {
+#pragma unroll
+        for (int i = 0; i < kSChunks; ++i) {
+            const bool maybe = (w[i] >> ((u[i] >> a.coarse_shift) & 31u)) & 1u;
+            w[i] = maybe ? exact32[u[i] >> 5] : 0u;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kSChunks; ++i) f[i] = __ballot((w[i] >> (u[i] & 31u)) & 1u);
+    if (left < kSChunks * kWave) {
+#pragma unroll
+        for (int i = 0; i < kSChunks; ++i) {
+            const int here = left - i * kWave;
+            f[i] &= here >= kWave ? ~0ull : here > 0 ? (1ull << here) - 1ull : 0ull;
+        }
+    }
+    int32_t count = 0;
+#pragma unroll
+    for (int i = 0; i < kSChunks; ++i) count += __popcll(f[i]);
+    return count;
+}
+
+// Writes the step's chunk records and its cached entries, the first of which goes to place `at` of s_nodes.
+__device__ __forceinline__ void write_step(const InducedArgs& a, int64_t e0, const uint32_t (&u)[kSChunks], int left,
+                                           const uint64_t (&f)[kSChunks], uint32_t at)
+{
+    const int lane = opaque_lane_id();
+    uint32_t lo = 0, hi = 0;                                             // lane i < kSChunks: chunk i's flags
+#pragma unroll
+    for (int i = 0; i < kSChunks; ++i) {
+        lo = lane == i ? (uint32_t) f[i] : lo;
+        hi = lane == i ? (uint32_t) (f[i] >> 32) : hi;
+    }
+    const int32_t count = __popc(lo) + __popc(hi);
+    ChunkRec r;
+    r.flags = ((uint64_t) hi << 32) | lo;
+    r.before = at + (uint32_t) (row_inclusive_scan(count) - count);
+    r.pad = 0;
+    if (lane < kSChunks && lane * kWave < left) a.srec[(e0 >> 6) + lane] = r;
+    int32_t* dst = a.s_nodes + at;
+#pragma unroll
+    for (int i = 0; i < kSChunks; ++i) {
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t) (f[i] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t) f[i], 0u));
+        if (__builtin_amdgcn_inverse_ballot_w64(f[i])) dst[below] = (int32_t) u[i];
+        dst += __popcll(f[i]);
+    }
+}
+
 // One pass over the CSR entry array: test every entry, write the chunk records and the compacted list.  A wave walks a
 // tile in steps of 1024 entries, each read once and kept in its lane's register until its place is known; the next
-// step's entries are on their way meanwhile, and no wave waits for another.  Bound by the stream of entries where the
-// exact bitmap fits LDS, by the rate of L2 requests (one per entry that passes the coarse bitmap) beyond.
-// 40 M entries (exact bitmap in LDS): 62 us, where a flag pass, a scan of its words and a compaction that read the entries
-// once more took 95; 400 M entries of a 40 M-node graph: 1.40 ms, before 1.92.
+// step's entries are on their way meanwhile, and no wave waits for another.  Bound by the stream of entries and the list where
+// the exact bitmap fits LDS, by the rate of L2 requests (one per entry that passes the coarse bitmap) beyond.  A chunk's flags
+// are a scalar and an entry's place among them two instructions: with the flags in lanes, from where every chunk fetched its
+// own and shifted them, the pass was bound by its instructions.
+// 40 M entries (exact bitmap in LDS): 45 us, before 61 (42 with tiles shared by the waves of a block, which then wait for one
+// another); 400 M entries of a 40 M-node graph: 1.38 ms, before 1.39.
 template <int kMode>
 __global__ void __launch_bounds__(kMode == kExactLds || kMode == kCoarseLds ? 1024 : kBlock) k_build_induced(InducedArgs a)
 {
@@ -59,93 +149,31 @@ __global__ void __launch_bounds__(kMode == kExactLds || kMode == kCoarseLds ? 10
         __syncthreads();
     }
     const uint32_t* lds32 = reinterpret_cast<const uint32_t*>(lds_bitmap16);
-    const uint32_t* exact32 = reinterpret_cast<const uint32_t*>(a.bitmap);
-    const uint32_t* coarse32 = reinterpret_cast<const uint32_t*>(a.coarse);
-    const int waves_per_block = (int) (blockDim.x >> 6);
-    const int32_t num_waves = (int32_t) gridDim.x * waves_per_block;
-    // entries of the step that begins at entry e0; those past the end of the array repeat its last entry
-    auto load = [&](int64_t e0, uint32_t (&dst)[kSChunks]) {
-        const int32_t* src = a.indices + e0;                                                   // wave-uniform
-        const int64_t left = a.num_entries - e0;
-        const int lane = lane_id();
-        if (left >= kSChunks * kWave) {
-#pragma unroll
-            for (int i = 0; i < kSChunks; ++i) dst[i] = (uint32_t) src[i * kWave + lane];
-        } else if (left > 0) {
-#pragma unroll
-            for (int i = 0; i < kSChunks; ++i) {
-                const int64_t at = i * kWave + lane;
-                dst[i] = (uint32_t) src[at < left ? at : left - 1];
-            }
-        }
-    };
+    const int wave = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
+    constexpr int64_t kStep = (int64_t) 1 << kSStepShift;
+    uint32_t u[kSChunks], ahead[kSChunks];
+    uint64_t f[kSChunks];
+    const int32_t num_waves = (int32_t) gridDim.x * (int32_t) (blockDim.x >> 6);
     // neighboring tiles go to different blocks: a graph of fewer tiles than the chip has waves still uses every CU
-    int32_t tile = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6)) * (int32_t) gridDim.x + (int32_t) blockIdx.x;
+    int32_t tile = wave * (int32_t) gridDim.x + (int32_t) blockIdx.x;
     if (tile >= a.tiles) return;
     const int64_t tile_entries = (int64_t) 1 << a.tile_shift;
     int64_t e0 = (int64_t) tile << a.tile_shift, tile_end = e0 + tile_entries;
     if (tile_end > a.num_entries) tile_end = a.num_entries;
     uint32_t at_tile = (uint32_t) e0;                                   // where the next cached entry goes
-    uint32_t u[kSChunks];
-#pragma unroll
-    for (int i = 0; i < kSChunks; ++i) u[i] = 0;
-    load(e0, u);
+    load_step(a, e0, u);
     for (;;) {
-        const int lane = opaque_lane_id();
         // the step after this one: in the same tile, or the first of the wave's next tile
-        int64_t e_next = e0 + ((int64_t) 1 << kSStepShift);
+        int64_t e_next = e0 + kStep;
         const bool tile_done = e_next >= tile_end;
         if (tile_done) e_next = ((int64_t) tile + num_waves) << a.tile_shift;
-        uint32_t ahead[kSChunks];
-#pragma unroll
-        for (int i = 0; i < kSChunks; ++i) ahead[i] = 0;
-        load(e_next, ahead);
-        uint32_t w[kSChunks];
-#pragma unroll
-        for (int i = 0; i < kSChunks; ++i) {
-            if (kMode == kExactLds)       w[i] = lds32[u[i] >> 5];
-            else if (kMode == kCoarseLds) w[i] = lds32[(u[i] >> a.coarse_shift) >> 5];
-            else if (kMode == kCoarse)    w[i] = coarse32[(u[i] >> a.coarse_shift) >> 5];
-            else                          w[i] = exact32[u[i] >> 5];
-        }
-        if (kMode == kCoarseLds || kMode == kCoarse) {
-#pragma unroll
-            for (int i = 0; i < kSChunks; ++i) {
-                const bool maybe = (w[i] >> ((u[i] >> a.coarse_shift) & 31u)) & 1u;
-                w[i] = maybe ? exact32[u[i] >> 5] : 0u;
-            }
-        }
-        const int left = (int) (tile_end - e0 < (1 << kSStepShift) ? tile_end - e0 : (1 << kSStepShift));
-        // lane i < kSChunks ends up with chunk i's flags
-        uint64_t mine = 0;
-#pragma unroll
-        for (int i = 0; i < kSChunks; ++i) {
-            const uint64_t f = __ballot(i * kWave + lane < left && ((w[i] >> (u[i] & 31u)) & 1u));
-            if (lane == i) mine = f;
-        }
-        const int32_t count = __popcll(mine);
-        const int32_t incl = wave_inclusive_scan(count);
-        const uint32_t before = at_tile + (uint32_t) (incl - count);
-        const int64_t g = (e0 >> 6) + lane;
-        if (lane < kSChunks && lane * kWave < left) {
-            ChunkRec r;
-            r.flags = mine;
-            r.before = before;
-            r.pad = 0;
-            a.srec[g] = r;
-        }
-        const uint64_t below = (1ull << lane) - 1ull;
-#pragma unroll
-        for (int i = 0; i < kSChunks; ++i) {
-            const uint32_t lo = (uint32_t) __builtin_amdgcn_readlane((int) (uint32_t) mine, i);
-            const uint32_t hi = (uint32_t) __builtin_amdgcn_readlane((int) (uint32_t) (mine >> 32), i);
-            const uint64_t f = ((uint64_t) hi << 32) | lo;
-            const uint32_t at = (uint32_t) __builtin_amdgcn_readlane((int) before, i);
-            if ((f >> lane) & 1ull) a.s_nodes[at + (uint32_t) __popcll(f & below)] = (int32_t) u[i];
-        }
-        at_tile += (uint32_t) __builtin_amdgcn_readlane(incl, kWave - 1);
+        load_step(a, e_next, ahead);
+        const int left = (int) (tile_end - e0 < kStep ? tile_end - e0 : kStep);
+        const int32_t count = test_step<kMode>(a, lds32, u, left, f);
+        write_step(a, e0, u, left, f, at_tile);
+        at_tile += (uint32_t) count;
         if (tile_done) {
-            if (lane == 0) a.s_count[tile] = (int32_t) (at_tile - (uint32_t) ((int64_t) tile << a.tile_shift));
+            if (opaque_lane_id() == 0) a.s_count[tile] = (int32_t) (at_tile - (uint32_t) ((int64_t) tile << a.tile_shift));
             tile += num_waves;
             if (tile >= a.tiles) break;
             tile_end = e_next + tile_entries < a.num_entries ? e_next + tile_entries : a.num_entries;
