@@ -165,28 +165,23 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     L.cache_block_begin = off;
     L.cache_bitmap = take((size_t) L.words * 8);
     L.cache_prefix = take((size_t) L.words * 4);
-    // A cache bitmap too big for LDS gets a coarse companion that does fit: one bit per 2^shift ids.  With a cache of
-    // about 1 % of the nodes it answers "not cached" without leaving the CU for most entries while the groups are small,
-    // and for a good part of them up to groups of a few dozen; what passes costs one request to the exact bitmap, and
-    // the rate of those requests bounds the pass.  (40 M nodes, 400 M entries: one bit per 32 ids in LDS passes half of
-    // the entries, 1.33 ms; one bit per 16 ids in L2, a request for every entry and for 46 % of them a second, 2.67 ms.)
-    L.coarse_shift = 0;
-    L.coarse_words = 0;
-    L.coarse_bitmap = 0;
+    // A cache bitmap too big for LDS gets a filter that does fit, and what the filter leaves open costs one request to L2, whose
+    // rate bounds the pass.  (40 M nodes, 400 M entries, 1 % cached: 37 % of the entries point into the cache; one bit per 32
+    // ids in LDS leaves 54 % open, 1.38 ms; one per 39 ids with the tags of 16 K nodes 40 %, 1.19 ms, and 1.02 ms where they
+    // ask the list of pairs.)  Up to 64 ids to a bit of LDS (83 M nodes); beyond, most entries would stay open: there a coarse
+    // bitmap of one bit per 16 ids lies in global memory, in every L2 (one bit per 64 ids in LDS, no tags, and the one in L2:
+    // 82 M nodes, 400 M entries 2.93 and 3.00 ms; one per 128 ids, 111 M nodes, 1.6 G entries: 16.0 and 10.7).
     if (uses_cache && (size_t) L.words * 8 > kLdsBitmapBytes) {
-        int sh = 1;
-        while (sh <= 6 && (size_t) (((n >> sh) + 63) / 64 + 1) * 8 > kLdsBitmapBytes) ++sh;
-        // Beyond one bit per 64 ids (more than 83 M nodes) most entries would pass: the coarse bitmap then stays in global
-        // memory, in every L2, at one bit per 16 ids.  A refresh with 400 M entries, 1 % cached, in LDS and in L2: 50 M nodes 2.08
-        // and 2.71 ms, 65 M 2.49 and 2.84, 82 M 2.93 and 3.00 (0.5 % cached 2.01 and 2.62); 111 M nodes, 1.6 G entries: a draw
-        // takes 16.0 ms with one bit per 128 ids in LDS, 10.7 from L2.
-        if (sh > 6) {
-            sh = 4;
+        if (n <= (int64_t) kLdsBitmapBytes * 8 * 64) {
+            L.filter = take(kFilterBytes);
+            L.filter_mult = (uint32_t) (((uint64_t) kFilterGroups << 32) / (uint64_t) n);
+        } else {
+            int sh = 4;
             if (const char* e = getenv("GNS_COARSE_SHIFT")) { const int v = atoi(e); if (v >= 1 && v <= 6) sh = v; }
+            L.coarse_shift = sh;
+            L.coarse_words = ((n >> sh) + 63) / 64 + 1;
+            L.coarse_bitmap = take((size_t) (L.coarse_words + 1) * 8);
         }
-        L.coarse_shift = sh;
-        L.coarse_words = ((n >> sh) + 63) / 64 + 1;
-        L.coarse_bitmap = take((size_t) (L.coarse_words + 1) * 8);
     }
     L.cache_nodes = take((size_t) (C > 0 ? C : 1) * 4);
     L.cache_feat = take((size_t) (C > 0 ? C : 1) * (size_t) (g->feat_dim > 0 ? g->feat_dim : 1) * 4);

@@ -94,6 +94,7 @@ struct DrawArgs {
     int32_t spins;
     uint64_t* cache_bitmap;
     int64_t words;
+    unsigned long long* filter;    // the cache filter's keys, or null
     int64_t cache_size;
     int32_t chunk_index;       // chunks of one draw are numbered from 0
 };
@@ -117,6 +118,7 @@ __global__ void __launch_bounds__(kBlock) k_cache_clear(DrawArgs a)
     }
     for (int64_t i = t; i < a.words; i += stride) a.cache_bitmap[i] = 0ull;
     for (int64_t i = t; i <= (int64_t) a.hmask; i += stride) a.table[i] = ~0ull;
+    for (int64_t i = t; a.filter && i < kFilterHot; i += stride) a.filter[i] = 0ull;
 }
 
 // the unique row i in [lo, hi) with indptr[i] <= e < indptr[i+1]
@@ -232,6 +234,10 @@ struct IndexArgs {
     const void* prob_prefix;
     int64_t prob_total;
     float* node_inv_pc;
+    CacheFilter filter;        // or null pointers
+    int64_t hot_from;          // rows shorter than this stay out of its slots
+    const void* g_indptr;      // the graph's offsets (the filter goes by row lengths whatever the probability)
+    int g_i64;
 };
 
 // A tile is kPer words per thread.  Latency-bound: one word per thread and many blocks while their number stays small
@@ -279,6 +285,12 @@ __global__ void __launch_bounds__(kBlock) k_cache_index(IndexArgs a)
         const double p = (double) deg / (double) a.prob_total;
         const double pc = (p >= 1.0) ? 1.0 : -expm1((double) a.cache_size * log1p(-p));
         a.node_inv_pc[u] = (float) (1.0 / pc);
+        if (a.filter.keys) {
+            const int64_t len = load_off_rt(a.g_indptr, a.g_i64, (int64_t) u + 1) - load_off_rt(a.g_indptr, a.g_i64, u);
+            const unsigned long long key = ((unsigned long long) (len < 0xFFFFFFFFll ? len : 0xFFFFFFFFll) << 32) | (uint32_t) u;
+            unsigned long long* slot = &a.filter.keys[(uint32_t) u % kFilterHot];
+            if (len >= a.hot_from && key > *slot) atomicMax(slot, key);
+        }
     }
 }
 
@@ -311,6 +323,38 @@ __global__ void __launch_bounds__(kBlock) k_cache_coarse(const int32_t* done, co
     }
     const uint64_t out = __ballot(any);
     if (lane_id() == 0) coarse[cw] = out;
+}
+
+// The first id of a group of the cache filter: the smallest whose product with mult has g in its upper half.
+__device__ __forceinline__ int64_t group_begin(uint32_t g, uint32_t mult)
+{
+    const uint64_t x = (uint64_t) g << 32;                     // below 2^53
+    uint64_t q = (uint64_t) ((double) x / (double) mult);      // at most one off
+    if (q * mult < x) ++q;
+    else if (q > 0 && (q - 1) * mult >= x) --q;
+    return (int64_t) q;
+}
+
+// The groups of the cache filter and, where there is a list of them, their first two nodes.  One lane per group.
+__global__ void __launch_bounds__(kBlock) k_cache_groups(const int32_t* done, const uint64_t* bitmap, int64_t n, CacheFilter f)
+{
+    if (done && *done < 0) return;
+    const uint32_t g = blockIdx.x * kBlock + threadIdx.x;      // the grid is exact
+    const int64_t lo = group_begin(g, f.mult), next = group_begin(g + 1u, f.mult), hi = next < n ? next : n;
+    uint32_t found = 0, pair = 0;
+    for (int64_t w = lo >> 6; w << 6 < hi; ++w) {
+        uint64_t word = bitmap[w];
+        if (w == lo >> 6) word &= ~0ull << (lo & 63);
+        if (hi - (w << 6) < 64) word &= (1ull << (hi - (w << 6))) - 1ull;
+        for (; word && found < 3; ++found, word &= word - 1) {
+            const uint32_t low = (uint32_t) ((w << 6) + __builtin_ctzll(word)) & kPairMask;
+            if (found == 0) pair = low | low << kPairBits;
+            if (found == 1) pair = (pair & kPairMask) | low << kPairBits;
+        }
+    }
+    const uint64_t any = __ballot(found > 0);
+    if (lane_id() == 0) *reinterpret_cast<uint64_t*>(f.groups + (g >> 5)) = any;
+    if (f.pairs && found > 0) f.pairs[g] = (uint16_t) (pair | (found > 2 ? kPairMore : 0u) | kPairSet);
 }
 
 // ---------------------------------------------------------------------------
@@ -385,6 +429,11 @@ static gns_status fill_cache(gns_ctx* c, int gen, const IndexArgs& x, bool i64, 
     if (i64) launch_cache_index<int64_t>(x, s);
     else     launch_cache_index<int32_t>(x, s);
     GNS_HIP_TRY(hipGetLastError(), "cache index launch");
+    if (L.filter) {
+        hipLaunchKernelGGL(k_cache_groups, dim3(kFilterGroups / kBlock), dim3(kBlock), 0, s, x.done, x.bitmap, c->graph.num_nodes,
+                           x.filter);
+        GNS_HIP_TRY(hipGetLastError(), "cache filter launch");
+    }
     if (L.coarse_shift > 0) {
         const unsigned cb = (unsigned) ((L.coarse_words + kBlock / kWave - 1) / (kBlock / kWave));
         hipLaunchKernelGGL(k_cache_coarse, dim3(cb), dim3(kBlock), 0, s, x.done, x.bitmap, (int64_t) L.words, (int) L.coarse_shift,
@@ -447,6 +496,7 @@ gns_status run_sample_cache(gns_ctx* c, uint64_t seed, uint64_t epoch, bool wait
     a.spins = c->union_spins;
     a.cache_bitmap = bitmap;
     a.words = L.words;
+    a.filter = cache_filter(c, gen).keys;
     a.cache_size = C;
     {
         int64_t blocks = ((int64_t) L.draw_hash_cap + kBlock * 4 - 1) / (kBlock * 4);
@@ -492,6 +542,12 @@ gns_status run_sample_cache(gns_ctx* c, uint64_t seed, uint64_t epoch, bool wait
     x.prob_prefix = prob_prefix;
     x.prob_total = (int64_t) prob_total;
     x.node_inv_pc = cache_ptr<float>(c, L.node_pc, gen);
+    x.filter = cache_filter(c, gen);
+    // Of |C| cached nodes kFilterHot have a slot: nodes that are unlikely to be among them (on a power law the rows of the C-th
+    // node are ten times the average, and lengths fall about as ranks grow) stay out of the atomics.
+    x.hot_from = c->graph.num_entries / c->graph.num_nodes * 3 * (C / (2 * kFilterHot));
+    x.g_indptr = c->graph.indptr;
+    x.g_i64 = c->graph.indptr_is_i64;
     if (wait_for_it) {
         // Two chunks and what follows them, then a look at the outcome.  While the cache is incomplete (a stream that repeats
         // itself a lot: a large share of the nodes, a concentrated probability) two chunks more are tried.

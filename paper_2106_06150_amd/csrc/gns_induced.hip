@@ -27,8 +27,8 @@ struct InducedArgs {
     int tile_shift;
     const uint64_t* bitmap;
     int64_t bitmap_words;
-    const uint64_t* coarse;    // one bit per 2^coarse_shift ids (kCoarseLds, kCoarse)
-    int64_t coarse_words;
+    CacheFilter filter;        // kFilterLds
+    const uint64_t* coarse;    // one bit per 2^coarse_shift ids (kCoarse)
     int coarse_shift;
     ChunkRec* srec;            // [num_chunks]
     int32_t* s_nodes;
@@ -38,9 +38,9 @@ struct InducedArgs {
 constexpr int kSChunks = 16;                             // chunks of a wave's step: their entries stay in registers
 constexpr int kSStepShift = 10;                          // entries of a step (a power of two)
 
-// Where the membership test looks first: the exact bitmap in LDS or in global memory, its coarse companion in LDS or in
-// global memory (then only entries whose group has a cached node read the exact bitmap).
-enum { kExact = 0, kExactLds = 1, kCoarseLds = 2, kCoarse = 3 };
+// Where the membership test looks first: the exact bitmap in LDS or in global memory, the cache filter in LDS, or a coarse
+// bitmap in global memory (after these only what they leave open reads the exact bitmap).
+enum { kExact = 0, kExactLds = 1, kFilterLds = 2, kCoarse = 3 };
 
 // Inclusive scan over each row of 16 lanes.
 __device__ __forceinline__ int32_t row_inclusive_scan(int32_t v)
@@ -68,7 +68,8 @@ __device__ __forceinline__ void load_step(const InducedArgs& a, int64_t e0, uint
 }
 
 // Membership flags of the step's chunks, the first `left` entries of it (scalars throughout); returns their number.
-template <int kMode>
+// kPairs: what the filter leaves open asks the list of pairs, and only what that leaves open the bitmap.
+template <int kMode, bool kPairs>
 __device__ __forceinline__ int32_t test_step(const InducedArgs& a, const uint32_t* lds32, const uint32_t (&u)[kSChunks], int left,
                                              uint64_t (&f)[kSChunks])
 {
@@ -76,13 +77,29 @@ __device__ __forceinline__ int32_t test_step(const InducedArgs& a, const uint32_
     const uint32_t* coarse32 = reinterpret_cast<const uint32_t*>(a.coarse);
     uint32_t w[kSChunks];
 #pragma unroll
-    for (int i = 0; i < kSChunks; ++i) {
+    for (int i = 0; kMode != kFilterLds && i < kSChunks; ++i) {
         if (kMode == kExactLds)       w[i] = lds32[u[i] >> 5];
-        else if (kMode == kCoarseLds) w[i] = lds32[(u[i] >> a.coarse_shift) >> 5];
         else if (kMode == kCoarse)    w[i] = coarse32[(u[i] >> a.coarse_shift) >> 5];
         else                          w[i] = exact32[u[i] >> 5];
     }
-    if (kMode == kCoarseLds || kMode == kCoarse) {
+    if (kMode == kFilterLds) {
+        filter_test<kSChunks>(lds32, a.filter.mult, u, w);
+#pragma unroll
+        for (int i = 0; i < kSChunks; ++i)
+            if (w[i] == 1u) w[i] = kPairs ? (uint32_t) a.filter.pairs[__umulhi(u[i], a.filter.mult)] : exact32[u[i] >> 5];
+        if (kPairs) {
+#pragma unroll
+            for (int i = 0; i < kSChunks; ++i) {
+                const uint32_t low = u[i] & kPairMask;
+                const bool same = (w[i] & kPairMask) == low || ((w[i] >> kPairBits) & kPairMask) == low;
+                if (w[i] + 1u > 1u) w[i] = same ? ~0u : (w[i] & kPairMore) ? 1u : 0u;           // neither ~0 nor 0: a pair
+            }
+#pragma unroll
+            for (int i = 0; i < kSChunks; ++i)
+                if (w[i] == 1u) w[i] = exact32[u[i] >> 5];
+        }
+    }
+    if (kMode == kCoarse) {
 #pragma unroll
         for (int i = 0; i < kSChunks; ++i) {
             const bool maybe = (w[i] >> ((u[i] >> a.coarse_shift) & 31u)) & 1u;
@@ -133,21 +150,19 @@ __device__ __forceinline__ void write_step(const InducedArgs& a, int64_t e0, con
 // One pass over the CSR entry array: test every entry, write the chunk records and the compacted list.  A wave walks a
 // tile in steps of 1024 entries, each read once and kept in its lane's register until its place is known; the next
 // step's entries are on their way meanwhile, and no wave waits for another.  Bound by the stream of entries and the list where
-// the exact bitmap fits LDS, by the rate of L2 requests (one per entry that passes the coarse bitmap) beyond.  A chunk's flags
+// the exact bitmap fits LDS, by the rate of L2 requests (one per entry that the filter leaves open) beyond.  A chunk's flags
 // are a scalar and an entry's place among them two instructions: with the flags in lanes, from where every chunk fetched its
 // own and shifted them, the pass was bound by its instructions.
 // 40 M entries (exact bitmap in LDS): 45 us, before 61 (42 with tiles shared by the waves of a block, which then wait for one
-// another); 400 M entries of a 40 M-node graph: 1.38 ms, before 1.39.
-template <int kMode>
-__global__ void __launch_bounds__(kMode == kExactLds || kMode == kCoarseLds ? 1024 : kBlock) k_build_induced(InducedArgs a)
+// another); 400 M entries of a 40 M-node graph, with the cache filter: 1.02 ms, before 1.38.
+template <int kMode, bool kPairs = false>
+__global__ void __launch_bounds__(kMode == kExactLds || kMode == kFilterLds ? 1024 : kBlock) k_build_induced(InducedArgs a)
 {
     extern __shared__ uint4 lds_bitmap16[];
     if (a.done && *a.done < 0) return;
-    if (kMode == kExactLds || kMode == kCoarseLds) {
-        stage_lds(lds_bitmap16, reinterpret_cast<const uint4*>(kMode == kExactLds ? a.bitmap : a.coarse),
-                  (int32_t) (((kMode == kExactLds ? a.bitmap_words : a.coarse_words) + 1) / 2));
-        __syncthreads();
-    }
+    if (kMode == kExactLds) stage_lds(lds_bitmap16, reinterpret_cast<const uint4*>(a.bitmap), (int32_t) ((a.bitmap_words + 1) / 2));
+    if (kMode == kFilterLds) stage_filter(lds_bitmap16, a.filter);
+    if (kMode == kExactLds || kMode == kFilterLds) __syncthreads();
     const uint32_t* lds32 = reinterpret_cast<const uint32_t*>(lds_bitmap16);
     const int wave = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
     constexpr int64_t kStep = (int64_t) 1 << kSStepShift;
@@ -169,7 +184,7 @@ __global__ void __launch_bounds__(kMode == kExactLds || kMode == kCoarseLds ? 10
         if (tile_done) e_next = ((int64_t) tile + num_waves) << a.tile_shift;
         load_step(a, e_next, ahead);
         const int left = (int) (tile_end - e0 < kStep ? tile_end - e0 : kStep);
-        const int32_t count = test_step<kMode>(a, lds32, u, left, f);
+        const int32_t count = test_step<kMode, kPairs>(a, lds32, u, left, f);
         write_step(a, e0, u, left, f, at_tile);
         at_tile += (uint32_t) count;
         if (tile_done) {
@@ -207,20 +222,22 @@ hipError_t launch_build_induced(gns_ctx* c, int cache_gen, const int32_t* done, 
     a.bitmap = cache_ptr<uint64_t>(c, L.cache_bitmap, cache_gen);
     a.bitmap_words = L.words;
     a.coarse = L.coarse_shift ? cache_ptr<uint64_t>(c, L.coarse_bitmap, cache_gen) : nullptr;
-    a.coarse_words = L.coarse_words;
+    a.filter = cache_filter(c, cache_gen);
     a.coarse_shift = L.coarse_shift;
     a.srec = cache_ptr<ChunkRec>(c, L.srec, cache_gen);
     a.s_nodes = cache_ptr<int32_t>(c, L.s_nodes, cache_gen);
     a.s_count = cache_ptr<int32_t>(c, L.s_count, cache_gen);
-    const size_t exact_bytes = (size_t) ((L.words + 1) / 2) * 16, coarse_bytes = (size_t) ((L.coarse_words + 1) / 2) * 16;
-    const bool lds = exact_bytes <= c->lds_bitmap_limit || (L.coarse_shift > 0 && coarse_bytes <= c->lds_bitmap_limit);
+    const size_t exact_bytes = (size_t) ((L.words + 1) / 2) * 16;
+    const bool lds = exact_bytes <= c->lds_bitmap_limit || (L.filter && kLdsBitmapBytes <= c->lds_bitmap_limit);
     const int threads = lds ? 1024 : kBlock;
     const int32_t cap = c->num_cus * (lds ? 1 : 8);
     const dim3 grid((unsigned) (a.tiles < cap ? a.tiles : cap)), block((unsigned) threads);
     if (exact_bytes <= c->lds_bitmap_limit)
         hipLaunchKernelGGL((k_build_induced<kExactLds>), grid, block, exact_bytes, s, a);
+    else if (lds && a.filter.pairs)
+        hipLaunchKernelGGL((k_build_induced<kFilterLds, true>), grid, block, kLdsBitmapBytes, s, a);
     else if (lds)
-        hipLaunchKernelGGL((k_build_induced<kCoarseLds>), grid, block, coarse_bytes, s, a);
+        hipLaunchKernelGGL((k_build_induced<kFilterLds>), grid, block, kLdsBitmapBytes, s, a);
     else if (L.coarse_shift > 0 && !getenv("GNS_NO_COARSE_L2"))
         hipLaunchKernelGGL((k_build_induced<kCoarse>), grid, block, 0, s, a);
     else

@@ -35,6 +35,36 @@ struct NodeTable {
     __device__ __forceinline__ uint32_t local(uint32_t e) const { return e & ((1u << shift) - 1u); }
 };
 
+// The cache filter in LDS: groups, then tags.
+__device__ __forceinline__ void stage_filter(uint4* lds, const CacheFilter& f)
+{
+    stage_lds(lds, reinterpret_cast<const uint4*>(f.groups), kFilterGroups / 128);
+    uint16_t* tags = reinterpret_cast<uint16_t*>(lds + kFilterGroups / 128);
+#pragma unroll 4
+    for (int32_t i = (int32_t) threadIdx.x; i < kFilterHot; i += (int32_t) blockDim.x) {
+        const unsigned long long key = f.keys[i];
+        tags[i] = key ? (uint16_t) ((uint32_t) key / kFilterHot + 1u) : (uint16_t) 0;
+    }
+}
+
+// What it says of nodes u[0 .. N): ~0 cached, 0 not, 1: to be looked up.  All reads first: left to itself the compiler puts the
+// second of a node behind the outcome of the first and waits for each.
+template <int N>
+__device__ __forceinline__ void filter_test(const uint32_t* lds32, uint32_t mult, const uint32_t* u, uint32_t* w)
+{
+    const uint16_t* tags = reinterpret_cast<const uint16_t*>(lds32 + kFilterGroups / 32);
+    uint32_t tag[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        w[i] = lds32[__umulhi(u[i], mult) >> 5];
+        tag[i] = tags[u[i] % kFilterHot];
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(w[i]), "+v"(tag[i]));
+#pragma unroll
+    for (int i = 0; i < N; ++i) w[i] = tag[i] == u[i] / kFilterHot + 1u ? ~0u : (w[i] >> (__umulhi(u[i], mult) & 31u)) & 1u;
+}
+
 struct SampleArgs {
     DeviceState* st;
     int layer_index;
@@ -63,7 +93,8 @@ struct SampleArgs {
     int32_t* plan_desc;        // [chunks] ids of the aligned chunks to flag
     uint64_t* flags;           // [ceil(nnz / 64)] bit e & 63 of word e >> 6: entry e points into the cache
     int64_t bitmap_words;
-    const uint64_t* coarse_bitmap;   // one bit per 2^coarse_shift ids (flag kernel, mode 2)
+    CacheFilter filter;              // (flag kernel, mode 2)
+    const uint64_t* coarse_bitmap;   // one bit per 2^coarse_shift ids (mode 3)
     int64_t coarse_words;
     int coarse_shift;
     const ChunkRec* srec;      // induced subgraph (GNS_FLAGS_PER_CACHE): chunk records and the cached entries' node ids
@@ -210,6 +241,8 @@ __device__ __forceinline__ SampleArgs bind_sample(const LayerArgs& g, int b, uin
         a.node_inv_pc = shifted(g.s.node_inv_pc);
         a.cache_bitmap = shifted(g.s.cache_bitmap);
         a.flags = shifted(g.s.flags);
+        a.filter.keys = shifted(g.s.filter.keys);
+        a.filter.groups = shifted(g.s.filter.groups);
         a.coarse_bitmap = shifted(g.s.coarse_bitmap);
         a.srec = shifted(g.s.srec);
         a.s_nodes = shifted(g.s.s_nodes);

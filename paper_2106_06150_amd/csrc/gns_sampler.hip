@@ -535,9 +535,9 @@ constexpr int kFlagBatch = 64;      // work-list entries a wave fetches at once 
 // bitmap reads, all tests -- so that the loads of the whole set are in flight together.
 //   kCareful: the set may hold the last chunk of the entry array, whose tail lanes lie beyond
 //   num_entries; those lanes re-read the last entry and are masked out of the ballot.
-//   kMode 0: the bitmap is read from global memory; 1: from LDS; 2: LDS holds the coarse bitmap (one bit
-//   per group of ids): only the entries whose group has a cached node go on to read the exact bitmap;
-//   3: as 2 with the coarse bitmap in global memory (small enough to stay in every XCD's L2).
+//   kMode 0: the bitmap is read from global memory; 1: from LDS; 2: LDS holds the cache filter, and only the entries it
+//   leaves open go on to read the exact bitmap; 3: a coarse bitmap (one bit per group of ids) in global memory, small
+//   enough to stay in every XCD's L2, does so for those whose group has no cached node.
 template <int kMode, bool kCareful>
 __device__ __forceinline__ void flag_chunk_set(const SampleArgs& a, const uint32_t* lds32, int32_t my_chunk, int sub,
                                                int lane, uint32_t* lo, uint32_t* hi)
@@ -557,13 +557,19 @@ __device__ __forceinline__ void flag_chunk_set(const SampleArgs& a, const uint32
     const uint32_t* exact32 = reinterpret_cast<const uint32_t*>(a.cache_bitmap);
     uint32_t w[kFlagUnroll];
 #pragma unroll
-    for (int i = 0; i < kFlagUnroll; ++i) {
+    for (int i = 0; kMode != 2 && i < kFlagUnroll; ++i) {
         if (kMode == 1)      w[i] = lds32[u[i] >> 5];
         else if (kMode == 0) w[i] = exact32[u[i] >> 5];
-        else if (kMode == 2) w[i] = lds32[(u[i] >> a.coarse_shift) >> 5];
         else                 w[i] = reinterpret_cast<const uint32_t*>(a.coarse_bitmap)[(u[i] >> a.coarse_shift) >> 5];
     }
-    if (kMode >= 2) {
+    if (kMode == 2) {
+#pragma unroll
+        for (int i = 0; i < kFlagUnroll; i += 8) filter_test<8>(lds32, a.filter.mult, u + i, w + i);
+#pragma unroll
+        for (int i = 0; i < kFlagUnroll; ++i)
+            if (w[i] == 1u) w[i] = exact32[u[i] >> 5];
+    }
+    if (kMode == 3) {
 #pragma unroll
         for (int i = 0; i < kFlagUnroll; ++i) {
             const bool maybe = (w[i] >> ((u[i] >> a.coarse_shift) & 31u)) & 1u;
@@ -578,8 +584,6 @@ __device__ __forceinline__ void flag_chunk_set(const SampleArgs& a, const uint32
     }
 }
 
-// kMode 1 / 2: the cache bitmap / its coarse companion is first copied into dynamic LDS (rounded up to
-// 16 bytes).  Every wave takes an equal, contiguous share of the work list.
 // One work list: every wave takes an equal, contiguous share of its Q chunks.
 template <int kMode>
 __device__ __forceinline__ void flag_work_list(const SampleArgs& a, const uint32_t* lds32, int64_t Q)
@@ -611,7 +615,7 @@ __device__ __forceinline__ void flag_work_list(const SampleArgs& a, const uint32
     }
 }
 
-// kMode 1 / 2: the cache bitmap / its coarse companion is first copied into dynamic LDS (rounded up to
+// kMode 1 / 2: the cache bitmap / the cache filter is first copied into dynamic LDS (rounded up to
 // 16 bytes).  The work lists of the group's `count` mini-batches are taken one after the other (they read
 // the same cache, so the bitmap is staged once).
 template <int kMode>
@@ -620,8 +624,8 @@ __global__ void k_flag_chunks(LayerArgs g, int count)
     extern __shared__ uint4 lds_bitmap16[];
     SampleArgs a = bind_sample(g, 0);
     if (kMode == 1 || kMode == 2) {
-        stage_lds(lds_bitmap16, reinterpret_cast<const uint4*>(kMode == 1 ? a.cache_bitmap : a.coarse_bitmap),
-                  (int32_t) (((kMode == 1 ? a.bitmap_words : a.coarse_words) + 1) / 2));
+        if (kMode == 1) stage_lds(lds_bitmap16, reinterpret_cast<const uint4*>(a.cache_bitmap), (int32_t) ((a.bitmap_words + 1) / 2));
+        else            stage_filter(lds_bitmap16, a.filter);
         __syncthreads();
     }
     const uint32_t* lds32 = reinterpret_cast<const uint32_t*>(lds_bitmap16);
@@ -880,6 +884,7 @@ void fill_sample_template(gns_ctx* c, int layer_index, SampleArgs* out)
     a.num_entries = c->graph.num_entries;
     a.flags = c->uses_cache && c->config.flag_mode == GNS_FLAGS_PER_BATCH ? cache_ptr<uint64_t>(c, L.edge_flags, gen) : nullptr;
     a.bitmap_words = L.words;
+    a.filter = cache_filter(c, gen);
     a.coarse_bitmap = L.coarse_shift ? cache_ptr<uint64_t>(c, L.coarse_bitmap, gen) : nullptr;
     a.coarse_words = L.coarse_words;
     a.coarse_shift = L.coarse_shift;
@@ -893,11 +898,10 @@ void fill_sample_template(gns_ctx* c, int layer_index, SampleArgs* out)
 static void launch_flag_kernel(gns_ctx* c, const LayerArgs& a, int count, hipStream_t s)
 {
     const size_t lds_bytes = (size_t) ((c->lay.words + 1) / 2) * 16;
-    const size_t coarse_bytes = (size_t) ((c->lay.coarse_words + 1) / 2) * 16;
     if (lds_bytes <= c->lds_bitmap_limit)
         hipLaunchKernelGGL((k_flag_chunks<1>), dim3((unsigned) c->num_cus), dim3(1024), lds_bytes, s, a, count);
-    else if (c->lay.coarse_shift > 0 && coarse_bytes <= c->lds_bitmap_limit)
-        hipLaunchKernelGGL((k_flag_chunks<2>), dim3((unsigned) c->num_cus), dim3(1024), coarse_bytes, s, a, count);
+    else if (c->lay.filter && kLdsBitmapBytes <= c->lds_bitmap_limit)
+        hipLaunchKernelGGL((k_flag_chunks<2>), dim3((unsigned) c->num_cus), dim3(1024), kLdsBitmapBytes, s, a, count);
     else if (c->lay.coarse_shift > 0 && !getenv("GNS_NO_COARSE_L2"))
     {
         const int per_cu = getenv("GNS_FLAG_BLOCKS_PER_CU") ? atoi(getenv("GNS_FLAG_BLOCKS_PER_CU")) : 2;

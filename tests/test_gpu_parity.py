@@ -1545,3 +1545,32 @@ def test_walk_hot_nodes_in_lds(n, offsets):
             assert np.array_equal(w, w_ref) and np.array_equal(pre, pre_ref)
     finally:
         gns.close()
+
+
+@pytest.mark.parametrize("flag_mode", [0, 1])
+@pytest.mark.parametrize("n", [1_310_021, 16_777_217, 17_000_003])
+def test_cache_filter_of_graphs_whose_bitmap_does_not_fit_lds(n, flag_mode):
+    """Cache bitmaps beyond LDS are tested through groups of ids, tags of hot nodes and, on the larger of these graphs, pairs
+    of cached nodes per group: a run of neighboring ids that are nearly all cached (groups with many), the last ids of the
+    graph, and nodes far apart (groups with one), sharing slots of the tags."""
+    rng = np.random.default_rng(n)
+    dense = np.arange(n - 30_000, n)                            # up to the last node
+    spread = rng.choice(n - 30_000, size=30_000, replace=False)
+    spread[:200] = 5 + 16384 * np.arange(200) % (n - 30_000)    # one slot
+    spread = np.unique(spread)
+    nodes = np.concatenate([dense, spread])
+    a, b = nodes[rng.integers(0, len(nodes), size=400_000)], nodes[rng.integers(0, len(nodes), size=400_000)]
+    a[:3000], b[:3000] = n - 1, nodes[rng.integers(0, len(nodes), size=3000)]       # a hub
+    keep = a != b
+    key = np.unique(np.concatenate([a[keep] * n + b[keep], b[keep] * n + a[keep]]))
+    ip = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(np.bincount(key // n, minlength=n), out=ip[1:])
+    ip, ix = torch.from_numpy(ip), torch.from_numpy((key % n).astype(np.int32))
+    gns = GpuGns(ip.to(torch.int32), ix, None, fanouts=(6, 5), policies=(CF, C), cache_size=35_000, max_seeds=600, flag_mode=flag_mode)
+    gns.indptr_cpu = ip
+    try:
+        seeds = torch.from_numpy(np.random.default_rng(3).choice(nodes, size=600, replace=False).astype(np.int32))
+        for epoch in range(3):                                  # both copies of the filter, one of them twice
+            full_parity(gns, cache_seed=48, epoch=epoch, batch_seed=900 + epoch, seeds=seeds)
+    finally:
+        gns.close()
