@@ -181,7 +181,7 @@ gns_status gns_block_capacity(const gns_graph* graph, const gns_config* config, 
  * or nine whose predecessor in the context's family went to another stream, is captured
  * into a HIP graph on first use (per set of block buffers) and replayed afterwards, whatever the cache generation;
  * with the environment variable GNS_NO_GRAPH set when the context is created (forks inherit it) its kernels are
- * launched one by one like those of shorter ones. */
+ * launched one by one like those of shorter ones.  Mini-batches of a few seeds whose layers scan no rows are one launch. */
 gns_status gns_create(gns_ctx** out_ctx, const gns_graph* graph, const gns_config* config,
                       void* workspace, size_t workspace_bytes, void* hip_stream);
 

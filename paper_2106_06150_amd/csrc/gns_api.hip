@@ -220,6 +220,10 @@ gns_status enqueue_batch(const Group& g, const BeginDyn& d, hipStream_t s)
 {
     gns_ctx* c = g.ctx[0];
     const int nl = c->config.num_layers;
+    if (c->prof_mask == 0 && small_batches(g, d)) {          // (stages are timed where they are launches)
+        const hipError_t e = launch_small(g, d, s);
+        return e == hipSuccess ? GNS_OK : ctx_fail(c, GNS_EHIP, "small batch", e);
+    }
     // the first layer's sampler enters the seeds itself where nothing runs in front of it
     const bool fused = first_layer_enters_seeds(c->config);
     hipError_t e = fused ? hipSuccess : launch_batch_begin(g, d, s);
@@ -902,7 +906,7 @@ gns_status gns_sample_blocks_group(gns_ctx* const* ctxs, int32_t count, const ui
     const bool side_by_side = root->has_sampled && root->last_sampled_on != s;
     root->has_sampled = true;
     root->last_sampled_on = s;
-    if (lead->prof_mask == 0 && lead->cap_stream && replayed(lead->config, side_by_side)) st = launch_batch_graph(g, dyn, s);
+    if (lead->prof_mask == 0 && lead->cap_stream && replayed(lead->config, side_by_side) && !small_batches(g, dyn)) st = launch_batch_graph(g, dyn, s);
     else                                                                                   st = enqueue_batch(g, dyn, s);
     if (st != GNS_OK) return st;
     const int nl = lead->config.num_layers;

@@ -100,13 +100,6 @@ void fill_group_args(const Group& g, LayerArgs* out)
     }
 }
 
-static inline BlockPtrs block_ptrs(const gns_block& k)
-{
-    BlockPtrs p;
-    p.indptr = k.indptr; p.indices = k.indices; p.src_nodes = k.src_nodes; p.row_eligible = k.row_eligible; p.weights = k.weights;
-    return p;
-}
-
 void set_group_layer(const Group& g, int layer_index, LayerArgs* out)
 {
     for (int b = 0; b < g.count; ++b) {

@@ -160,6 +160,13 @@ struct BlockPtrs {
     float* weights;
 };
 
+static inline BlockPtrs block_ptrs(const gns_block& k)
+{
+    BlockPtrs p;
+    p.indptr = k.indptr; p.indices = k.indices; p.src_nodes = k.src_nodes; p.row_eligible = k.row_eligible; p.weights = k.weights;
+    return p;
+}
+
 // What differs between the mini-batches of a group.
 struct BatchSlot {
     char* ws;                  // the batch's context: its per-batch scratch
@@ -286,6 +293,82 @@ __device__ __forceinline__ FinishArgs bind_finish(const LayerArgs& g, int b, boo
     return a;
 }
 
+// ---------------------------------------------------------------------------
+// What a row's entries are drawn from: its CSR segment (UNIFORM), its cached neighbors in the induced subgraph
+// (CACHE_ONLY), or those first and then the rest of its CSR segment (CACHE_FIRST).
+enum { kListRow = 0, kListCached = 1, kListCachedFirst = 2 };
+
+__device__ __forceinline__ uint64_t bits_below(int64_t e)
+{
+    return (1ull << (e & 63)) - 1ull;
+}
+
+// The cached neighbors of one row in the induced subgraph: `count` of them, the first `here` from s_nodes[first] on (all
+// of them unless the row crosses a tile), the others from the offsets of tiles tile + 1, tile + 2, ... on.
+struct CachedList {
+    uint32_t first, here, count, tile;
+};
+
+__device__ __forceinline__ CachedList cached_list(const SampleArgs& a, const RowExtent& ext)
+{
+    CachedList r;
+    const bool some = ext.end > ext.start;
+    const int64_t start = some ? ext.start : 0, last = some ? ext.end - 1 : 0;
+    const ChunkRec rs = a.srec[start >> 6];
+    const ChunkRec re = a.srec[last >> 6];
+    const uint32_t stop = re.before + (uint32_t) __popcll(re.flags & (bits_below(last) * 2 + 1));
+    r.first = rs.before + (uint32_t) __popcll(rs.flags & bits_below(start));
+    r.tile = (uint32_t) (start >> a.s_tile_shift);
+    r.here = r.count = some ? stop - r.first : 0u;
+    const uint32_t last_tile = (uint32_t) (last >> a.s_tile_shift);
+    if (r.tile != last_tile) {                       // rare: tiles are much longer than rows
+        r.here = r.count = (r.tile << a.s_tile_shift) + (uint32_t) a.s_count[r.tile] - r.first;
+        for (uint32_t t = r.tile + 1; t < last_tile; ++t) r.count += (uint32_t) a.s_count[t];
+        r.count += stop - (last_tile << a.s_tile_shift);
+    }
+    return r;
+}
+
+// Place in s_nodes of the row's cached neighbor of rank `rank`, here <= rank < count.
+__device__ __forceinline__ int64_t later_tile(const SampleArgs& a, const CachedList& r, uint32_t rank)
+{
+    uint32_t left = rank - r.here, t = r.tile + 1;
+    for (;; ++t) {
+        const uint32_t n = (uint32_t) a.s_count[t];
+        if (left < n) return (int64_t) (t << a.s_tile_shift) + left;
+        left -= n;
+    }
+}
+
+// CSR entry of the row [start, end) that is the `rank`-th among those not in the cache (rank is below their number).
+__device__ __forceinline__ int64_t uncached_entry(const SampleArgs& a, const RowExtent& ext, uint32_t rank)
+{
+    const int64_t first = ext.start >> 6, last = (ext.end - 1) >> 6;
+    for (int64_t c = first;; ++c) {
+        uint64_t open = ~a.srec[c].flags;
+        if (c == first) open &= ~bits_below(ext.start);
+        if (c == last) open &= bits_below(ext.end - 1) * 2 + 1;
+        const uint32_t n = (uint32_t) __popcll(open);
+        if (rank < n || c == last) return (c << 6) + select_bit64(open, (int) rank);
+        rank -= n;
+    }
+}
+
+// Section 3.4: coefficient p^C_u * k / min(k, N_C(v)), weight = 1 / coefficient (fp32 from the 1/p^C table on); the factor
+// of 1/p^C for a row of m cached neighbors of which cnt are drawn.
+__device__ __forceinline__ float cached_scale(const SampleArgs& a, uint32_t m, int cnt)
+{
+    return a.wmode == GNS_W_UNBIASED ? (float) m / (float) (cnt > 0 ? cnt : 1) : (float) cnt / (float) a.fanout;
+}
+
+// Fill neighbors: weight 1 (a node-wise sample), or the inverse inclusion probability of a uniform subset of the
+// uncached neighbors in the unbiased mode.
+__device__ __forceinline__ float fill_weight(const SampleArgs& a, uint32_t others, int fill)
+{
+    return a.wmode == GNS_W_UNBIASED ? (float) others / (float) (fill > 0 ? fill : 1) : 1.0f;
+}
+
+// ---------------------------------------------------------------------------
 // Relabel: every sampled edge of a finished layer gets its neighbor's local id (from the scratch slot if the sampler
 // already found one, else from the node table) and is compacted to its CSR position.  `block` of `nblocks` blocks of
 // kBlock threads, kRelabelUnroll slots per thread in flight.  It only needs that layer's union step, so it shares a
@@ -422,5 +505,8 @@ bool first_layer_enters_seeds(const gns_config& config);
 int rows_per_sum(const Group& g, int layer_index);
 // The batch's first launch when the first layer is direct: seeds and sampling in one.
 hipError_t launch_first_layer(const Group& g, const BeginDyn& d, hipStream_t s);
+// gns_small.hip: whether every mini-batch of the group fits a block of its own, and the one launch that samples them so.
+bool small_batches(const Group& g, const BeginDyn& d);
+hipError_t launch_small(const Group& g, const BeginDyn& d, hipStream_t s);
 
 }  // namespace gns

@@ -1574,3 +1574,50 @@ def test_cache_filter_of_graphs_whose_bitmap_does_not_fit_lds(n, flag_mode):
             full_parity(gns, cache_seed=48, epoch=epoch, batch_seed=900 + epoch, seeds=seeds)
     finally:
         gns.close()
+
+
+@pytest.mark.parametrize("count,seeds", [(1, 1), (2, 9), (2, 10), (1, 38), (1, 39), (16, 3), (5, 17)])
+@pytest.mark.parametrize("fanouts,policies,wmode", [((10, 5), (U, C), 0), ((16, 1), (CF, CF), 1), ((3, 3, 3), (C, U, C), 0), ((5, 7), (U, U), 0),
+                                                    ((2, 2, 2, 2), (CF, U, CF, C), 1)])
+def test_small_batches_in_one_launch(count, seeds, fanouts, policies, wmode):
+    """Mini-batches of a few seeds are sampled by a block each; the same contexts then take a batch too large for that, and a
+    small one again.  Hub rows, rows without neighbors, clustered ids, bad seeds; every batch against the oracle."""
+    ip, ix = _small(n=3000, avg=10, seed=67)
+    n, F, bs = 3000, 12, 400
+    feat = _feat(n, F, seed=9)
+    uses_cache = any(p != U for p in policies)
+    gns = GpuGns(ip, ix, feat, fanouts=fanouts, policies=policies, cache_size=200 if uses_cache else 0, max_seeds=bs, wmode=wmode, flag_mode=1)
+    ctxs, keep, bufs, call = _group_setup(gns, count)
+    last = len(fanouts) - 1
+    try:
+        bitmap = None
+        if uses_cache:
+            B.gns_sample_cache(gns.ctx, 47, 0)
+        for rnd, size in enumerate((seeds, bs, 1, seeds)):
+            if uses_cache and rnd == 3:
+                B.gns_sample_cache(gns.ctx, 47, 1)
+            if uses_cache:
+                bitmap = oracle.sample_cache(ip.numpy(), 47, int(rnd == 3), 200)[1]
+            ids = [synth.uniform_seed_batch(n, max(1, size - b % 2), 60 * rnd + b).cuda() for b in range(count)]
+            call.sample([500 * rnd + b for b in range(count)], ids)
+            xin = [torch.zeros((b.array[last].cap_src, F), dtype=torch.float32, device=gns.device) for b in bufs]
+            hout = [torch.zeros((b.array[last].cap_dst, F), dtype=torch.float32, device=gns.device) for b in bufs]
+            call.gather([b.tensors[last]["src_nodes"] for b in bufs], [-1] * count, xin)
+            call.aggregate(last, xin, F, hout)
+            call.wait()
+            for b in range(count):
+                ref = oracle.sample_blocks(ip.numpy(), ix.numpy(), bitmap, 200 if uses_cache else 0, 500 * rnd + b, ids[b].cpu().numpy(),
+                                           list(fanouts), list(policies), wmode)
+                _check_group_batch(gns, bufs[b], ref, feat, xin[b], hout[b], F)
+        for bad in ([5, 5, 7], [5, -1, 7], [5, n, 7]):
+            ids = [torch.tensor(bad if b == count - 1 else [b, b + 20], dtype=torch.int32).cuda() for b in range(count)]
+            call.sample(list(range(count)), ids)
+            with pytest.raises(B.GnsError) as e:
+                call.wait()
+            assert e.value.status == B.GNS_EINVAL
+        call.sample(list(range(count)), [torch.tensor([b, b + 20], dtype=torch.int32).cuda() for b in range(count)])
+        call.wait()                                             # reported once
+    finally:
+        for f in ctxs[1:]:
+            B.gns_destroy(f)
+        gns.close()
