@@ -50,7 +50,8 @@ __device__ __forceinline__ Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint3
 // batches each has its node table, extents and scratch in two L2s instead of in all eight.  Groups of four, the blocks of
 // a batch over all XCDs and dealt: k_sample_rows of the input layer 43 -> 42 us on 1 M nodes, 26 -> 21 with the upper layers
 // cache first, 65 -> 61 on 40 M nodes (the layer above it 30 -> 24), k_relabel_last 11.6 -> 8.9, 8.7 -> 6.7 and 16.6 -> 10.9.
-// dealt == 1: the batch is blockIdx.y.
+// dealt == 1: the batch is blockIdx.y.  kOne: the group is a single batch, of which every block is one; what a kernel reads of
+// its arguments then hangs on no other argument (a mini-batch of 256 seeds, seven launches: 1.2 us).
 constexpr int kXcds = 8;
 
 struct GroupBlock {
@@ -58,9 +59,11 @@ struct GroupBlock {
     int32_t block;             // its block; the last few may lie past the number of blocks asked for
 };
 
+template <bool kOne>
 __device__ __forceinline__ GroupBlock group_block(int dealt)
 {
     const uint32_t id = blockIdx.x;
+    if (kOne) return {0, (int32_t) id};
     if (dealt == 1) return {(int) blockIdx.y, (int32_t) id};
     const uint32_t turn = id / kXcds, eight = turn / (uint32_t) dealt;
     const uint32_t p = (id % kXcds) * (uint32_t) dealt + (turn - eight * (uint32_t) dealt);      // of the 8 * dealt blocks of a turn

@@ -62,7 +62,7 @@ hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s)
 // A bad seed is reported by stamping the batch id, so no flag needs resetting while other blocks may be setting it.
 __global__ void __launch_bounds__(kBlock) k_batch_begin(LayerArgs g, BeginDyn d)
 {
-    const auto [b, block] = group_block(g.dealt);
+    const auto [b, block] = group_block<false>(g.dealt);
     const int32_t num_seeds = d.num_seeds[b];
     const NodeTable tab = bind_table(g, b, d.stamp[b]);
     const int32_t q = block * kBlock + (int32_t) threadIdx.x;
@@ -272,12 +272,12 @@ __device__ __forceinline__ void union_sparse_tile(const FinishArgs& a, int32_t t
 // other tiles -> offsets of the new nodes), so it is one launch (two, with the tile counts in a launch of their own,
 // cost another 4.6 us each, three times per mini-batch), the tiles are small, and new nodes are spread over threads.
 // kPerMax: words of a tile per thread at most; 0: the bitmap has a summary (union_sparse_tile).
-template <int kPerMax>
+template <int kPerMax, bool kOne>
 __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
 {
     __shared__ int32_t smem[kBlock / kWave + 1];
-    const auto [b, block] = group_block(g.dealt);
-    if (block >= g.blocks) return;
+    const auto [b, block] = group_block<kOne>(g.dealt);
+    if (!kOne && block >= g.blocks) return;
     const FinishArgs a = bind_finish(g, b, true);
     // the tile's marked words, kMarkCap at a time: the word, its index in the tile, the number of marks before it
     __shared__ uint64_t s_word[kMarkCap];
@@ -435,20 +435,24 @@ hipError_t launch_finish_layer(const Group& g, int layer_index, hipStream_t s)
     const dim3 grid = group_grid(g, a, a.blocks);
     // by summary, or by words of a tile per thread: the kernel's loops over them are unrolled for 1, 4 or 32
     const int per = a.f.mark_tile_words / kBlock, spins = c->union_spins;
-    if (a.off.has_summary) hipLaunchKernelGGL(k_union<0>, grid, dim3(kBlock), 0, s, a, spins);
-    else if (per <= 1) hipLaunchKernelGGL(k_union<1>, grid, dim3(kBlock), 0, s, a, spins);
-    else if (per <= 4) hipLaunchKernelGGL(k_union<4>, grid, dim3(kBlock), 0, s, a, spins);
-    else               hipLaunchKernelGGL((k_union<kMarkTileMax / kBlock>), grid, dim3(kBlock), 0, s, a, spins);
+    with_one(g, [&](auto kOne) {
+        constexpr bool one = decltype(kOne)::value;
+        if (a.off.has_summary) hipLaunchKernelGGL((k_union<0, one>), grid, dim3(kBlock), 0, s, a, spins);
+        else if (per <= 1) hipLaunchKernelGGL((k_union<1, one>), grid, dim3(kBlock), 0, s, a, spins);
+        else if (per <= 4) hipLaunchKernelGGL((k_union<4, one>), grid, dim3(kBlock), 0, s, a, spins);
+        else               hipLaunchKernelGGL((k_union<kMarkTileMax / kBlock, one>), grid, dim3(kBlock), 0, s, a, spins);
+    });
     return hipGetLastError();
 }
 
 // The last layer's relabel has no following sampler to ride with; its launch also leaves the hub list and the
 // seed bitmap empty for the next mini-batch and writes the counts to the context's pinned host mirror, where
 // gns_sample_blocks_wait finds them.
+template <bool kOne>
 __global__ void __launch_bounds__(kBlock) k_relabel_last(LayerArgs g)
 {
-    const auto [b, block] = group_block(g.dealt);
-    if (block >= g.blocks) return;
+    const auto [b, block] = group_block<kOne>(g.dealt);
+    if (!kOne && block >= g.blocks) return;
     const FinishArgs a = bind_finish(g, b, true);
     relabel_body(a, block, g.blocks);
     if (block == 0) {
@@ -474,7 +478,7 @@ hipError_t launch_relabel(const Group& g, int layer_index, hipStream_t s)
     set_group_layer(g, layer_index, &a);
     fill_finish_template(g, layer_index, &a.f);
     a.blocks = relabel_grid(c, layer_index);
-    hipLaunchKernelGGL(k_relabel_last, group_grid(g, a, a.blocks), dim3(kBlock), 0, s, a);
+    with_one(g, [&](auto kOne) { hipLaunchKernelGGL(k_relabel_last<decltype(kOne)::value>, group_grid(g, a, a.blocks), dim3(kBlock), 0, s, a); });
     return hipGetLastError();
 }
 

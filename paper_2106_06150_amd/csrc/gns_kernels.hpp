@@ -7,6 +7,7 @@
 // context's per-batch scratch, and one BatchSlot per batch (where its scratch lies, its block buffers).
 // Every kernel first binds the templates to its own batch.
 #pragma once
+#include <type_traits>
 #include "gns_internal.h"
 #include "gns_device.hpp"
 
@@ -481,6 +482,13 @@ struct Group {
     gns_block* blocks[kMaxGroup];    // each: the caller's array of num_layers blocks
 };
 
+// f(kOne): calls it with whether the group is a single batch as a compile-time constant.
+template <typename F>
+inline void with_one(const Group& g, F&& f)
+{
+    if (g.count == 1) f(std::integral_constant<bool, true>());
+    else              f(std::integral_constant<bool, false>());
+}
 // Grid of a group's launch with `blocks` blocks per batch.
 inline dim3 group_grid(const Group& g, const LayerArgs& a, int64_t blocks)
 {

@@ -21,7 +21,6 @@
 // the node-indexed mark bitmap that the frontier stage turns into the src list.
 #include <string.h>
 #include <stdlib.h>
-#include <type_traits>
 #include "gns_kernels.hpp"
 
 namespace gns {
@@ -274,15 +273,15 @@ __device__ __forceinline__ void sample_block_rows(const LayerArgs& g, const Begi
     if (threadIdx.x == 0) a.sums_rows[block] = sum;
 }
 
-template <int K, int kList>
+template <int K, int kList, bool kOne>
 __global__ void __launch_bounds__(kBlock) k_sample_rows(LayerArgs g, int W, int relabel_blocks)
 {
     // the last relabel_blocks blocks finish the previous layer's block instead (see relabel_body); they are
     // dispatched after this layer's rows, whose dependent loads set the length of the launch
     __shared__ int32_t smem[kBlock / kWave + 1];
     __shared__ WaveRows<K> rows[kBlock / kWave];
-    const GroupBlock q = group_block(g.dealt);
-    if (q.block >= g.blocks) return;
+    const GroupBlock q = group_block<kOne>(g.dealt);
+    if (!kOne && q.block >= g.blocks) return;
     const int32_t nblocks = g.blocks - relabel_blocks;
     if (q.block >= nblocks) {
         relabel_body(bind_finish(g, q.b, false), q.block - nblocks, relabel_blocks);
@@ -295,12 +294,12 @@ __global__ void __launch_bounds__(kBlock) k_sample_rows(LayerArgs g, int W, int 
 }
 
 // The first layer of a mini-batch, in the launch that enters its seeds.
-template <int K, int kList>
+template <int K, int kList, bool kOne>
 __global__ void __launch_bounds__(kBlock) k_sample_first(LayerArgs g, BeginDyn d, int W)
 {
     __shared__ int32_t smem[kBlock / kWave + 1];
     __shared__ WaveRows<K> rows[kBlock / kWave];
-    const auto [b, block] = group_block(g.dealt);
+    const auto [b, block] = group_block<kOne>(g.dealt);
     const int32_t R = d.num_seeds[b];
     if (block == 0 && threadIdx.x == 0) begin_state(g, d, b);
     if ((int64_t) block * (kBlock / kWave) * W >= R) return;
@@ -310,12 +309,12 @@ __global__ void __launch_bounds__(kBlock) k_sample_first(LayerArgs g, BeginDyn d
 
 // ---------------------------------------------------------------------------
 // Direct layers with fan-outs above 16: a wave per row, one slot per lane.
-template <int kList>
+template <int kList, bool kOne>
 __global__ void __launch_bounds__(kBlock) k_sample_wide(LayerArgs g, int relabel_blocks)
 {
     __shared__ int32_t smem[kBlock / kWave + 1];
-    const GroupBlock q = group_block(g.dealt);
-    if (q.block >= g.blocks) return;
+    const GroupBlock q = group_block<kOne>(g.dealt);
+    if (!kOne && q.block >= g.blocks) return;
     const int32_t nblocks = g.blocks - relabel_blocks;
     if (q.block >= nblocks) {
         relabel_body(bind_finish(g, q.b, false), q.block - nblocks, relabel_blocks);
@@ -405,13 +404,14 @@ constexpr int kPlanTile = kBlock;
 
 // One launch: a tile's block passes its number of chunks on to the blocks of later tiles (sum_before), as the union step's
 // blocks do with the rows' samples.  Two launches fewer: a mini-batch with a scan of its rows 189 -> 185 us.
+template <bool kOne>
 __global__ void __launch_bounds__(kBlock) k_plan(LayerArgs g, int relabel_blocks, int spins)
 {
     __shared__ int32_t smem[kBlock / kWave + 1];
     __shared__ int32_t s_off[kPlanTile + 1];
     __shared__ int32_t s_g0[kPlanTile];
-    const auto [b, tile] = group_block(g.dealt);
-    if (tile >= g.blocks) return;
+    const auto [b, tile] = group_block<kOne>(g.dealt);
+    if (!kOne && tile >= g.blocks) return;
     const int32_t ntiles = g.blocks - relabel_blocks;
     if (tile >= ntiles) {
         relabel_body(bind_finish(g, b, false), tile - ntiles, relabel_blocks);
@@ -747,11 +747,11 @@ __device__ __forceinline__ void select_row(const SampleArgs& a, int64_t row, boo
 // the batch) would keep the rest of their wave waiting, so for G < 64 the row blocks skip them
 // and hub_blocks further blocks give each of them a whole wave (64 * kHubWords words per step).
 // Block order: hub blocks, row blocks.
-template <int G>
+template <int G, bool kOne>
 __global__ void __launch_bounds__(kBlock) k_select_rows(LayerArgs g, int hub_blocks)
 {
-    const GroupBlock q = group_block(g.dealt);
-    if (q.block >= g.blocks) return;
+    const GroupBlock q = group_block<kOne>(g.dealt);
+    if (!kOne && q.block >= g.blocks) return;
     const SampleArgs a = bind_sample(g, q.b);
     const int wave_in_block = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
     if (q.block < hub_blocks) {
@@ -903,8 +903,10 @@ hipError_t launch_first_layer(const Group& g, const BeginDyn& d, hipStream_t s)
     const dim3 grid = group_grid(g, a, ((int64_t) c->config.max_seeds + rows_per_block - 1) / rows_per_block);
     with_unroll(a.s.fanout, [&](auto K) {
         with_list(c, 0, [&](auto kList) {
-            hipLaunchKernelGGL((k_sample_first<decltype(K)::value, decltype(kList)::value>), grid, dim3(kBlock), 0, s, a, d,
-                               rows_per_block / (kBlock / kWave));
+            with_one(g, [&](auto kOne) {
+                hipLaunchKernelGGL((k_sample_first<decltype(K)::value, decltype(kList)::value, decltype(kOne)::value>), grid, dim3(kBlock),
+                                   0, s, a, d, rows_per_block / (kBlock / kWave));
+            });
         });
     });
     return hipGetLastError();
@@ -953,13 +955,15 @@ hipError_t launch_sample_layer(const Group& g, int layer_index, hipStream_t s)
         if (blocks > cap) blocks = cap;
         const dim3 grid = grid_of(blocks + rl);
         with_list(c, layer_index, [&](auto kList) {
-            if (!narrow) {
-                hipLaunchKernelGGL((k_sample_wide<decltype(kList)::value>), grid, tb, 0, s, a, rl);
-                return;
-            }
-            with_unroll(a.s.fanout, [&](auto K) {
-                hipLaunchKernelGGL((k_sample_rows<decltype(K)::value, decltype(kList)::value>), grid, tb, 0, s, a,
-                                   rows_per_block / (kBlock / kWave), rl);
+            with_one(g, [&](auto kOne) {
+                if (!narrow) {
+                    hipLaunchKernelGGL((k_sample_wide<decltype(kList)::value, decltype(kOne)::value>), grid, tb, 0, s, a, rl);
+                    return;
+                }
+                with_unroll(a.s.fanout, [&](auto K) {
+                    hipLaunchKernelGGL((k_sample_rows<decltype(K)::value, decltype(kList)::value, decltype(kOne)::value>), grid, tb, 0, s,
+                                       a, rows_per_block / (kBlock / kWave), rl);
+                });
             });
         });
         return hipGetLastError();
@@ -978,7 +982,7 @@ hipError_t launch_sample_layer(const Group& g, int layer_index, hipStream_t s)
         StageTimer t(c, GNS_STAGE_PLAN, s);
         const unsigned plan_blocks = (unsigned) ((rows_max + kPlanTile - 1) / kPlanTile);
         const dim3 grid = grid_of((int64_t) plan_blocks + rl);
-        hipLaunchKernelGGL(k_plan, grid, tb, 0, s, a, rl, c->union_spins);
+        with_one(g, [&](auto kOne) { hipLaunchKernelGGL(k_plan<decltype(kOne)::value>, grid, tb, 0, s, a, rl, c->union_spins); });
     }
     {
         StageTimer t(c, GNS_STAGE_FLAG, s);
@@ -989,9 +993,12 @@ hipError_t launch_sample_layer(const Group& g, int layer_index, hipStream_t s)
     const int hub_blocks = (G < 64) ? (int) (rows_max / (kBlock / kWave) < (int64_t) c->num_cus * 2
                                                  ? rows_max / (kBlock / kWave) + 1 : (int64_t) c->num_cus * 2) : 0;
     const dim3 rb = grid_of(row_blocks + hub_blocks);
-    if (G == 8)       hipLaunchKernelGGL(k_select_rows<8>, rb, tb, 0, s, a, hub_blocks);
-    else if (G == 16) hipLaunchKernelGGL(k_select_rows<16>, rb, tb, 0, s, a, hub_blocks);
-    else              hipLaunchKernelGGL(k_select_rows<64>, rb, tb, 0, s, a, hub_blocks);
+    with_one(g, [&](auto kOne) {
+        constexpr bool one = decltype(kOne)::value;
+        if (G == 8)       hipLaunchKernelGGL((k_select_rows<8, one>), rb, tb, 0, s, a, hub_blocks);
+        else if (G == 16) hipLaunchKernelGGL((k_select_rows<16, one>), rb, tb, 0, s, a, hub_blocks);
+        else              hipLaunchKernelGGL((k_select_rows<64, one>), rb, tb, 0, s, a, hub_blocks);
+    });
     return hipGetLastError();
 }
 
