@@ -115,7 +115,6 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     L.seed_mark = take((size_t) L.words * 8);
     L.seed_copy = take((size_t) cfg->max_seeds * 4);
     L.row_ext = take((size_t) L.rows[cfg->num_layers] * 16);
-    L.hub_rows = take(L.lists_hubs ? (size_t) L.rows[cfg->num_layers] * 4 : 0);
     for (int par = 0; par < 2; ++par) {
         L.s_nbr[par] = take((size_t) L.max_edges * 4);
         L.s_w[par] = take((size_t) L.max_edges * 4);
@@ -127,6 +126,7 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     L.row_sums = take((size_t) L.row_tiles * 8);
     L.plan_tiles = (L.max_rows + kBlock - 1) / kBlock;
     L.plan_sums = take((size_t) L.plan_tiles * 8);
+    L.hub_rows = take(L.lists_hubs ? (size_t) L.max_rows * 4 : 0);
     if (uses_cache) {
         // a dst row of deg entries touches at most deg/64 + 2 aligned chunks; dst rows are distinct
         L.max_chunks = g->num_entries / 64 + 2 * L.max_rows + 64;

@@ -4,7 +4,7 @@
 // The sampler leaves, per dst row, up to k neighbor ids at a fixed stride, their number, the sums of those
 // numbers over blocks of rows, and one bit per sampled id in a node-indexed mark bitmap.  Here:
 //   begin    the batch's first kernel where the first layer's sampler does not do it itself: scalars, seeds
-//            with their local ids into the node table, their CSR extents and hub entries
+//            with their local ids into the node table, their CSR extents
 //   union    row tiles scan the row counts into indptr; bitmap tiles count their marks, learn the counts of
 //            the tiles before them and write the marked ids in ascending order behind the dst prefix, one
 //            thread per new id, each entered in the node table with its local id, its CSR extent recorded;
@@ -92,7 +92,6 @@ void fill_group_args(const Group& g, LayerArgs* out)
     o.sums_rows = L.sums_rows; o.tile_sums = L.tile_sums; o.row_sums = L.row_sums; o.plan_sums = L.plan_sums;
     o.cache_block_bytes = L.cache_block_bytes;
     o.uses_cache = c->uses_cache ? 1 : 0;
-    o.lists_hubs = L.lists_hubs ? 1 : 0;
     o.marks_seeds = first_layer_enters_seeds(c->config) ? 1 : 0;
     for (int b = 0; b < kMaxGroup; ++b) {
         out->b[b].ws = g.ctx[b < g.count ? b : 0]->ws;
@@ -168,7 +167,6 @@ __device__ __forceinline__ void emit_new_node(const FinishArgs& a, int32_t pos, 
     ext.start = load_off_rt(a.g_indptr, a.g_i64, node);
     ext.end = load_off_rt(a.g_indptr, a.g_i64, (int64_t) node + 1);
     a.row_ext[pos] = ext;
-    append_hub_rows(a.st, a.hub_rows, is_hub_extent(ext.start, ext.end), pos);
 }
 
 // The bitmap side of the union step on graphs whose bitmap has a summary.  A tile has far more words than marks there, so
@@ -445,7 +443,7 @@ hipError_t launch_finish_layer(const Group& g, int layer_index, hipStream_t s)
     return hipGetLastError();
 }
 
-// The last layer's relabel has no following sampler to ride with; its launch also leaves the hub list and the
+// The last layer's relabel has no following sampler to ride with; its launch also leaves the
 // seed bitmap empty for the next mini-batch and writes the counts to the context's pinned host mirror, where
 // gns_sample_blocks_wait finds them.
 template <bool kOne>
@@ -463,10 +461,7 @@ __global__ void __launch_bounds__(kBlock) k_relabel_last(LayerArgs g)
             if (seeds[i] >= 0 && (int64_t) seeds[i] < a.num_nodes) seed_mark[seeds[i] >> 6] = 0ull;
         if (threadIdx.x <= GNS_MAX_LAYERS) q.host->num_dst[threadIdx.x] = a.st->num_dst[threadIdx.x];
         if (threadIdx.x < GNS_MAX_LAYERS) q.host->num_edges[threadIdx.x] = a.st->num_edges[threadIdx.x];
-        if (threadIdx.x == 0) {
-            a.st->hub_count = 0;                                     // the next batch starts a new hub list
-            q.host->bad_seed = a.st->bad_seed;
-        }
+        if (threadIdx.x == 0) q.host->bad_seed = a.st->bad_seed;
     }
 }
 

@@ -15,7 +15,7 @@ struct DeviceState {
     int32_t num_edges[GNS_MAX_LAYERS];
     uint32_t key0, key1;                  // Philox key of the current batch (lo32(seed), hi32(seed))
     uint32_t bad_seed;                    // id of the last batch that had a seed out of range or repeated
-    int32_t hub_count;                    // entries of the batch's hub-row list (reset by the batch's last kernel)
+    int32_t hub_count[GNS_MAX_LAYERS];    // entries of a scanning layer's hub-row list (reset by the batch's first kernel)
     int32_t draw_distinct[2];             // cache draw: nodes in the cache before a chunk (by the chunk's parity)
     int32_t draw_done_chunk;              //   index of the chunk that completed the cache, -1 while incomplete
     int32_t plan_chunks;                  // CACHE_ONLY sampler: aligned chunks in the current work list
@@ -71,14 +71,14 @@ struct Layout {
     size_t mark_summary;      // one bit per word of the mark bitmap: "this word has a mark" (large graphs only)
     int64_t summary_words;    // 0: no summary
     size_t seed_copy;         // [max_seeds] the batch's seeds, copied by its first kernel
-    size_t hub_rows;          // [max nodes of a batch] rows whose CSR segment spans more than kHubChunks chunks
+    size_t hub_rows;          // [max_rows] the layer's rows whose CSR segment spans more than kHubChunks chunks
     size_t row_ext;           // [max nodes of a batch] CSR extent of every node of the batch's list (append-only)
     size_t seed_mark;         // bitmap of the batch's seeds (first layer sampled by the lane kernel)
     size_t table;             // [n] node table: local id of every node of the batch, stamped (the last per-batch section)
     int table_shift;          // bits of a local id in a table entry
     uint32_t max_stamp;
     size_t static_table;      // node table of gns_sample_blocks_static where the library's array cannot hold it (shared; 0: none)
-    bool lists_hubs;          // some layer gives hub rows a wave of their own
+    bool lists_hubs;          // some layer scans its rows and gives the hubs among them a wave of their own
     // per-layer sampler scratch (fixed stride fanout)
     size_t s_nbr[2], s_w[2], s_cnt[2];     // double-buffered by layer parity
     // CACHE_ONLY sampler: chunk work list, CSR-aligned membership flags

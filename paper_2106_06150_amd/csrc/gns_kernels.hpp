@@ -77,7 +77,7 @@ struct SampleArgs {
     const int32_t* dst_nodes;
     RowExtent* row_ext;        // CSR extent of every dst row's node (written when the node joined the batch)
     const float* node_inv_pc;  // 1 / p^C_u for the nodes of the cache
-    const int32_t* hub_rows;   // rows of the batch whose CSR segment spans more than kHubChunks chunks
+    int32_t* hub_rows;         // rows of the layer whose CSR segment spans more than kHubChunks chunks
     const uint64_t* cache_bitmap;
     int32_t* s_nbr;
     float* s_w;
@@ -133,7 +133,6 @@ struct FinishArgs {
     RowExtent* row_ext;            // [nodes of the batch] the union step appends the new nodes' CSR extents
     const void* g_indptr;          // the graph's offsets
     int g_i64;
-    int32_t* hub_rows;             // the union step appends the new nodes that are hubs
     int64_t num_nodes;
     int32_t last_layer;            // its new nodes have no rows to be sampled
 };
@@ -149,7 +148,6 @@ struct WsOffsets {
     int32_t uses_cache;
     int32_t has_summary;
     int32_t table_shift;
-    int32_t lists_hubs;            // some layer gives hub rows a wave of their own
     int32_t marks_seeds;           // the first layer's launch fills the seed bitmap
 };
 
@@ -230,7 +228,7 @@ __device__ __forceinline__ SampleArgs bind_sample(const LayerArgs& g, int b, uin
     const int par = g.s.layer_index & 1;             // sampler scratch is double-buffered by layer parity
     a.dst_nodes = q.dst;
     a.row_ext = at<RowExtent>(ws, g.off.row_ext);
-    a.hub_rows = g.off.lists_hubs ? at<int32_t>(ws, g.off.hub_rows) : nullptr;
+    a.hub_rows = at<int32_t>(ws, g.off.hub_rows);
     a.s_nbr = at<int32_t>(ws, g.off.s_nbr[par]);
     a.s_w = at<float>(ws, g.off.s_w[par]);
     a.s_cnt = at<int32_t>(ws, g.off.s_cnt[par]);
@@ -290,7 +288,6 @@ __device__ __forceinline__ FinishArgs bind_finish(const LayerArgs& g, int b, boo
     a.weights = blk.weights;
     a.src_nodes = blk.src_nodes;
     a.row_ext = at<RowExtent>(ws, g.off.row_ext);
-    a.hub_rows = g.off.lists_hubs ? at<int32_t>(ws, g.off.hub_rows) : nullptr;
     return a;
 }
 
@@ -409,9 +406,8 @@ __device__ __forceinline__ void relabel_body(const FinishArgs& a, int32_t block,
     }
 }
 
-// A node whose CSR segment touches more than kHubChunks aligned 64-entry chunks is a hub: the
-// CACHE_ONLY sampler gives such rows a whole wave each.  Nodes are classified when they join the
-// batch's node list; the list of hub rows is append-only like the node list itself.
+// A row whose CSR segment touches more than kHubChunks aligned 64-entry chunks is a hub: the sampler that reads rows' flag
+// words gives it a whole wave.
 constexpr int kHubChunks = 32;
 
 __device__ __forceinline__ bool is_hub_extent(int64_t start, int64_t end)
@@ -419,25 +415,12 @@ __device__ __forceinline__ bool is_hub_extent(int64_t start, int64_t end)
     return end > start && ((end - 1) >> 6) - (start >> 6) + 1 > kHubChunks;
 }
 
-// Appends `row` for the calling lanes that have is_hub set: one atomic per wave.
-__device__ __forceinline__ void append_hub_rows(DeviceState* st, int32_t* hub_rows, bool is_hub, int32_t row)
-{
-    const uint64_t m = __ballot(is_hub && hub_rows != nullptr);      // no list without a cache layer
-    if (m == 0) return;
-    const int lane = lane_id();
-    const int leader = __builtin_ctzll(m);
-    int32_t base = 0;
-    if (lane == leader) base = atomicAdd(&st->hub_count, (int32_t) __popcll(m));
-    base = __shfl(base, leader, kWave);
-    if (is_hub && hub_rows) hub_rows[base + __popcll(m & ((1ull << lane) - 1ull))] = row;
-}
-
 // The batch's scalars, published for its later kernels; one thread of the batch's first kernel.
 __device__ __forceinline__ void begin_state(const LayerArgs& g, const BeginDyn& d, int b)
 {
     DeviceState* st = bind_state(g, b);
     st->num_dst[0] = d.num_seeds[b];
-    for (int l = 0; l < GNS_MAX_LAYERS; ++l) { st->num_edges[l] = 0; st->num_dst[l + 1] = 0; }
+    for (int l = 0; l < GNS_MAX_LAYERS; ++l) { st->num_edges[l] = 0; st->num_dst[l + 1] = 0; st->hub_count[l] = 0; }
     st->key0 = d.key0[b];
     st->key1 = d.key1[b];
     st->stamp = d.stamp[b];
@@ -469,8 +452,6 @@ __device__ __forceinline__ void enter_seed(const LayerArgs& g, const BeginDyn& d
     }
     at<int32_t>(ws, g.off.seed_copy)[q] = u;
     at<RowExtent>(ws, g.off.row_ext)[q] = ext;
-    append_hub_rows(bind_state(g, b), g.off.lists_hubs ? at<int32_t>(ws, g.off.hub_rows) : nullptr,
-                    is_hub_extent(ext.start, ext.end), q);
     if (bad) bind_state(g, b)->bad_seed = d.batch_id[b];
 }
 

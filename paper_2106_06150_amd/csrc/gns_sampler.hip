@@ -410,6 +410,7 @@ __global__ void __launch_bounds__(kBlock) k_plan(LayerArgs g, int relabel_blocks
     __shared__ int32_t smem[kBlock / kWave + 1];
     __shared__ int32_t s_off[kPlanTile + 1];
     __shared__ int32_t s_g0[kPlanTile];
+    __shared__ int32_t s_hubs[kBlock / kWave], s_first_hub;
     const auto [b, tile] = group_block<kOne>(g.dealt);
     if (!kOne && tile >= g.blocks) return;
     const int32_t ntiles = g.blocks - relabel_blocks;
@@ -424,12 +425,20 @@ __global__ void __launch_bounds__(kBlock) k_plan(LayerArgs g, int relabel_blocks
     RowExtent ext = {0, 0};
     if (r < R) ext = a.row_ext[r];
     s_g0[threadIdx.x] = (int32_t) (ext.start >> 6);
+    const bool hub = is_hub_extent(ext.start, ext.end);
+    const uint64_t hubs = __ballot(hub);
+    if (lane_id() == 0) s_hubs[threadIdx.x >> 6] = __popcll(hubs);
     int32_t total;
     s_off[threadIdx.x] = block_exclusive_scan(chunks_touched(ext.start, ext.end), smem, &total);
     const uint32_t tag = launch_tag(a.st, a.layer_index);
     if (threadIdx.x == 0) {
         s_off[kPlanTile] = total;
         publish_sum(a.plan_sums, tile, tag, (uint32_t) total);
+        // behind the sum others wait for: the tile's hubs take their places in the layer's list (s_hubs is complete: the scan
+        // has synchronised)
+        int32_t hub_total = 0;
+        for (int w = 0; w < kBlock / kWave; ++w) hub_total += s_hubs[w];
+        if (hub_total) s_first_hub = atomicAdd(&a.st->hub_count[a.layer_index], hub_total);
     }
     // chunks of all earlier tiles
     const int32_t before = sum_before(a.plan_sums, tag, tile, spins, smem, [&](int32_t t) {
@@ -440,6 +449,11 @@ __global__ void __launch_bounds__(kBlock) k_plan(LayerArgs g, int relabel_blocks
     });
     if (tile == (R - 1) / kPlanTile && threadIdx.x == 0) a.st->plan_chunks = before + total;
     __syncthreads();
+    if (hub) {
+        int32_t place = s_first_hub + __popcll(hubs & ((1ull << lane_id()) - 1ull));
+        for (int w = 0; w < (int) (threadIdx.x >> 6); ++w) place += s_hubs[w];
+        a.hub_rows[place] = r;
+    }
     // one thread per work-list entry: its row is the last one whose offset is <= j
     for (int32_t j = (int32_t) threadIdx.x; j < total; j += kBlock) {
         int32_t lo = 0, hi = kPlanTile;
@@ -743,8 +757,9 @@ __device__ __forceinline__ void select_row(const SampleArgs& a, int64_t row, boo
     }
 }
 
-// G lanes per dst row, one flag word per lane and step.  Hub rows (listed when their nodes joined
-// the batch) would keep the rest of their wave waiting, so for G < 64 the row blocks skip them
+// G lanes per dst row, one flag word per lane and step.  Hub rows (listed by k_plan with one
+// atomic per 256 rows: an atomic per wave where nodes join the batch made the union step of a layer of 73 K new nodes 3.5 us
+// longer) would keep the rest of their wave waiting, so for G < 64 the row blocks skip them
 // and hub_blocks further blocks give each of them a whole wave (64 * kHubWords words per step).
 // Block order: hub blocks, row blocks.
 template <int G, bool kOne>
@@ -755,7 +770,7 @@ __global__ void __launch_bounds__(kBlock) k_select_rows(LayerArgs g, int hub_blo
     const SampleArgs a = bind_sample(g, q.b);
     const int wave_in_block = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
     if (q.block < hub_blocks) {
-        const int32_t H = a.st->hub_count;
+        const int32_t H = a.st->hub_count[a.layer_index];
         const int32_t nhw = hub_blocks * (kBlock / kWave);
         for (int32_t h = q.block * (kBlock / kWave) + wave_in_block; h < H; h += nhw) {
             const int lane = opaque_lane_id();
