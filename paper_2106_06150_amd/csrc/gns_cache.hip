@@ -12,9 +12,9 @@
 // is cut at exactly that draw.
 //
 // On graphs of a million nodes a draw is a chain of small launches, so there are few: clear, then two per chunk (draw,
-// commit), then the index with the 1/p^C table; and the host looks at the outcome behind two chunks and all of it, once for
-// most caches.  What follows an incomplete cache stands down on the device: half of 1 M nodes take 562 us, 16 M of 40 M nodes
-// 9.35 ms, where filling everything behind the first two chunks and again at the end took 728 us and 12.5 ms.
+// commit), then the index with the 1/p^C table; and the host looks at the outcome behind the first chunk or two and all of it,
+// once for most caches, then behind two more at a time.  What follows an incomplete cache stands down on the device: half of 1 M
+// nodes take 358 us, 16 M of 40 M nodes 11.0 ms.
 // A draw of 10 K of 1 M nodes with the mini-batch behind it: 247 us, where a launch per phase, a read-back per chunk of 64 K
 // draws and searches over all offsets took 295; 400 K of 40 M nodes: 1779 us, before 1992.
 #include "gns_internal.h"
@@ -549,15 +549,19 @@ gns_status run_sample_cache(gns_ctx* c, uint64_t seed, uint64_t epoch, bool wait
     x.g_indptr = c->graph.indptr;
     x.g_i64 = c->graph.indptr_is_i64;
     if (wait_for_it) {
-        // Two chunks and what follows them, then a look at the outcome.  While the cache is incomplete (a stream that repeats
-        // itself a lot: a large share of the nodes, a concentrated probability) two chunks more are tried.
+        // A chunk and what follows it, then a look at the outcome.  While the cache is incomplete (a stream that repeats
+        // itself a lot: a large share of the nodes, a concentrated probability) two chunks more are tried, for more than a
+        // twentieth of the nodes from the start on: a chunk that stands down is two launches in front of everything else, a
+        // second look a wait.  One and two chunks first: 100 of 10 K nodes 39 and 48 us, 10 K of 1 M 81 and 85, 50 K 102 and
+        // 105, 100 K 164 and 148.
+        const bool one = C <= c->nonzero_degree_nodes / 20;
         x.done = &c->d_state->draw_done_chunk;
         do {
             if (drawn >= stop) {
                 c->pending = false;                    // the copy an enqueued draw may have filled is gone
                 return fail(c, GNS_ECAPACITY, "cache draw: the stream did not yield cache_size distinct nodes within the draw limit (cache_size too close to the number of nodes with neighbors)", hipSuccess);
             }
-            for (int k = 0; k < 2 && drawn < stop; ++k) GNS_HIP_TRY(enqueue_chunk(), "cache draw launch");
+            for (int k = drawn == 0 && one ? 1 : 2; k > 0 && drawn < stop; --k) GNS_HIP_TRY(enqueue_chunk(), "cache draw launch");
             x.tag = next_tag();
             const gns_status st = fill_cache(c, gen, x, i64, s);
             if (st != GNS_OK) return st;
