@@ -504,7 +504,11 @@ static void launch_walk_step(const gns_ctx* c, const WalkStepArgs& a, int in, bo
 }
 
 // Exclusive prefix sum of n 64-bit values in three phases (tile sums, one block over the tile
-// sums, per-tile scan) with the saturating addition above, plus the number of non-zero values.
+// sums, per-tile scan) with the saturating addition above, plus the number of non-zero values.  Of up to kScanTiles tiles every
+// block of the last phase adds up those before its own itself, without a launch for it (1 M nodes: 18.1 us for three phases,
+// 14.3 for two; 4 M nodes 54 and 39).
+constexpr int64_t kScanTiles = 2048;
+
 __device__ __forceinline__ unsigned long long wave_inclusive_sat_scan(unsigned long long v)
 {
     const int lane = opaque_lane_id();
@@ -585,11 +589,15 @@ __global__ void __launch_bounds__(kBlock) k_walk_scan_phase2(unsigned long long*
     }
 }
 
+// kSums: `tiles` holds the tiles' sums, else what comes before each of them.
+template <bool kSums>
 __global__ void __launch_bounds__(kBlock) k_walk_scan_phase3(const unsigned long long* w, int64_t n,
-                                                             const unsigned long long* tile_offsets,
-                                                             long long* prefix, const DeviceState* st)
+                                                             const unsigned long long* tiles, const int32_t* tile_nonzero,
+                                                             long long* prefix, DeviceState* st)
 {
     __shared__ unsigned long long smem[kBlock / kWave + 1];
+    __shared__ int32_t smem32[kBlock / kWave + 1];
+    const bool last = blockIdx.x == gridDim.x - 1;
     const int64_t base = (int64_t) blockIdx.x * kTile + (int64_t) threadIdx.x * kItems;
     unsigned long long x[kItems];
     unsigned long long sum = 0;
@@ -598,14 +606,33 @@ __global__ void __launch_bounds__(kBlock) k_walk_scan_phase3(const unsigned long
         x[i] = (base + i < n) ? w[base + i] : 0ull;
         sum = sat_add(sum, x[i]);
     }
-    unsigned long long total;
-    unsigned long long off = sat_add(tile_offsets[blockIdx.x], block_exclusive_sat_scan(sum, smem, &total));
+    unsigned long long before = 0, total;
+    if (kSums) {
+        int32_t nz = 0;
+        unsigned long long mine = 0;
+        for (int32_t t = (int32_t) threadIdx.x; t < (int32_t) blockIdx.x; t += kBlock) mine = sat_add(mine, tiles[t]);
+        for (int32_t t = (int32_t) threadIdx.x; last && t < (int32_t) gridDim.x; t += kBlock) nz += tile_nonzero[t];
+        (void) block_exclusive_sat_scan(mine, smem, &before);
+        if (last) nz = block_sum(nz, smem32);
+        if (last && threadIdx.x == 0) st->walk_support = nz;
+    } else {
+        before = tiles[blockIdx.x];
+    }
+    unsigned long long off = sat_add(before, block_exclusive_sat_scan(sum, smem, &total));
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
         if (base + i < n) prefix[base + i] = (long long) off;
         off = sat_add(off, x[i]);
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) prefix[n] = (long long) st->walk_total;
+    if (!last || threadIdx.x != 0) return;
+    if (kSums) {
+        const unsigned long long all = sat_add(before, total);
+        st->walk_total = all;
+        if (all >= kWalkLimit) st->walk_error = 2;
+        prefix[n] = (long long) all;
+    } else {
+        prefix[n] = (long long) st->walk_total;
+    }
 }
 
 gns_status run_walk_probability(gns_ctx* c, const int32_t* train_nodes, int64_t num_train, int32_t scale_log2,
@@ -656,8 +683,12 @@ gns_status run_walk_probability(gns_ctx* c, const int32_t* train_nodes, int64_t 
     }
     const int64_t tiles = (n + kTile - 1) / kTile;
     hipLaunchKernelGGL(k_walk_scan_phase1, dim3((unsigned) tiles), dim3(kBlock), 0, s, cur, n, tile_sums, tile_nz);
-    hipLaunchKernelGGL(k_walk_scan_phase2, dim3(1), dim3(kBlock), 0, s, tile_sums, tile_nz, tiles, c->d_state);
-    hipLaunchKernelGGL(k_walk_scan_phase3, dim3((unsigned) tiles), dim3(kBlock), 0, s, cur, n, tile_sums, prefix, c->d_state);
+    if (tiles <= kScanTiles) {
+        hipLaunchKernelGGL(k_walk_scan_phase3<true>, dim3((unsigned) tiles), dim3(kBlock), 0, s, cur, n, tile_sums, tile_nz, prefix, c->d_state);
+    } else {
+        hipLaunchKernelGGL(k_walk_scan_phase2, dim3(1), dim3(kBlock), 0, s, tile_sums, tile_nz, tiles, c->d_state);
+        hipLaunchKernelGGL(k_walk_scan_phase3<false>, dim3((unsigned) tiles), dim3(kBlock), 0, s, cur, n, tile_sums, tile_nz, prefix, c->d_state);
+    }
     hipError_t e = hipGetLastError();
     // only the walk's own fields (walk_total, walk_support, walk_error): a draw in flight leaves its outcome beside them
     if (e == hipSuccess)
