@@ -84,32 +84,56 @@ __device__ __forceinline__ int32_t mark_if_new(const SampleArgs& a, uint32_t u)
 }
 
 // ---------------------------------------------------------------------------
-// Direct layers with fan-outs up to 16.  A wave takes W rows (W a power of two up to 64) in two stages:
+// Direct layers with fan-outs up to 16.  A wave takes W rows (W a power of two up to kWaveRows) in two stages:
 //   draw   one row per lane: extent, chunk records, Floyd's draw for the whole row (the loops over the slots are
-//          unrolled, the chosen ranks stay in registers); the Philox blocks of the W rows are spread over all lanes;
+//          unrolled, the chosen ranks stay in registers and are sorted there: an entry's slot is then its place in the row);
+//          the Philox blocks of the W rows are spread over all lanes;
 //   fetch  one drawn entry per lane: the W * k (row, slot) pairs are dealt to the lanes, kFetch at a time with
 //          their reads in flight together: entry -> node table and 1/p^C -> mark, scratch.
 // The stages have opposite needs.  The draw is instruction-bound (a Philox block is forty quarter-rate multiplies), and
 // with a slot per lane every lane of a row repeats it; the fetch is a chain of scattered reads, and with a row per lane
-// half of the slots a lane holds sit in branches that wait for one another.  W is chosen by the launch: 64 where there
-// are rows enough to fill the chip, fewer for the small layers next to the seeds, whose launches are as long as that chain.
-// Groups of four on the graph of 1 M nodes: 9.9 / 27 / 44 us for the three layers (entering the seeds included), where a
-// lane group per row on the upper and a row per lane on the input layer took 15.7 / 28 / 55; the input layer is now bound by
-// the lines its records and drawn entries pull in (1.5 M L2 misses), no longer by instructions.
+// half of the slots a lane holds sit in branches that wait for one another.
+// The sort (38 instructions a row of 8 slots) takes the place of a count, per entry, of the row's smaller ranks: that read
+// the row's slots from LDS for every entry and held 103 registers, four waves per SIMD where 60 let eight run, and entries
+// in ascending order share the lines of list and scratch.  Groups of four on the graph of 1 M nodes, three layers (entering
+// the seeds included): 9.9 / 25 / 36.6 us, with the count (and up to 64 rows per wave) 9.9 / 27 / 41.5, where a lane group
+// per row on the upper and a row per lane on the input layer took 15.7 / 28 / 55; on 40 M nodes 10 / 23 / 57 for 10 / 24 / 60.
+// The input layer is bound by the lines its records and drawn entries pull in (1.3 M L2 misses).
 // kFirst: also the batch's first kernel.  No sampled node has a local id yet as far as that launch can know, so every one
 // is marked, and the union step takes the seeds out again (seed bitmap).
-constexpr int kFetch = 5;
+constexpr int kFetch = 5;                        // 2 and 3: the same within 2 %
+constexpr int kWaveRows = 32;                    // at most, see wave_rows
 
 template <int K>
 struct WaveRows {
     static_assert(K % 4 == 0, "whole Philox blocks");
     static constexpr int kSlots = K;
-    uint32_t slot[kWave][kSlots];                // Philox words, then the chosen ranks (top bit: of the fill; ~0: none)
-    int64_t start[kWave], end[kWave];            // CSR extent
-    uint32_t first[kWave], here[kWave], tile[kWave];     // CachedList
-    int32_t count[kWave];                        // entries drawn from the list, and in all, << 8
-    float scale[kWave], fill_w[kWave];
+    uint32_t slot[kWaveRows][kSlots];            // Philox words, then the chosen ranks, ascending (top bit: of the fill; ~0: none)
+    int64_t start[kWaveRows], end[kWaveRows];    // CSR extent
+    uint32_t first[kWaveRows], here[kWaveRows], tile[kWaveRows];     // CachedList
+    int32_t count[kWaveRows];                    // entries drawn from the list, and in all, << 8
+    float scale[kWaveRows], fill_w[kWaveRows];
 };
+
+// Batcher's odd-even merge sort of a lane's slots, ascending; 19, 42 and 63 exchanges for 8, 12 and 16.
+template <int K>
+__device__ __forceinline__ void sort_slots(uint32_t (&v)[K])
+{
+#pragma unroll
+    for (int p = 1; p < K; p *= 2) {
+#pragma unroll
+        for (int q = p; q >= 1; q /= 2) {
+#pragma unroll
+            for (int i = 0; i + q < K; ++i) {
+                if (i >= q % p && (i - q % p) % (2 * q) < q && i / (2 * p) == (i + q) / (2 * p)) {
+                    const uint32_t lo = v[i] < v[i + q] ? v[i] : v[i + q];
+                    v[i + q] = v[i] < v[i + q] ? v[i + q] : v[i];
+                    v[i] = lo;
+                }
+            }
+        }
+    }
+}
 
 template <int K, int kList, bool kFirst>
 __device__ __forceinline__ void sample_wave_rows(const LayerArgs& g, const BeginDyn* d, const SampleArgs& a, int b, int32_t row0,
@@ -131,7 +155,7 @@ __device__ __forceinline__ void sample_wave_rows(const LayerArgs& g, const Begin
         vi = a.dst_nodes[row];
     }
     const int blocks = (k + 3) >> 2;
-    for (int t = lane; t < kWave * blocks; t += kWave) {
+    for (int t = lane; t < kWaveRows * blocks; t += kWave) {
         // task t: block t / W of row t % W (tasks past the last repeat nothing of use; the shuffle wants every lane)
         const int r = t & (W - 1), c = t >> __builtin_ctz((unsigned) W);
         if (!__any(c < blocks)) break;
@@ -181,6 +205,7 @@ __device__ __forceinline__ void sample_wave_rows(const LayerArgs& g, const Begin
             }
             chosen[s] = s < total ? c : 0xFFFFFFFFu;
         }
+        sort_slots(chosen);
 #pragma unroll
         for (int c = 0; c < WaveRows<K>::kSlots / 4; ++c)
             *reinterpret_cast<uint4*>(&w.slot[lane][4 * c]) = make_uint4(chosen[4 * c], chosen[4 * c + 1], chosen[4 * c + 2], chosen[4 * c + 3]);
@@ -204,7 +229,7 @@ __device__ __forceinline__ void sample_wave_rows(const LayerArgs& g, const Begin
     const int items = W * k;
     const uint32_t inv_k = 65535u / (uint32_t) k + 1u;          // j / k = j * inv_k >> 16, exact for j < 4096
     for (int j0 = 0; j0 < items; j0 += kWave * kFetch) {
-        int r[kFetch], pos[kFetch];
+        int r[kFetch];
         bool mine[kFetch], is_fill[kFetch];
         int64_t place[kFetch];
 #pragma unroll
@@ -217,13 +242,6 @@ __device__ __forceinline__ void sample_wave_rows(const LayerArgs& g, const Begin
             mine[i] = j < items && s < counts >> 8;
             is_fill[i] = kList == kListCachedFirst && s >= (counts & 255);
             const uint32_t rank = w.slot[r[i]][s];
-            int p = 0;
-#pragma unroll
-            for (int c = 0; c < WaveRows<K>::kSlots / 4; ++c) {
-                const uint4 o = *reinterpret_cast<const uint4*>(&w.slot[r[i]][4 * c]);
-                p += (o.x < rank ? 1 : 0) + (o.y < rank ? 1 : 0) + (o.z < rank ? 1 : 0) + (o.w < rank ? 1 : 0);
-            }
-            pos[i] = p;
             place[i] = 0;
             if (kList == kListRow) {
                 if (mine[i]) place[i] = w.start[r[i]] + (int64_t) rank;
@@ -252,7 +270,7 @@ __device__ __forceinline__ void sample_wave_rows(const LayerArgs& g, const Begin
             int32_t out = (int32_t) u[i];
             if (!kFirst && a.tab.current(e[i])) out = -1 - (int32_t) a.tab.local(e[i]);
             else mark_node(a, u[i]);
-            const int64_t at = (int64_t) (row0 + r[i]) * k + pos[i];
+            const int64_t at = (int64_t) row0 * k + (j0 + i * kWave + lane);
             a.s_nbr[at] = out;
             if (kList != kListRow) a.s_w[at] = is_fill[i] ? w.fill_w[r[i]] : inv_pc[i] * w.scale[r[i]];
         }
@@ -867,16 +885,17 @@ bool first_layer_enters_seeds(const gns_config& config)
     return direct_layer(config, 0) && config.fanout[0] <= 16;
 }
 
-// Rows per wave of the two-stage sampler: as many as leave sixteen waves for every CU at the layer's worst-case number of
-// rows, a power of two between 4 and 64.  That number is all the host knows; input layers have 0.2 (cache first) to 0.5 of it
-// (fan-outs 15, 10 on 1 M nodes), so their launches have fewer waves than that.  Layers of 4 x 12,600 rows, fan-out 10: 37 us
-// with 64 rows per wave, 27 us with 16.
+// Rows per wave of the two-stage sampler: as many as leave 32 waves for every CU (all it holds) at the layer's worst-case
+// number of rows, a power of two between 4 and 32.  That number is all the host knows; input layers have 0.2 (cache first) to
+// 0.5 of it (fan-outs 15, 10 on 1 M nodes), so their launches have fewer waves than that.  Layers of 4 x 12,600 rows, fan-out
+// 10: 25 us with 8 rows per wave, 26 with 16, 37 with 64; of 4 x 92,400 rows, fan-out 5: 36.5 us with 32, 37.5 with 64, 42
+// with 16 (twice the blocks).
 static int wave_rows(const Group& g, int layer_index)
 {
     const gns_ctx* c = g.ctx[0];
     const int64_t rows = c->lay.rows[layer_index] * g.count;
     int W = 4;
-    while (W < kWave && (int64_t) W * c->num_cus * 16 < rows) W *= 2;
+    while (W < kWaveRows && (int64_t) W * c->num_cus * 32 < rows) W *= 2;
     return W;
 }
 

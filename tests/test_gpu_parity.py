@@ -1520,6 +1520,32 @@ def test_group_sizes_that_share_the_xcds_unevenly(count, fanouts, policies, flag
         gns.close()
 
 
+@pytest.mark.parametrize("fanout,policy", [(1, C), (5, CF), (8, C), (9, U), (12, CF), (13, C), (16, U), (16, CF)])
+def test_ranks_sorted_by_waves_of_thirty_two_rows(fanout, policy):
+    """Layers of more than 131,072 rows at most, whose waves take the most rows; fan-outs at the edges of the sorted lengths,
+    rows with fewer entries than slots, with as many and with more, and last waves that are not full."""
+    n, bs, csize, count = 40000, 2100, 0 if policy == U else 3000, 4
+    ip, ix = _small(n=n, avg=12, seed=77, hub=60)
+    gns = GpuGns(ip, ix, None, fanouts=(15, fanout), policies=(U, policy), cache_size=csize, max_seeds=bs, flag_mode=1)
+    ctxs, keep, bufs, call = _group_setup(gns, count)
+    try:
+        if csize:
+            B.gns_sample_cache(gns.ctx, 47, 0)
+        cache = oracle.sample_cache(ip.numpy(), 47, 0, max(csize, 1))
+        seeds = [synth.uniform_seed_batch(n, bs - 700 * b, 400 + b).cuda() for b in range(count - 1)]
+        seeds.append(seeds[0][:1].contiguous())
+        call.sample([9 + b for b in range(count)], seeds)
+        call.wait()
+        for b in range(count):
+            ref = oracle.sample_blocks(ip.numpy(), ix.numpy(), cache[1], csize, 9 + b, seeds[b].cpu().numpy(),
+                                       [15, fanout], [U, policy])
+            compare_blocks([bufs[b].views(j) for j in range(2)], ref)
+    finally:
+        for f in ctxs[1:]:
+            B.gns_destroy(f)
+        gns.close()
+
+
 @pytest.mark.parametrize("offsets", [torch.int32, torch.int64])
 @pytest.mark.parametrize("n", [26_623, 26_625, 53_249, 130_000])
 def test_walk_hot_nodes_in_lds(n, offsets):
