@@ -88,20 +88,21 @@ __device__ __forceinline__ int32_t mark_if_new(const SampleArgs& a, uint32_t u)
 //   draw   one row per lane: extent, chunk records, Floyd's draw for the whole row (the loops over the slots are
 //          unrolled, the chosen ranks stay in registers and are sorted there: an entry's slot is then its place in the row);
 //          the Philox blocks of the W rows are spread over all lanes;
-//   fetch  one drawn entry per lane: the W * k (row, slot) pairs are dealt to the lanes, kFetch at a time with
-//          their reads in flight together: entry -> node table and 1/p^C -> mark, scratch.
+//   fetch  one drawn entry per lane: the W * k (row, slot) pairs are dealt to the lanes in turns of 64, the list's
+//          entry -> node table and 1/p^C -> mark, scratch.
 // The stages have opposite needs.  The draw is instruction-bound (a Philox block is forty quarter-rate multiplies), and
 // with a slot per lane every lane of a row repeats it; the fetch is a chain of scattered reads, and with a row per lane
 // half of the slots a lane holds sit in branches that wait for one another.
 // The sort (38 instructions a row of 8 slots) takes the place of a count, per entry, of the row's smaller ranks: that read
-// the row's slots from LDS for every entry and held 103 registers, four waves per SIMD where 60 let eight run, and entries
-// in ascending order share the lines of list and scratch.  Groups of four on the graph of 1 M nodes, three layers (entering
-// the seeds included): 9.9 / 25 / 36.6 us, with the count (and up to 64 rows per wave) 9.9 / 27 / 41.5, where a lane group
-// per row on the upper and a row per lane on the input layer took 15.7 / 28 / 55; on 40 M nodes 10 / 23 / 57 for 10 / 24 / 60.
+// the row's slots from LDS for every entry and held 103 registers, four waves per SIMD where 36 let seven or eight run, and
+// entries in ascending order share the lines of list and scratch.  With that many waves a lane has one entry on its way at a
+// time: five, which few waves needed, are turns that small layers have no entries for (upper layers cache first: 21 us for
+// 23.5; input layer on 40 M nodes 55 for 57.5).  Groups of four on the graph of 1 M nodes, three layers (entering
+// the seeds included): 9.3 / 25.4 / 36.8 us, with the count (and up to 64 rows per wave) 9.9 / 27 / 41.5, where a lane group
+// per row on the upper and a row per lane on the input layer took 15.7 / 28 / 55; on 40 M nodes 9.5 / 22 / 55 for 10 / 24 / 60.
 // The input layer is bound by the lines its records and drawn entries pull in (1.3 M L2 misses).
 // kFirst: also the batch's first kernel.  No sampled node has a local id yet as far as that launch can know, so every one
 // is marked, and the union step takes the seeds out again (seed bitmap).
-constexpr int kFetch = 5;                        // 2 and 3: the same within 2 %
 constexpr int kWaveRows = 32;                    // at most, see wave_rows
 
 template <int K>
@@ -228,52 +229,29 @@ __device__ __forceinline__ void sample_wave_rows(const LayerArgs& g, const Begin
     // ---- fetch
     const int items = W * k;
     const uint32_t inv_k = 65535u / (uint32_t) k + 1u;          // j / k = j * inv_k >> 16, exact for j < 4096
-    for (int j0 = 0; j0 < items; j0 += kWave * kFetch) {
-        int r[kFetch];
-        bool mine[kFetch], is_fill[kFetch];
-        int64_t place[kFetch];
-#pragma unroll
-        for (int i = 0; i < kFetch; ++i) {
-            const int j = j0 + i * kWave + lane;
-            const int q = j < items ? j : 0;
-            r[i] = (int) ((uint32_t) q * inv_k >> 16);
-            const int s = q - r[i] * k;
-            const int counts = w.count[r[i]];
-            mine[i] = j < items && s < counts >> 8;
-            is_fill[i] = kList == kListCachedFirst && s >= (counts & 255);
-            const uint32_t rank = w.slot[r[i]][s];
-            place[i] = 0;
-            if (kList == kListRow) {
-                if (mine[i]) place[i] = w.start[r[i]] + (int64_t) rank;
-            } else if (mine[i]) {
-                place[i] = (int64_t) (w.first[r[i]] + rank);
-                if (is_fill[i]) {
-                    place[i] = uncached_entry(a, RowExtent{w.start[r[i]], w.end[r[i]]}, rank & 0x7FFFFFFFu);
-                } else if (rank >= w.here[r[i]]) {              // rare: the row crosses a tile
-                    place[i] = later_tile(a, CachedList{w.first[r[i]], w.here[r[i]], 0u, w.tile[r[i]]}, rank);
-                }
-            }
-        }
-        uint32_t u[kFetch], e[kFetch];
-        float inv_pc[kFetch];
-#pragma unroll
-        for (int i = 0; i < kFetch; ++i) u[i] = (uint32_t) (kList == kListRow || is_fill[i] ? a.indices : a.s_nodes)[place[i]];
-#pragma unroll
-        for (int i = 0; i < kFetch; ++i) {
-            if (!mine[i]) u[i] = 0u;
-            e[i] = kFirst ? 0u : a.tab.entry[u[i]];
-            inv_pc[i] = kList == kListRow ? 1.0f : a.node_inv_pc[u[i]];
-        }
-#pragma unroll
-        for (int i = 0; i < kFetch; ++i) {
-            if (!mine[i]) continue;
-            int32_t out = (int32_t) u[i];
-            if (!kFirst && a.tab.current(e[i])) out = -1 - (int32_t) a.tab.local(e[i]);
-            else mark_node(a, u[i]);
-            const int64_t at = (int64_t) row0 * k + (j0 + i * kWave + lane);
-            a.s_nbr[at] = out;
-            if (kList != kListRow) a.s_w[at] = is_fill[i] ? w.fill_w[r[i]] : inv_pc[i] * w.scale[r[i]];
-        }
+    for (int j0 = 0; j0 < items; j0 += kWave) {
+        const int j = j0 + lane;
+        const int q = j < items ? j : 0;
+        const int r = (int) ((uint32_t) q * inv_k >> 16);
+        const int s = q - r * k;
+        const int counts = w.count[r];
+        if (j >= items || s >= counts >> 8) continue;
+        const uint32_t rank = w.slot[r][s];
+        const bool is_fill = kList == kListCachedFirst && s >= (counts & 255);
+        int64_t place;
+        if (kList == kListRow)         place = w.start[r] + (int64_t) rank;
+        else if (is_fill)              place = uncached_entry(a, RowExtent{w.start[r], w.end[r]}, rank & 0x7FFFFFFFu);
+        else if (rank >= w.here[r])    place = later_tile(a, CachedList{w.first[r], w.here[r], 0u, w.tile[r]}, rank);      // rare: the row crosses a tile
+        else                           place = (int64_t) (w.first[r] + rank);
+        const uint32_t u = (uint32_t) (kList == kListRow || is_fill ? a.indices : a.s_nodes)[place];
+        const uint32_t e = kFirst ? 0u : a.tab.entry[u];
+        const float inv_pc = kList == kListRow ? 1.0f : a.node_inv_pc[u];
+        int32_t out = (int32_t) u;
+        if (!kFirst && a.tab.current(e)) out = -1 - (int32_t) a.tab.local(e);
+        else mark_node(a, u);
+        const int64_t at = (int64_t) row0 * k + j;
+        a.s_nbr[at] = out;
+        if (kList != kListRow) a.s_w[at] = is_fill ? w.fill_w[r] : inv_pc * w.scale[r];
     }
     __builtin_amdgcn_wave_barrier();
 }
