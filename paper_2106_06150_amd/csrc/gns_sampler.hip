@@ -464,7 +464,7 @@ __global__ void __launch_bounds__(kBlock) k_plan(LayerArgs g, int relabel_blocks
 constexpr int kFlagUnroll = 32;     // chunks a wave keeps in flight
 constexpr int kFlagBatch = 64;      // work-list entries a wave fetches at once (one per lane)
 
-// Membership words of kFlagUnroll chunks, chunk ids in lanes sub .. sub+kFlagUnroll-1 of my_chunk
+// Membership words of kUnroll chunks, chunk ids in lanes sub .. sub+kUnroll-1 of my_chunk
 // (every one a valid chunk id).  Lane l tests entry l of each chunk; the ballot of chunk sub+i
 // lands in lane sub+i of (*lo, *hi).  Three passes over the unrolled set -- all index loads, all
 // bitmap reads, all tests -- so that the loads of the whole set are in flight together.
@@ -473,7 +473,7 @@ constexpr int kFlagBatch = 64;      // work-list entries a wave fetches at once 
 //   kMode 0: the bitmap is read from global memory; 1: from LDS; 2: LDS holds the cache filter, and only the entries it
 //   leaves open go on to read the exact bitmap; 3: a coarse bitmap (one bit per group of ids) in global memory, small
 //   enough to stay in every XCD's L2, does so for those whose group has no cached node.
-template <int kMode, bool kCareful>
+template <int kMode, int kUnroll, bool kCareful>
 __device__ __forceinline__ void flag_chunk_set(const SampleArgs& a, const uint32_t* lds32, int32_t my_chunk, int sub,
                                                int lane, uint32_t* lo, uint32_t* hi)
 {
@@ -481,54 +481,56 @@ __device__ __forceinline__ void flag_chunk_set(const SampleArgs& a, const uint32
     const int last_lanes = (int) (a.num_entries - (last_chunk << 6));          // 1..64 entries in the last chunk
     const int lane_clamped = lane < last_lanes ? lane : last_lanes - 1;
     const uint64_t last_mask = last_lanes == 64 ? ~0ull : ((1ull << last_lanes) - 1ull);
-    uint32_t u[kFlagUnroll];
+    uint32_t u[kUnroll];
 #pragma unroll
-    for (int i = 0; i < kFlagUnroll; ++i) {
+    for (int i = 0; i < kUnroll; ++i) {
         const int32_t g = __builtin_amdgcn_readlane(my_chunk, sub + i);
         const int32_t* row = a.indices + ((int64_t) g << 6);                   // wave-uniform base
         const int off = (kCareful && g == last_chunk) ? lane_clamped : lane;
         u[i] = (uint32_t) row[off];
     }
     const uint32_t* exact32 = reinterpret_cast<const uint32_t*>(a.cache_bitmap);
-    uint32_t w[kFlagUnroll];
+    uint32_t w[kUnroll];
 #pragma unroll
-    for (int i = 0; kMode != 2 && i < kFlagUnroll; ++i) {
+    for (int i = 0; kMode != 2 && i < kUnroll; ++i) {
         if (kMode == 1)      w[i] = lds32[u[i] >> 5];
         else if (kMode == 0) w[i] = exact32[u[i] >> 5];
         else                 w[i] = reinterpret_cast<const uint32_t*>(a.coarse_bitmap)[(u[i] >> a.coarse_shift) >> 5];
     }
     if (kMode == 2) {
 #pragma unroll
-        for (int i = 0; i < kFlagUnroll; i += 8) filter_test<8>(lds32, a.filter.mult, u + i, w + i);
+        for (int i = 0; i < kUnroll; i += 8) filter_test<8>(lds32, a.filter.mult, u + i, w + i);
 #pragma unroll
-        for (int i = 0; i < kFlagUnroll; ++i)
+        for (int i = 0; i < kUnroll; ++i)
             if (w[i] == 1u) w[i] = exact32[u[i] >> 5];
     }
     if (kMode == 3) {
 #pragma unroll
-        for (int i = 0; i < kFlagUnroll; ++i) {
+        for (int i = 0; i < kUnroll; ++i) {
             const bool maybe = (w[i] >> ((u[i] >> a.coarse_shift) & 31u)) & 1u;
             w[i] = maybe ? exact32[u[i] >> 5] : 0u;
         }
     }
 #pragma unroll
-    for (int i = 0; i < kFlagUnroll; ++i) {
+    for (int i = 0; i < kUnroll; ++i) {
         uint64_t ballot = __ballot((w[i] >> (u[i] & 31u)) & 1u);
         if (kCareful && __builtin_amdgcn_readlane(my_chunk, sub + i) == last_chunk) ballot &= last_mask;
         if (lane == sub + i) { *lo = (uint32_t) ballot; *hi = (uint32_t) (ballot >> 32); }
     }
 }
 
-// One work list: every wave takes an equal, contiguous share of its Q chunks.
-template <int kMode>
+// One work list: every wave takes an equal, contiguous share of its Q chunks, in sets of kUnroll.
+template <int kMode, int kUnroll>
 __device__ __forceinline__ void flag_work_list(const SampleArgs& a, const uint32_t* lds32, int64_t Q)
 {
     if (Q <= 0 || a.num_entries <= 0) return;
     const int waves_per_block = (int) (blockDim.x >> 6);
-    const int64_t wave_global = (int64_t) blockIdx.x * waves_per_block +
-                                __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
+    const int wave = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
+    // a list of fewer sets than there are waves is spread over the blocks
+    const int64_t wave_global = kUnroll < kFlagUnroll ? (int64_t) wave * gridDim.x + blockIdx.x : (int64_t) blockIdx.x * waves_per_block + wave;
     const int64_t num_waves = (int64_t) gridDim.x * waves_per_block;
-    const int64_t share = (Q + num_waves - 1) / num_waves;
+    int64_t share = (Q + num_waves - 1) / num_waves;
+    if (kUnroll < kFlagUnroll && share < kUnroll) share = kUnroll;
     const int64_t begin = wave_global * share;
     const int64_t end = (begin + share < Q) ? begin + share : Q;
     const int64_t last_chunk = (a.num_entries - 1) >> 6;
@@ -542,9 +544,9 @@ __device__ __forceinline__ void flag_work_list(const SampleArgs& a, const uint32
         const int32_t my_chunk = a.plan_desc[q];
         const bool careful = last_is_partial && __ballot((int64_t) my_chunk == last_chunk) != 0ull;
         uint32_t lo = 0, hi = 0;
-        for (int sub = 0; sub < here; sub += kFlagUnroll) {                            // scalar bounds
-            if (careful) flag_chunk_set<kMode, true>(a, lds32, my_chunk, sub, lane, &lo, &hi);
-            else         flag_chunk_set<kMode, false>(a, lds32, my_chunk, sub, lane, &lo, &hi);
+        for (int sub = 0; sub < here; sub += kUnroll) {                                // scalar bounds
+            if (careful) flag_chunk_set<kMode, kUnroll, true>(a, lds32, my_chunk, sub, lane, &lo, &hi);
+            else         flag_chunk_set<kMode, kUnroll, false>(a, lds32, my_chunk, sub, lane, &lo, &hi);
         }
         if (lane < here) a.flags[my_chunk] = ((uint64_t) hi << 32) | lo;
     }
@@ -552,13 +554,28 @@ __device__ __forceinline__ void flag_work_list(const SampleArgs& a, const uint32
 
 // kMode 1 / 2: the cache bitmap / the cache filter is first copied into dynamic LDS (rounded up to
 // 16 bytes).  The work lists of the group's `count` mini-batches are taken one after the other (they read
-// the same cache, so the bitmap is staged once).
+// the same cache, so the bitmap is staged once).  Short lists ask the exact
+// bitmap in global memory instead, in small sets: staging takes 4 us (1 M nodes) to 10 us (the filter) whatever the list's
+// length.  One seed, fan-outs 15, 10 on 0.1 to 20 M nodes: 8 to 13 us staged, 4.2 direct; at four chunks per wave 8.7 and 6.1
+// (1 M nodes), at six 15 and 8 (2 M) to 10.6 (20 M).  The direct pass grows by 64 requests a chunk at the L2s' rate, so the lines
+// lie at five and eight.
+constexpr int kFlagShortUnroll = 4;
+
 template <int kMode>
 __global__ void k_flag_chunks(LayerArgs g, int count)
 {
     extern __shared__ uint4 lds_bitmap16[];
     SampleArgs a = bind_sample(g, 0);
     if (kMode == 1 || kMode == 2) {
+        int64_t all = 0;
+        for (int b = 0; b < count; ++b) all += bind_state(g, b)->plan_chunks;
+        if (all <= (int64_t) (kMode == 1 ? 5 : 8) * gridDim.x * (blockDim.x >> 6)) {
+            for (int b = 0; b < count; ++b) {
+                if (b > 0) a = bind_sample(g, b);
+                flag_work_list<0, kFlagShortUnroll>(a, nullptr, (int64_t) a.st->plan_chunks);
+            }
+            return;
+        }
         if (kMode == 1) stage_lds(lds_bitmap16, reinterpret_cast<const uint4*>(a.cache_bitmap), (int32_t) ((a.bitmap_words + 1) / 2));
         else            stage_filter(lds_bitmap16, a.filter);
         __syncthreads();
@@ -566,7 +583,7 @@ __global__ void k_flag_chunks(LayerArgs g, int count)
     const uint32_t* lds32 = reinterpret_cast<const uint32_t*>(lds_bitmap16);
     for (int b = 0; b < count; ++b) {
         if (b > 0) a = bind_sample(g, b);
-        flag_work_list<kMode>(a, lds32, (int64_t) a.st->plan_chunks);
+        flag_work_list<kMode, kFlagUnroll>(a, lds32, (int64_t) a.st->plan_chunks);
     }
 }
 

@@ -1602,6 +1602,32 @@ def test_cache_filter_of_graphs_whose_bitmap_does_not_fit_lds(n, flag_mode):
         gns.close()
 
 
+@pytest.mark.parametrize("n,avg", [(60_000, 40), (1_400_000, 6)])
+def test_short_and_long_lists_of_chunks_to_flag(n, avg):
+    """Lists of up to five (the bitmap fits LDS) and eight chunks (it does not) for each of 4096 waves are tested against the
+    bitmap in global memory, longer ones against what is staged in LDS: a row, lists on both sides of the lines, and a
+    group whose lists are short each and long together."""
+    ip, ix = random_symmetric_csr(n, avg, np.random.default_rng(n))
+    ip, ix = torch.from_numpy(ip), torch.from_numpy(ix)
+    fanouts, policies, csize, bs = (10, 5), (U, C), n // 50, 3600
+    gns = GpuGns(ip, ix, None, fanouts=fanouts, policies=policies, cache_size=csize, max_seeds=bs, flag_mode=0)
+    ctxs, keep, bufs, call = _group_setup(gns, 3)
+    try:
+        for trial, count in enumerate((1, 700, bs)):
+            full_parity(gns, cache_seed=49, epoch=0, batch_seed=60 + trial, seeds=synth.uniform_seed_batch(n, count, 500 + trial))
+        cache = oracle.sample_cache(ip.numpy(), 49, 0, csize)
+        seeds = [synth.uniform_seed_batch(n, 1300 - b, 510 + b).cuda() for b in range(3)]
+        call.sample([70 + b for b in range(3)], seeds)
+        call.wait()
+        for b in range(3):
+            ref = oracle.sample_blocks(ip.numpy(), ix.numpy(), cache[1], csize, 70 + b, seeds[b].cpu().numpy(), list(fanouts), list(policies))
+            compare_blocks([bufs[b].views(j) for j in range(2)], ref)
+    finally:
+        for f in ctxs[1:]:
+            B.gns_destroy(f)
+        gns.close()
+
+
 @pytest.mark.parametrize("count,seeds", [(1, 1), (2, 9), (2, 10), (1, 38), (1, 39), (16, 3), (5, 17)])
 @pytest.mark.parametrize("fanouts,policies,wmode", [((10, 5), (U, C), 0), ((16, 1), (CF, CF), 1), ((3, 3, 3), (C, U, C), 0), ((5, 7), (U, U), 0),
                                                     ((2, 2, 2, 2), (CF, U, CF, C), 1)])
