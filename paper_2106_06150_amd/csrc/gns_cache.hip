@@ -12,11 +12,11 @@
 // is cut at exactly that draw.
 //
 // On graphs of a million nodes a draw is a chain of small launches, so there are few: clear, then two per chunk (draw,
-// commit), then the index with the 1/p^C table; and the host looks at the outcome behind the first chunk or two and all of it,
-// once for most caches, then behind two more at a time.  What follows an incomplete cache stands down on the device: half of 1 M
+// commit), then the index with the 1/p^C table and on large graphs the filter's groups; and the host looks at the outcome behind
+// the first chunk or two and all of it, once for most caches, then behind two more at a time.  What follows an incomplete cache stands down on the device: half of 1 M
 // nodes take 358 us, 16 M of 40 M nodes 11.0 ms.
-// A draw of 10 K of 1 M nodes with the mini-batch behind it: 247 us, where a launch per phase, a read-back per chunk of 64 K
-// draws and searches over all offsets took 295; 400 K of 40 M nodes: 1779 us, before 1992.
+// A draw of 10 K of 1 M nodes with the mini-batch behind it: 228 us, where a launch per phase, a read-back per chunk of 64 K
+// draws and searches over all offsets took 50 us more; 400 K of 40 M nodes: 1420 us.
 #include "gns_internal.h"
 #include "gns_device.hpp"
 #include <string.h>
@@ -335,11 +335,16 @@ __device__ __forceinline__ int64_t group_begin(uint32_t g, uint32_t mult)
     return (int64_t) q;
 }
 
-// The groups of the cache filter and, where there is a list of them, their first two nodes.  One lane per group.
+// The groups of the cache filter, the tags of its hot nodes, and, where there is a list of them, the groups' first two nodes.
+// One lane per group.  (With the tags made from the keys by every block that stages the filter, that took 1.2 us longer.)
 __global__ void __launch_bounds__(kBlock) k_cache_groups(const int32_t* done, const uint64_t* bitmap, int64_t n, CacheFilter f)
 {
     if (done && *done < 0) return;
     const uint32_t g = blockIdx.x * kBlock + threadIdx.x;      // the grid is exact
+    if (g < kFilterHot) {
+        const unsigned long long key = f.keys[g];
+        f.tags[g] = key ? (uint16_t) ((uint32_t) key / kFilterHot + 1u) : (uint16_t) 0;
+    }
     const int64_t lo = group_begin(g, f.mult), next = group_begin(g + 1u, f.mult), hi = next < n ? next : n;
     uint32_t found = 0, pair = 0;
     for (int64_t w = lo >> 6; w << 6 < hi; ++w) {

@@ -42,11 +42,12 @@ constexpr int32_t kFilterGroups = (int32_t) (kLdsBitmapBytes - 2 * kFilterHot) *
 struct CacheFilter {
     unsigned long long* keys;     // [kFilterHot] (row length, id) of slot (id % kFilterHot)'s node, 0: none
     uint32_t* groups;             // [kFilterGroups / 32] behind them
+    uint16_t* tags;               // [kFilterHot] behind them: what stands in LDS for the keys
     uint16_t* pairs;              // [kFilterGroups] behind them, or null; of groups without a cached node stale
     uint32_t mult;                // group of an id: the upper half of id * mult
 };
 constexpr uint32_t kPairBits = 7, kPairMask = (1u << kPairBits) - 1u, kPairMore = 1u << 14, kPairSet = 1u << 15;
-constexpr size_t kFilterBytes = (size_t) kFilterHot * 8 + kFilterGroups / 8 + (size_t) kFilterGroups * 2;
+constexpr size_t kFilterBytes = (size_t) kFilterHot * (8 + 2) + kFilterGroups / 8 + (size_t) kFilterGroups * 2;
 // The pass over the entries with the list and without: 40 M nodes (a bitmap of 5 MB) 1020 and 1188 us, 28 M 705 and 749,
 // 20 M 813 and 843, 12 M 378 and 358.
 constexpr int64_t kFilterPairsNodes = (int64_t) 16 << 20;
@@ -232,11 +233,12 @@ static inline T* cache_ptr(const gns_ctx* c, size_t off, int gen)
 // The cache filter in the given generation (null pointers: none).
 static inline CacheFilter cache_filter(const gns_ctx* c, int gen)
 {
-    CacheFilter f = {nullptr, nullptr, nullptr, c->lay.filter_mult};
+    CacheFilter f = {nullptr, nullptr, nullptr, nullptr, c->lay.filter_mult};
     if (c->lay.filter) {
         f.keys = cache_ptr<unsigned long long>(c, c->lay.filter, gen);
         f.groups = reinterpret_cast<uint32_t*>(f.keys + kFilterHot);
-        if (c->graph.num_nodes > kFilterPairsNodes) f.pairs = reinterpret_cast<uint16_t*>(f.groups + kFilterGroups / 32);
+        f.tags = reinterpret_cast<uint16_t*>(f.groups + kFilterGroups / 32);
+        if (c->graph.num_nodes > kFilterPairsNodes) f.pairs = f.tags + kFilterHot;
     }
     return f;
 }

@@ -36,16 +36,10 @@ struct NodeTable {
     __device__ __forceinline__ uint32_t local(uint32_t e) const { return e & ((1u << shift) - 1u); }
 };
 
-// The cache filter in LDS: groups, then tags.
+// The cache filter in LDS: groups, then tags, as they stand in memory.
 __device__ __forceinline__ void stage_filter(uint4* lds, const CacheFilter& f)
 {
-    stage_lds(lds, reinterpret_cast<const uint4*>(f.groups), kFilterGroups / 128);
-    uint16_t* tags = reinterpret_cast<uint16_t*>(lds + kFilterGroups / 128);
-#pragma unroll 4
-    for (int32_t i = (int32_t) threadIdx.x; i < kFilterHot; i += (int32_t) blockDim.x) {
-        const unsigned long long key = f.keys[i];
-        tags[i] = key ? (uint16_t) ((uint32_t) key / kFilterHot + 1u) : (uint16_t) 0;
-    }
+    stage_lds(lds, reinterpret_cast<const uint4*>(f.groups), kFilterGroups / 128 + kFilterHot / 8);
 }
 
 // What it says of nodes u[0 .. N): ~0 cached, 0 not, 1: to be looked up.  All reads first: left to itself the compiler puts the
