@@ -49,7 +49,8 @@
  *      GNS_MARK_SUMMARY_MIN_WORDS=<n>  bitmaps of at least n words keep a
  *        summary (one bit per word; default 65536)
  *      GNS_COARSE_SHIFT=<1..6>  ids per bit (as a power of two) of the coarse
- *        cache bitmap of graphs whose bitmap does not fit LDS
+ *        cache bitmap of graphs too large for the cache filter in LDS (more
+ *        than 83 M nodes)
  *      GNS_NO_COARSE_L2=1  flag pass of such graphs without the coarse bitmap
  *      GNS_FLAG_BLOCKS_PER_CU=<n>  grid of that flag pass (default 2)
  *      GNS_UNION_SPINS=<n>  how often a block of the union step polls for another
