@@ -156,6 +156,23 @@ __global__ void __launch_bounds__(kThreads) k_sample_small(SmallArgs g)
         }
         __syncthreads();
     }
+    auto publish_state = [&](uint32_t bad_seed) {                // one thread: what later calls read of this batch
+        q.st->key0 = q.key0;
+        q.st->key1 = q.key1;
+        q.st->stamp = q.stamp;
+        q.st->batch_id = q.batch_id;
+        q.st->cache_gen = q.cache_gen;
+        if (bad_seed) q.st->bad_seed = bad_seed;
+        q.host->bad_seed = bad_seed ? bad_seed : q.st->bad_seed;
+    };
+    // Repeated and invalid seeds are rows beside the graph's nodes, for which neither the arrays here nor the block buffers
+    // have room: such a batch ends empty.
+    if (w.bad) {
+        if (tid <= g.num_layers) q.st->num_dst[tid] = q.host->num_dst[tid] = 0;
+        if (tid < g.num_layers) q.st->num_edges[tid] = q.host->num_edges[tid] = 0;
+        if (tid == 0) publish_state(q.batch_id);
+        return;
+    }
     for (int layer = 0; layer < g.num_layers; ++layer) {
         const BlockPtrs out = g.blk[(int) blockIdx.x * g.num_layers + layer];
         const int k = g.fanout[layer], k4 = (k + 3) & ~3, blocks = k4 >> 2;
@@ -389,17 +406,12 @@ __global__ void __launch_bounds__(kThreads) k_sample_small(SmallArgs g)
     }
     if (tid == 0) {
         q.st->num_dst[g.num_layers] = q.host->num_dst[g.num_layers] = R;
-        q.st->key0 = q.key0;
-        q.st->key1 = q.key1;
-        q.st->stamp = q.stamp;
-        q.st->batch_id = q.batch_id;
-        q.st->cache_gen = q.cache_gen;
-        if (w.bad) q.st->bad_seed = q.batch_id;
-        q.host->bad_seed = w.bad ? q.batch_id : q.st->bad_seed;
+        publish_state(0);
     }
 }
 
-// Whether the worst case of the group's seeds fits blocks of kThreads threads.
+// Whether the worst case of the group's seeds fits blocks of kThreads threads.  That of distinct seeds, whose batch has no more
+// nodes than the graph; of others the kernel enters the seeds only.
 template <int kThreads>
 static bool small_fits(const Group& g, const BeginDyn& d)
 {

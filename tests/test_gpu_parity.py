@@ -1673,3 +1673,52 @@ def test_small_batches_in_one_launch(count, seeds, fanouts, policies, wmode):
         for f in ctxs[1:]:
             B.gns_destroy(f)
         gns.close()
+
+
+def _guarded_blocks(gns):
+    """Block buffers with sentinel words behind every array, and a check that they are untouched."""
+    bufs, guards = B.BlockBuffers(gns.graph, gns.config, gns.device), []
+    for b, t in zip(bufs.array, bufs.tensors):
+        for name in ("indptr", "indices", "src_nodes", "row_eligible", "weights"):
+            big = torch.full((t[name].numel() + 4096,), 77, dtype=t[name].dtype, device=gns.device)
+            guards.append(big[t[name].numel():])
+            t[name] = big[:t[name].numel()]
+            setattr(b, name, big.data_ptr())
+    return bufs, lambda: all(bool((g == 77).all()) for g in guards)
+
+
+def _many_bad_seeds(n, count):
+    """Seed lists whose rows do not fit beside the nodes they lead to: repeats, ids out of range, or both."""
+    ids = torch.arange(count, dtype=torch.int32)
+    return {"twice": ids // 2 % n, "one": torch.zeros_like(ids), "outside": ids + n, "negative": -1 - ids, "mixed": torch.where(ids % 3 == 0, ids + n, ids % n)}
+
+
+@pytest.mark.parametrize("n,count,fanouts,policies", [(100, 1000, (4, 16), (U, U)), (1000, 1000, (4, 4), (U, C)), (1000, 1000, (4, 4), (CF, CF)),
+                                                      (100, 500, (8, 2, 1), (U, CF, C)), (64, 200, (1, 16), (C, U))])
+def test_small_batches_of_many_bad_seeds(n, count, fanouts, policies):
+    """Repeated and invalid seeds in a mini-batch that a block of its own samples, more of them than the graph leaves room for:
+    reported, nothing written past a buffer, no rows left for the calls behind, and the next mini-batch is right."""
+    ip, ix = _small(n=n, avg=12, seed=71)
+    csize = n // 4 if any(p != U for p in policies) else 0
+    gns = GpuGns(ip, ix, _feat(n, 8), fanouts=fanouts, policies=policies, cache_size=csize, max_seeds=count, flag_mode=1)
+    last = len(fanouts) - 1
+    try:
+        gns.blocks, untouched = _guarded_blocks(gns)
+        for seeds in _many_bad_seeds(n, count).values():
+            if csize:
+                B.gns_sample_cache(gns.ctx, 47, 0)
+            B.gns_sample_blocks_async(gns.ctx, 5, seeds.cuda(), gns.blocks.array)
+            x = torch.full((gns.blocks.array[last].cap_src, 8), 3.0, device=gns.device)
+            h = torch.full((gns.blocks.array[last].cap_dst, 8), 3.0, device=gns.device)
+            B.gns_gather_features(gns.ctx, gns.blocks.tensors[last]["src_nodes"], -1, x)
+            B.gns_aggregate(gns.ctx, gns.blocks.array[last], x, 8, h)
+            with pytest.raises(B.GnsError) as e:
+                B.gns_sample_blocks_wait(gns.ctx, gns.blocks.array)
+            assert e.value.status == B.GNS_EINVAL
+            assert untouched()
+            assert all(b.num_dst == b.num_src == b.num_edges == 0 for b in gns.blocks.array)
+            assert bool((x == 3.0).all()) and bool((h == 3.0).all())
+            full_parity(gns, cache_seed=47, epoch=0, batch_seed=6, seeds=torch.arange(0, n, 3, dtype=torch.int32))
+            assert untouched()
+    finally:
+        gns.close()
