@@ -63,7 +63,7 @@ hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s)
 __global__ void __launch_bounds__(kBlock) k_batch_begin(LayerArgs g, BeginDyn d)
 {
     const auto [b, block] = group_block<false>(g.dealt);
-    const int32_t num_seeds = d.num_seeds[b];
+    const int32_t num_seeds = seed_rows(g, d, b);
     const NodeTable tab = bind_table(g, b, d.stamp[b]);
     const int32_t q = block * kBlock + (int32_t) threadIdx.x;
     if (q == 0) begin_state(g, d, b);
@@ -157,8 +157,10 @@ __device__ __forceinline__ uint32_t count_tile(const FinishArgs& a, int32_t tile
 
 // The node of bit `bit` of bitmap word `word` joins the batch's list at place `pos`.  Nodes that join in the last layer are
 // no layer's rows: nothing reads their extents, and on a graph whose offsets fit no L2 the read of one is a trip to memory.
+// Behind repeated or invalid seeds the list can be longer than the graph has nodes; it is cut where its buffers end.
 __device__ __forceinline__ void emit_new_node(const FinishArgs& a, int32_t pos, int64_t word, int bit)
 {
+    if (pos >= a.max_src) return;
     const uint32_t node = (uint32_t) (word * 64 + bit);
     a.src_nodes[pos] = (int32_t) node;
     a.tab.entry[node] = a.tab.make((uint32_t) pos);
@@ -167,6 +169,12 @@ __device__ __forceinline__ void emit_new_node(const FinishArgs& a, int32_t pos, 
     ext.start = load_off_rt(a.g_indptr, a.g_i64, node);
     ext.end = load_off_rt(a.g_indptr, a.g_i64, (int64_t) node + 1);
     a.row_ext[pos] = ext;
+}
+
+// Nodes of the batch behind the layer: its rows and the new nodes, as many as the list takes.
+__device__ __forceinline__ void publish_nodes(const FinishArgs& a, int32_t nodes)
+{
+    a.st->num_dst[a.layer_index + 1] = nodes < a.max_src ? nodes : a.max_src;
 }
 
 // The bitmap side of the union step on graphs whose bitmap has a summary.  A tile has far more words than marks there, so
@@ -236,7 +244,7 @@ __device__ __forceinline__ void union_sparse_tile(const FinishArgs& a, int32_t t
     int32_t before = 0;
     if (total > 0 || last)
         before = sum_before(a.tile_sums, tag, tile, spins, smem, [&](int32_t t) { return count_tile(a, t); });
-    if (last && tid == 0) a.st->num_dst[a.layer_index + 1] = R + before + total;
+    if (last && tid == 0) publish_nodes(a, R + before + total);
     // the count is out: from here on the marks may go
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -347,7 +355,7 @@ __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
         const bool last = tile == a.mark_tiles - 1;
         int32_t before = 0;
         if (total > 0 || last) before = sum_before(a.tile_sums, tag, tile, spins, smem, [&](int32_t t) { return count_tile(a, t); });
-        if (last && threadIdx.x == 0) a.st->num_dst[a.layer_index + 1] = R + before + total;
+        if (last && threadIdx.x == 0) publish_nodes(a, R + before + total);
         // The count is out (its store is older than the reads that sum_before waited for, or than the barriers of the
         // scan below): from here on the marks may go.
         const int32_t widx = block_exclusive_scan(nz, smem, &total_nz);     // marked words before this thread's words
@@ -410,6 +418,7 @@ void fill_finish_template(const Group& g, int layer_index, FinishArgs* out)
     a.g_i64 = c->graph.indptr_is_i64;
     a.num_nodes = c->graph.num_nodes;
     a.last_layer = layer_index == c->config.num_layers - 1 ? 1 : 0;
+    a.max_src = (int32_t) L.rows[layer_index + 1];
 }
 
 int relabel_grid(const gns_ctx* c, int layer_index)

@@ -85,7 +85,8 @@ struct SampleArgs {
     // CACHE_ONLY: per-batch plan and the CSR-aligned membership flags
     int64_t num_entries;
     unsigned long long* plan_sums;   // [row tiles] (tag, chunks of the tile), see sum_before
-    int32_t* plan_desc;        // [chunks] ids of the aligned chunks to flag
+    int32_t* plan_desc;        // [max_chunks] ids of the aligned chunks to flag
+    uint32_t max_chunks;       // what the chunks of distinct rows come to at most
     uint64_t* flags;           // [ceil(nnz / 64)] bit e & 63 of word e >> 6: entry e points into the cache
     int64_t bitmap_words;
     CacheFilter filter;              // (flag kernel, mode 2)
@@ -129,6 +130,7 @@ struct FinishArgs {
     int g_i64;
     int64_t num_nodes;
     int32_t last_layer;            // its new nodes have no rows to be sampled
+    int32_t max_src;               // places of the layer's src list and of row_ext
 };
 
 // Byte offsets of the sections of a context's per-batch scratch (the same for every context of a family).
@@ -409,11 +411,19 @@ __device__ __forceinline__ bool is_hub_extent(int64_t start, int64_t end)
     return end > start && ((end - 1) >> 6) - (start >> 6) + 1 > kHubChunks;
 }
 
+// Rows of the first layer: the seeds, but no more than the buffers take (of more seeds than nodes some are bad).
+__device__ __forceinline__ int32_t seed_rows(const LayerArgs& g, const BeginDyn& d, int b)
+{
+    return (int64_t) d.num_seeds[b] < g.f.num_nodes ? d.num_seeds[b] : (int32_t) g.f.num_nodes;
+}
+
 // The batch's scalars, published for its later kernels; one thread of the batch's first kernel.
 __device__ __forceinline__ void begin_state(const LayerArgs& g, const BeginDyn& d, int b)
 {
     DeviceState* st = bind_state(g, b);
-    st->num_dst[0] = d.num_seeds[b];
+    const int32_t rows = seed_rows(g, d, b);
+    st->num_dst[0] = rows;
+    if (rows < d.num_seeds[b]) st->bad_seed = d.batch_id[b];
     for (int l = 0; l < GNS_MAX_LAYERS; ++l) { st->num_edges[l] = 0; st->num_dst[l + 1] = 0; st->hub_count[l] = 0; }
     st->key0 = d.key0[b];
     st->key1 = d.key1[b];

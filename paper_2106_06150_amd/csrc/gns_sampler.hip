@@ -296,7 +296,7 @@ __global__ void __launch_bounds__(kBlock) k_sample_first(LayerArgs g, BeginDyn d
     __shared__ int32_t smem[kBlock / kWave + 1];
     __shared__ WaveRows<K> rows[kBlock / kWave];
     const auto [b, block] = group_block<kOne>(g.dealt);
-    const int32_t R = d.num_seeds[b];
+    const int32_t R = seed_rows(g, d, b);
     if (block == 0 && threadIdx.x == 0) begin_state(g, d, b);
     if ((int64_t) block * (kBlock / kWave) * W >= R) return;
     const SampleArgs a = bind_sample(g, b, d.stamp[b], d.cache_gen[b]);
@@ -443,13 +443,19 @@ __global__ void __launch_bounds__(kBlock) k_plan(LayerArgs g, int relabel_blocks
             n += (uint32_t) chunks_touched(a.row_ext[q].start, a.row_ext[q].end);
         return n;
     });
-    if (tile == (R - 1) / kPlanTile && threadIdx.x == 0) a.st->plan_chunks = before + total;
+    // Rows of repeated seeds can have more chunks together than there is room for, or than 32 bits count; what such a batch
+    // samples is of no matter, but its list has to end in bounds and hold chunks of the graph.
+    if (tile == (R - 1) / kPlanTile && threadIdx.x == 0) {
+        const uint32_t chunks = (uint32_t) before + (uint32_t) total;
+        a.st->plan_chunks = (int32_t) (chunks < a.max_chunks ? chunks : a.max_chunks);
+    }
     __syncthreads();
     if (hub) {
         int32_t place = s_first_hub + __popcll(hubs & ((1ull << lane_id()) - 1ull));
         for (int w = 0; w < (int) (threadIdx.x >> 6); ++w) place += s_hubs[w];
         a.hub_rows[place] = r;
     }
+    const uint32_t last_chunk = (uint32_t) ((a.num_entries - 1) >> 6);
     // one thread per work-list entry: its row is the last one whose offset is <= j
     for (int32_t j = (int32_t) threadIdx.x; j < total; j += kBlock) {
         int32_t lo = 0, hi = kPlanTile;
@@ -457,7 +463,8 @@ __global__ void __launch_bounds__(kBlock) k_plan(LayerArgs g, int relabel_blocks
             const int32_t mid = (lo + hi) >> 1;
             if (s_off[mid] <= j) lo = mid; else hi = mid;
         }
-        a.plan_desc[before + j] = s_g0[lo] + (j - s_off[lo]);
+        const uint32_t place = (uint32_t) before + (uint32_t) j, chunk = (uint32_t) s_g0[lo] + (uint32_t) (j - s_off[lo]);
+        if (place < a.max_chunks) a.plan_desc[place] = (int32_t) (chunk < last_chunk ? chunk : last_chunk);
     }
 }
 
@@ -835,6 +842,7 @@ void fill_sample_template(gns_ctx* c, int layer_index, SampleArgs* out)
     a.node_inv_pc = c->uses_cache ? cache_ptr<float>(c, L.node_pc, gen) : nullptr;
     a.cache_bitmap = cache_ptr<uint64_t>(c, L.cache_bitmap, gen);
     a.num_entries = c->graph.num_entries;
+    a.max_chunks = (uint32_t) L.max_chunks;
     a.flags = c->uses_cache && c->config.flag_mode == GNS_FLAGS_PER_BATCH ? cache_ptr<uint64_t>(c, L.edge_flags, gen) : nullptr;
     a.bitmap_words = L.words;
     a.filter = cache_filter(c, gen);

@@ -1722,3 +1722,40 @@ def test_small_batches_of_many_bad_seeds(n, count, fanouts, policies):
             assert untouched()
     finally:
         gns.close()
+
+
+@pytest.mark.parametrize("graph", ["small", "star"])
+@pytest.mark.parametrize("fanouts,policies,flag_mode", [((15, 10), (U, C), 1), ((18, 3), (CF, C), 1), ((6, 4), (U, C), 0), ((9, 3), (C, CF), 0),
+                                                        ((4, 4, 4), (U, U, U), 0)])
+def test_many_bad_seeds(graph, fanouts, policies, flag_mode, monkeypatch):
+    """As above for the sequences of launches, replayed ones and gns_sample_blocks_static among them: more seeds than nodes, nodes
+    behind repeated seeds beyond the end of the list, and a hub's chunks a few thousand times over."""
+    n, count = 900, 2600
+    ip, ix = _small(n=n, avg=10, seed=73) if graph == "small" else _star_graph(n, 800, 4, 5)
+    csize = 60 if any(p != U for p in policies) else 0
+    monkeypatch.setenv("GNS_MARK_SUMMARY_MIN_WORDS", "1" if graph == "star" else "65536")
+    gns = GpuGns(ip, ix, _feat(n, 8), fanouts=fanouts, policies=policies, cache_size=csize, max_seeds=count, flag_mode=flag_mode)
+    last = len(fanouts) - 1
+    try:
+        gns.blocks, untouched = _guarded_blocks(gns)
+        if csize:
+            B.gns_sample_cache(gns.ctx, 48, 0)
+        hub = int((ip[1:] - ip[:-1]).argmax())
+        for ids in list(_many_bad_seeds(n, count).values()) + [torch.full((count,), hub, dtype=torch.int32), torch.arange(1700, dtype=torch.int32) % 850]:
+            seeds = ids.cuda()
+            B.gns_sample_blocks_async(gns.ctx, 5, seeds, gns.blocks.array)
+            x = torch.empty((gns.blocks.array[last].cap_src, 8), device=gns.device)
+            h = torch.empty((gns.blocks.array[last].cap_dst, 8), device=gns.device)
+            B.gns_gather_features(gns.ctx, gns.blocks.tensors[last]["src_nodes"], -1, x)
+            B.gns_aggregate(gns.ctx, gns.blocks.array[last], x, 8, h)
+            for wait in (lambda: B.gns_sample_blocks_wait(gns.ctx, gns.blocks.array),
+                         lambda: B.gns_sample_blocks_static(gns.ctx, 5, seeds, gns.blocks.array)):
+                with pytest.raises(B.GnsError) as e:
+                    wait()
+                assert e.value.status == B.GNS_EINVAL
+                assert untouched()
+                assert all(b.num_dst <= b.cap_dst and b.num_src <= b.cap_src and b.num_edges <= b.cap_edges for b in gns.blocks.array)
+            full_parity(gns, cache_seed=48, epoch=0, batch_seed=6, seeds=torch.arange(1, n, dtype=torch.int32))
+            assert untouched()
+    finally:
+        gns.close()
