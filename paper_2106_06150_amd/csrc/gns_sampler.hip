@@ -526,20 +526,10 @@ __device__ __forceinline__ void flag_chunk_set(const SampleArgs& a, const uint32
     }
 }
 
-// One work list: every wave takes an equal, contiguous share of its Q chunks, in sets of kUnroll.
+// Chunks begin .. end - 1 of a work list (the same for all lanes of a wave), in sets of kUnroll.
 template <int kMode, int kUnroll>
-__device__ __forceinline__ void flag_work_list(const SampleArgs& a, const uint32_t* lds32, int64_t Q)
+__device__ __forceinline__ void flag_list_part(const SampleArgs& a, const uint32_t* lds32, int64_t begin, int64_t end)
 {
-    if (Q <= 0 || a.num_entries <= 0) return;
-    const int waves_per_block = (int) (blockDim.x >> 6);
-    const int wave = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
-    // a list of fewer sets than there are waves is spread over the blocks
-    const int64_t wave_global = kUnroll < kFlagUnroll ? (int64_t) wave * gridDim.x + blockIdx.x : (int64_t) blockIdx.x * waves_per_block + wave;
-    const int64_t num_waves = (int64_t) gridDim.x * waves_per_block;
-    int64_t share = (Q + num_waves - 1) / num_waves;
-    if (kUnroll < kFlagUnroll && share < kUnroll) share = kUnroll;
-    const int64_t begin = wave_global * share;
-    const int64_t end = (begin + share < Q) ? begin + share : Q;
     const int64_t last_chunk = (a.num_entries - 1) >> 6;
     const bool last_is_partial = (a.num_entries & 63) != 0;
     for (int64_t c0 = begin; c0 < end; c0 += kFlagBatch) {
@@ -560,38 +550,51 @@ __device__ __forceinline__ void flag_work_list(const SampleArgs& a, const uint32
 }
 
 // kMode 1 / 2: the cache bitmap / the cache filter is first copied into dynamic LDS (rounded up to
-// 16 bytes).  The work lists of the group's `count` mini-batches are taken one after the other (they read
-// the same cache, so the bitmap is staged once).  Short lists ask the exact
-// bitmap in global memory instead, in small sets: staging takes 4 us (1 M nodes) to 10 us (the filter) whatever the list's
-// length.  One seed, fan-outs 15, 10 on 0.1 to 20 M nodes: 8 to 13 us staged, 4.2 direct; at four chunks per wave 8.7 and 6.1
-// (1 M nodes), at six 15 and 8 (2 M) to 10.6 (20 M).  The direct pass grows by 64 requests a chunk at the L2s' rate, so the lines
-// lie at five and eight.
-constexpr int kFlagShortUnroll = 4;
+// 16 bytes).  The work lists of the group's `count` mini-batches, which read the same cache, are shared out as one: every wave
+// takes an equal part, which may go on from one list to the next.  Each list shared out by itself, one after the other, cost its
+// chain of reads every time: lists of four mini-batches 20.5 to 24 us on up to 1.3 M nodes and 37 to 43 on 2 to 20 M, as one 8.5 to 15
+// and 14 to 27.
+// Short lists ask the exact bitmap in global memory instead, in small sets: staging takes 4 us to 10 us (the filter) whatever the
+// lists' length.  Below one chunk per wave 7.5 to 9 us staged (bitmap) or 12.5 to 16 (filter) and 4 to 5 direct.  The direct pass
+// grows by 64 requests a chunk at the L2s' rate: at 7 to 8 chunks per wave 8.7 to 10 and 6.1 to 7.3 us (bitmap), 13 to 16 and 9.4 to
+// 10.7 (filter), at 10 as long or longer on 1 M nodes and more, for single lists and for groups of two and four.
+constexpr int kFlagShortUnroll = 4, kFlagShort = 8;          // chunks: of a set, of a wave at most
 
 template <int kMode>
 __global__ void k_flag_chunks(LayerArgs g, int count)
 {
     extern __shared__ uint4 lds_bitmap16[];
-    SampleArgs a = bind_sample(g, 0);
-    if (kMode == 1 || kMode == 2) {
-        int64_t all = 0;
-        for (int b = 0; b < count; ++b) all += bind_state(g, b)->plan_chunks;
-        if (all <= (int64_t) (kMode == 1 ? 5 : 8) * gridDim.x * (blockDim.x >> 6)) {
-            for (int b = 0; b < count; ++b) {
-                if (b > 0) a = bind_sample(g, b);
-                flag_work_list<0, kFlagShortUnroll>(a, nullptr, (int64_t) a.st->plan_chunks);
-            }
-            return;
-        }
-        if (kMode == 1) stage_lds(lds_bitmap16, reinterpret_cast<const uint4*>(a.cache_bitmap), (int32_t) ((a.bitmap_words + 1) / 2));
-        else            stage_filter(lds_bitmap16, a.filter);
-        __syncthreads();
-    }
     const uint32_t* lds32 = reinterpret_cast<const uint32_t*>(lds_bitmap16);
-    for (int b = 0; b < count; ++b) {
-        if (b > 0) a = bind_sample(g, b);
-        flag_work_list<kMode, kFlagUnroll>(a, lds32, (int64_t) a.st->plan_chunks);
+    SampleArgs a = bind_sample(g, 0);                    // the batches differ in their lists only
+    const int wave = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
+    const int64_t waves_per_block = (int64_t) (blockDim.x >> 6), num_waves = (int64_t) gridDim.x * waves_per_block;
+    const int lane = lane_id();
+    const int32_t chunks = lane < count ? bind_state(g, lane)->plan_chunks : 0;          // lane b: of list b
+    int64_t all = 0;
+    for (int b = 0; b < count; ++b) all += __builtin_amdgcn_readlane(chunks, b);
+    // chunks begin .. end - 1 of all lists
+    auto flag = [&](auto mode, auto unroll, int64_t begin, int64_t end) {
+        for (int b = 0; b < count && end > 0; ++b) {
+            const int64_t Q = __builtin_amdgcn_readlane(chunks, b);
+            a.plan_desc = at<int32_t>(g.b[b].ws, g.off.plan_desc);
+            flag_list_part<decltype(mode)::value, decltype(unroll)::value>(a, lds32, begin > 0 ? begin : 0, end < Q ? end : Q);
+            begin -= Q;
+            end -= Q;
+        }
+    };
+    int64_t share = (all + num_waves - 1) / num_waves;
+    if ((kMode == 1 || kMode == 2) && share <= kFlagShort) {
+        // a list of fewer sets than there are waves is spread over the blocks
+        if (share < kFlagShortUnroll) share = kFlagShortUnroll;
+        const int64_t begin = ((int64_t) wave * gridDim.x + blockIdx.x) * share;
+        flag(std::integral_constant<int, 0>(), std::integral_constant<int, kFlagShortUnroll>(), begin, begin + share);
+        return;
     }
+    if (kMode == 1) stage_lds(lds_bitmap16, reinterpret_cast<const uint4*>(a.cache_bitmap), (int32_t) ((a.bitmap_words + 1) / 2));
+    if (kMode == 2) stage_filter(lds_bitmap16, a.filter);
+    if (kMode == 1 || kMode == 2) __syncthreads();
+    const int64_t begin = ((int64_t) blockIdx.x * waves_per_block + wave) * share;
+    flag(std::integral_constant<int, kMode>(), std::integral_constant<int, kFlagUnroll>(), begin, begin + share);
 }
 
 // group-wide helpers for G consecutive lanes (G a power of two)

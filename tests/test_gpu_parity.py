@@ -1604,8 +1604,8 @@ def test_cache_filter_of_graphs_whose_bitmap_does_not_fit_lds(n, flag_mode):
 
 @pytest.mark.parametrize("n,avg", [(60_000, 40), (1_400_000, 6)])
 def test_short_and_long_lists_of_chunks_to_flag(n, avg):
-    """Lists of up to five (the bitmap fits LDS) and eight chunks (it does not) for each of 4096 waves are tested against the
-    bitmap in global memory, longer ones against what is staged in LDS: a row, lists on both sides of the lines, and a
+    """Lists of up to eight chunks for each of 4096 waves are tested against the bitmap in global memory, longer ones against
+    what is staged in LDS (the bitmap, or a filter where it does not fit): a row, lists on both sides of the line, and a
     group whose lists are short each and long together."""
     ip, ix = random_symmetric_csr(n, avg, np.random.default_rng(n))
     ip, ix = torch.from_numpy(ip), torch.from_numpy(ix)
@@ -1758,4 +1758,30 @@ def test_many_bad_seeds(graph, fanouts, policies, flag_mode, monkeypatch):
             full_parity(gns, cache_seed=48, epoch=0, batch_seed=6, seeds=torch.arange(1, n, dtype=torch.int32))
             assert untouched()
     finally:
+        gns.close()
+
+
+@pytest.mark.parametrize("n,avg", [(60_000, 40), (1_400_000, 6)])
+@pytest.mark.parametrize("sizes", [(1,) * 16, (1, 90, 2, 300), (400, 1, 1, 1, 400), (3000, 1, 2900, 7, 3000, 1)])
+def test_lists_of_chunks_of_a_group_shared_out_as_one(sizes, n, avg):
+    """The waves' parts go on from one mini-batch's list to the next, in short lists and in long ones: lists of one row between
+    others, lists that all fall to a few waves, and one that begins and ends in the middle of parts."""
+    ip, ix = random_symmetric_csr(n, avg, np.random.default_rng(n + 1))
+    ip, ix = torch.from_numpy(ip), torch.from_numpy(ix)
+    fanouts, policies, csize = (10, 5), (U, C), n // 50
+    gns = GpuGns(ip, ix, None, fanouts=fanouts, policies=policies, cache_size=csize, max_seeds=max(sizes), flag_mode=0)
+    ctxs, keep, bufs, call = _group_setup(gns, len(sizes))
+    try:
+        B.gns_sample_cache(gns.ctx, 49, 0)
+        cache = oracle.sample_cache(ip.numpy(), 49, 0, csize)
+        for rnd in range(2):
+            seeds = [synth.uniform_seed_batch(n, size, 520 + 20 * rnd + b).cuda() for b, size in enumerate(sizes)]
+            call.sample([80 + b for b in range(len(sizes))], seeds)
+            call.wait()
+            for b in range(len(sizes)):
+                ref = oracle.sample_blocks(ip.numpy(), ix.numpy(), cache[1], csize, 80 + b, seeds[b].cpu().numpy(), list(fanouts), list(policies))
+                compare_blocks([bufs[b].views(j) for j in range(2)], ref)
+    finally:
+        for f in ctxs[1:]:
+            B.gns_destroy(f)
         gns.close()
