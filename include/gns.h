@@ -56,6 +56,8 @@
  *      GNS_UNION_SPINS=<n>  how often a block of the union step polls for another
  *        block's count before it counts that part of the bitmap itself
  *        (default 256)
+ *      GNS_WALK_NO_HOT=1  steps of the random-walk probability without the hot nodes'
+ *        values in LDS
  *      GNS_NO_GRAPH=1  enqueue a mini-batch's kernels one by one instead of
  *        replaying a captured HIP graph
  */

@@ -4,6 +4,7 @@
 // is independent of the order of the additions; then its exclusive prefix sum, which takes the
 // place of the CSR offsets in the cache draw (a uniform integer below the total picks the node
 // whose prefix interval holds it) and in Section 3.4's p_u.
+#include <stdlib.h>
 #include "gns_internal.h"
 #include "gns_device.hpp"
 
@@ -21,6 +22,8 @@ struct HotCopy {
     uint16_t tag[kHotSlots];
 };
 static_assert(kHotSlots % 32 == 0 && sizeof(HotCopy) == kHotSlots * 6 && sizeof(HotCopy) % 16 == 0, "copied 16 bytes at a time");
+
+constexpr int64_t kHotNodes = (int64_t) kHotSlots * kNoTag;     // of larger graphs the tags do not tell all nodes apart
 size_t walk_hot_bytes() { return 2 * sizeof(HotCopy); }
 
 // What the walk begins with: no training node, no error, and the holders of the hot nodes' slots.  A block finds those of
@@ -36,6 +39,7 @@ __global__ void __launch_bounds__(kBlock) k_walk_init(unsigned long long* bits, 
     const int64_t t = (int64_t) blockIdx.x * kBlock + threadIdx.x;
     if (t == 0) st->walk_error = 0;
     for (int64_t i = t; i < words; i += (int64_t) gridDim.x * kBlock) bits[i] = 0ull;
+    if (!hot) return;
     // the longest row, of those the last; 0: no row of the slot has an entry
     const int32_t slot = (int32_t) (blockIdx.x * kInitSlots + threadIdx.x % kInitSlots);
     constexpr int64_t kStep = (int64_t) kHotSlots * kInitParts;
@@ -107,7 +111,7 @@ struct WalkStepArgs {
     unsigned long long unit;      // kBits: what a set bit stands for
     const void* cur;
     void* nxt;
-    const HotCopy* hot_cur;       // kNarrow: the hot nodes' values in cur
+    const HotCopy* hot_cur;       // kNarrow: the hot nodes' values in cur, null: no table of them
     HotCopy* hot_nxt;             // where those in nxt go if that is narrow
     DeviceState* st;
 };
@@ -209,7 +213,9 @@ __device__ __forceinline__ unsigned long long step_value(unsigned long long own,
 }
 
 // kBits and kWide.  1 M nodes, 40 M entries: the first step takes 54 us; 66 with shares of equal rows, windows read as far as
-// they belong to a list, and none read ahead across lists.
+// they belong to a list, and none read ahead across lists.  Where the bits do not fit LDS, only entries of the list ask for
+// theirs (lists of 64 rows fill half to two thirds of their windows on graphs of ten entries a row): 5 M nodes, 200 M entries 0.86 ms,
+// 20 M nodes, 400 M entries 1.92, 40 M nodes 2.68, where windows asked whole took 1.02, 2.43 and 4.45.
 template <typename OffT, int kIn, bool kWideOut, bool kLds>
 __global__ void __launch_bounds__(kLds ? 1024 : kBlock) k_walk_step(WalkStepArgs a)
 {
@@ -268,7 +274,7 @@ __global__ void __launch_bounds__(kLds ? 1024 : kBlock) k_walk_step(WalkStepArgs
 #pragma unroll
                 for (int t = 0; t < kUnroll; ++t) {
                     const int q = t * kWave + lane;
-                    const uint32_t w = kLds ? lds_bits[(uint32_t) j[t] >> 5] : bits[(uint32_t) j[t] >> 5];
+                    const uint32_t w = kLds ? lds_bits[(uint32_t) j[t] >> 5] : bits[q >= from && q < to ? (uint32_t) j[t] >> 5 : 0u];
                     const uint64_t m = __ballot(q >= from && q < to && ((w >> (j[t] & 31)) & 1u));
                     if (lane == t) mine = m;
                 }
@@ -337,7 +343,7 @@ __global__ void __launch_bounds__(kLds ? 1024 : kBlock) k_walk_step(WalkStepArgs
             else {
                 static_cast<uint32_t*>(a.nxt)[i] = (uint32_t) out;
                 const uint32_t tag = (uint32_t) i / kHotSlots, slot = (uint32_t) i - tag * kHotSlots;
-                if (a.hot_nxt->tag[slot] == tag) a.hot_nxt->value[slot] = (uint32_t) out;
+                if (a.hot_nxt && a.hot_nxt->tag[slot] == tag) a.hot_nxt->value[slot] = (uint32_t) out;
             }
             if (bad) a.st->walk_error = 2;
         }
@@ -351,17 +357,19 @@ struct __attribute__((packed, aligned(4))) Ids4 { int32_t id[4]; };
 // slot there leaves L2 alone: 37 % of them on a power law of 1 M nodes (gamma 2.1), 18 % at 40 M.  A lane has four consecutive
 // entries of every 256, so the running sum takes one wave-wide scan per 256 entries; the next window's ids, the next rows'
 // beginnings and the rows' own values are on their way while a window is summed.
-// 1 M nodes, 40 M entries: 158 us a step, 168 G requests/s out of the CUs; 226 with every value from the L2s.
-template <typename OffT, bool kWideOut>
-__global__ void __launch_bounds__(1024) k_walk_narrow(WalkStepArgs a)
+// 1 M nodes, 40 M entries: 158 us a step, 168 G requests/s out of the CUs; 226 with every value from the L2s.  With the table
+// and without, a step on larger graphs: 5 M nodes, 200 M entries 2.09 and 2.46 ms, 20 M nodes, 400 M entries 5.68 and 6.52, 40 M nodes
+// 6.10 and 7.05.  !kHot: graphs of more than 1.7 G nodes, whose tags do not tell all nodes apart.
+template <typename OffT, bool kWideOut, bool kHot>
+__global__ void __launch_bounds__(kHot ? 1024 : kBlock) k_walk_narrow(WalkStepArgs a)
 {
     extern __shared__ uint4 lds_hot[];
-    constexpr int kSub = 2, kWindow = kSub * 4 * kWave;
+    constexpr int kSub = 2, kWindow = kSub * 4 * kWave, kWaves = (kHot ? 1024 : kBlock) / kWave;
     const uint32_t* cur = static_cast<const uint32_t*>(a.cur);
-    const int64_t wave = (int64_t) blockIdx.x * 16 + __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
+    const int64_t wave = (int64_t) blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
     int64_t row_lo, row_hi;
-    wave_share<OffT>(a, wave, (int64_t) gridDim.x * 16, &row_lo, &row_hi);
-    {
+    wave_share<OffT>(a, wave, (int64_t) gridDim.x * kWaves, &row_lo, &row_hi);
+    if (kHot) {
         constexpr int kLoads = (int) (sizeof(HotCopy) / 16), kTurns = (kLoads + 1023) / 1024;
         const uint4* src = reinterpret_cast<const uint4*>(a.hot_cur);
         uint4 v[kTurns];
@@ -427,8 +435,8 @@ __global__ void __launch_bounds__(1024) k_walk_narrow(WalkStepArgs a)
                     const int q = (s * kWave + lane) * 4 + e;
                     const uint32_t id = (uint32_t) j[s][e], tag = id / kHotSlots, slot = id - tag * kHotSlots;
                     in[s][e] = q >= from && q < to;
-                    hit[s][e] = hot->tag[slot] == tag;
-                    hot_v[s][e] = hot->value[slot];
+                    hit[s][e] = kHot && hot->tag[slot] == tag;
+                    hot_v[s][e] = kHot ? hot->value[slot] : 0u;
                     v[s][e] = cur[in[s][e] && !hit[s][e] ? id : 0u];              // lanes with nothing to read share one line
                 }
 #pragma unroll
@@ -465,7 +473,7 @@ __global__ void __launch_bounds__(1024) k_walk_narrow(WalkStepArgs a)
             else {
                 static_cast<uint32_t*>(a.nxt)[i] = (uint32_t) out;
                 const uint32_t tag = (uint32_t) i / kHotSlots, slot = (uint32_t) i - tag * kHotSlots;
-                if (hot->tag[slot] == tag) a.hot_nxt->value[slot] = (uint32_t) out;
+                if (kHot && hot->tag[slot] == tag) a.hot_nxt->value[slot] = (uint32_t) out;
             }
             if (bad) a.st->walk_error = 2;
         }
@@ -484,10 +492,10 @@ template <typename OffT>
 static void launch_walk_step(const gns_ctx* c, const WalkStepArgs& a, int in, bool wide_out, hipStream_t s)
 {
     const size_t bit_bytes = (size_t) ((a.n + 31) / 32) * 4;
-    if (in == kNarrow) {
+    if (in == kNarrow && a.hot_cur) {
         const dim3 grid = walk_grid(a, 16, c->num_cus), block(1024);
-        if (wide_out) hipLaunchKernelGGL((k_walk_narrow<OffT, true>), grid, block, sizeof(HotCopy), s, a);
-        else          hipLaunchKernelGGL((k_walk_narrow<OffT, false>), grid, block, sizeof(HotCopy), s, a);
+        if (wide_out) hipLaunchKernelGGL((k_walk_narrow<OffT, true, true>), grid, block, sizeof(HotCopy), s, a);
+        else          hipLaunchKernelGGL((k_walk_narrow<OffT, false, true>), grid, block, sizeof(HotCopy), s, a);
         return;
     }
     if (in == kBits && (bit_bytes + 15) / 16 * 16 <= c->lds_bitmap_limit) {
@@ -498,7 +506,9 @@ static void launch_walk_step(const gns_ctx* c, const WalkStepArgs& a, int in, bo
         return;
     }
     const dim3 grid = walk_grid(a, kBlock / kWave, (int64_t) c->num_cus * 8), block(kBlock);
-    if (in == kWide)   hipLaunchKernelGGL((k_walk_step<OffT, kWide, true, false>), grid, block, 0, s, a);
+    if (in == kNarrow && wide_out) hipLaunchKernelGGL((k_walk_narrow<OffT, true, false>), grid, block, 0, s, a);
+    else if (in == kNarrow) hipLaunchKernelGGL((k_walk_narrow<OffT, false, false>), grid, block, 0, s, a);
+    else if (in == kWide) hipLaunchKernelGGL((k_walk_step<OffT, kWide, true, false>), grid, block, 0, s, a);
     else if (wide_out) hipLaunchKernelGGL((k_walk_step<OffT, kBits, true, false>), grid, block, 0, s, a);
     else               hipLaunchKernelGGL((k_walk_step<OffT, kBits, false, false>), grid, block, 0, s, a);
 }
@@ -648,7 +658,8 @@ gns_status run_walk_probability(gns_ctx* c, const int32_t* train_nodes, int64_t 
     unsigned long long* tile_sums = ws_ptr<unsigned long long>(c, L.walk_tiles);
     int32_t* tile_nz = ws_ptr<int32_t>(c, L.walk_tiles_nz);
 
-    HotCopy* hot = ws_ptr<HotCopy>(c, L.walk_hot);
+    const bool has_hot = n <= kHotNodes && sizeof(HotCopy) <= c->lds_bitmap_limit && !getenv("GNS_WALK_NO_HOT");
+    HotCopy* hot = has_hot ? ws_ptr<HotCopy>(c, L.walk_hot) : nullptr;
 
     // P^0 as a bitmap of the training nodes
     const int64_t words = (n + 63) / 64;
@@ -658,8 +669,6 @@ gns_status run_walk_probability(gns_ctx* c, const int32_t* train_nodes, int64_t 
     else     hipLaunchKernelGGL((k_walk_init<int32_t>), init, dim3(kBlock), 0, s, cur, words, c->graph.indptr, n, hot, c->d_state);
     hipLaunchKernelGGL(k_walk_seed, dim3((unsigned) ((num_train + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, train_nodes,
                        num_train, n, reinterpret_cast<uint32_t*>(cur), c->d_state);
-    // 32-bit vectors where the hot nodes' tags hold every node and their table fits LDS
-    const bool narrow_fits = n <= (int64_t) kHotSlots * kNoTag && sizeof(HotCopy) <= c->lds_bitmap_limit;
     unsigned long long bound = 1ull << scale_log2;       // no entry of the current vector exceeds it
     for (int l = 0; l < c->config.num_layers; ++l) {
         WalkStepArgs a;
@@ -671,12 +680,12 @@ gns_status run_walk_probability(gns_ctx* c, const int32_t* train_nodes, int64_t 
         a.unit = 1ull << scale_log2;
         a.cur = cur;
         a.nxt = nxt;
-        a.hot_cur = &hot[l & 1];
-        a.hot_nxt = &hot[(l + 1) & 1];
+        a.hot_cur = hot ? &hot[l & 1] : nullptr;
+        a.hot_nxt = hot ? &hot[(l + 1) & 1] : nullptr;
         a.st = c->d_state;
-        const int in = l == 0 ? kBits : narrow_fits && (bound >> 32) == 0 ? kNarrow : kWide;
+        const int in = l == 0 ? kBits : (bound >> 32) == 0 ? kNarrow : kWide;
         bound = bound >= kWalkLimit / 128 ? kWalkLimit : bound * (unsigned long long) (1 + a.k);
-        const bool wide_out = l == c->config.num_layers - 1 || !narrow_fits || (bound >> 32) != 0;
+        const bool wide_out = l == c->config.num_layers - 1 || (bound >> 32) != 0;
         if (i64) launch_walk_step<int64_t>(c, a, in, wide_out, s);
         else     launch_walk_step<int32_t>(c, a, in, wide_out, s);
         unsigned long long* t = cur; cur = nxt; nxt = t;

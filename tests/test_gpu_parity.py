@@ -1785,3 +1785,31 @@ def test_lists_of_chunks_of_a_group_shared_out_as_one(sizes, n, avg):
         for f in ctxs[1:]:
             B.gns_destroy(f)
         gns.close()
+
+
+@pytest.mark.parametrize("n,degrees,hot", [(1_310_000, (0,), True), (1_310_000, (1023, 1, 0), True), (1_310_001, (0, 1024, 0, 2049, 5, 0), False),
+                                           (3000, (0, 0, 0, 7), False), (26_625, (1023, 1, 0), False)])
+def test_walk_windows_beyond_lds_and_without_the_hot_nodes(n, degrees, hot, monkeypatch):
+    """The windows above where the training nodes' bits do not fit LDS, so that entries outside a list ask for none; and the
+    steps on 32-bit values without the hot nodes' table, which graphs of more than 1.7 G nodes take."""
+    if not hot:
+        monkeypatch.setenv("GNS_WALK_NO_HOT", "1")
+    rng = np.random.default_rng(n + len(degrees))
+    deg = np.zeros(n, dtype=np.int64)
+    deg[500:700] = [degrees[i % len(degrees)] for i in range(200)]
+    deg[[3, 64, 1200]] = (17, 1024, 33)
+    if n > 3000:
+        deg[-70_000 if n > 100_000 else -20_000:-1] += rng.integers(0, 12, size=69_999 if n > 100_000 else 19_999)
+    ip = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    ix = np.concatenate([np.unique(rng.integers(0, n, size=4 * d + 64))[:d] if d < n // 8 else np.sort(rng.choice(n, d, replace=False)) for d in deg if d]).astype(np.int32)
+    assert len(ix) == ip[-1]
+    ip, ix = torch.from_numpy(ip), torch.from_numpy(ix)
+    gns = GpuGns(ip, ix, None, fanouts=(3, 2, 4), policies=(U, U, C), cache_size=2, max_seeds=8, cache_probability=B.GNS_PROB_WALK)
+    try:
+        train = torch.arange(1, n, 3, dtype=torch.int32)
+        for scale in (20, 33):
+            w, pre, _, _ = gns.walk_probability(train, scale)
+            w_ref, pre_ref = oracle.walk_weights(ip.numpy(), ix.numpy(), train.numpy(), [3, 2, 4], scale_log2=scale)
+            assert np.array_equal(w, w_ref) and np.array_equal(pre, pre_ref)
+    finally:
+        gns.close()
