@@ -269,7 +269,9 @@ void fill_begin_dyn(const Group& g, const uint64_t* seeds, const int32_t* const*
     for (int b = 0; b < g.count; ++b) {
         gns_ctx* c = g.ctx[b];
         out->seeds[b] = seeds_dev[b];
-        out->num_seeds[b] = num_seeds[b];
+        const bool too_many = (int64_t) num_seeds[b] > c->graph.num_nodes;
+        out->num_seeds[b] = too_many ? (int32_t) c->graph.num_nodes : num_seeds[b];
+        out->too_many |= (uint32_t) too_many << b;
         out->key0[b] = (uint32_t) seeds[b];
         out->key1[b] = (uint32_t) (seeds[b] >> 32);
         out->batch_id[b] = c->batch_id + 1;

@@ -63,7 +63,7 @@ hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s)
 __global__ void __launch_bounds__(kBlock) k_batch_begin(LayerArgs g, BeginDyn d)
 {
     const auto [b, block] = group_block<false>(g.dealt);
-    const int32_t num_seeds = seed_rows(g, d, b);
+    const int32_t num_seeds = d.num_seeds[b];
     const NodeTable tab = bind_table(g, b, d.stamp[b]);
     const int32_t q = block * kBlock + (int32_t) threadIdx.x;
     if (q == 0) begin_state(g, d, b);

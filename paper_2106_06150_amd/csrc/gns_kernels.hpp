@@ -182,7 +182,8 @@ struct LayerArgs {
 // What changes from one replay of a group's launch sequence to the next (arguments of the first kernel).
 struct BeginDyn {
     const int32_t* seeds[kMaxGroup];
-    int32_t num_seeds[kMaxGroup];
+    int32_t num_seeds[kMaxGroup];  // no more than the graph has nodes: the buffers have no room for more rows
+    uint32_t too_many;             // bit b: there were more, so that some of them are bad
     uint32_t key0[kMaxGroup], key1[kMaxGroup];
     uint32_t batch_id[kMaxGroup];
     uint32_t stamp[kMaxGroup];     // what the batch's entries of the node table carry
@@ -411,19 +412,12 @@ __device__ __forceinline__ bool is_hub_extent(int64_t start, int64_t end)
     return end > start && ((end - 1) >> 6) - (start >> 6) + 1 > kHubChunks;
 }
 
-// Rows of the first layer: the seeds, but no more than the buffers take (of more seeds than nodes some are bad).
-__device__ __forceinline__ int32_t seed_rows(const LayerArgs& g, const BeginDyn& d, int b)
-{
-    return (int64_t) d.num_seeds[b] < g.f.num_nodes ? d.num_seeds[b] : (int32_t) g.f.num_nodes;
-}
-
 // The batch's scalars, published for its later kernels; one thread of the batch's first kernel.
 __device__ __forceinline__ void begin_state(const LayerArgs& g, const BeginDyn& d, int b)
 {
     DeviceState* st = bind_state(g, b);
-    const int32_t rows = seed_rows(g, d, b);
-    st->num_dst[0] = rows;
-    if (rows < d.num_seeds[b]) st->bad_seed = d.batch_id[b];
+    st->num_dst[0] = d.num_seeds[b];
+    if (d.too_many >> b & 1u) st->bad_seed = d.batch_id[b];
     for (int l = 0; l < GNS_MAX_LAYERS; ++l) { st->num_edges[l] = 0; st->num_dst[l + 1] = 0; st->hub_count[l] = 0; }
     st->key0 = d.key0[b];
     st->key1 = d.key1[b];

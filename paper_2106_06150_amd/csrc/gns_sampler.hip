@@ -296,7 +296,7 @@ __global__ void __launch_bounds__(kBlock) k_sample_first(LayerArgs g, BeginDyn d
     __shared__ int32_t smem[kBlock / kWave + 1];
     __shared__ WaveRows<K> rows[kBlock / kWave];
     const auto [b, block] = group_block<kOne>(g.dealt);
-    const int32_t R = seed_rows(g, d, b);
+    const int32_t R = d.num_seeds[b];
     if (block == 0 && threadIdx.x == 0) begin_state(g, d, b);
     if ((int64_t) block * (kBlock / kWave) * W >= R) return;
     const SampleArgs a = bind_sample(g, b, d.stamp[b], d.cache_gen[b]);

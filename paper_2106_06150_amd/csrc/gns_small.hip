@@ -22,6 +22,7 @@ struct SmallSlot {
     DeviceState* host;
     const int32_t* seeds;
     int32_t num_seeds;
+    int32_t bad;                                 // there are more seeds than nodes
     uint32_t key0, key1;
     uint32_t batch_id, stamp;
     int32_t cache_gen;
@@ -141,7 +142,7 @@ __global__ void __launch_bounds__(kThreads) k_sample_small(SmallArgs g)
         uint32_t deg = 0;
         if (valid) extent(u, &start, &deg);
         for (int i = tid; i < Lds::kHash; i += kThreads) w.key[i] = ~0u;
-        if (tid == 0) { w.fresh_count = 0; w.bad = 0; }
+        if (tid == 0) { w.fresh_count = 0; w.bad = q.bad; }
         __syncthreads();
         if (tid < R) {
             w.list[tid] = (uint32_t) u;
@@ -466,6 +467,7 @@ hipError_t launch_small(const Group& g, const BeginDyn& d, hipStream_t s)
         q.host = g.ctx[b]->h_state_dev;
         q.seeds = d.seeds[b];
         q.num_seeds = d.num_seeds[b];
+        q.bad = (int32_t) (d.too_many >> b & 1u);
         q.key0 = d.key0[b];
         q.key1 = d.key1[b];
         q.batch_id = d.batch_id[b];
