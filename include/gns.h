@@ -326,7 +326,7 @@ gns_status gns_aggregate_group(gns_ctx* const* ctxs, int32_t count, const gns_bl
  * graph, config and current cache are theirs).  The call allocates nothing: no hipMalloc, no
  * host allocation, no HIP graph (the kernels are launched one by one on hip_stream, which is
  * synchronised before the call returns).  GNS_ECAPACITY if the per-batch scratch of this graph
- * and config (what gns_fork_workspace_bytes reports, without the 4 bytes per node of the node table, which
+ * and config (what gns_fork_workspace_bytes reports, without 32 KB and the 4 bytes per node of the node table, which
  * large graphs keep in the context's workspace) exceeds the array: nothing is launched.
  * All calls on one GPU share that GPU's array, whatever their context: it is re-initialised at
  * the start of every call (the node table too: 4 bytes per node are written), and calls that overlap on one GPU race.  gns_gather_features and

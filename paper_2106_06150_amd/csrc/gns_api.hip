@@ -520,7 +520,7 @@ size_t gns_workspace_bytes(const gns_graph* graph, const gns_config* config)
 {
     Layout L;
     if (!compute_layout(graph, config, &L, g_create_err, sizeof(g_create_err))) return 0;
-    return L.total;
+    return L.total + kPlacesBytes;
 }
 
 gns_status gns_block_capacity(const gns_graph* graph, const gns_config* config, int32_t layer_index,
@@ -549,8 +549,8 @@ gns_status gns_create(gns_ctx** out_ctx, const gns_graph* graph, const gns_confi
         snprintf(g_create_err, sizeof(g_create_err), "workspace must be a 256-byte aligned device pointer");
         return GNS_EINVAL;
     }
-    if (workspace_bytes < L.total) {
-        snprintf(g_create_err, sizeof(g_create_err), "workspace too small: need %zu bytes", L.total);
+    if (workspace_bytes < L.total + kPlacesBytes) {
+        snprintf(g_create_err, sizeof(g_create_err), "workspace too small: need %zu bytes", L.total + kPlacesBytes);
         return GNS_ECAPACITY;
     }
     gns_ctx* c = new (std::nothrow) gns_ctx;
@@ -559,7 +559,7 @@ gns_status gns_create(gns_ctx** out_ctx, const gns_graph* graph, const gns_confi
     c->graph = *graph;
     c->config = *config;
     c->lay = L;
-    c->ws = static_cast<char*>(workspace);
+    c->ws = scratch_begin(workspace, 0);
     c->shared_ws = c->ws;
     c->root = c;
     c->d_state = ws_ptr<DeviceState>(c, L.state);
@@ -701,7 +701,7 @@ gns_status gns_profile_collect(gns_ctx* ctx, int32_t stage, double* total_ms, in
 
 size_t gns_fork_workspace_bytes(const gns_ctx* parent)
 {
-    return parent ? parent->lay.shared_begin : 0;
+    return parent ? parent->lay.shared_begin + kPlacesBytes : 0;
 }
 
 gns_status gns_fork(gns_ctx* parent, void* workspace, size_t workspace_bytes, void* hip_stream, gns_ctx** out_child)
@@ -711,9 +711,9 @@ gns_status gns_fork(gns_ctx* parent, void* workspace, size_t workspace_bytes, vo
     gns_ctx* root = parent->root;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u))
         return ctx_fail(parent, GNS_EINVAL, "workspace must be a 256-byte aligned device pointer");
-    if (workspace_bytes < root->lay.shared_begin) return ctx_fail(parent, GNS_ECAPACITY, "fork workspace too small");
+    if (workspace_bytes < root->lay.shared_begin + kPlacesBytes) return ctx_fail(parent, GNS_ECAPACITY, "fork workspace too small");
     gns_ctx* c = nullptr;
-    const gns_status st = make_child(root, workspace, root->cap_stream != nullptr, &c);
+    const gns_status st = make_child(root, scratch_begin(workspace, ++root->forks_made), root->cap_stream != nullptr, &c);
     if (st != GNS_OK) { snprintf(parent->err, sizeof(parent->err), "%s", root->err); return st; }
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     hipError_t e = init_batch_scratch(c, s);

@@ -1813,3 +1813,50 @@ def test_walk_windows_beyond_lds_and_without_the_hot_nodes(n, degrees, hot, monk
             assert np.array_equal(w, w_ref) and np.array_equal(pre, pre_ref)
     finally:
         gns.close()
+
+
+@pytest.mark.parametrize("offset", [0, 256, 4096 - 256, 3 * 4096, 7 * 4096 + 256])
+def test_workspaces_at_any_place(offset):
+    """A context's scratch begins at a place of its own in its workspace: workspaces of just the bytes asked for, which lie
+    differently to the pages, hold it with all that is behind it; one byte less is refused."""
+    ip, ix = _small(n=2500, avg=11, seed=79)
+    n, csize, bs, place, guard = 2500, 200, 70, 1 << 15, 4096
+    dev = torch.device("cuda:0")
+    feat = _feat(n, 8).to(dev)
+    ipd, ixd = ip.to(dev), ix.to(dev)
+    graph, config = B.make_graph(ipd, ixd, feat), B.make_config([12, 5], [U, C], csize, bs, flag_mode=1)
+    room = []
+
+    def workspace(size):
+        room.append((torch.full((size + 2 * place + guard,), 77, dtype=torch.uint8, device=dev), size))
+        begin = -room[-1][0].data_ptr() % place + offset
+        room[-1] += (begin,)
+        return room[-1][0][begin:begin + size]
+
+    size = B.gns_workspace_bytes(graph, config)
+    with pytest.raises(B.GnsError) as e:
+        B.gns_create(graph, config, workspace(size)[:-1])
+    assert e.value.status == B.GNS_ECAPACITY
+    ctxs = [B.gns_create(graph, config, workspace(size))]
+    try:
+        need = B.gns_fork_workspace_bytes(ctxs[0])
+        with pytest.raises(B.GnsError) as e:
+            B.gns_fork(ctxs[0], workspace(need)[:-1])
+        assert e.value.status == B.GNS_ECAPACITY
+        ctxs += [B.gns_fork(ctxs[0], workspace(need)) for _ in range(9)]
+        bufs = [B.BlockBuffers(graph, config, dev) for _ in ctxs]
+        cache = oracle.sample_cache(ip.numpy(), 50, 0, csize)
+        B.gns_sample_cache(ctxs[0], 50, 0)
+        call = B.GroupCall(ctxs, [b.array for b in bufs])
+        seeds = [synth.uniform_seed_batch(n, bs, 700 + b).cuda() for b in range(len(ctxs))]
+        for rnd in range(2):
+            call.sample([90 + b for b in range(len(ctxs))], seeds)
+            call.wait()
+            for b in range(len(ctxs)):
+                ref = oracle.sample_blocks(ip.numpy(), ix.numpy(), cache[1], csize, 90 + b, seeds[b].cpu().numpy(), [12, 5], [U, C])
+                compare_blocks([bufs[b].views(j) for j in range(2)], ref)
+        for t, size, begin in room:
+            assert bool((t[:begin] == 77).all()) and bool((t[begin + size:] == 77).all())
+    finally:
+        for c in reversed(ctxs):
+            B.gns_destroy(c)
