@@ -161,7 +161,7 @@ __global__ void __launch_bounds__(kMode == kExactLds || kMode == kFilterLds ? 10
     extern __shared__ uint4 lds_bitmap16[];
     if (a.done && *a.done < 0) return;
     if (kMode == kExactLds) stage_lds(lds_bitmap16, reinterpret_cast<const uint4*>(a.bitmap), (int32_t) ((a.bitmap_words + 1) / 2));
-    if (kMode == kFilterLds) stage_filter(lds_bitmap16, a.filter);
+    if (kMode == kFilterLds) stage_filter(lds_bitmap16, a.filter.groups);
     if (kMode == kExactLds || kMode == kFilterLds) __syncthreads();
     const uint32_t* lds32 = reinterpret_cast<const uint32_t*>(lds_bitmap16);
     const int wave = __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));

@@ -36,10 +36,10 @@ struct NodeTable {
     __device__ __forceinline__ uint32_t local(uint32_t e) const { return e & ((1u << shift) - 1u); }
 };
 
-// The cache filter in LDS: groups, then tags, as they stand in memory.
-__device__ __forceinline__ void stage_filter(uint4* lds, const CacheFilter& f)
+// The cache filter in LDS: CacheFilter::groups, then the tags, as they stand in memory.
+__device__ __forceinline__ void stage_filter(uint4* lds, const uint32_t* groups)
 {
-    stage_lds(lds, reinterpret_cast<const uint4*>(f.groups), kFilterGroups / 128 + kFilterHot / 8);
+    stage_lds(lds, reinterpret_cast<const uint4*>(groups), kFilterGroups / 128 + kFilterHot / 8);
 }
 
 // What it says of nodes u[0 .. N): ~0 cached, 0 not, 1: to be looked up.  All reads first: left to itself the compiler puts the
@@ -89,9 +89,9 @@ struct SampleArgs {
     uint32_t max_chunks;       // what the chunks of distinct rows come to at most
     uint64_t* flags;           // [ceil(nnz / 64)] bit e & 63 of word e >> 6: entry e points into the cache
     int64_t bitmap_words;
-    CacheFilter filter;              // (flag kernel, mode 2)
+    const uint32_t* filter_groups;   // CacheFilter::groups with the tags behind them, and its mult (flag kernel, mode 2)
+    uint32_t filter_mult;
     const uint64_t* coarse_bitmap;   // one bit per 2^coarse_shift ids (mode 3)
-    int64_t coarse_words;
     int coarse_shift;
     const ChunkRec* srec;      // induced subgraph (GNS_FLAGS_PER_CACHE): chunk records and the cached entries' node ids
     const int32_t* s_nodes;
@@ -244,8 +244,7 @@ __device__ __forceinline__ SampleArgs bind_sample(const LayerArgs& g, int b, uin
         a.node_inv_pc = shifted(g.s.node_inv_pc);
         a.cache_bitmap = shifted(g.s.cache_bitmap);
         a.flags = shifted(g.s.flags);
-        a.filter.keys = shifted(g.s.filter.keys);
-        a.filter.groups = shifted(g.s.filter.groups);
+        a.filter_groups = shifted(g.s.filter_groups);
         a.coarse_bitmap = shifted(g.s.coarse_bitmap);
         a.srec = shifted(g.s.srec);
         a.s_nodes = shifted(g.s.s_nodes);

@@ -506,7 +506,7 @@ __device__ __forceinline__ void flag_chunk_set(const SampleArgs& a, const uint32
     }
     if (kMode == 2) {
 #pragma unroll
-        for (int i = 0; i < kUnroll; i += 8) filter_test<8>(lds32, a.filter.mult, u + i, w + i);
+        for (int i = 0; i < kUnroll; i += 8) filter_test<8>(lds32, a.filter_mult, u + i, w + i);
 #pragma unroll
         for (int i = 0; i < kUnroll; ++i)
             if (w[i] == 1u) w[i] = exact32[u[i] >> 5];
@@ -591,7 +591,7 @@ __global__ void k_flag_chunks(LayerArgs g, int count)
         return;
     }
     if (kMode == 1) stage_lds(lds_bitmap16, reinterpret_cast<const uint4*>(a.cache_bitmap), (int32_t) ((a.bitmap_words + 1) / 2));
-    if (kMode == 2) stage_filter(lds_bitmap16, a.filter);
+    if (kMode == 2) stage_filter(lds_bitmap16, a.filter_groups);
     if (kMode == 1 || kMode == 2) __syncthreads();
     const int64_t begin = ((int64_t) blockIdx.x * waves_per_block + wave) * share;
     flag(std::integral_constant<int, kMode>(), std::integral_constant<int, kFlagUnroll>(), begin, begin + share);
@@ -848,9 +848,9 @@ void fill_sample_template(gns_ctx* c, int layer_index, SampleArgs* out)
     a.max_chunks = (uint32_t) L.max_chunks;
     a.flags = c->uses_cache && c->config.flag_mode == GNS_FLAGS_PER_BATCH ? cache_ptr<uint64_t>(c, L.edge_flags, gen) : nullptr;
     a.bitmap_words = L.words;
-    a.filter = cache_filter(c, gen);
+    a.filter_groups = cache_filter(c, gen).groups;
+    a.filter_mult = L.filter_mult;
     a.coarse_bitmap = L.coarse_shift ? cache_ptr<uint64_t>(c, L.coarse_bitmap, gen) : nullptr;
-    a.coarse_words = L.coarse_words;
     a.coarse_shift = L.coarse_shift;
     const bool induced = c->uses_cache && c->config.flag_mode == GNS_FLAGS_PER_CACHE;
     a.srec = induced ? cache_ptr<ChunkRec>(c, L.srec, gen) : nullptr;
