@@ -168,11 +168,12 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     // A cache bitmap too big for LDS gets a filter that does fit, and what the filter leaves open costs one request to L2, whose
     // rate bounds the pass.  (40 M nodes, 400 M entries, 1 % cached: 37 % of the entries point into the cache; one bit per 32
     // ids in LDS leaves 54 % open, 1.38 ms; one per 39 ids with the tags of 16 K nodes 40 %, 1.19 ms, and 1.02 ms where they
-    // ask the list of pairs.)  Up to 64 ids to a bit of LDS (83 M nodes); beyond, most entries would stay open: there a coarse
-    // bitmap of one bit per 16 ids lies in global memory, in every L2 (one bit per 64 ids in LDS, no tags, and the one in L2:
-    // 82 M nodes, 400 M entries 2.93 and 3.00 ms; one per 128 ids, 111 M nodes, 1.6 G entries: 16.0 and 10.7).
+    // ask the list of pairs.)  Up to 83 M nodes, 80 ids to a group; beyond, most entries would stay open: there a coarse
+    // bitmap of one bit per 16 ids lies in global memory, in every L2.  The line is that of a bit per 64 ids in all of LDS, no
+    // tags, against the one in L2 (82 M nodes, 400 M entries: 2.93 and 3.00 ms; 111 M nodes, 1.6 G entries, 128 ids to a bit:
+    // 16.0 and 10.7).
     if (uses_cache && (size_t) L.words * 8 > kLdsBitmapBytes) {
-        if (n <= (int64_t) kLdsBitmapBytes * 8 * 64) {
+        if (n <= kFilterNodes) {
             L.filter = take(kFilterBytes);
             L.filter_mult = (uint32_t) (((uint64_t) kFilterGroups << 32) / (uint64_t) n);
         } else {

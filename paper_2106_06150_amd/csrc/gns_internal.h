@@ -47,6 +47,9 @@ struct CacheFilter {
     uint32_t mult;                // group of an id: the upper half of id * mult
 };
 constexpr uint32_t kPairBits = 7, kPairMask = (1u << kPairBits) - 1u, kPairMore = 1u << 14, kPairSet = 1u << 15;
+// Graphs of more nodes than this have no filter.  At the line a group has up to 81 ids.
+constexpr int64_t kFilterNodes = (int64_t) kLdsBitmapBytes * 8 * 64;
+static_assert(kFilterNodes / kFilterGroups + 2 <= 1 << kPairBits, "a pair tells the ids of a group apart");
 constexpr size_t kFilterBytes = (size_t) kFilterHot * (8 + 2) + kFilterGroups / 8 + (size_t) kFilterGroups * 2;
 // The pass over the entries with the list and without: 40 M nodes (a bitmap of 5 MB) 1020 and 1188 us, 28 M 705 and 749,
 // 20 M 813 and 843, 12 M 378 and 358.
@@ -319,13 +322,13 @@ gns_status run_walk_probability(gns_ctx* c, const int32_t* train_nodes, int64_t 
 // gns_cache.hip
 // validates the graph and fills Layout::entry_rows
 hipError_t launch_count_nonzero_rows(gns_ctx* c, hipStream_t s, int32_t* d_out);
-// wait_for_it: enqueue chunks two at a time, with what follows a complete cache behind them, and look at the outcome until it
-// is complete or refused; otherwise enqueue a fixed number of chunks (later ones stand down once the cache is complete) and
-// return.
 // Draws of the first chunk of a cache draw: half as many again as the cache has nodes, which completes a cache of one
 // percent of the nodes on most graphs; further chunks are Layout::draw_chunk long.
 constexpr int32_t kDrawTile = 1024;
 constexpr int64_t first_draws(int64_t cache_size) { return cache_size + cache_size / 2 + 2048; }
+// wait_for_it: enqueue one chunk or two, with what follows a complete cache behind them, and look at the outcome, then two more
+// at a time until it is complete or refused; otherwise enqueue a fixed number of chunks (later ones stand down once the cache
+// is complete) and return.
 gns_status run_sample_cache(gns_ctx* c, uint64_t seed, uint64_t epoch, bool wait_for_it, hipStream_t s);
 gns_status activate_cache(gns_ctx* c);
 gns_status retire_cache(gns_ctx* c);

@@ -1574,11 +1574,12 @@ def test_walk_hot_nodes_in_lds(n, offsets):
 
 
 @pytest.mark.parametrize("flag_mode", [0, 1])
-@pytest.mark.parametrize("n", [1_310_021, 16_777_217, 17_000_003])
+@pytest.mark.parametrize("n", [1_310_021, 16_777_217, 17_000_003, 83_361_792, 83_361_793])
 def test_cache_filter_of_graphs_whose_bitmap_does_not_fit_lds(n, flag_mode):
     """Cache bitmaps beyond LDS are tested through groups of ids, tags of hot nodes and, on the larger of these graphs, pairs
     of cached nodes per group: a run of neighboring ids that are nearly all cached (groups with many), the last ids of the
-    graph, and nodes far apart (groups with one), sharing slots of the tags."""
+    graph, and nodes far apart (groups with one), sharing slots of the tags.  The last two sizes are the largest with that
+    filter, whose groups have up to 81 ids, and the smallest with the coarse bitmap."""
     rng = np.random.default_rng(n)
     dense = np.arange(n - 30_000, n)                            # up to the last node
     spread = rng.choice(n - 30_000, size=30_000, replace=False)
