@@ -892,10 +892,13 @@ bool first_layer_enters_seeds(const gns_config& config)
 }
 
 // Rows per wave of the two-stage sampler: as many as leave 32 waves for every CU (all it holds) at the layer's worst-case
-// number of rows, a power of two between 4 and 32.  That number is all the host knows; input layers have 0.2 (cache first) to
+// number of rows, a power of two between 4 and 32.  (A mini-batch's grid ends at 16 waves for every CU, so single ones take their
+// rows in more turns.)  That number is all the host knows; input layers have 0.2 (cache first) to
 // 0.5 of it (fan-outs 15, 10 on 1 M nodes), so their launches have fewer waves than that.  Layers of 4 x 12,600 rows, fan-out
 // 10: 25 us with 8 rows per wave, 26 with 16, 37 with 64; of 4 x 92,400 rows, fan-out 5: 36.5 us with 32, 37.5 with 64, 42
-// with 16 (twice the blocks).
+// with 16 (twice the blocks).  Mini-batches far below what their context takes have few waves of many rows: input layer of
+// four times 256 and 64 seeds where contexts take 1024 16.6 and 11.1 us, 128 where they take 2048 13.2; 25.5, 18.2 and 22.0 with
+// up to 64 rows per wave, half as many waves aimed at, five entries of a lane on their way and places by a count.
 static int wave_rows(const Group& g, int layer_index)
 {
     const gns_ctx* c = g.ctx[0];
