@@ -41,37 +41,81 @@ struct GatherArgs {
     const float* store;          // device store or device-visible pinned host store
 };
 
-// kLanes lanes per row; kVec: rows are moved as float4 (feat_dim % 4 == 0, 16-byte aligned bases)
-template <int kLanes, bool kVec>
+// Four consecutive floats at any 4-byte address, moved at once.
+typedef float Float4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// kLanes lanes per row, four floats a lane (F >= 4: where F is no multiple of four the last lane's reach back into those before).
+// Bound by the copy.  Two things stood in its way or in the aggregation's:
+//  - the chain of every row, node -> bitmap -> rank -> row.  A wave looks up the rows of its next kLanes turns at once, one
+//    per lane, and a turn is a read and a store.
+//  - what the copy left in the caches.  Cached rows are what the input layer's aggregation reads, some dozens of times each: stored
+//    plainly they are still there by then.  All other reads and stores pass the caches by, so as not to displace them.
+// Groups of four, on states that change from call to call, this kernel and the aggregation behind it: 1 M nodes (4 x 90 K rows of
+// 512 bytes) 66.5 + 73 -> 68 + 52 us (all stores past the caches 65 + 85, reads plain 61 + 66, all stores plain 65 + 73), with the
+// upper layers cache first 34 + 38.5 -> 32 + 31, 40 M nodes 78 + 54 -> 66 + 52; one mini-batch of 90 K rows 21 + 21.5 -> 20.5 + 16.4.
+template <int kLanes>
 __global__ void __launch_bounds__(kBlock) k_gather(GatherArgs a)
 {
     if (a.unless_negative && *a.unless_negative < 0) return;
-    const int lane = (int) (threadIdx.x % kLanes);
-    const int64_t groups_per_block = kBlock / kLanes;
-    const int64_t group = (int64_t) blockIdx.x * groups_per_block + threadIdx.x / kLanes;
-    const int64_t num_groups = (int64_t) gridDim.x * groups_per_block;
-    const int64_t F = a.feat_dim;
+    constexpr uint32_t kRows = kWave / kLanes;               // rows a wave copies in a turn
+    constexpr int32_t kNone = INT32_MIN;
     const GatherBatch q = a.b[blockIdx.y];
-    const int64_t count = q.num_nodes_dev ? (int64_t) *q.num_nodes_dev : (int64_t) q.num_nodes;
-    for (int64_t row = group; row < count; row += num_groups) {
+    const uint32_t count = (uint32_t) (q.num_nodes_dev ? *q.num_nodes_dev : q.num_nodes);
+    const uint32_t wave = blockIdx.x * (kBlock / kWave) + (uint32_t) __builtin_amdgcn_readfirstlane((int) (threadIdx.x >> 6));
+    const uint32_t stride = gridDim.x * (kBlock / kWave) * kRows;
+    const int64_t F = a.feat_dim;
+    for (uint32_t row0 = wave * kRows; row0 < count; row0 += stride * kLanes) {
+        const int lane = opaque_lane_id();
+        const uint32_t sub = (uint32_t) lane / kLanes;
+        // lane l: row l % kRows of turn l / kRows: its node, ~(its place in the cache table), or kNone
+        const uint64_t mine = row0 + (uint64_t) (lane / kRows) * stride + lane % kRows;
+        int32_t ref = kNone;
+        if (mine < count) {
+            const int32_t u = q.nodes[mine];
+            if (u >= 0 && (int64_t) u < a.n) {
+                ref = u;
+                if (a.use_cache) {
+                    const uint64_t word = a.cache_bitmap[u >> 6], bit = 1ull << (u & 63);
+                    if (word & bit) ref = ~(a.cache_prefix[u >> 6] + __popcll(word & (bit - 1ull)));
+                }
+            }
+        }
+        const uint32_t turns = (count - row0 + stride - 1) / stride;
+        for (uint32_t t = 0; t < turns && t < kLanes; ++t) {
+            const int32_t r = __shfl(ref, (int) (t * kRows + sub), kWave);
+            const uint32_t row = row0 + t * stride + sub;
+            if (row >= count) continue;
+            const float* src = r >= 0 ? a.store + (int64_t) r * F : a.cache_feat + (int64_t) ~r * F;
+            float* dst = q.out + (int64_t) row * F;
+            for (int64_t c = 4 * (lane % kLanes); c < F; c += 4 * kLanes) {
+                const int64_t at = c < F - 4 ? c : F - 4;
+                Float4u v = {0.f, 0.f, 0.f, 0.f};
+                if (r != kNone) v = __builtin_nontemporal_load(reinterpret_cast<const Float4u*>(src + at));
+                if (r < 0) {
+                    asm volatile("; cached row");            // (the two stores would become one, without the hint)
+                    *reinterpret_cast<Float4u*>(dst + at) = v;
+                    asm volatile("; cached row");
+                } else {
+                    __builtin_nontemporal_store(v, reinterpret_cast<Float4u*>(dst + at));
+                }
+            }
+        }
+    }
+}
+
+// Rows of fewer than four floats, a lane each.
+__global__ void __launch_bounds__(kBlock) k_gather_thin(GatherArgs a)
+{
+    if (a.unless_negative && *a.unless_negative < 0) return;
+    const GatherBatch q = a.b[blockIdx.y];
+    const int64_t count = q.num_nodes_dev ? *q.num_nodes_dev : q.num_nodes;
+    for (int64_t row = (int64_t) blockIdx.x * kBlock + threadIdx.x; row < count; row += (int64_t) gridDim.x * kBlock) {
         const int32_t u = q.nodes[row];
         const bool valid = u >= 0 && (int64_t) u < a.n;
-        const float* src = nullptr;
-        if (valid) {
-            if (a.use_cache && bitmap_test(a.cache_bitmap, (uint32_t) u))
-                src = a.cache_feat + (int64_t) bitmap_rank(a.cache_bitmap, a.cache_prefix, (uint32_t) u) * F;
-            else
-                src = a.store + (int64_t) u * F;
-        }
-        float* dst = q.out + row * F;
-        if (kVec) {
-            const float4* s4 = reinterpret_cast<const float4*>(src);
-            float4* d4 = reinterpret_cast<float4*>(dst);
-            for (int i = lane; i < (int) (F >> 2); i += kLanes)
-                store_streaming(d4 + i, valid ? s4[i] : make_float4(0.f, 0.f, 0.f, 0.f));
-        } else {
-            for (int i = lane; i < (int) F; i += kLanes) dst[i] = valid ? src[i] : 0.f;
-        }
+        const float* src = a.store + (int64_t) u * a.feat_dim;
+        if (valid && a.use_cache && bitmap_test(a.cache_bitmap, (uint32_t) u))
+            src = a.cache_feat + (int64_t) bitmap_rank(a.cache_bitmap, a.cache_prefix, (uint32_t) u) * a.feat_dim;
+        for (int i = 0; i < a.feat_dim; ++i) q.out[row * a.feat_dim + i] = valid ? src[i] : 0.f;
     }
 }
 
@@ -82,15 +126,14 @@ static inline int lanes_for(int64_t units)
     return l;
 }
 
-template <bool kVec>
 static void gather_dispatch(int lanes, dim3 blocks, hipStream_t s, const GatherArgs& a)
 {
     switch (lanes) {
-        case 4:  hipLaunchKernelGGL((k_gather<4, kVec>), blocks, dim3(kBlock), 0, s, a); break;
-        case 8:  hipLaunchKernelGGL((k_gather<8, kVec>), blocks, dim3(kBlock), 0, s, a); break;
-        case 16: hipLaunchKernelGGL((k_gather<16, kVec>), blocks, dim3(kBlock), 0, s, a); break;
-        case 32: hipLaunchKernelGGL((k_gather<32, kVec>), blocks, dim3(kBlock), 0, s, a); break;
-        default: hipLaunchKernelGGL((k_gather<64, kVec>), blocks, dim3(kBlock), 0, s, a); break;
+        case 4:  hipLaunchKernelGGL((k_gather<4>), blocks, dim3(kBlock), 0, s, a); break;
+        case 8:  hipLaunchKernelGGL((k_gather<8>), blocks, dim3(kBlock), 0, s, a); break;
+        case 16: hipLaunchKernelGGL((k_gather<16>), blocks, dim3(kBlock), 0, s, a); break;
+        case 32: hipLaunchKernelGGL((k_gather<32>), blocks, dim3(kBlock), 0, s, a); break;
+        default: hipLaunchKernelGGL((k_gather<64>), blocks, dim3(kBlock), 0, s, a); break;
     }
 }
 
@@ -105,7 +148,6 @@ hipError_t launch_gather(gns_ctx* const* ctxs, int count, const int32_t* const* 
     memset(&a, 0, sizeof(a));
     a.unless_negative = unless_negative;
     int64_t most = 0;
-    bool aligned = true;
     for (int b = 0; b < count; ++b) {
         GatherBatch& q = a.b[b];
         q.nodes = nodes[b];
@@ -116,7 +158,6 @@ hipError_t launch_gather(gns_ctx* const* ctxs, int count, const int32_t* const* 
             q.num_nodes = (int32_t) L.rows[c->config.num_layers];
         }
         if (q.num_nodes > most) most = q.num_nodes;
-        aligned = aligned && (reinterpret_cast<uintptr_t>(out[b]) & 15u) == 0;
     }
     if (most == 0) return hipSuccess;
     a.n = c->graph.num_nodes;
@@ -127,16 +168,16 @@ hipError_t launch_gather(gns_ctx* const* ctxs, int count, const int32_t* const* 
     a.cache_prefix = cache_ptr<int32_t>(c, L.cache_prefix, gen);
     a.cache_feat = cache_ptr<float>(c, L.cache_feat, gen);
     a.store = c->graph.feat_dev ? c->graph.feat_dev : c->graph.feat_host_pinned;
-    const int64_t F = a.feat_dim;
-    const bool vec = (F % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.store) & 15u) == 0) && aligned;
-    const int lanes = lanes_for(vec ? F / 4 : F);
-    const int64_t groups_per_block = kBlock / lanes;
-    int64_t blocks = (most + groups_per_block - 1) / groups_per_block;
-    const int64_t cap = (int64_t) c->num_cus * 8;        // what is resident together; beyond that a group copies several rows
+    const bool thin = a.feat_dim < 4;
+    const int lanes = lanes_for((a.feat_dim + 3) / 4);
+    const int64_t rows_per_block = thin ? kBlock : kBlock / lanes;
+    int64_t blocks = (most + rows_per_block - 1) / rows_per_block;
+    // what is resident together, of all batches; beyond that a group copies several rows (twice or four times as many: the same)
+    const int64_t cap = ((int64_t) c->num_cus * 8 + count - 1) / count;
     if (blocks > cap) blocks = cap;
     const dim3 grid((unsigned) blocks, (unsigned) count);
-    if (vec) gather_dispatch<true>(lanes, grid, s, a);
-    else     gather_dispatch<false>(lanes, grid, s, a);
+    if (thin) hipLaunchKernelGGL(k_gather_thin, grid, dim3(kBlock), 0, s, a);
+    else      gather_dispatch(lanes, grid, s, a);
     return hipGetLastError();
 }
 

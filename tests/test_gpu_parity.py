@@ -64,6 +64,33 @@ def test_feature_widths_and_host_store(F):
             gns.close()
 
 
+@pytest.mark.parametrize("F,count,on_host", [(1, 700, False), (3, 700, False), (4, 600_000, False), (5, 700, False), (17, 90_000, False),
+                                             (66, 700, True), (100, 700, False), (130, 700, False), (255, 5_000, True), (257, 700, False), (300, 700, False)])
+def test_gather_of_any_list(F, count, on_host):
+    """gns_gather_features alone on a list that no sampler made: cached and other nodes, repeated ones, ids outside the graph
+    (rows of zeros); widths around multiples of four and of the lanes per row, an output that is aligned to four bytes only,
+    more rows than a wave looks up at once, and nothing written past the last row."""
+    ip, ix = _small()
+    n = ip.numel() - 1
+    feat = _feat(n, F, seed=F)
+    gns = GpuGns(ip, ix, feat, fanouts=(4, 3), policies=(U, C), cache_size=n // 4, max_seeds=8, feat_on_host=on_host)
+    try:
+        B.gns_sample_cache(gns.ctx, 5, 0)
+        rng = np.random.default_rng(F)
+        nodes = rng.integers(-3, n + 3, size=count).astype(np.int32)
+        nodes[:4] = (-1, n, np.iinfo(np.int32).max, np.iinfo(np.int32).min)
+        buf = torch.full((count * F + 2,), 7.0, dtype=torch.float32, device="cuda:0")
+        out = buf[1:1 + count * F].view(count, F)
+        B.gns_gather_features(gns.ctx, torch.from_numpy(nodes).to("cuda:0"), count, out)
+        torch.cuda.synchronize()
+        ok = (nodes >= 0) & (nodes < n)
+        want = np.where(ok[:, None], feat.numpy()[np.where(ok, nodes, 0)], np.float32(0))
+        assert (out.cpu().numpy() == want).all()
+        assert float(buf[0]) == 7.0 and float(buf[-1]) == 7.0
+    finally:
+        gns.close()
+
+
 @pytest.mark.parametrize("F,rows,max_deg", [(128, 70_000, 5), (128, 3_000, 20), (64, 40_000, 9), (256, 20_000, 12),
                                             (100, 40_000, 9), (8, 5_000, 20), (1024, 600, 9)])
 def test_aggregate_on_hand_made_blocks(F, rows, max_deg):
