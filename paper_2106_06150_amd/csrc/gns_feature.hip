@@ -7,17 +7,25 @@
 #include "gns_device.hpp"
 #include <string.h>
 #include <stdlib.h>
+#include <type_traits>
 
 namespace gns {
 
+// Four consecutive floats at any 4-byte address, moved at once.
+typedef float Float4u __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ float4 load_floats(const char* p)
+{
+    const Float4u v = *reinterpret_cast<const Float4u*>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+
 // Output rows are written once and not read again by the writing kernel: a non-temporal store keeps
 // them from displacing the rows other waves still want from L2.
-__device__ __forceinline__ void store_streaming(float4* p, const float4& v)
+__device__ __forceinline__ void store_floats(char* p, const float4& r)
 {
-    __builtin_nontemporal_store(v.x, &p->x);
-    __builtin_nontemporal_store(v.y, &p->y);
-    __builtin_nontemporal_store(v.z, &p->z);
-    __builtin_nontemporal_store(v.w, &p->w);
+    const Float4u v = {r.x, r.y, r.z, r.w};
+    __builtin_nontemporal_store(v, reinterpret_cast<Float4u*>(p));
 }
 
 // One launch serves a group of mini-batches: blockIdx.y picks the batch.
@@ -40,9 +48,6 @@ struct GatherArgs {
     const float* cache_feat;
     const float* store;          // device store or device-visible pinned host store
 };
-
-// Four consecutive floats at any 4-byte address, moved at once.
-typedef float Float4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // kLanes lanes per row, four floats a lane (F >= 4: where F is no multiple of four the last lane's reach back into those before).
 // Bound by the copy.  Two things stood in its way or in the aggregation's:
@@ -204,89 +209,14 @@ struct AggArgs : AggBatch {
     int32_t feat_dim;
 };
 
-// Rows of at most kLanes float4 columns, one column per lane: the plain form of the loop below, for widths whose
-// rows do not start on cache-line boundaries or do not fill several columns per lane.  Branch-free inner loop:
-// the first kSlots lanes of a row's group read one edge each (index and weight, one coalesced read), every lane
-// then takes edge t from lane t of its group, so the reads of up to kSlots source rows are issued back to back;
-// in a slot past its row's end a lane group stands aside (weight 0 on zeros), rows with more than kSlots edges
-// take further rounds.  All lanes of the wave stay converged: trip counts are wave-uniform (the shuffles need
-// every source lane).
-template <int kLanes>
-__device__ __forceinline__ void aggregate_rows_one_column(const AggArgs& a, int64_t group, int64_t num_groups, int64_t count,
-                                                          uint32_t num_src)
-{
-    constexpr int kSlots = kLanes < 8 ? kLanes : 8;
-    const int lane = (int) (threadIdx.x % kLanes);
-    const int64_t F = a.feat_dim;
-    const int64_t F4 = F >> 2;
-    const int col = lane < (int) F4 ? lane : (int) F4 - 1;       // idle lanes repeat the last column
-    const bool has = lane < (int) F4;
-    const float4* x4 = reinterpret_cast<const float4*>(a.x_src) + col;
-    // row j of x_src starts at float4 index j * F4: a shift when F4 is a power of two and the product fits
-    // 32 bits (integer multiplies run at a quarter of the rate of other vector instructions)
-    const bool by_shift = (F4 & (F4 - 1)) == 0 && (uint64_t) num_src * (uint64_t) F4 < ((uint64_t) 1 << 32);
-    const uint32_t f4_shift = (uint32_t) __builtin_ctzll((unsigned long long) F4);
-    const int64_t trips = (count + num_groups - 1) / num_groups;                 // the same for every group
-    for (int64_t it = 0; it < trips; ++it) {
-        const int64_t row = group + it * num_groups;
-        const bool live = row < count;
-        int32_t b = 0, e = 0;
-        if (live) { b = a.indptr[row]; e = a.indptr[row + 1]; }
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int32_t q0 = b; __any(q0 < e); q0 += kSlots) {
-            const int32_t here = e - q0 < kSlots ? (e - q0 > 0 ? e - q0 : 0) : kSlots;   // edges of this round
-            const bool mine = lane < here;
-            uint32_t my_j = mine ? (uint32_t) a.indices[q0 + lane] : 0u;
-            float my_w = mine ? a.weights[q0 + lane] : 0.f;
-            const bool bad = my_j >= num_src;                    // an index outside [0, num_src) is skipped
-            if (bad) { my_j = 0u; my_w = 0.f; }
-            const bool any_bad = __any(bad && mine);
-            float4 x[kSlots];
-            float w[kSlots];
-#pragma unroll
-            for (int t = 0; t < kSlots; ++t) {
-                w[t] = 0.f;
-                x[t] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (t < 4 || __any(t < here)) {                  // slots no row of this wave needs are skipped
-                    const uint32_t j = (uint32_t) __shfl((int) my_j, t, kLanes);
-                    const float wt = __shfl(my_w, t, kLanes);
-                    if (t < here) {                              // a row without an edge in this slot stands aside
-                        w[t] = wt;
-                        x[t] = by_shift ? x4[j << f4_shift] : x4[(int64_t) j * F4];
-                    }
-                }
-            }
-            if (any_bad) {
-                // rare: a skipped edge must not contribute even a NaN of the row it was redirected to
-#pragma unroll
-                for (int t = 0; t < kSlots; ++t)
-                    if (__shfl((int) (bad && mine), t, kLanes)) x[t] = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-#pragma unroll
-            for (int t = 0; t < kSlots; ++t) {                    // edge order, one fma per term
-                if (t < 4 || __any(t < here)) {
-                    acc.x = fmaf(w[t], x[t].x, acc.x);
-                    acc.y = fmaf(w[t], x[t].y, acc.y);
-                    acc.z = fmaf(w[t], x[t].z, acc.z);
-                    acc.w = fmaf(w[t], x[t].w, acc.w);
-                }
-            }
-        }
-        if (e > b) {                                              // (a row without edges has read nothing: 0)
-            const float inv_n = 1.0f / (float) (e - b);           // one division per row, then four products
-            acc.x *= inv_n; acc.y *= inv_n; acc.z *= inv_n; acc.w *= inv_n;
-        }
-        if (live && has) store_streaming(reinterpret_cast<float4*>(a.out + row * F) + lane, acc);
-    }
-}
-
-// Rows whose features are float4-aligned and fit kLanes * kPer float4 columns: a group of kLanes lanes owns a
-// dst row, lane l accumulates columns l, l + kLanes, ... (kPer of them).  Branch-free inner loop: the first
-// kSlots lanes of the group hold one edge each (index and weight, one coalesced read), every lane then takes
+// Columns col0 .. col0 + 4 kLanes kPer - 1 of a call's rows (F >= 4): a group of kLanes lanes owns a dst row, lane l accumulates four
+// columns from col0 + 4 l on, and from 4 kLanes further on, ... (kPer times).  Any width and any alignment to four bytes: where F is
+// no multiple of four the last lane's columns reach back into those before, and two lanes compute and store the same.  Branch-free inner
+// loop: the first kSlots lanes of the group hold one edge each (index and weight, one coalesced read), every lane then takes
 // edge t from lane t of its group, so the reads of the source rows are issued back to back; in a slot past its
 // row's end a lane group stands aside (weight 0 on zeros: the texture addressers only work for lanes that take
-// part in a read), rows with more than kSlots edges take further rounds.  All lanes of the wave stay converged: trip counts are wave-uniform (the shuffles need
-// every source lane).
+// part in a read), rows with more than kSlots edges take further rounds.  All lanes of the wave stay converged: trip counts
+// are wave-uniform (the shuffles need every source lane).
 // A row is a chain of dependent accesses (row extent -> edges -> source rows -> store); it is software-pipelined
 // over the rows a group visits: while the source rows of row i are in flight, the edges of row i+1 and the
 // extent of row i+2 are being read.  (What bounds the kernel on 128-float rows is the rate at which the L2s
@@ -295,27 +225,28 @@ __device__ __forceinline__ void aggregate_rows_one_column(const AggArgs& a, int6
 // a few percent only.)
 // The hardware counts outstanding vector memory operations in order, and the compiler can only leave the
 // younger ones in flight across a use of an older one if it knows how many there are: a read or store inside
-// a branch makes it wait for everything.  Hence every access of the steady state is unconditional -- reads
+// a branch makes it wait for everything.  Hence the accesses of the steady state are unconditional -- reads
 // of rows or edges that do not exist go to a valid address (the first extent) and their value is replaced,
-// lanes past the last column repeat it, and the last trip, in which some groups have no row, stands apart -- and
-// only rare cases (a row with more than kSlots edges, slots beyond the fourth) sit in branches.
+// and the last trip, in which some groups have no row, stands apart -- and only rare cases (a row with more than
+// kSlots edges, slots beyond the fourth) sit in branches.  Lanes past the last column (kRagged) stand aside in the last of the
+// kPer reads and stores all the same: what a read costs the texture addressers is more than the wait.
 // kOff32: every byte offset into x_src fits 32 bits and row index and row size fit 24 bits, so an address is
 // the uniform base plus one 32-bit vector offset (one multiply-add per load).
-template <int kLanes, int kPer, bool kOff32>
-__device__ __forceinline__ void aggregate_rows(const AggArgs& a, uint32_t group, uint32_t num_groups, uint32_t count,
+template <int kLanes, int kPer, bool kRagged, bool kQuotient, bool kOff32>
+__device__ __forceinline__ void aggregate_rows(const AggArgs& a, uint32_t col0, uint32_t group, uint32_t num_groups, uint32_t count,
                                                uint32_t num_src)
 {
     constexpr int kSlots = kLanes < 8 ? kLanes : 8;                      // edges a round covers (one per lane)
-    constexpr int kFlight = (kPer >= 4 && kSlots > 4) ? 5 : kSlots;     // source rows read together
+    constexpr int kFlight = (kPer >= 3 && kSlots > 4) ? 5 : kSlots;     // source rows read together
     const int lane = (int) (threadIdx.x % kLanes);
     const uint32_t F = (uint32_t) a.feat_dim;
-    const uint32_t F4 = F >> 2;
     const uint32_t row_bytes = F * 4u;
-    uint32_t col_bytes[kPer];                   // lanes past the last column repeat it
+    const bool in_last = !kRagged || col0 + 4u * ((uint32_t) lane + (uint32_t) (kPer - 1) * kLanes) < F;
+    uint32_t col_bytes[kPer];
 #pragma unroll
     for (int p = 0; p < kPer; ++p) {
-        const uint32_t cidx = (uint32_t) lane + (uint32_t) p * kLanes;
-        col_bytes[p] = (cidx < F4 ? cidx : F4 - 1u) * 16u;
+        const uint32_t c = col0 + 4u * ((uint32_t) lane + (uint32_t) p * kLanes);
+        col_bytes[p] = (c < F - 4u ? c : F - 4u) * 4u;
     }
     const char* x_bytes = reinterpret_cast<const char*>(a.x_src);
     const uint32_t trips = (count + num_groups - 1u) / num_groups;       // the same for every group (count > 0)
@@ -366,12 +297,13 @@ __device__ __forceinline__ void aggregate_rows(const AggArgs& a, uint32_t group,
                     w[u] = wt;
 #pragma unroll
                     for (int p = 0; p < kPer; ++p) {
+                        if (kRagged && p == kPer - 1 && !in_last) continue;
                         if (kOff32) {
                             const uint32_t off = __umul24(j, row_bytes) + col_bytes[p];     // both factors < 2^24
-                            x[u][p] = *reinterpret_cast<const float4*>(x_bytes + off);
+                            x[u][p] = load_floats(x_bytes + off);
                         } else {
                             const uint64_t off = (uint64_t) j * row_bytes + col_bytes[p];
-                            x[u][p] = *reinterpret_cast<const float4*>(x_bytes + off);
+                            x[u][p] = load_floats(x_bytes + off);
                         }
                     }
                 }
@@ -419,13 +351,21 @@ __device__ __forceinline__ void aggregate_rows(const AggArgs& a, uint32_t group,
             }
         }
         const bool some = e > b;                                           // (a row without edges has read nothing: 0)
-        const float inv_n = some ? 1.0f / (float) (e - b) : 0.f;           // one division per row, then the products
-        float4* o4 = reinterpret_cast<float4*>(a.out + (int64_t) row * F);
+        const float n = some ? (float) (e - b) : 1.f;
+        const float inv_n = some ? 1.0f / n : 0.f;                         // one division per row, then the products
+        // kQuotient: x / n to the last bit, from the product and what it leaves (not for infinities, whose product it is)
+        auto mean = [&](float x) {
+            const float q = x * inv_n;
+            if (!kQuotient) return q;
+            const float left = fmaf(-q, n, x);
+            return left == left ? fmaf(left, inv_n, q) : q;
+        };
+        char* o = reinterpret_cast<char*>(a.out + (int64_t) row * F);
 #pragma unroll
         for (int p = 0; p < kPer; ++p) {
-            const float4 r = make_float4(acc[p].x * inv_n, acc[p].y * inv_n, acc[p].z * inv_n, acc[p].w * inv_n);
-            // a lane past the last column has computed the last column once more: it stores the same value there
-            store(o4 + (col_bytes[p] >> 4), r);
+            if (kRagged && p == kPer - 1 && !in_last) continue;
+            const float4 r = make_float4(mean(acc[p].x), mean(acc[p].y), mean(acc[p].z), mean(acc[p].w));
+            store(o + col_bytes[p], r);
         }
     };
 
@@ -445,102 +385,129 @@ __device__ __forceinline__ void aggregate_rows(const AggArgs& a, uint32_t group,
                   extent(it + 2, b2, e2);       // two rows ahead
                   edge(b1, e1, j1, w1);         // one row ahead
               },
-              [](float4* dst, const float4& r) { store_streaming(dst, r); });
+              [](char* dst, const float4& r) { store_floats(dst, r); });
         b0 = b1; e0 = e1; b1 = b2; e1 = e2; j0 = j1; w0 = w1;
     }
     const uint32_t row = group + (trips - 1u) * num_groups;
     const bool live = row < count;
-    visit(row, b0, e0, j0, w0, []() {}, [&](float4* dst, const float4& r) { if (live) store_streaming(dst, r); });
+    visit(row, b0, e0, j0, w0, []() {}, [&](char* dst, const float4& r) { if (live) store_floats(dst, r); });
 }
 
-template <int kLanes, int kPer, bool kVec>
+// Rows of more columns than the lanes take are visited once per window of columns (blockIdx.z).
+template <int kLanes, int kPer, bool kRagged, bool kQuotient>
 __global__ void __launch_bounds__(kBlock) k_aggregate(AggGroup g)
 {
     AggArgs a;
     static_cast<AggBatch&>(a) = g.b[blockIdx.y];
     a.feat_dim = g.feat_dim;
     const int lane = (int) (threadIdx.x % kLanes);
-    const int64_t groups_per_block = kBlock / kLanes;
-    const int64_t group = (int64_t) blockIdx.x * groups_per_block + threadIdx.x / kLanes;
-    const int64_t num_groups = (int64_t) gridDim.x * groups_per_block;
-    const int64_t F = a.feat_dim;
+    const uint32_t groups_per_block = kBlock / kLanes;
+    const uint32_t group = blockIdx.x * groups_per_block + threadIdx.x / kLanes;
+    const uint32_t num_groups = gridDim.x * groups_per_block;
+    const uint32_t F = (uint32_t) a.feat_dim;
+    const int64_t rows = a.num_dst_dev ? (int64_t) *a.num_dst_dev : (int64_t) a.num_dst;
+    const uint32_t num_src = (uint32_t) (a.num_src_dev ? *a.num_src_dev : a.num_src);
+    if (rows <= 0) return;
+    const uint32_t count = (uint32_t) rows;
+    if (num_src == 0) {             // no source row to read (and none may be touched): every edge is skipped
+        for (int64_t row = group; row < rows; row += num_groups)
+            for (uint32_t i = (uint32_t) lane; i < F; i += kLanes) a.out[row * F + i] = 0.f;
+        return;
+    }
+    const bool off32 = (uint64_t) num_src * F * 4u < ((uint64_t) 1 << 32) && num_src < (1u << 24) && F < (1u << 22);
+    const uint32_t col0 = blockIdx.z * (4 * kLanes * kPer);
+    if (off32) aggregate_rows<kLanes, kPer, kRagged, kQuotient, true>(a, col0, group, num_groups, count, num_src);
+    else       aggregate_rows<kLanes, kPer, kRagged, kQuotient, false>(a, col0, group, num_groups, count, num_src);
+}
+
+// Rows of fewer than four floats, a lane per column.
+__global__ void __launch_bounds__(kBlock) k_aggregate_thin(AggGroup g)
+{
+    const AggBatch a = g.b[blockIdx.y];
+    const int64_t F = g.feat_dim;
+    const int i = (int) (threadIdx.x % 4);
     const int64_t count = a.num_dst_dev ? (int64_t) *a.num_dst_dev : (int64_t) a.num_dst;
     const uint32_t num_src = (uint32_t) (a.num_src_dev ? *a.num_src_dev : a.num_src);
-    constexpr int kEdges = 8;       // edges whose rows are in flight together
-    if (count <= 0) return;
-    if (num_src == 0) {             // no source row to read (and none may be touched): every edge is skipped
-        for (int64_t row = group; row < count; row += num_groups)
-            for (int i = lane; i < (int) F; i += kLanes) a.out[row * F + i] = 0.f;
-        return;
-    }
-    if (kVec && kPer == 1 && F <= 4 * kLanes) {
-        aggregate_rows_one_column<kLanes>(a, group, num_groups, count, num_src);
-        return;
-    }
-    if (kVec && F <= 4 * kLanes * kPer) {
-        if ((uint64_t) num_src * (uint64_t) F * 4u < ((uint64_t) 1 << 32) && num_src < (1u << 24) && F < (1 << 22))
-            aggregate_rows<kLanes, kPer, true>(a, (uint32_t) group, (uint32_t) num_groups, (uint32_t) count, num_src);
-        else
-            aggregate_rows<kLanes, kPer, false>(a, (uint32_t) group, (uint32_t) num_groups, (uint32_t) count, num_src);
-        return;
-    }
-    for (int64_t row = group; row < count; row += num_groups) {
+    if (i >= F) return;
+    for (int64_t row = (int64_t) blockIdx.x * (kBlock / 4) + threadIdx.x / 4; row < count; row += (int64_t) gridDim.x * (kBlock / 4)) {
         const int32_t b = a.indptr[row], e = a.indptr[row + 1];
-        const float n_v = (float) (e - b);
-        if (kVec) {
-            const float4* x4 = reinterpret_cast<const float4*>(a.x_src);
-            float4* o4 = reinterpret_cast<float4*>(a.out + row * F);
-            const int64_t F4 = F >> 2;
-            for (int i = lane; i < (int) F4; i += kLanes) {
-                float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-                for (int32_t q0 = b; q0 < e; q0 += kEdges) {
-                    float w[kEdges];
-                    float4 x[kEdges];
-#pragma unroll
-                    for (int t = 0; t < kEdges; ++t) {
-                        const int32_t q = q0 + t;
-                        const uint32_t j = (q < e) ? (uint32_t) a.indices[q] : 0xFFFFFFFFu;
-                        const bool ok = j < num_src;
-                        w[t] = ok ? a.weights[q] : 0.f;
-                        x[t] = x4[(int64_t) (ok ? j : 0u) * F4 + i];
-                        if (!ok) x[t] = make_float4(0.f, 0.f, 0.f, 0.f);
-                    }
-#pragma unroll
-                    for (int t = 0; t < kEdges; ++t) {       // edge order, one fma per term
-                        if (q0 + t < e) {
-                            acc.x = fmaf(w[t], x[t].x, acc.x);
-                            acc.y = fmaf(w[t], x[t].y, acc.y);
-                            acc.z = fmaf(w[t], x[t].z, acc.z);
-                            acc.w = fmaf(w[t], x[t].w, acc.w);
-                        }
-                    }
-                }
-                if (e > b) { acc.x /= n_v; acc.y /= n_v; acc.z /= n_v; acc.w /= n_v; }
-                o4[i] = acc;
-            }
-        } else {
-            for (int i = lane; i < (int) F; i += kLanes) {
-                float acc = 0.f;
-                for (int32_t q = b; q < e; ++q) {
-                    const uint32_t j = (uint32_t) a.indices[q];
-                    if (j < num_src) acc = fmaf(a.weights[q], a.x_src[(int64_t) j * F + i], acc);
-                }
-                if (e > b) acc /= n_v;
-                a.out[row * F + i] = acc;
-            }
+        float acc = 0.f;
+        for (int32_t q = b; q < e; ++q) {
+            const uint32_t j = (uint32_t) a.indices[q];
+            if (j < num_src) acc = fmaf(a.weights[q], a.x_src[(int64_t) j * F + i], acc);
         }
+        if (e > b) acc /= (float) (e - b);
+        a.out[row * F + i] = acc;
     }
 }
 
-template <int kPer, bool kVec>
-static void aggregate_dispatch(int lanes, dim3 blocks, hipStream_t s, const AggGroup& a)
+// Lanes per row and columns (of four floats) per lane, for rows of F4 columns.  A read costs the lanes that take part in it and the
+// lines it touches: so few lanes are left over, and as much of a row as possible is read as one piece, unless rows are whole
+// lines (F4 % 8 == 0), of which eight lanes read one each time.  us for four mini-batches of 85 K rows (1 M nodes) behind their gather, lanes x columns:
+//   F4   8 x 1   8 x 2   8 x 3   8 x 4  16 x 2  16 x 3  16 x 4  32 x 2     one column a lane, no row ahead
+//    5    23.8    24.4                                                      29
+//    9            31.8    31.0            36.5
+//   12            34.0            38.2                                      44
+//   17                    45.4    45.4    49.5                              70
+//   21                    53.0    56.4    52.5
+//   24                    40.4    45.3    49.2                              46
+//   25                            59.1    55.4                              72
+//   31                            69.2    62.2
+//   32                            49.3    53.4
+//   33                                            70.2    72.4    81.3
+//   40                                            65.5    75.0    80.0
+//   48                                            75.2    80.7    83.4      81
+//   50                                                    98.7    93.4     129
+//   64                                                   101.9    98.0
+// Widths that are no multiple of four took 91 (F = 19), 285 (99) and 623 (255) with a float per lane, an edge at a time.
+struct AggLanes {
+    int lanes, per;
+};
+
+static AggLanes aggregate_lanes(int64_t F4)
 {
-    switch (lanes) {
-        case 4:  hipLaunchKernelGGL((k_aggregate<4, kPer, kVec>), blocks, dim3(kBlock), 0, s, a); break;
-        case 8:  hipLaunchKernelGGL((k_aggregate<8, kPer, kVec>), blocks, dim3(kBlock), 0, s, a); break;
-        case 16: hipLaunchKernelGGL((k_aggregate<16, kPer, kVec>), blocks, dim3(kBlock), 0, s, a); break;
-        case 32: hipLaunchKernelGGL((k_aggregate<32, kPer, kVec>), blocks, dim3(kBlock), 0, s, a); break;
-        default: hipLaunchKernelGGL((k_aggregate<64, kPer, kVec>), blocks, dim3(kBlock), 0, s, a); break;
+    if (F4 <= 4) return {4, 1};
+    if (F4 <= 8) return {8, 1};
+    if (F4 <= 16) return {8, 2};
+    if (F4 <= 20 || F4 == 24) return {8, 3};
+    if (F4 == 32) return {8, 4};
+    if (F4 <= 32) return {16, 2};
+    if (F4 <= 48) return {16, 3};
+    if (F4 <= 64) return {32, 2};
+    if (F4 <= 96) return {32, 3};
+    if (F4 <= 128) return {32, 4};
+    if (F4 <= 192) return {64, 3};
+    return {64, 4};
+}
+
+static void aggregate_dispatch(AggLanes q, bool full, bool quotient, dim3 grid, hipStream_t s, const AggGroup& a)
+{
+    auto go = [&](auto lanes, auto per, auto ragged, auto quotient) {
+        hipLaunchKernelGGL((k_aggregate<decltype(lanes)::value, decltype(per)::value, decltype(ragged)::value, decltype(quotient)::value>), grid,
+                           dim3(kBlock), 0, s, a);
+    };
+    auto with = [&](auto lanes, auto per) {
+        if (quotient)  go(lanes, per, std::true_type(), std::true_type());
+        else if (full) go(lanes, per, std::false_type(), std::false_type());
+        else           go(lanes, per, std::true_type(), std::false_type());
+    };
+    using std::integral_constant;
+    if (q.lanes == 4)       with(integral_constant<int, 4>(), integral_constant<int, 1>());
+    else if (q.lanes == 8) {
+        if (q.per == 1)      with(integral_constant<int, 8>(), integral_constant<int, 1>());
+        else if (q.per == 2) with(integral_constant<int, 8>(), integral_constant<int, 2>());
+        else if (q.per == 3) with(integral_constant<int, 8>(), integral_constant<int, 3>());
+        else                 with(integral_constant<int, 8>(), integral_constant<int, 4>());
+    } else if (q.lanes == 16) {
+        if (q.per == 2)      with(integral_constant<int, 16>(), integral_constant<int, 2>());
+        else                 with(integral_constant<int, 16>(), integral_constant<int, 3>());
+    } else if (q.lanes == 32) {
+        if (q.per == 2)      with(integral_constant<int, 32>(), integral_constant<int, 2>());
+        else if (q.per == 3) with(integral_constant<int, 32>(), integral_constant<int, 3>());
+        else                 with(integral_constant<int, 32>(), integral_constant<int, 4>());
+    } else {
+        if (q.per == 3)      with(integral_constant<int, 64>(), integral_constant<int, 3>());
+        else                 with(integral_constant<int, 64>(), integral_constant<int, 4>());
     }
 }
 
@@ -575,27 +542,22 @@ hipError_t launch_aggregate(gns_ctx* const* ctxs, int count, const gns_block* co
     }
     if (most == 0) return hipSuccess;
     a.feat_dim = feat_dim;
-    const int64_t F = feat_dim;
-    const bool vec = (F % 4 == 0) && aligned;
-    // float4 columns per lane.  Rows that start on cache-line boundaries and are at least two lines long are spread
-    // over few lanes with several columns each, which keeps the per-edge bookkeeping small (on 128-float rows 8 lanes
-    // x 4 columns is ahead of 16 x 2 and 32 x 1 once other kernels share the chip); other widths take one column per
-    // lane, so that a row is read as one contiguous piece.
-    const int64_t F4 = F / 4;
-    const int per = (vec && F4 % 8 == 0) ? (F4 >= 32 ? 4 : (F4 >= 16 ? 2 : 1)) : 1;
-    const int lanes = lanes_for(vec ? (F4 + per - 1) / per : F);
-    const int64_t groups_per_block = kBlock / lanes;
+    const int64_t F4 = ((int64_t) feat_dim + 3) / 4;
+    const bool thin = feat_dim < 4;
+    // x / n is rounded once, not as a product with 1 / n (four more instructions a float, up to 6 of 76 us at F = 130):
+    // widths and bases that are no multiple of four floats, and wide rows
+    const bool quotient = feat_dim % 4 != 0 || !aligned || feat_dim > 1024 || (feat_dim > 256 && F4 % 8 != 0);
+    const AggLanes q = aggregate_lanes(F4);
+    const int64_t groups_per_block = kBlock / q.lanes;
     int64_t blocks = (most + groups_per_block - 1) / groups_per_block;
-    // Several columns per lane: about the blocks that are resident together (beyond that a group visits several
-    // rows, which its pipeline wants anyway); a larger grid is no faster alone and 7 % slower next to another
-    // stream's kernels.
-    const int64_t cap = (int64_t) c->num_cus * (per > 1 ? 4 : 16);
+    // About the blocks that are resident together (beyond that a group visits several rows, which its pipeline wants anyway);
+    // a larger grid is no faster alone and 7 % slower next to another stream's kernels.
+    const int64_t cap = (int64_t) c->num_cus * (thin ? 16 : 4);
     if (blocks > cap) blocks = cap;
-    const dim3 grid((unsigned) blocks, (unsigned) count);
-    if (!vec) aggregate_dispatch<1, false>(lanes, grid, s, a);
-    else if (per == 4) aggregate_dispatch<4, true>(lanes, grid, s, a);
-    else if (per == 2) aggregate_dispatch<2, true>(lanes, grid, s, a);
-    else aggregate_dispatch<1, true>(lanes, grid, s, a);
+    const dim3 grid((unsigned) blocks, (unsigned) count, (unsigned) ((F4 + q.lanes * q.per - 1) / (q.lanes * q.per)));
+    if (thin) hipLaunchKernelGGL(k_aggregate_thin, grid, dim3(kBlock), 0, s, a);
+    // (32 lanes: the form for rows that leave lanes over is ahead where none are, 98 us for 105 at F = 256)
+    else      aggregate_dispatch(q, feat_dim == 4 * q.lanes * q.per && q.lanes != 32, quotient, grid, s, a);
     return hipGetLastError();
 }
 

@@ -132,6 +132,53 @@ def test_aggregate_on_hand_made_blocks(F, rows, max_deg):
         gns.close()
 
 
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("F", [1, 3, 4, 5, 16, 17, 31, 32, 33, 64, 66, 80, 81, 96, 99, 127, 128, 129, 161, 192, 193, 255, 256, 257, 300, 512, 516, 1023, 1028, 2100])
+def test_aggregate_widths(F, shift):
+    """gns_aggregate at the widths where its lanes per row change, and at buffers aligned to four bytes only: rows with 0..9 edges, one
+    edge out of range (it is skipped), nothing written around the output."""
+    rng = np.random.default_rng(F)
+    rows = 3000 if F < 300 else 500
+    num_src = rows + 200
+    deg = rng.integers(0, 10, size=rows)
+    deg[0] = 3
+    indptr = np.zeros(rows + 1, dtype=np.int32)
+    indptr[1:] = np.cumsum(deg)
+    E = int(indptr[-1])
+    indices = rng.integers(0, num_src, size=E).astype(np.int32)
+    weights = rng.uniform(0.5, 40.0, size=E).astype(np.float32)
+    x = rng.standard_normal((num_src, F)).astype(np.float32)
+    x_ref, w_ref = x.astype(np.float64), weights.astype(np.float64)
+    w_ref[1] = 0.0                                                       # of the edge that is skipped
+    ref, scale = np.zeros((rows, F)), np.zeros((rows, F))
+    owner = np.repeat(np.arange(rows), deg)
+    np.add.at(ref, owner, w_ref[:, None] * x_ref[indices])
+    np.add.at(scale, owner, np.abs(w_ref[:, None] * x_ref[indices]))
+    ref /= np.maximum(deg, 1)[:, None]
+    scale /= np.maximum(deg, 1)[:, None]
+    indices[1] = num_src
+    dev = torch.device("cuda:0")
+    ip, ix = _small(n=300)
+    gns = GpuGns(ip, ix, None, fanouts=(2,), policies=(U,), cache_size=10, max_seeds=8)
+    try:
+        t = {k: torch.from_numpy(v).to(dev) for k, v in dict(indptr=indptr, indices=indices, weights=weights).items()}
+        xs = torch.zeros(num_src * F + 4, dtype=torch.float32, device=dev)[shift:shift + num_src * F].view(num_src, F)
+        xs.copy_(torch.from_numpy(x))
+        blk = B.gns_block()
+        blk.num_dst, blk.num_src, blk.num_edges = rows, num_src, E
+        blk.indptr, blk.indices, blk.weights = t["indptr"].data_ptr(), t["indices"].data_ptr(), t["weights"].data_ptr()
+        buf = torch.full((rows * F + 8,), 7.0, dtype=torch.float32, device=dev)
+        out = buf[4 + shift:4 + shift + rows * F].view(rows, F)
+        B.gns_aggregate(gns.ctx, blk, xs, F, out)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy()
+        assert (got[deg == 0] == 0).all()
+        assert (np.abs(got.astype(np.float64) - ref) <= AGG_RTOL * scale).all()
+        assert (buf[:4 + shift] == 7.0).all() and (buf[4 + shift + rows * F:] == 7.0).all()
+    finally:
+        gns.close()
+
+
 @pytest.mark.parametrize("policies", [(U, C), (CF, CF)])
 def test_unbiased_weight_mode(policies):
     ip, ix = _small()
