@@ -132,6 +132,16 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
         L.max_chunks = g->num_entries / 64 + 2 * L.max_rows + 64;
         if (L.max_chunks >= (int64_t) 1 << 31) GNS_BAD("graph too large for 32-bit chunk ids");
         L.plan_desc = take((size_t) L.max_chunks * 4);
+        // With the induced subgraph no layer has a work list of chunks.
+        const int last = cfg->num_layers - 1;
+        const int64_t bytes = (C + 63) / 64 * 64;
+        L.slot_tile = kSlotTile;
+        while (L.slot_tile < kSlotTile * kSlotReads && (bytes > L.slot_tile * 128 || bytes > L.slot_tile * L.mark_tiles)) L.slot_tile *= 2;
+        const bool one_launch = bytes <= kSlotsMax;
+        if (cfg->flag_mode == GNS_FLAGS_PER_CACHE && last > 0 && cfg->policy[last] == GNS_CACHE_ONLY &&
+            (one_launch || bytes <= L.slot_tile * L.mark_tiles) &&                      // (places for the tiles' sums)
+            bytes + (one_launch ? 0 : bytes / 64 * (int64_t) sizeof(SlotWord)) <= L.max_chunks * 4)
+            L.slot_marks = bytes;
     }
     // last of the per-batch sections: gns_sample_blocks_static keeps this one elsewhere on large graphs
     L.table = take((size_t) n * 4);
@@ -188,7 +198,7 @@ bool compute_layout(const gns_graph* g, const gns_config* cfg, Layout* out, char
     L.cache_feat = take((size_t) (C > 0 ? C : 1) * (size_t) (g->feat_dim > 0 ? g->feat_dim : 1) * 4);
     if (uses_cache) {
         if (cfg->flag_mode == GNS_FLAGS_PER_BATCH) L.edge_flags = take((size_t) (g->num_entries / 64 + 1) * 8);
-        L.node_pc = take((size_t) n * 4);
+        L.node_pc = take((size_t) n * (L.slot_marks ? sizeof(CachedNode) : 4));
         if (cfg->flag_mode == GNS_FLAGS_PER_CACHE) {
             L.srec = take((size_t) (g->num_entries / 64 + 1) * 16);
             L.s_nodes = take((size_t) g->num_entries * 4);
@@ -239,8 +249,12 @@ gns_status enqueue_batch(const Group& g, const BeginDyn& d, hipStream_t s)
         if (e != hipSuccess) return ctx_fail(c, GNS_EHIP, "sample layer", e);
         {
             StageTimer t(c, GNS_STAGE_FINISH + i, s);
-            e = launch_finish_layer(g, i, s);
-            if (e == hipSuccess && i == nl - 1) e = launch_relabel(g, i, s);
+            if (i == nl - 1 && finishes_at_once(c)) {
+                e = launch_finish_cached(g, s);
+            } else {
+                e = launch_finish_layer(g, i, s);
+                if (e == hipSuccess && i == nl - 1) e = launch_relabel(g, i, s);
+            }
         }
         if (e != hipSuccess) return ctx_fail(c, GNS_EHIP, "finish layer", e);
     }
@@ -359,9 +373,10 @@ static void graph_release(BatchGraph& g)
 // 82, of five 77 and 82 (two sequences of groups of two: nine 98 and 101, seven 84 and 85).  So from eight launches on where
 // the family's sequences come on different streams, else from ten on, where replaying halves the host's time (fourteen on
 // one stream: the host 116 us directly, 60 replayed; the device 131 and 136).
-static bool replayed(const gns_config& config, bool side_by_side)
+static bool replayed(const gns_ctx* c, bool side_by_side)
 {
-    int launches = first_layer_enters_seeds(config) ? 1 : 2;                  // the last relabel, k_batch_begin
+    const gns_config& config = c->config;
+    int launches = (finishes_at_once(c) ? 0 : 1) + (first_layer_enters_seeds(config) ? 0 : 1);        // the last relabel, k_batch_begin
     for (int i = 0; i < config.num_layers; ++i) launches += direct_layer(config, i) ? 2 : 4;
     return launches > (side_by_side ? 7 : 9);
 }
@@ -909,7 +924,7 @@ gns_status gns_sample_blocks_group(gns_ctx* const* ctxs, int32_t count, const ui
     const bool side_by_side = root->has_sampled && root->last_sampled_on != s;
     root->has_sampled = true;
     root->last_sampled_on = s;
-    if (lead->prof_mask == 0 && lead->cap_stream && replayed(lead->config, side_by_side) && !small_batches(g, dyn)) st = launch_batch_graph(g, dyn, s);
+    if (lead->prof_mask == 0 && lead->cap_stream && replayed(lead, side_by_side) && !small_batches(g, dyn)) st = launch_batch_graph(g, dyn, s);
     else                                                                                   st = enqueue_batch(g, dyn, s);
     if (st != GNS_OK) return st;
     const int nl = lead->config.num_layers;

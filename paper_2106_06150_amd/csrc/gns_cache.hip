@@ -233,7 +233,8 @@ struct IndexArgs {
     int64_t cache_size;
     const void* prob_prefix;
     int64_t prob_total;
-    float* node_inv_pc;
+    float* node_inv_pc;        // or
+    CachedNode* node_slot;     //   this, and the other null
     CacheFilter filter;        // or null pointers
     int64_t hot_from;          // rows shorter than this stay out of its slots
     const void* g_indptr;      // the graph's offsets (the filter goes by row lengths whatever the probability)
@@ -284,7 +285,9 @@ __global__ void __launch_bounds__(kBlock) k_cache_index(IndexArgs a)
         const int64_t deg = load_off<OffT>(a.prob_prefix, (int64_t) u + 1) - load_off<OffT>(a.prob_prefix, u);
         const double p = (double) deg / (double) a.prob_total;
         const double pc = (p >= 1.0) ? 1.0 : -expm1((double) a.cache_size * log1p(-p));
-        a.node_inv_pc[u] = (float) (1.0 / pc);
+        const float inv_pc = (float) (1.0 / pc);
+        if (a.node_slot) a.node_slot[u] = {inv_pc, before + i};
+        else             a.node_inv_pc[u] = inv_pc;
         if (a.filter.keys) {
             const int64_t len = load_off_rt(a.g_indptr, a.g_i64, (int64_t) u + 1) - load_off_rt(a.g_indptr, a.g_i64, u);
             const unsigned long long key = ((unsigned long long) (len < 0xFFFFFFFFll ? len : 0xFFFFFFFFll) << 32) | (uint32_t) u;
@@ -546,7 +549,8 @@ gns_status run_sample_cache(gns_ctx* c, uint64_t seed, uint64_t epoch, bool wait
     x.cache_size = C;
     x.prob_prefix = prob_prefix;
     x.prob_total = (int64_t) prob_total;
-    x.node_inv_pc = cache_ptr<float>(c, L.node_pc, gen);
+    x.node_inv_pc = L.slot_marks ? nullptr : cache_ptr<float>(c, L.node_pc, gen);
+    x.node_slot = L.slot_marks ? cache_ptr<CachedNode>(c, L.node_pc, gen) : nullptr;
     x.filter = cache_filter(c, gen);
     // Of |C| cached nodes kFilterHot have a slot: nodes that are unlikely to be among them (on a power law the rows of the C-th
     // node are ten times the average, and lengths fall about as ranks grow) stay out of the atomics.

@@ -11,6 +11,9 @@ constexpr int kItems = 8;                   // items per thread in a scan tile
 constexpr int kTile = kBlock * kItems;      // 2048 items per scan tile
 constexpr int kMarkTileMin = 64;             // frontier mark bitmap: words per tile, a power of two chosen per graph
 constexpr int kMarkTileMax = 32 * kBlock;    //   so that the tiles number about a hundred (at most 32 words per thread)
+constexpr int kSlotsMax = 1 << 16;           // slots of a cache whose new nodes are finished in one launch, see k_finish_cached
+constexpr int kSlotTile = 16 * kBlock;       // slots of a tile of the union step beyond: so many times 1 to kSlotReads
+constexpr int kSlotReads = 8;
 constexpr int kMarkCap = 1024;               // marked words of a tile the union step keeps in LDS at a time
 
 constexpr uint32_t kTagCache = 0x43414348u;     // 'CACH'

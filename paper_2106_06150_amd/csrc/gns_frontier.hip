@@ -12,6 +12,7 @@
 //   relabel  every sampled edge looks its neighbor's local id up and is
 //            compacted to its CSR position (inside the next layer's first sampler
 //            launch; the last layer has a launch of its own, which also writes the counts to the host)
+//   finish   union and relabel of an input layer that samples from the cache only (k_finish_cached)
 // Sorted order comes from walking the bitmap, so the result does not depend on
 // the order in which threads ran.
 #include <string.h>
@@ -67,6 +68,7 @@ __global__ void __launch_bounds__(kBlock) k_batch_begin(LayerArgs g, BeginDyn d)
     const NodeTable tab = bind_table(g, b, d.stamp[b]);
     const int32_t q = block * kBlock + (int32_t) threadIdx.x;
     if (q == 0) begin_state(g, d, b);
+    clear_slot_marks(g, b, block);
     if (q < num_seeds) {
         const int32_t u = d.seeds[b][q];
         enter_seed(g, d, b, tab, q, u, seed_extent(g, u), false);
@@ -89,6 +91,7 @@ void fill_group_args(const Group& g, LayerArgs* out)
     o.table_shift = L.table_shift;
     for (int p = 0; p < 2; ++p) { o.s_nbr[p] = L.s_nbr[p]; o.s_w[p] = L.s_w[p]; o.s_cnt[p] = L.s_cnt[p]; }
     o.plan_desc = L.plan_desc;
+    o.slot_marks = (uint64_t) L.slot_marks;
     o.sums_rows = L.sums_rows; o.tile_sums = L.tile_sums; o.row_sums = L.row_sums; o.plan_sums = L.plan_sums;
     o.cache_block_bytes = L.cache_block_bytes;
     o.uses_cache = c->uses_cache ? 1 : 0;
@@ -274,10 +277,88 @@ __device__ __forceinline__ void union_sparse_tile(const FinishArgs& a, int32_t t
     }
 }
 
+// Sixteen marks of a byte each, 0 or 1, as bits.
+__device__ __forceinline__ uint16_t mark_bits(const uint4& m)
+{
+    auto four = [](uint32_t v) { return v * 0x10204080u >> 28; };             // the lowest bits of four bytes, in order
+    return (uint16_t) (four(m.x) | four(m.y) << 4 | four(m.z) << 8 | four(m.w) << 12);
+}
+
+// New nodes lo, lo + step, ... below hi of those that `words` words of marks in LDS hold, with the marks before each word beside it:
+// calls f(node, its word, its bit) by the thread.
+template <typename F>
+__device__ __forceinline__ void each_marked(const uint64_t* bits, const int32_t* before, int32_t words, int32_t lo, int32_t hi, int32_t step, F&& f)
+{
+    for (int32_t j = lo; j < hi; j += step) {
+        int32_t l = 0, h = words;                                // the last word with no more than j marks before it
+        while (h - l > 1) {
+            const int32_t mid = (l + h) >> 1;
+            if (before[mid] <= j) l = mid; else h = mid;
+        }
+        f(j, l, select_bit64(bits[l], j - before[l]));
+    }
+}
+
+// The bitmap side of the union step for a layer that marks by slots (see k_finish_cached) of a cache too large for that one
+// launch.  What is before a word of marks is left for the relabel, 16 bytes for 64 slots; the marks stay (the next mini-batch's
+// first kernel clears them).
+__device__ __forceinline__ void union_slot_tile(const FinishArgs& a, int32_t tile, int32_t R, int spins, int32_t* smem, uint64_t* s_bits,
+                                                int32_t* s_before)
+{
+    const int tid = (int) threadIdx.x;
+    const int32_t T = a.slot_tile, base = tile * T, here = a.slots - base < T ? a.slots - base : T;
+    const uint4* marks = reinterpret_cast<const uint4*>(a.slot_mark + base);
+    uint16_t* bits16 = reinterpret_cast<uint16_t*>(s_bits);
+    const int32_t pieces = here / 16, words = here / 64;
+    uint4 m[kSlotReads];
+#pragma unroll
+    for (int x = 0; x < kSlotReads; ++x) {
+        const int32_t i = x * kBlock + tid;
+        m[x] = marks[i < pieces ? i : pieces - 1];
+    }
+#pragma unroll
+    for (int x = 0; x < kSlotReads; ++x) {
+        const int32_t i = x * kBlock + tid;
+        if (i < pieces) bits16[i] = mark_bits(m[x]);
+    }
+    __syncthreads();
+    constexpr int kPer = kSlotTile * kSlotReads / 64 / kBlock;
+    uint64_t word[kPer];
+    int32_t marked = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        word[i] = tid * kPer + i < words ? s_bits[tid * kPer + i] : 0ull;
+        marked += __popcll(word[i]);
+    }
+    int32_t total;
+    int32_t run = block_exclusive_scan(marked, smem, &total);
+    const uint32_t tag = launch_tag(a.st, a.layer_index);
+    if (tid == 0) publish_sum(a.tile_sums, tile, tag, (uint32_t) total);
+    const bool last = tile == a.mark_tiles - 1;
+    if (total == 0 && !last) return;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        if (tid * kPer + i < words) s_before[tid * kPer + i] = run;
+        run += __popcll(word[i]);
+    }
+    const int32_t before = sum_before(a.tile_sums, tag, tile, spins, smem, [&](int32_t t) {
+        uint32_t n = 0;
+        for (int32_t i = t * T; i < (t + 1) * T; i += 16)                    // a full tile: one follows
+            n += (uint32_t) __popc((uint32_t) mark_bits(*reinterpret_cast<const uint4*>(a.slot_mark + i)));
+        return n;
+    });
+    if (last && tid == 0) publish_nodes(a, R + before + total);
+    __syncthreads();
+    for (int32_t i = tid; i < words; i += kBlock) a.slot_words[base / 64 + i] = {s_bits[i], before + s_before[i], 0};
+    each_marked(s_bits, s_before, words, tid, total, kBlock, [&](int32_t j, int32_t w, int bit) {
+        if (R + before + j < a.max_src) a.src_nodes[R + before + j] = a.cache_nodes[base + w * 64 + bit];
+    });
+}
+
 // The union step of one layer.  Latency-bound: every block is a chain of a few dependent reads (tile words -> counts of
 // other tiles -> offsets of the new nodes), so it is one launch (two, with the tile counts in a launch of their own,
 // cost another 4.6 us each, three times per mini-batch), the tiles are small, and new nodes are spread over threads.
-// kPerMax: words of a tile per thread at most; 0: the bitmap has a summary (union_sparse_tile).
+// kPerMax: words of a tile per thread at most; 0: the bitmap has a summary (union_sparse_tile); -1: marks are by slot.
 template <int kPerMax, bool kOne>
 __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
 {
@@ -326,6 +407,8 @@ __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
             if (r0 + i < R) a.indptr[r0 + i] = off;
             off += c[i];
         }
+    } else if constexpr (kPerMax < 0) {
+        union_slot_tile(a, block - a.row_tiles_max, R, spins, smem, s_word, s_off);
     } else if constexpr (kPerMax == 0) {
         union_sparse_tile(a, block - a.row_tiles_max, R, spins, smem, s_word, s_widx, s_off);
     } else {
@@ -419,6 +502,13 @@ void fill_finish_template(const Group& g, int layer_index, FinishArgs* out)
     a.num_nodes = c->graph.num_nodes;
     a.last_layer = layer_index == c->config.num_layers - 1 ? 1 : 0;
     a.max_src = (int32_t) L.rows[layer_index + 1];
+    a.by_slot = L.slot_marks && a.last_layer ? 1 : 0;
+    if (a.by_slot) {
+        a.slots = (int32_t) L.slot_marks;
+        a.slot_tile = L.slot_tile;
+        a.mark_tiles = (a.slots + a.slot_tile - 1) / a.slot_tile;
+        a.cache_nodes = cache_ptr<int32_t>(c, L.cache_nodes, 0);
+    }
 }
 
 int relabel_grid(const gns_ctx* c, int layer_index)
@@ -444,7 +534,8 @@ hipError_t launch_finish_layer(const Group& g, int layer_index, hipStream_t s)
     const int per = a.f.mark_tile_words / kBlock, spins = c->union_spins;
     with_one(g, [&](auto kOne) {
         constexpr bool one = decltype(kOne)::value;
-        if (a.off.has_summary) hipLaunchKernelGGL((k_union<0, one>), grid, dim3(kBlock), 0, s, a, spins);
+        if (a.f.by_slot) hipLaunchKernelGGL((k_union<-1, one>), grid, dim3(kBlock), 0, s, a, spins);
+        else if (a.off.has_summary) hipLaunchKernelGGL((k_union<0, one>), grid, dim3(kBlock), 0, s, a, spins);
         else if (per <= 1) hipLaunchKernelGGL((k_union<1, one>), grid, dim3(kBlock), 0, s, a, spins);
         else if (per <= 4) hipLaunchKernelGGL((k_union<4, one>), grid, dim3(kBlock), 0, s, a, spins);
         else               hipLaunchKernelGGL((k_union<kMarkTileMax / kBlock, one>), grid, dim3(kBlock), 0, s, a, spins);
@@ -452,9 +543,27 @@ hipError_t launch_finish_layer(const Group& g, int layer_index, hipStream_t s)
     return hipGetLastError();
 }
 
-// The last layer's relabel has no following sampler to ride with; its launch also leaves the
-// seed bitmap empty for the next mini-batch and writes the counts to the context's pinned host mirror, where
-// gns_sample_blocks_wait finds them.
+// What the last launch of a batch does besides: the seed bitmap left empty for the next mini-batch, and the counts written to the
+// context's pinned host mirror, where gns_sample_blocks_wait finds them.  By one block; `nodes` and `edges` are the last layer's.
+__device__ __forceinline__ void clear_seed_marks(const LayerArgs& g, int b, const FinishArgs& a)
+{
+    char* ws = g.b[b].ws;
+    const int32_t* seeds = at<int32_t>(ws, g.off.seed_copy);
+    uint64_t* seed_mark = at<uint64_t>(ws, g.off.seed_mark);
+    for (int32_t i = (int32_t) threadIdx.x; g.off.marks_seeds && i < a.st->num_dst[0]; i += kBlock)
+        if (seeds[i] >= 0 && (int64_t) seeds[i] < a.num_nodes) seed_mark[seeds[i] >> 6] = 0ull;
+}
+
+__device__ __forceinline__ void report_counts(const LayerArgs& g, int b, const FinishArgs& a, int32_t nodes, int32_t edges)
+{
+    DeviceState* host = g.b[b].host;
+    const int i = (int) threadIdx.x;
+    if (i <= GNS_MAX_LAYERS) host->num_dst[i] = i == a.layer_index + 1 ? nodes : a.st->num_dst[i];
+    if (i < GNS_MAX_LAYERS) host->num_edges[i] = i == a.layer_index ? edges : a.st->num_edges[i];
+    if (i == 0) host->bad_seed = a.st->bad_seed;
+}
+
+// The last layer's relabel has no following sampler to ride with.
 template <bool kOne>
 __global__ void __launch_bounds__(kBlock) k_relabel_last(LayerArgs g)
 {
@@ -463,14 +572,8 @@ __global__ void __launch_bounds__(kBlock) k_relabel_last(LayerArgs g)
     const FinishArgs a = bind_finish(g, b, true);
     relabel_body(a, block, g.blocks);
     if (block == 0) {
-        const BatchSlot& q = g.b[b];
-        const int32_t* seeds = at<int32_t>(q.ws, g.off.seed_copy);
-        uint64_t* seed_mark = at<uint64_t>(q.ws, g.off.seed_mark);
-        for (int32_t i = (int32_t) threadIdx.x; g.off.marks_seeds && i < a.st->num_dst[0]; i += kBlock)
-            if (seeds[i] >= 0 && (int64_t) seeds[i] < a.num_nodes) seed_mark[seeds[i] >> 6] = 0ull;
-        if (threadIdx.x <= GNS_MAX_LAYERS) q.host->num_dst[threadIdx.x] = a.st->num_dst[threadIdx.x];
-        if (threadIdx.x < GNS_MAX_LAYERS) q.host->num_edges[threadIdx.x] = a.st->num_edges[threadIdx.x];
-        if (threadIdx.x == 0) q.host->bad_seed = a.st->bad_seed;
+        clear_seed_marks(g, b, a);
+        report_counts(g, b, a, a.st->num_dst[a.layer_index + 1], a.st->num_edges[a.layer_index]);
     }
 }
 
@@ -483,6 +586,156 @@ hipError_t launch_relabel(const Group& g, int layer_index, hipStream_t s)
     fill_finish_template(g, layer_index, &a.f);
     a.blocks = relabel_grid(c, layer_index);
     with_one(g, [&](auto kOne) { hipLaunchKernelGGL(k_relabel_last<decltype(kOne)::value>, group_grid(g, a, a.blocks), dim3(kBlock), 0, s, a); });
+    return hipGetLastError();
+}
+
+// Union and relabel of an input layer that samples from the cache only, in one launch.  Its new nodes are cached nodes, which the
+// sampler has marked by their slots, a byte each with a plain store; slots ascend with node ids.  So a block reads all marks, knows from
+// them how many come before each slot, and needs nothing of any other block: it relabels and compacts its kBlock rows, and the blocks
+// share out the list of the new nodes.  Latency-bound: rows, edges and marks are read at once, and what follows is in LDS.
+// Every block reads all marks, which sets the line for the cache's size (kSlotsMax, 64 KB: a mini-batch of 13 blocks 10.1 us where 35 K
+// slots take 9.4 and 10 K 7.2, against 8.7 + 3.2, 5.8 + 3.8 and 5.9 + 4.4 with marks in the bitmap of all nodes and two launches, whose gap
+// comes on top); larger caches have union_slot_tile and k_relabel_last.
+// Groups of four on 1 M nodes (10 K cached) 9.1 + 9.4 -> 11.2 us and the sampler 37.6 -> 37.6, on 6.5 M nodes (65 K cached) 11.4 + 7.8 ->
+// 11.9 and the sampler 39.7 -> 27.0: its marks were atomics, two each, carried out at the memory.  On 40 M nodes (400 K cached)
+// sampler, union and relabel 54 + 17.1 + 11.7 -> 45.4 + 10.7 + 9.3.
+constexpr int kFinishFlight = 8;                 // edges of a thread on their way
+
+template <bool kOne>
+__global__ void __launch_bounds__(kBlock) k_finish_cached(LayerArgs g)
+{
+    __shared__ uint64_t s_sums[kBlock / kWave];
+    __shared__ int32_t s_part[kBlock / kWave];
+    __shared__ uint64_t s_bits[kSlotsMax / 64];
+    __shared__ int32_t s_before[kSlotsMax / 64];
+    __shared__ int32_t s_off[kBlock], s_num[kBlock];
+    const auto [b, block] = group_block<kOne>(g.dealt);
+    if (!kOne && block >= g.blocks) return;
+    const FinishArgs a = bind_finish(g, b, true);
+    const int32_t R = a.st->num_dst[a.layer_index];
+    const int32_t base = block * kBlock;
+    if (base >= R) return;
+    const int tid = (int) threadIdx.x;
+    const int32_t k = a.fanout, rows = R - base < kBlock ? R - base : kBlock, items = rows * k;
+    const int32_t first = base * k;                              // below 2^31: checked when the workspace is sized
+    const int32_t num = tid < rows ? a.s_cnt[base + tid] : 0;
+    int32_t u[kFinishFlight];
+    float w[kFinishFlight];
+    auto load = [&](int32_t q0) {
+#pragma unroll
+        for (int i = 0; i < kFinishFlight; ++i) {
+            const int32_t j = (q0 + i) * kBlock + tid, t = first + (j < items ? j : items - 1);
+            u[i] = a.s_nbr[t];
+            w[i] = a.s_w[t];
+        }
+    };
+    load(0);
+    // marks: sixteen slots a read, 0 or 1 each, into bits; a thread's reads are on their way together
+    const uint4* marks = reinterpret_cast<const uint4*>(a.slot_mark);
+    uint16_t* bits16 = reinterpret_cast<uint16_t*>(s_bits);
+    const int32_t pieces = a.slots / 16;
+    auto bits_of = [&](auto reads) {
+        constexpr int kReads = decltype(reads)::value;
+        for (int32_t i0 = tid; i0 < pieces; i0 += kReads * kBlock) {
+            uint4 m[kReads];
+#pragma unroll
+            for (int x = 0; x < kReads; ++x) {
+                const int32_t i = i0 + x * kBlock;
+                m[x] = marks[i < pieces ? i : pieces - 1];
+            }
+#pragma unroll
+            for (int x = 0; x < kReads; ++x) {
+                const int32_t i = i0 + x * kBlock;
+                if (i < pieces) bits16[i] = mark_bits(m[x]);
+            }
+        }
+    };
+    if (pieces <= kBlock)          bits_of(std::integral_constant<int, 1>());
+    else if (pieces <= 3 * kBlock) bits_of(std::integral_constant<int, 3>());
+    else                           bits_of(std::integral_constant<int, 8>());
+    int32_t part = 0;                                            // samples of the rows before
+    for (int32_t t = tid; t < block * (kBlock / a.rows_per_sum); t += kBlock) part += a.sums_rows[t];
+    __syncthreads();
+    // Places of the rows' edges and of the words' marks by one scan, each a half of 64 bits.
+    const int32_t words = a.slots / 64, per = (words + kBlock - 1) / kBlock;
+    int32_t marked = 0;
+    for (int32_t i = tid * per; i < (tid + 1) * per && i < words; ++i) marked += __popcll(s_bits[i]);
+    const int lane = opaque_lane_id(), wave = opaque(tid >> 6);
+    uint64_t sums = (uint64_t) (uint32_t) marked << 32 | (uint32_t) num;
+    const uint64_t own = sums;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint64_t up = __shfl_up((unsigned long long) sums, d, kWave);
+        if (lane >= d) sums += up;
+    }
+    part = wave_sum(part);
+    if (lane == kWave - 1) { s_sums[wave] = sums; s_part[wave] = part; }
+    __syncthreads();
+    uint64_t all = 0, start = sums - own;
+    int32_t before = 0;
+#pragma unroll
+    for (int x = 0; x < kBlock / kWave; ++x) {
+        if (x < wave) start += s_sums[x];
+        all += s_sums[x];
+        before += s_part[x];
+    }
+    const int32_t total = (int32_t) (uint32_t) all, fresh = (int32_t) (all >> 32);
+    s_off[tid] = (int32_t) (uint32_t) start;
+    s_num[tid] = num;
+    int32_t run = (int32_t) (start >> 32);
+    for (int32_t i = tid * per; i < (tid + 1) * per && i < words; ++i) {
+        s_before[i] = run;
+        run += __popcll(s_bits[i]);
+    }
+    __syncthreads();
+    if (tid < rows) a.indptr[base + tid] = before + s_off[tid];
+    for (int32_t q0 = 0; q0 < k; q0 += kFinishFlight) {
+        if (q0 > 0) load(q0);
+#pragma unroll
+        for (int i = 0; i < kFinishFlight; ++i) {
+            const int32_t j = (q0 + i) * kBlock + tid;
+            const int32_t row = (int32_t) (((float) j + 0.5f) * (float) a.inv_fanout);         // j / k: exact below 2^16
+            const int32_t s = j - row * k;
+            if (j >= items || s >= s_num[row]) continue;
+            int32_t local = -1 - u[i];
+            if (u[i] >= 0) local = R + s_before[u[i] >> 6] + __popcll(s_bits[u[i] >> 6] & bits_below(u[i]));
+            const int32_t o = before + s_off[row] + s;
+            a.indices[o] = local;
+            a.weights[o] = w[i];
+        }
+    }
+    // the new nodes: a wave per word of marks, or where blocks are few by all their threads
+    const int32_t blocks = (R + kBlock - 1) / kBlock, w0 = block * (kBlock / kWave) + wave;
+    auto emit = [&](int32_t n, int32_t word, int bit) {
+        if (R + n < a.max_src) a.src_nodes[R + n] = a.cache_nodes[word * 64 + bit];
+    };
+    if (words <= blocks * (kBlock / kWave)) {
+        if (w0 < words && (s_bits[w0] >> lane & 1ull)) emit(s_before[w0] + __popcll(s_bits[w0] & bits_below(lane)), w0, lane);
+    } else {
+        each_marked(s_bits, s_before, words, base + tid, fresh, blocks * kBlock, emit);
+    }
+    if (block == 0) clear_seed_marks(g, b, a);
+    if (base + kBlock >= R) {
+        const int32_t nodes = R + fresh < a.max_src ? R + fresh : a.max_src, edges = before + total;
+        if (tid == 0) {
+            a.indptr[R] = edges;
+            a.st->num_edges[a.layer_index] = edges;
+            a.st->num_dst[a.layer_index + 1] = nodes;
+        }
+        report_counts(g, b, a, nodes, edges);
+    }
+}
+
+hipError_t launch_finish_cached(const Group& g, hipStream_t s)
+{
+    gns_ctx* c = g.ctx[0];
+    const int layer_index = c->config.num_layers - 1;
+    LayerArgs a;
+    fill_group_args(g, &a);
+    set_group_layer(g, layer_index, &a);
+    fill_finish_template(g, layer_index, &a.f);
+    a.blocks = (int32_t) ((c->lay.rows[layer_index] + kBlock - 1) / kBlock);
+    with_one(g, [&](auto kOne) { hipLaunchKernelGGL(k_finish_cached<decltype(kOne)::value>, group_grid(g, a, a.blocks), dim3(kBlock), 0, s, a); });
     return hipGetLastError();
 }
 

@@ -55,6 +55,12 @@ constexpr size_t kFilterBytes = (size_t) kFilterHot * (8 + 2) + kFilterGroups / 
 // 20 M 813 and 843, 12 M 378 and 358.
 constexpr int64_t kFilterPairsNodes = (int64_t) 16 << 20;
 
+// What a layer that draws from the cache looks up of a node, in one read.
+struct alignas(8) CachedNode {
+    float inv_pc;              // 1 / p^C_u
+    int32_t slot;              // its place in the list of cached nodes
+};
+
 struct Layout {
     // persistent cache structures
     size_t cache_bitmap, cache_prefix, cache_nodes, cache_feat;
@@ -66,7 +72,7 @@ struct Layout {
     // random-walk cache probability (only with GNS_PROB_WALK): two weight vectors, their prefix, scan partials
     size_t walk_a, walk_b, prob_prefix, walk_tiles, walk_tiles_nz;
     size_t walk_hot;          //   and the hot nodes' table (HotCopy[2])
-    size_t node_pc;           // [n] floats: 1 / p^C_u (Section 3.4), filled for the nodes of the current cache
+    size_t node_pc;           // [n] floats: 1 / p^C_u (Section 3.4), filled for the nodes of the current cache; with slot_marks CachedNode
     // cache-draw scratch
     size_t draw_table, draw_slot, draw_sums, index_sums;
     size_t entry_rows;        // row that owns entry 64 * i of the CSR entry array (Eq. (1) draws; filled by gns_create)
@@ -93,6 +99,11 @@ struct Layout {
     int s_tile_shift;
 
     int64_t max_chunks;
+    // The input layer's new nodes are marked by their slots of the cache, a byte each: bytes of the marks, in the place of plan_desc
+    // (0: they are marked in the bitmap of all nodes), behind them for caches of more than kSlotsMax slots a SlotWord for every 64,
+    // and slots of a tile of the union step there
+    int64_t slot_marks;
+    int32_t slot_tile;
     // scan partials
     size_t sums_rows, tile_sums, row_sums, plan_sums;
     size_t info;              // outcome of the graph validation
@@ -347,6 +358,7 @@ hipError_t launch_sample_layer(const Group& g, int layer_index, hipStream_t s);
 hipError_t launch_batch_begin(const Group& g, const BeginDyn& d, hipStream_t s);
 hipError_t launch_relabel(const Group& g, int layer_index, hipStream_t s);
 hipError_t launch_finish_layer(const Group& g, int layer_index, hipStream_t s);
+hipError_t launch_finish_cached(const Group& g, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long* p, size_t n, unsigned long long v, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s);
 

@@ -70,7 +70,10 @@ struct SampleArgs {
     const int32_t* indices;
     const int32_t* dst_nodes;
     RowExtent* row_ext;        // CSR extent of every dst row's node (written when the node joined the batch)
-    const float* node_inv_pc;  // 1 / p^C_u for the nodes of the cache
+    const float* node_inv_pc;  // 1 / p^C_u for the nodes of the cache, or
+    const CachedNode* node_slot;     //   that and their slots (the other is null)
+    int by_slot;               // the layer's new nodes are marked in slot_mark
+    uint8_t* slot_mark;        // [slots of the cache]
     int32_t* hub_rows;         // rows of the layer whose CSR segment spans more than kHubChunks chunks
     const uint64_t* cache_bitmap;
     int32_t* s_nbr;
@@ -97,6 +100,15 @@ struct SampleArgs {
     const int32_t* s_nodes;
     const int32_t* s_count;    // cached entries of every tile of 2^s_tile_shift entries
     int s_tile_shift;
+};
+
+// Marks of 64 slots, and the marks before them.
+struct alignas(16) SlotWord {
+    uint64_t bits;
+    int32_t before;
+    int32_t pad;
+
+    __device__ __forceinline__ int32_t rank(uint32_t slot) const { return before + __popcll(bits & ((1ull << (slot & 63u)) - 1ull)); }
 };
 
 struct FinishArgs {
@@ -131,6 +143,12 @@ struct FinishArgs {
     int64_t num_nodes;
     int32_t last_layer;            // its new nodes have no rows to be sampled
     int32_t max_src;               // places of the layer's src list and of row_ext
+    int by_slot;                   // the layer's new nodes are marked by slots of the cache
+    int32_t slots;                 //   their number, rounded up to whole words of marks
+    int32_t slot_tile;             //   slots of a tile (then tiles are of slots, not of bitmap words)
+    uint8_t* slot_mark;            //   [slots]
+    SlotWord* slot_words;          //   [slots / 64] written by the union step for the relabel
+    const int32_t* cache_nodes;    //   the cached nodes by slot
 };
 
 // Byte offsets of the sections of a context's per-batch scratch (the same for every context of a family).
@@ -138,7 +156,8 @@ struct WsOffsets {
     uint64_t state, mark, mark_summary, seed_mark, seed_copy, row_ext, hub_rows;
     uint64_t table;
     uint64_t s_nbr[2], s_w[2], s_cnt[2];
-    uint64_t plan_desc;
+    uint64_t plan_desc;            // where slot_marks is not 0: the marks by slot
+    uint64_t slot_marks;           // bytes of them
     uint64_t sums_rows, tile_sums, row_sums, plan_sums;
     uint64_t cache_block_bytes;    // distance between the two copies of what a cache draw writes
     int32_t uses_cache;
@@ -237,11 +256,13 @@ __device__ __forceinline__ SampleArgs bind_sample(const LayerArgs& g, int b, uin
     a.tab = bind_table(g, b, stamp);
     a.plan_sums = at<unsigned long long>(ws, g.off.plan_sums);
     a.plan_desc = at<int32_t>(ws, g.off.plan_desc);
+    a.slot_mark = at<uint8_t>(ws, g.off.plan_desc);
     if (g.off.uses_cache) {
         auto shifted = [&](auto* ptr) {
             return ptr ? reinterpret_cast<decltype(ptr)>(reinterpret_cast<uintptr_t>(ptr) + gen_shift) : ptr;
         };
         a.node_inv_pc = shifted(g.s.node_inv_pc);
+        a.node_slot = shifted(g.s.node_slot);
         a.cache_bitmap = shifted(g.s.cache_bitmap);
         a.flags = shifted(g.s.flags);
         a.filter_groups = shifted(g.s.filter_groups);
@@ -284,6 +305,11 @@ __device__ __forceinline__ FinishArgs bind_finish(const LayerArgs& g, int b, boo
     a.weights = blk.weights;
     a.src_nodes = blk.src_nodes;
     a.row_ext = at<RowExtent>(ws, g.off.row_ext);
+    if (g.f.by_slot) {
+        a.slot_mark = at<uint8_t>(ws, g.off.plan_desc);
+        a.slot_words = at<SlotWord>(ws, g.off.plan_desc + g.off.slot_marks);
+        a.cache_nodes = reinterpret_cast<const int32_t*>(reinterpret_cast<uintptr_t>(a.cache_nodes) + (a.st->cache_gen ? g.off.cache_block_bytes : 0));
+    }
     return a;
 }
 
@@ -348,6 +374,13 @@ __device__ __forceinline__ int64_t uncached_entry(const SampleArgs& a, const Row
     }
 }
 
+// What is known of cached node u (slot: only where the context marks by slots).
+__device__ __forceinline__ CachedNode cached_node(const SampleArgs& a, uint32_t u)
+{
+    if (a.node_slot) return a.node_slot[u];
+    return {a.node_inv_pc[u], 0};
+}
+
 // Section 3.4: coefficient p^C_u * k / min(k, N_C(v)), weight = 1 / coefficient (fp32 from the 1/p^C table on); the factor
 // of 1/p^C for a row of m cached neighbors of which cnt are drawn.
 __device__ __forceinline__ float cached_scale(const SampleArgs& a, uint32_t m, int cnt)
@@ -393,9 +426,11 @@ __device__ __forceinline__ void relabel_body(const FinishArgs& a, int32_t block,
 #pragma unroll
         for (int i = 0; i < kRelabelUnroll; ++i) {
             const bool search = ok[i] && u[i] >= 0;
-            const uint32_t e = a.tab.entry[search ? u[i] : 0];
+            int32_t local;
+            if (a.by_slot) local = R + a.slot_words[search ? u[i] >> 6 : 0].rank((uint32_t) u[i]);
+            else           local = (int32_t) a.tab.local(a.tab.entry[search ? u[i] : 0]);
             if (ok[i]) {
-                a.indices[o[i]] = search ? (int32_t) a.tab.local(e) : -1 - u[i];
+                a.indices[o[i]] = search ? local : -1 - u[i];
                 a.weights[o[i]] = w[i];
             }
         }
@@ -423,6 +458,15 @@ __device__ __forceinline__ void begin_state(const LayerArgs& g, const BeginDyn& 
     st->stamp = d.stamp[b];
     st->batch_id = d.batch_id[b];
     st->cache_gen = d.cache_gen[b];
+}
+
+// Clears the marks by slot for the batch: a share of them by every block of its first kernel.
+__device__ __forceinline__ void clear_slot_marks(const LayerArgs& g, int b, int32_t block)
+{
+    if (g.off.slot_marks == 0) return;
+    const uint32_t blocks = g.dealt > 1 ? gridDim.x / (uint32_t) g.dealt : gridDim.x;
+    uint4* marks = at<uint4>(g.b[b].ws, g.off.plan_desc);
+    for (uint32_t i = (uint32_t) block * kBlock + threadIdx.x; i < g.off.slot_marks / 16; i += blocks * kBlock) marks[i] = make_uint4(0, 0, 0, 0);
 }
 
 // Seed q of the batch, node u: the CSR extent of its row (empty for an id out of range).
@@ -485,6 +529,8 @@ void fill_first_args(const Group& g, LayerArgs* out);
 int relabel_grid(const gns_ctx* c, int layer_index);
 // Whether a layer is sampled without a plan or flag pass in front: UNIFORM, or from the induced subgraph.
 bool direct_layer(const gns_config& config, int layer_index);
+// Whether the input layer's union and relabel are one launch.
+inline bool finishes_at_once(const gns_ctx* c) { return c->lay.slot_marks > 0 && c->lay.slot_marks <= kSlotsMax; }
 // Whether the first layer's sampler is also the batch's first kernel (k_batch_begin runs in front of the others).
 bool first_layer_enters_seeds(const gns_config& config);
 // Rows whose sampled neighbors the layer's sampler sums up (0: it does not, the union step's blocks do).

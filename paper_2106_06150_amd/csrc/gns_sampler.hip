@@ -18,7 +18,8 @@
 // one, else its global id), s_w[r*k + i] for i < s_cnt[r] (UNIFORM layers: no weights, they are 1),
 // row_eligible[r], the dst node as the r-th src node, and the sum of s_cnt over the rows of a block;
 // every emitted id that has no local id yet (it is not a dst node of this layer) also sets its bit in
-// the node-indexed mark bitmap that the frontier stage turns into the src list.
+// the node-indexed mark bitmap that the frontier stage turns into the src list.  An input layer that samples from the cache
+// only, with the induced subgraph, marks by slots of the cache instead and leaves a new node's slot (see k_finish_cached).
 #include <string.h>
 #include <stdlib.h>
 #include "gns_kernels.hpp"
@@ -81,6 +82,15 @@ __device__ __forceinline__ int32_t mark_if_new(const SampleArgs& a, uint32_t u)
     if (a.tab.current(e)) return -1 - (int32_t) a.tab.local(e);
     mark_node(a, u);
     return (int32_t) u;
+}
+
+// The same in a layer that marks by slot: what is left for a new node is its slot.
+__device__ __forceinline__ int32_t mark_if_new_slot(const SampleArgs& a, uint32_t u, int32_t slot)
+{
+    const uint32_t e = a.tab.entry[u];
+    if (a.tab.current(e)) return -1 - (int32_t) a.tab.local(e);
+    a.slot_mark[slot] = 1;
+    return slot;
 }
 
 // ---------------------------------------------------------------------------
@@ -245,13 +255,19 @@ __device__ __forceinline__ void sample_wave_rows(const LayerArgs& g, const Begin
         else                           place = (int64_t) (w.first[r] + rank);
         const uint32_t u = (uint32_t) (kList == kListRow || is_fill ? a.indices : a.s_nodes)[place];
         const uint32_t e = kFirst ? 0u : a.tab.entry[u];
-        const float inv_pc = kList == kListRow ? 1.0f : a.node_inv_pc[u];
+        const CachedNode c = kList == kListRow || is_fill ? CachedNode{1.0f, 0} : cached_node(a, u);
         int32_t out = (int32_t) u;
-        if (!kFirst && a.tab.current(e)) out = -1 - (int32_t) a.tab.local(e);
-        else mark_node(a, u);
+        if (!kFirst && a.tab.current(e)) {
+            out = -1 - (int32_t) a.tab.local(e);
+        } else if (kList == kListCached && a.by_slot) {
+            out = c.slot;
+            a.slot_mark[c.slot] = 1;
+        } else {
+            mark_node(a, u);
+        }
         const int64_t at = (int64_t) row0 * k + j;
         a.s_nbr[at] = out;
-        if (kList != kListRow) a.s_w[at] = is_fill ? w.fill_w[r] : inv_pc * w.scale[r];
+        if (kList != kListRow) a.s_w[at] = is_fill ? w.fill_w[r] : c.inv_pc * w.scale[r];
     }
     __builtin_amdgcn_wave_barrier();
 }
@@ -298,9 +314,11 @@ __global__ void __launch_bounds__(kBlock) k_sample_first(LayerArgs g, BeginDyn d
     const auto [b, block] = group_block<kOne>(g.dealt);
     const int32_t R = d.num_seeds[b];
     if (block == 0 && threadIdx.x == 0) begin_state(g, d, b);
-    if ((int64_t) block * (kBlock / kWave) * W >= R) return;
-    const SampleArgs a = bind_sample(g, b, d.stamp[b], d.cache_gen[b]);
-    sample_block_rows<K, kList, true>(g, &d, a, b, block, W, R, d.key0[b], d.key1[b], rows, smem);
+    if ((int64_t) block * (kBlock / kWave) * W < R) {
+        const SampleArgs a = bind_sample(g, b, d.stamp[b], d.cache_gen[b]);
+        sample_block_rows<K, kList, true>(g, &d, a, b, block, W, R, d.key0[b], d.key1[b], rows, smem);
+    }
+    clear_slot_marks(g, b, block);
 }
 
 // ---------------------------------------------------------------------------
@@ -361,8 +379,10 @@ __global__ void __launch_bounds__(kBlock) k_sample_wide(LayerArgs g, int relabel
             else                          place = (int64_t) cached.first + val;
             const uint32_t u = (uint32_t) (kList == kListRow || is_fill ? a.indices : a.s_nodes)[place];
             const int64_t at = (int64_t) row * k + pos;
-            if (kList != kListRow) a.s_w[at] = is_fill ? fill_weight(a, others, fill) : a.node_inv_pc[u] * cached_scale(a, m, cnt);
-            a.s_nbr[at] = mark_if_new(a, u);
+            CachedNode c = {1.0f, 0};
+            if (kList != kListRow && !is_fill) c = cached_node(a, u);
+            if (kList != kListRow) a.s_w[at] = is_fill ? fill_weight(a, others, fill) : c.inv_pc * cached_scale(a, m, cnt);
+            a.s_nbr[at] = kList == kListCached && a.by_slot ? mark_if_new_slot(a, u, c.slot) : mark_if_new(a, u);
         }
         if (live && s == 0) {
             a.s_cnt[row] = cnt + fill;
@@ -842,7 +862,9 @@ void fill_sample_template(gns_ctx* c, int layer_index, SampleArgs* out)
     a.policy = c->config.policy[layer_index];
     a.indices = c->graph.indices;
     const int gen = 0;
-    a.node_inv_pc = c->uses_cache ? cache_ptr<float>(c, L.node_pc, gen) : nullptr;
+    a.node_inv_pc = c->uses_cache && !L.slot_marks ? cache_ptr<float>(c, L.node_pc, gen) : nullptr;
+    a.node_slot = L.slot_marks ? cache_ptr<CachedNode>(c, L.node_pc, gen) : nullptr;
+    a.by_slot = L.slot_marks && layer_index == c->config.num_layers - 1 ? 1 : 0;
     a.cache_bitmap = cache_ptr<uint64_t>(c, L.cache_bitmap, gen);
     a.num_entries = c->graph.num_entries;
     a.max_chunks = (uint32_t) L.max_chunks;

@@ -123,6 +123,7 @@ __global__ void __launch_bounds__(kThreads) k_sample_small(SmallArgs g)
             if (ptr) ptr = reinterpret_cast<std::remove_reference_t<decltype(ptr)>>(reinterpret_cast<uintptr_t>(ptr) + g.cache_block_bytes);
         };
         shift(a.node_inv_pc);
+        shift(a.node_slot);
         shift(a.srec);
         shift(a.s_nodes);
         shift(a.s_count);
@@ -290,7 +291,7 @@ __global__ void __launch_bounds__(kThreads) k_sample_small(SmallArgs g)
                 const int t = i * kThreads + tid;
                 if (i * kThreads >= items || !mine[i]) continue;
                 const int r = (int) ((uint32_t) t * inv_k >> 16);
-                if (t - r * k < (w.count[r] & 255)) weight[i] *= a.node_inv_pc[u[i]];
+                if (t - r * k < (w.count[r] & 255)) weight[i] *= cached_node(a, u[i]).inv_pc;
             }
         }
         __syncthreads();                                         // places and nodes share their memory

@@ -50,6 +50,26 @@ def test_small_graph_parity(offsets, fanouts, policies, flag_mode):
         gns.close()
 
 
+@pytest.mark.parametrize("n,cache,fanouts,seeds,tile_words", [
+    (3000, 64, (3, 9), 257, 0), (3000, 65, (4, 4, 8), 256, 0), (4000, 3000, (5, 17), 700, 0), (4000, 3900, (2, 64), 1100, 0),
+    (90_000, 65_536, (12, 5), 1500, 0), (90_000, 65_537, (12, 5), 1500, 0), (150_000, 140_000, (16, 5), 400, 0), (150_000, 140_000, (16, 20), 400, 512)])
+def test_input_layer_marked_by_slots(n, cache, fanouts, seeds, tile_words, monkeypatch):
+    """Input layers from the cache only on the induced subgraph, whose new nodes are marked by their slots of the cache: caches up to
+    what is finished in one launch and beyond (tiles of slots of the smallest and of the largest length), last words of marks that are
+    full and not, rows around whole blocks, more slots a row than a thread has on its way; mini-batches one after the other, whose
+    marks are cleared in between, and a second cache, whose structures lie elsewhere."""
+    if tile_words:
+        monkeypatch.setenv("GNS_MARK_TILE_WORDS", str(tile_words))
+    ip, ix = _small(n=n, avg=9, seed=n)
+    gns = GpuGns(ip, ix, None, fanouts=fanouts, policies=(U,) * (len(fanouts) - 1) + (C,), cache_size=cache, max_seeds=seeds, flag_mode=1)
+    try:
+        for trial in range(3):
+            batch = synth.uniform_seed_batch(n, seeds - 75 * trial, trial)
+            full_parity(gns, cache_seed=9, epoch=trial // 2, batch_seed=50 + trial, seeds=batch)
+    finally:
+        gns.close()
+
+
 @pytest.mark.parametrize("F", [1, 3, 4, 32, 64, 96, 100, 128, 256, 260, 1024])
 def test_feature_widths_and_host_store(F):
     ip, ix = _small(n=1500)
