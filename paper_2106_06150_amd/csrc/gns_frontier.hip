@@ -158,21 +158,41 @@ __device__ __forceinline__ uint32_t count_tile(const FinishArgs& a, int32_t tile
     return n;
 }
 
-// The node of bit `bit` of bitmap word `word` joins the batch's list at place `pos`.  Nodes that join in the last layer are
+// Node `node` joins the batch's list at place `pos`.  Nodes that join in the last layer are
 // no layer's rows: nothing reads their extents, and on a graph whose offsets fit no L2 the read of one is a trip to memory.
 // Behind repeated or invalid seeds the list can be longer than the graph has nodes; it is cut where its buffers end.
-__device__ __forceinline__ void emit_new_node(const FinishArgs& a, int32_t pos, int64_t word, int bit)
+__device__ __forceinline__ RowExtent new_extent(const FinishArgs& a, uint32_t node)
 {
-    if (pos >= a.max_src) return;
-    const uint32_t node = (uint32_t) (word * 64 + bit);
-    a.src_nodes[pos] = (int32_t) node;
-    a.tab.entry[node] = a.tab.make((uint32_t) pos);
-    if (a.last_layer) return;
-    RowExtent ext;
+    RowExtent ext = {0, 0};
+    if (a.last_layer) return ext;
     ext.start = load_off_rt(a.g_indptr, a.g_i64, node);
     ext.end = load_off_rt(a.g_indptr, a.g_i64, (int64_t) node + 1);
-    a.row_ext[pos] = ext;
+    return ext;
 }
+
+__device__ __forceinline__ void emit_new_node(const FinishArgs& a, int32_t pos, uint32_t node, const RowExtent& ext)
+{
+    if (pos >= a.max_src) return;
+    a.src_nodes[pos] = (int32_t) node;
+    a.tab.entry[node] = a.tab.make((uint32_t) pos);
+    if (!a.last_layer) a.row_ext[pos] = ext;
+}
+
+// New node j of those whose words stand in LDS (count of them, the first at bitmap word `base`): its id.
+__device__ __forceinline__ uint32_t new_node(const uint64_t* s_word, const int32_t* s_widx, const int32_t* s_off, int32_t count, int64_t base, int32_t j)
+{
+    int32_t lo = 0, hi = count;                              // the last word whose offset is <= j
+    while (hi - lo > 1) {
+        const int32_t mid = (lo + hi) >> 1;
+        if (s_off[mid] <= j) lo = mid; else hi = mid;
+    }
+    return (uint32_t) ((base + s_widx[lo]) * 64 + select_bit64(s_word[lo], j - s_off[lo]));
+}
+
+// What a thread reads of its first new nodes while the counts of the tiles before are on their way: a trip to memory behind that
+// wait otherwise (groups of four, first and second layer: 1 M nodes 8.7 and 13.2 -> 8.5 and 12.3 us, 40 M 14.8 and 22.6 -> 12.5 and 21.4;
+// a mini-batch of 100 seeds on 1 M nodes 7.1 -> 6.1).
+constexpr int kAhead = 2;
 
 // Nodes of the batch behind the layer: its rows and the new nodes, as many as the list takes.
 __device__ __forceinline__ void publish_nodes(const FinishArgs& a, int32_t nodes)
@@ -244,6 +264,16 @@ __device__ __forceinline__ void union_sparse_tile(const FinishArgs& a, int32_t t
     const uint32_t tag = launch_tag(a.st, a.layer_index);
     if (tid == 0) publish_sum(a.tile_sums, tile, tag, (uint32_t) total);
     const bool last = tile == a.mark_tiles - 1;
+    const int32_t ahead = words <= kMarkCap ? total : 0;     // nodes known from the words in LDS
+    uint32_t node[kAhead];
+    RowExtent ext[kAhead];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+        if (i * kBlock + tid >= ahead) continue;
+        node[i] = new_node(s_word, s_widx, s_off, words, base, i * kBlock + tid);
+        ext[i] = new_extent(a, node[i]);
+    }
     int32_t before = 0;
     if (total > 0 || last)
         before = sum_before(a.tile_sums, tag, tile, spins, smem, [&](int32_t t) { return count_tile(a, t); });
@@ -264,14 +294,15 @@ __device__ __forceinline__ void union_sparse_tile(const FinishArgs& a, int32_t t
         for (int i = 0; i < kPer; ++i)
             if (widx[i] >= 0) a.mark[base + widx[i]] = 0ull;                 // ready for the next layer
         const int32_t here = words - p0 < kMarkCap ? words - p0 : kMarkCap;
-        // one thread per new node: its word (the last one whose offset is <= j), then its bit
-        for (int32_t j = node_lo + tid; j < node_lo + in_pass; j += kBlock) {
-            int32_t lo = 0, hi = here;
-            while (hi - lo > 1) {
-                const int32_t mid = (lo + hi) >> 1;
-                if (s_off[mid] <= j) lo = mid; else hi = mid;
-            }
-            emit_new_node(a, R + before + j, base + s_widx[lo], select_bit64(s_word[lo], j - s_off[lo]));
+        // one thread per new node
+        if (ahead > 0) {
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+                if (i * kBlock + tid < ahead) emit_new_node(a, R + before + i * kBlock + tid, node[i], ext[i]);
+        }
+        for (int32_t j = node_lo + tid + (ahead > 0 ? kAhead * kBlock : 0); j < node_lo + in_pass; j += kBlock) {
+            const uint32_t u = new_node(s_word, s_widx, s_off, here, base, j);
+            emit_new_node(a, R + before + j, u, new_extent(a, u));
         }
         node_lo += in_pass;
     }
@@ -420,14 +451,22 @@ __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
         const int first = (int) threadIdx.x * per;
         uint64_t word[kPerMax];
         load_marks<kPerMax>(a, base, first, per, T, word);
-        uint32_t marked = 0;                                             // words to clear (a marked seed is no new node)
+        uint64_t seeds[kPerMax];                                         // a marked seed is no new node
+#pragma unroll
+        for (int i = 0; i < kPerMax; ++i) seeds[i] = 0ull;
+        if (a.seed_mark) {
+#pragma unroll
+            for (int i = 0; i < kPerMax; ++i) {
+                const int64_t w = base + first + i;
+                if (i < per && first + i < T && w < a.words) seeds[i] = a.seed_mark[w];
+            }
+        }
+        uint32_t marked = 0;                                             // words to clear
         int32_t cnt = 0, nz = 0;
 #pragma unroll
         for (int i = 0; i < kPerMax; ++i) {
-            if (word[i]) {
-                marked |= 1u << i;
-                if (a.seed_mark) word[i] &= ~a.seed_mark[base + first + i];
-            }
+            if (word[i]) marked |= 1u << i;
+            word[i] &= ~seeds[i];
             cnt += __popcll(word[i]);
             nz += word[i] ? 1 : 0;
         }
@@ -436,20 +475,9 @@ __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
         const uint32_t tag = launch_tag(a.st, a.layer_index);
         if (threadIdx.x == 0) publish_sum(a.tile_sums, tile, tag, (uint32_t) total);
         const bool last = tile == a.mark_tiles - 1;
-        int32_t before = 0;
-        if (total > 0 || last) before = sum_before(a.tile_sums, tag, tile, spins, smem, [&](int32_t t) { return count_tile(a, t); });
-        if (last && threadIdx.x == 0) publish_nodes(a, R + before + total);
-        // The count is out (its store is older than the reads that sum_before waited for, or than the barriers of the
-        // scan below): from here on the marks may go.
         const int32_t widx = block_exclusive_scan(nz, smem, &total_nz);     // marked words before this thread's words
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < kPerMax; ++i)
-            if (marked & (1u << i)) a.mark[base + first + i] = 0ull;         // ready for the next layer
-        if (total == 0) return;
         // The marked words go through LDS in order, kMarkCap at a time (most tiles need one pass).
-        for (int32_t p0 = 0; p0 < total_nz; p0 += kMarkCap) {
+        auto fill = [&](int32_t p0) {
             int32_t my = widx, my_off = off;
 #pragma unroll
             for (int i = 0; i < kPerMax; ++i) {
@@ -463,20 +491,48 @@ __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
                     my_off += __popcll(word[i]);
                 }
             }
-            __syncthreads();
-            const int32_t in_pass = total_nz - p0 < kMarkCap ? total_nz - p0 : kMarkCap;
-            const int32_t node_lo = s_off[0];
-            const int32_t node_hi = s_off[in_pass - 1] + __popcll(s_word[in_pass - 1]);
-            // one thread per new node: locate its word (last word whose offset is <= j), then its bit
-            for (int32_t j = node_lo + (int32_t) threadIdx.x; j < node_hi; j += kBlock) {
-                int32_t lo = 0, hi = in_pass;                            // answer in [lo, hi)
-                while (hi - lo > 1) {
-                    const int32_t mid = (lo + hi) >> 1;
-                    if (s_off[mid] <= j) lo = mid; else hi = mid;
-                }
-                emit_new_node(a, R + before + j, base + s_widx[lo], select_bit64(s_word[lo], j - s_off[lo]));
+        };
+        fill(0);
+        __syncthreads();
+        const int tid = (int) threadIdx.x;
+        int32_t in_pass = total_nz < kMarkCap ? total_nz : kMarkCap;
+        int32_t node_hi = total_nz > 0 ? s_off[in_pass - 1] + __popcll(s_word[in_pass - 1]) : 0;
+        uint32_t node[kAhead];
+        RowExtent ext[kAhead];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            if (i * kBlock + tid >= node_hi) continue;
+            node[i] = new_node(s_word, s_widx, s_off, in_pass, base, i * kBlock + tid);
+            ext[i] = new_extent(a, node[i]);
+        }
+        int32_t before = 0;
+        if (total > 0 || last) before = sum_before(a.tile_sums, tag, tile, spins, smem, [&](int32_t t) { return count_tile(a, t); });
+        if (last && tid == 0) publish_nodes(a, R + before + total);
+        // The count is out (its store is older than the reads that sum_before waited for, or than the barriers of the
+        // scan above): from here on the marks may go.
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kPerMax; ++i)
+            if (marked & (1u << i)) a.mark[base + first + i] = 0ull;         // ready for the next layer
+        if (total == 0) return;
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+            if (i * kBlock + tid < node_hi) emit_new_node(a, R + before + i * kBlock + tid, node[i], ext[i]);
+        // the others, one thread per new node
+        for (int32_t p0 = 0, j = kAhead * kBlock + tid;;) {
+            for (; j < node_hi; j += kBlock) {
+                const uint32_t u = new_node(s_word, s_widx, s_off, in_pass, base, j);
+                emit_new_node(a, R + before + j, u, new_extent(a, u));
             }
+            p0 += kMarkCap;
+            if (p0 >= total_nz) break;
             __syncthreads();
+            fill(p0);
+            __syncthreads();
+            in_pass = total_nz - p0 < kMarkCap ? total_nz - p0 : kMarkCap;
+            j = s_off[0] + tid;
+            node_hi = s_off[in_pass - 1] + __popcll(s_word[in_pass - 1]);
         }
     }
 }
