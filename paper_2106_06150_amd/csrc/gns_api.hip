@@ -924,8 +924,13 @@ gns_status gns_sample_blocks_group(gns_ctx* const* ctxs, int32_t count, const ui
     const bool side_by_side = root->has_sampled && root->last_sampled_on != s;
     root->has_sampled = true;
     root->last_sampled_on = s;
-    if (lead->prof_mask == 0 && lead->cap_stream && replayed(lead, side_by_side) && !small_batches(g, dyn)) st = launch_batch_graph(g, dyn, s);
-    else                                                                                   st = enqueue_batch(g, dyn, s);
+    if (lead->prof_mask == 0 && lead->cap_stream && replayed(lead, side_by_side) && !small_batches(g, dyn)) {
+        bound_rows(g, nullptr);
+        st = launch_batch_graph(g, dyn, s);
+    } else {
+        bound_rows(g, &dyn);
+        st = enqueue_batch(g, dyn, s);
+    }
     if (st != GNS_OK) return st;
     const int nl = lead->config.num_layers;
     for (int b = 0; b < count; ++b) {

@@ -118,11 +118,9 @@ void set_group_layer(const Group& g, int layer_index, LayerArgs* out)
 // Enqueues the first kernel of a group of mini-batches.
 hipError_t launch_batch_begin(const Group& g, const BeginDyn& d, hipStream_t s)
 {
-    gns_ctx* c = g.ctx[0];
     LayerArgs a;
     fill_first_args(g, &a);
-    // the grid is sized for the largest batch: the same launch serves every replay
-    const dim3 grid = group_grid(g, a, ((int64_t) c->config.max_seeds + kBlock - 1) / kBlock);
+    const dim3 grid = group_grid(g, a, (g.rows[0] + kBlock - 1) / kBlock);
     hipLaunchKernelGGL(k_batch_begin, grid, dim3(kBlock), 0, s, a, d);
     return hipGetLastError();
 }
@@ -550,7 +548,7 @@ void fill_finish_template(const Group& g, int layer_index, FinishArgs* out)
     a.rows_per_sum = rows_per_sum(g, layer_index);
     a.inv_fanout = 1.0 / (double) a.fanout;
     a.unit_weights = c->config.policy[layer_index] == GNS_UNIFORM ? 1 : 0;
-    a.row_tiles_max = (int32_t) ((L.rows[layer_index] + kTile - 1) / kTile);
+    a.row_tiles_max = (int32_t) ((g.rows[layer_index] + kTile - 1) / kTile);
     a.mark_tiles = (int32_t) L.mark_tiles;
     a.mark_tile_words = L.mark_tile_words;
     a.g_indptr = c->graph.indptr;
@@ -567,9 +565,10 @@ void fill_finish_template(const Group& g, int layer_index, FinishArgs* out)
     }
 }
 
-int relabel_grid(const gns_ctx* c, int layer_index)
+int relabel_grid(const Group& g, int layer_index)
 {
-    const int64_t max_slots = c->lay.rows[layer_index] * (int64_t) c->config.fanout[layer_index];
+    const gns_ctx* c = g.ctx[0];
+    const int64_t max_slots = g.rows[layer_index] * (int64_t) c->config.fanout[layer_index];
     int64_t rb = (max_slots + kBlock * kRelabelUnroll - 1) / (kBlock * kRelabelUnroll);
     if (rb > (int64_t) c->num_cus * 2) rb = (int64_t) c->num_cus * 2;
     if (rb < 1) rb = 1;
@@ -635,12 +634,11 @@ __global__ void __launch_bounds__(kBlock) k_relabel_last(LayerArgs g)
 
 hipError_t launch_relabel(const Group& g, int layer_index, hipStream_t s)
 {
-    gns_ctx* c = g.ctx[0];
     LayerArgs a;
     fill_group_args(g, &a);
     set_group_layer(g, layer_index, &a);
     fill_finish_template(g, layer_index, &a.f);
-    a.blocks = relabel_grid(c, layer_index);
+    a.blocks = relabel_grid(g, layer_index);
     with_one(g, [&](auto kOne) { hipLaunchKernelGGL(k_relabel_last<decltype(kOne)::value>, group_grid(g, a, a.blocks), dim3(kBlock), 0, s, a); });
     return hipGetLastError();
 }
@@ -790,7 +788,7 @@ hipError_t launch_finish_cached(const Group& g, hipStream_t s)
     fill_group_args(g, &a);
     set_group_layer(g, layer_index, &a);
     fill_finish_template(g, layer_index, &a.f);
-    a.blocks = (int32_t) ((c->lay.rows[layer_index] + kBlock - 1) / kBlock);
+    a.blocks = (int32_t) ((g.rows[layer_index] + kBlock - 1) / kBlock);
     with_one(g, [&](auto kOne) { hipLaunchKernelGGL(k_finish_cached<decltype(kOne)::value>, group_grid(g, a, a.blocks), dim3(kBlock), 0, s, a); });
     return hipGetLastError();
 }

@@ -502,7 +502,27 @@ struct Group {
     int count;
     gns_ctx* ctx[kMaxGroup];
     gns_block* blocks[kMaxGroup];    // each: the caller's array of num_layers blocks
+    int64_t rows[GNS_MAX_LAYERS + 1];        // what a batch's layers have at most, see bound_rows
 };
+
+// Grids and rows per wave go by the rows that the group's own seeds can lead to, where a launch serves this call alone (d); a captured
+// one serves calls with any number of seeds.  A context often takes more seeds than a call brings, and blocks without rows are not
+// free, nor are waves of many rows.  Batches of 16, 100 and 256 seeds in contexts for 1024 on 1 M nodes 74.7 -> 68.8, 75.0 -> 71.6 and
+// 78.3 -> 76.0 us (a call with gather and aggregation), groups of four times 64 and 256 76.0 -> 72.5 and 116.6 -> 112.7, four times 100 on 40 M nodes
+// 92.2 -> 87.1.
+// (The limit is the lists' length, not the graph's: behind repeated seeds a list can be longer than that.)
+inline void bound_rows(Group& g, const BeginDyn* d)
+{
+    const gns_ctx* c = g.ctx[0];
+    const Layout& L = c->lay;
+    g.rows[0] = d ? 1 : L.rows[0];
+    for (int b = 0; d && b < g.count; ++b)
+        if (d->num_seeds[b] > g.rows[0]) g.rows[0] = d->num_seeds[b];
+    for (int i = 0; i < c->config.num_layers; ++i) {
+        const int64_t next = g.rows[i] * (1 + c->config.fanout[i]);
+        g.rows[i + 1] = next < L.rows[i + 1] ? next : L.rows[i + 1];
+    }
+}
 
 // f(kOne): calls it with whether the group is a single batch as a compile-time constant.
 template <typename F>
@@ -526,7 +546,7 @@ void fill_sample_template(gns_ctx* c, int layer_index, SampleArgs* out);
 void fill_finish_template(const Group& g, int finish_layer, FinishArgs* out);
 // The fixed arguments of the group's first kernel.
 void fill_first_args(const Group& g, LayerArgs* out);
-int relabel_grid(const gns_ctx* c, int layer_index);
+int relabel_grid(const Group& g, int layer_index);
 // Whether a layer is sampled without a plan or flag pass in front: UNIFORM, or from the induced subgraph.
 bool direct_layer(const gns_config& config, int layer_index);
 // Whether the input layer's union and relabel are one launch.

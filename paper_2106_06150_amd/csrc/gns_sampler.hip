@@ -915,16 +915,14 @@ bool first_layer_enters_seeds(const gns_config& config)
 
 // Rows per wave of the two-stage sampler: as many as leave 32 waves for every CU (all it holds) at the layer's worst-case
 // number of rows, a power of two between 4 and 32.  (A mini-batch's grid ends at 16 waves for every CU, so single ones take their
-// rows in more turns.)  That number is all the host knows; input layers have 0.2 (cache first) to
+// rows in more turns.)  The worst case of the call's seeds (bound_rows) is all the host knows; input layers have 0.2 (cache first) to
 // 0.5 of it (fan-outs 15, 10 on 1 M nodes), so their launches have fewer waves than that.  Layers of 4 x 12,600 rows, fan-out
 // 10: 25 us with 8 rows per wave, 26 with 16, 37 with 64; of 4 x 92,400 rows, fan-out 5: 36.5 us with 32, 37.5 with 64, 42
-// with 16 (twice the blocks).  Mini-batches far below what their context takes have few waves of many rows: input layer of
-// four times 256 and 64 seeds where contexts take 1024 16.6 and 11.1 us, 128 where they take 2048 13.2; 25.5, 18.2 and 22.0 with
-// up to 64 rows per wave, half as many waves aimed at, five entries of a lane on their way and places by a count.
+// with 16 (twice the blocks).  Captured launches go by the context's worst case: mini-batches far below it have few waves of many rows there.
 static int wave_rows(const Group& g, int layer_index)
 {
     const gns_ctx* c = g.ctx[0];
-    const int64_t rows = c->lay.rows[layer_index] * g.count;
+    const int64_t rows = g.rows[layer_index] * g.count;
     int W = 4;
     while (W < kWaveRows && (int64_t) W * c->num_cus * 32 < rows) W *= 2;
     return W;
@@ -963,9 +961,8 @@ hipError_t launch_first_layer(const Group& g, const BeginDyn& d, hipStream_t s)
     gns_ctx* c = g.ctx[0];
     LayerArgs a;
     fill_first_args(g, &a);
-    // the grid is sized for the largest batch: the same launch serves every replay
     const int rows_per_block = rows_per_sum(g, 0);
-    const dim3 grid = group_grid(g, a, ((int64_t) c->config.max_seeds + rows_per_block - 1) / rows_per_block);
+    const dim3 grid = group_grid(g, a, (g.rows[0] + rows_per_block - 1) / rows_per_block);
     with_unroll(a.s.fanout, [&](auto K) {
         with_list(c, 0, [&](auto kList) {
             with_one(g, [&](auto kOne) {
@@ -992,7 +989,6 @@ void fill_first_args(const Group& g, LayerArgs* out)
 hipError_t launch_sample_layer(const Group& g, int layer_index, hipStream_t s)
 {
     gns_ctx* c = g.ctx[0];
-    const Layout& L = c->lay;
     LayerArgs a;
     fill_group_args(g, &a);
     set_group_layer(g, layer_index, &a);
@@ -1000,14 +996,14 @@ hipError_t launch_sample_layer(const Group& g, int layer_index, hipStream_t s)
     int rl = 0;
     if (layer_index > 0) {
         fill_finish_template(g, layer_index - 1, &a.f);
-        rl = relabel_grid(c, layer_index - 1);
+        rl = relabel_grid(g, layer_index - 1);
     }
     auto grid_of = [&](int64_t blocks) {
         a.blocks = (int32_t) blocks;
         return group_grid(g, a, blocks);
     };
 
-    const int64_t rows_max = L.rows[layer_index];
+    const int64_t rows_max = g.rows[layer_index];
     const dim3 tb(kBlock);
     const int policy = c->config.policy[layer_index];
     if (direct_layer(c->config, layer_index)) {

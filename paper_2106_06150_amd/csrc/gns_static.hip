@@ -100,6 +100,7 @@ extern "C" gns_status gns_sample_blocks_static(gns_ctx* ctx, uint64_t seed, cons
         BeginDyn dyn;
         c->stamp = 1;                     // the table has just been cleared
         fill_begin_dyn(g, &seed, &seeds_dev, &num_seeds, &dyn);
+        bound_rows(g, &dyn);
         st = enqueue_batch(g, dyn, s);
     }
     if (st == GNS_OK) {
