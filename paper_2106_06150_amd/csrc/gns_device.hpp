@@ -114,22 +114,41 @@ __device__ __forceinline__ int opaque(int x)
 }
 __device__ __forceinline__ int opaque_lane_id() { return opaque(lane_id()); }
 
+// Six steps that read other lanes' registers: through LDS (shuffles) every one is a trip there, and a block's scan of 256 numbers 0.4 us.
+// One step: adds the value kCtrl selects from a lower lane (0 where there is none).  All lanes of the wave call it.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ unsigned long long dpp_add(unsigned long long v)
+{
+    const uint32_t lo = (uint32_t) __builtin_amdgcn_update_dpp(0, (int) (uint32_t) v, kCtrl, kRowMask, 0xf, false);
+    const uint32_t hi = (uint32_t) __builtin_amdgcn_update_dpp(0, (int) (uint32_t) (v >> 32), kCtrl, kRowMask, 0xf, false);
+    return v + (((unsigned long long) hi << 32) | lo);
+}
+
+__device__ __forceinline__ unsigned long long wave_inclusive_scan64(unsigned long long v)
+{
+    v = dpp_add<0x111, 0xf>(v);      // row_shr:1, 2, 4, 8 within the rows of 16 lanes
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);      // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 __device__ __forceinline__ int32_t wave_inclusive_scan(int32_t v)
 {
-    const int lane = opaque_lane_id();
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const int32_t up = __shfl_up(v, d, kWave);
-        if (lane >= d) v += up;
-    }
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
     return v;
 }
 
 __device__ __forceinline__ int32_t wave_sum(int32_t v)
 {
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
-    return v;
+    return __builtin_amdgcn_readlane(wave_inclusive_scan(v), kWave - 1);
 }
 
 // Exclusive scan over the kBlock threads of a block; *total receives the block

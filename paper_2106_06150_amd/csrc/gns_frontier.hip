@@ -168,6 +168,17 @@ __device__ __forceinline__ RowExtent new_extent(const FinishArgs& a, uint32_t no
     return ext;
 }
 
+// The same without a branch, in which a read would be waited for: the offsets as four words of 32 bits, of which those of 32-bit offsets
+// are two.
+__device__ __forceinline__ RowExtent extent_of(const FinishArgs& a, uint32_t node)
+{
+    const uint64_t at = a.last_layer ? 0u : node;
+    const uint32_t* p = reinterpret_cast<const uint32_t*>(a.g_indptr) + (at << a.g_i64);
+    const uint32_t start = p[0], end = p[1 << a.g_i64];
+    const uint32_t start_hi = p[a.g_i64], end_hi = p[(1 << a.g_i64) + a.g_i64];
+    return {(int64_t) ((uint64_t) (a.g_i64 ? start_hi : 0u) << 32 | start), (int64_t) ((uint64_t) (a.g_i64 ? end_hi : 0u) << 32 | end)};
+}
+
 __device__ __forceinline__ void emit_new_node(const FinishArgs& a, int32_t pos, uint32_t node, const RowExtent& ext)
 {
     if (pos >= a.max_src) return;
@@ -188,8 +199,7 @@ __device__ __forceinline__ uint32_t new_node(const uint64_t* s_word, const int32
 }
 
 // What a thread reads of its first new nodes while the counts of the tiles before are on their way: a trip to memory behind that
-// wait otherwise (groups of four, first and second layer: 1 M nodes 8.7 and 13.2 -> 8.5 and 12.3 us, 40 M 14.8 and 22.6 -> 12.5 and 21.4;
-// a mini-batch of 100 seeds on 1 M nodes 7.1 -> 6.1).
+// wait otherwise.  Groups of four, first and second layer: 1 M nodes 8.7 and 13.2 -> 6.9 and 11.1 us, 40 M 14.8 and 22.6 -> 12.5 and 21.4.
 constexpr int kAhead = 2;
 
 // Nodes of the batch behind the layer: its rows and the new nodes, as many as the list takes.
@@ -268,9 +278,9 @@ __device__ __forceinline__ void union_sparse_tile(const FinishArgs& a, int32_t t
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kAhead; ++i) {
-        if (i * kBlock + tid >= ahead) continue;
-        node[i] = new_node(s_word, s_widx, s_off, words, base, i * kBlock + tid);
-        ext[i] = new_extent(a, node[i]);
+        const int32_t j = i * kBlock + tid;
+        node[i] = ahead > 0 ? new_node(s_word, s_widx, s_off, words, base, j < ahead ? j : ahead - 1) : 0u;
+        ext[i] = extent_of(a, node[i]);
     }
     int32_t before = 0;
     if (total > 0 || last)
@@ -499,9 +509,9 @@ __global__ void __launch_bounds__(kBlock) k_union(LayerArgs g, int spins)
         RowExtent ext[kAhead];
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) {
-            if (i * kBlock + tid >= node_hi) continue;
-            node[i] = new_node(s_word, s_widx, s_off, in_pass, base, i * kBlock + tid);
-            ext[i] = new_extent(a, node[i]);
+            const int32_t j = i * kBlock + tid;
+            node[i] = node_hi > 0 ? new_node(s_word, s_widx, s_off, in_pass, base, j < node_hi ? j : node_hi - 1) : 0u;
+            ext[i] = extent_of(a, node[i]);
         }
         int32_t before = 0;
         if (total > 0 || last) before = sum_before(a.tile_sums, tag, tile, spins, smem, [&](int32_t t) { return count_tile(a, t); });
@@ -653,7 +663,7 @@ hipError_t launch_relabel(const Group& g, int layer_index, hipStream_t s)
 // Groups of four on 1 M nodes (10 K cached) 9.1 + 9.4 -> 11.2 us and the sampler 37.6 -> 37.6, on 6.5 M nodes (65 K cached) 11.4 + 7.8 ->
 // 11.9 and the sampler 39.7 -> 27.0: its marks were atomics, two each, carried out at the memory.  On 40 M nodes (400 K cached)
 // sampler, union and relabel 54 + 17.1 + 11.7 -> 45.4 + 10.7 + 9.3.
-constexpr int kFinishFlight = 8;                 // edges of a thread on their way
+constexpr int kFinishFlight = 6;                 // edges of a thread on their way
 
 template <bool kOne>
 __global__ void __launch_bounds__(kBlock) k_finish_cached(LayerArgs g)
@@ -673,6 +683,10 @@ __global__ void __launch_bounds__(kBlock) k_finish_cached(LayerArgs g)
     const int32_t k = a.fanout, rows = R - base < kBlock ? R - base : kBlock, items = rows * k;
     const int32_t first = base * k;                              // below 2^31: checked when the workspace is sized
     const int32_t num = tid < rows ? a.s_cnt[base + tid] : 0;
+    // the batch begins with its seeds: a bit of the seed bitmap per row to clear
+    int32_t marked_seed = -1;
+    if (g.off.marks_seeds && base + tid < a.st->num_dst[0]) marked_seed = at<int32_t>(g.b[b].ws, g.off.seed_copy)[base + tid];
+    if ((int64_t) marked_seed >= a.num_nodes) marked_seed = -1;
     int32_t u[kFinishFlight];
     float w[kFinishFlight];
     auto load = [&](int32_t q0) {
@@ -715,13 +729,8 @@ __global__ void __launch_bounds__(kBlock) k_finish_cached(LayerArgs g)
     int32_t marked = 0;
     for (int32_t i = tid * per; i < (tid + 1) * per && i < words; ++i) marked += __popcll(s_bits[i]);
     const int lane = opaque_lane_id(), wave = opaque(tid >> 6);
-    uint64_t sums = (uint64_t) (uint32_t) marked << 32 | (uint32_t) num;
-    const uint64_t own = sums;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const uint64_t up = __shfl_up((unsigned long long) sums, d, kWave);
-        if (lane >= d) sums += up;
-    }
+    const uint64_t own = (uint64_t) (uint32_t) marked << 32 | (uint32_t) num;
+    const uint64_t sums = wave_inclusive_scan64(own);
     part = wave_sum(part);
     if (lane == kWave - 1) { s_sums[wave] = sums; s_part[wave] = part; }
     __syncthreads();
@@ -745,17 +754,24 @@ __global__ void __launch_bounds__(kBlock) k_finish_cached(LayerArgs g)
     if (tid < rows) a.indptr[base + tid] = before + s_off[tid];
     for (int32_t q0 = 0; q0 < k; q0 += kFinishFlight) {
         if (q0 > 0) load(q0);
+        // (all that LDS is asked for first, whether or not an edge is there)
+        int32_t o[kFinishFlight], local[kFinishFlight];
+        bool ok[kFinishFlight];
 #pragma unroll
         for (int i = 0; i < kFinishFlight; ++i) {
-            const int32_t j = (q0 + i) * kBlock + tid;
-            const int32_t row = (int32_t) (((float) j + 0.5f) * (float) a.inv_fanout);         // j / k: exact below 2^16
-            const int32_t s = j - row * k;
-            if (j >= items || s >= s_num[row]) continue;
-            int32_t local = -1 - u[i];
-            if (u[i] >= 0) local = R + s_before[u[i] >> 6] + __popcll(s_bits[u[i] >> 6] & bits_below(u[i]));
-            const int32_t o = before + s_off[row] + s;
-            a.indices[o] = local;
-            a.weights[o] = w[i];
+            const int32_t j = (q0 + i) * kBlock + tid, jc = j < items ? j : items - 1;
+            const int32_t row = (int32_t) (((float) jc + 0.5f) * (float) a.inv_fanout);        // jc / k: exact below 2^16
+            const int32_t s = jc - row * k, slot = u[i] >= 0 ? u[i] : 0;
+            ok[i] = j < items && s < s_num[row];
+            o[i] = before + s_off[row] + s;
+            const int32_t word = ok[i] ? slot >> 6 : 0;                  // (places without an edge hold anything)
+            local[i] = R + s_before[word] + __popcll(s_bits[word] & bits_below(slot));
+        }
+#pragma unroll
+        for (int i = 0; i < kFinishFlight; ++i) {
+            if (!ok[i]) continue;
+            a.indices[o[i]] = u[i] >= 0 ? local[i] : -1 - u[i];
+            a.weights[o[i]] = w[i];
         }
     }
     // the new nodes: a wave per word of marks, or where blocks are few by all their threads
@@ -768,7 +784,7 @@ __global__ void __launch_bounds__(kBlock) k_finish_cached(LayerArgs g)
     } else {
         each_marked(s_bits, s_before, words, base + tid, fresh, blocks * kBlock, emit);
     }
-    if (block == 0) clear_seed_marks(g, b, a);
+    if (marked_seed >= 0) at<uint64_t>(g.b[b].ws, g.off.seed_mark)[marked_seed >> 6] = 0ull;
     if (base + kBlock >= R) {
         const int32_t nodes = R + fresh < a.max_src ? R + fresh : a.max_src, edges = before + total;
         if (tid == 0) {

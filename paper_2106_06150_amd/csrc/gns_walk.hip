@@ -157,26 +157,6 @@ __device__ __forceinline__ void wave_share(const WalkStepArgs& a, int64_t wave, 
     *row_hi = at[1];
 }
 
-// One DPP step of a wave-wide inclusive scan: adds the value kCtrl selects from a lower lane (0 where there is none).
-template <int kCtrl, int kRowMask>
-__device__ __forceinline__ unsigned long long dpp_add(unsigned long long v)
-{
-    const uint32_t lo = (uint32_t) __builtin_amdgcn_update_dpp(0, (int) (uint32_t) v, kCtrl, kRowMask, 0xf, false);
-    const uint32_t hi = (uint32_t) __builtin_amdgcn_update_dpp(0, (int) (uint32_t) (v >> 32), kCtrl, kRowMask, 0xf, false);
-    return v + (((unsigned long long) hi << 32) | lo);
-}
-
-__device__ __forceinline__ unsigned long long wave_inclusive_scan64(unsigned long long v)
-{
-    v = dpp_add<0x111, 0xf>(v);      // row_shr:1, 2, 4, 8 within the rows of 16 lanes
-    v = dpp_add<0x112, 0xf>(v);
-    v = dpp_add<0x114, 0xf>(v);
-    v = dpp_add<0x118, 0xf>(v);
-    v = dpp_add<0x142, 0xa>(v);      // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xc>(v);      // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
 __device__ __forceinline__ unsigned long long read_lane64(unsigned long long v, int lane)
 {
     const uint32_t lo = (uint32_t) __builtin_amdgcn_readlane((int) (uint32_t) v, lane);
