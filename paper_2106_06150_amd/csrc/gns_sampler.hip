@@ -417,6 +417,7 @@ __device__ __forceinline__ int32_t chunks_touched(int64_t start, int64_t end)
 
 // Plan tiles are kPlanTile rows (one row per thread): many small blocks keep the expansion parallel.
 constexpr int kPlanTile = kBlock;
+constexpr int kPlanFlight = 8;      // entries of a thread that look their rows up together
 
 // One launch: a tile's block passes its number of chunks on to the blocks of later tiles (sum_before), as the union step's
 // blocks do with the rows' samples.  Two launches fewer: a mini-batch with a scan of its rows 189 -> 185 us.
@@ -424,7 +425,7 @@ template <bool kOne>
 __global__ void __launch_bounds__(kBlock) k_plan(LayerArgs g, int relabel_blocks, int spins)
 {
     __shared__ int32_t smem[kBlock / kWave + 1];
-    __shared__ int32_t s_off[kPlanTile + 1];
+    __shared__ int32_t s_off[kPlanTile];
     __shared__ int32_t s_g0[kPlanTile];
     __shared__ int32_t s_hubs[kBlock / kWave], s_first_hub;
     const auto [b, tile] = group_block<kOne>(g.dealt);
@@ -447,15 +448,35 @@ __global__ void __launch_bounds__(kBlock) k_plan(LayerArgs g, int relabel_blocks
     int32_t total;
     s_off[threadIdx.x] = block_exclusive_scan(chunks_touched(ext.start, ext.end), smem, &total);
     const uint32_t tag = launch_tag(a.st, a.layer_index);
+    if (threadIdx.x == 0) publish_sum(a.plan_sums, tile, tag, (uint32_t) total);
+    __syncthreads();
+    // behind the sum others wait for: the tile's hubs take their places in the layer's list
+    int32_t first_hub = 0;
     if (threadIdx.x == 0) {
-        s_off[kPlanTile] = total;
-        publish_sum(a.plan_sums, tile, tag, (uint32_t) total);
-        // behind the sum others wait for: the tile's hubs take their places in the layer's list (s_hubs is complete: the scan
-        // has synchronised)
         int32_t hub_total = 0;
+#pragma unroll
         for (int w = 0; w < kBlock / kWave; ++w) hub_total += s_hubs[w];
-        if (hub_total) s_first_hub = atomicAdd(&a.st->hub_count[a.layer_index], hub_total);
+        if (hub_total) first_hub = atomicAdd(&a.st->hub_count[a.layer_index], hub_total);
     }
+    const uint32_t last_chunk = (uint32_t) ((a.num_entries - 1) >> 6);
+    // Entries j, j + kBlock, ... of the tile's work list: an entry's row is the last one whose offset is <= it (rows without a chunk
+    // have the offset of the row behind them).
+    auto entries = [&](int32_t j, uint32_t (&chunk)[kPlanFlight]) {
+        int32_t row[kPlanFlight];
+#pragma unroll
+        for (int i = 0; i < kPlanFlight; ++i) row[i] = 0;
+#pragma unroll
+        for (int step = kPlanTile / 2; step > 0; step /= 2)
+#pragma unroll
+            for (int i = 0; i < kPlanFlight; ++i) row[i] += s_off[row[i] + step] <= j + i * kBlock ? step : 0;
+#pragma unroll
+        for (int i = 0; i < kPlanFlight; ++i) {
+            const uint32_t c = (uint32_t) s_g0[row[i]] + (uint32_t) (j + i * kBlock - s_off[row[i]]);
+            chunk[i] = c < last_chunk ? c : last_chunk;
+        }
+    };
+    uint32_t chunk[kPlanFlight];
+    entries((int32_t) threadIdx.x, chunk);                       // (while the sums of the tiles before are on their way)
     // chunks of all earlier tiles
     const int32_t before = sum_before(a.plan_sums, tag, tile, spins, smem, [&](int32_t t) {
         uint32_t n = 0;
@@ -469,22 +490,22 @@ __global__ void __launch_bounds__(kBlock) k_plan(LayerArgs g, int relabel_blocks
         const uint32_t chunks = (uint32_t) before + (uint32_t) total;
         a.st->plan_chunks = (int32_t) (chunks < a.max_chunks ? chunks : a.max_chunks);
     }
+    if (threadIdx.x == 0) s_first_hub = first_hub;
     __syncthreads();
     if (hub) {
         int32_t place = s_first_hub + __popcll(hubs & ((1ull << lane_id()) - 1ull));
         for (int w = 0; w < (int) (threadIdx.x >> 6); ++w) place += s_hubs[w];
         a.hub_rows[place] = r;
     }
-    const uint32_t last_chunk = (uint32_t) ((a.num_entries - 1) >> 6);
-    // one thread per work-list entry: its row is the last one whose offset is <= j
-    for (int32_t j = (int32_t) threadIdx.x; j < total; j += kBlock) {
-        int32_t lo = 0, hi = kPlanTile;
-        while (hi - lo > 1) {
-            const int32_t mid = (lo + hi) >> 1;
-            if (s_off[mid] <= j) lo = mid; else hi = mid;
+    for (int32_t j = (int32_t) threadIdx.x;;) {
+#pragma unroll
+        for (int i = 0; i < kPlanFlight; ++i) {
+            const uint32_t place = (uint32_t) before + (uint32_t) (j + i * kBlock);
+            if (j + i * kBlock < total && place < a.max_chunks) a.plan_desc[place] = (int32_t) chunk[i];
         }
-        const uint32_t place = (uint32_t) before + (uint32_t) j, chunk = (uint32_t) s_g0[lo] + (uint32_t) (j - s_off[lo]);
-        if (place < a.max_chunks) a.plan_desc[place] = (int32_t) (chunk < last_chunk ? chunk : last_chunk);
+        j += kPlanFlight * kBlock;
+        if (j >= total) break;
+        entries(j, chunk);
     }
 }
 
