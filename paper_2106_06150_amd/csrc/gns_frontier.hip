@@ -198,9 +198,64 @@ __device__ __forceinline__ uint32_t new_node(const uint64_t* s_word, const int32
     return (uint32_t) ((base + s_widx[lo]) * 64 + select_bit64(s_word[lo], j - s_off[lo]));
 }
 
+// Places of the last of v[0 .. count) that are <= q, where v ascends in LDS and v[0] <= q: kN searches step by step together, whose
+// reads one after the other are a chain of 30 and more.  `count` (>= 1) is the same for the whole block.
+template <int kN>
+__device__ __forceinline__ void last_not_above(const int32_t* v, int32_t count, const int32_t (&q)[kN], int32_t (&at)[kN])
+{
+    const int32_t end = __builtin_amdgcn_readfirstlane(count) - 1;
+#pragma unroll
+    for (int i = 0; i < kN; ++i) at[i] = 0;
+    for (int32_t step = end > 0 ? 1 << (31 - __clz(end)) : 0; step > 0; step >>= 1)
+#pragma unroll
+        for (int i = 0; i < kN; ++i) {
+            const int32_t m = at[i] + step < end ? at[i] + step : end;
+            at[i] = v[m] <= q[i] ? m : at[i];
+        }
+}
+
 // What a thread reads of its first new nodes while the counts of the tiles before are on their way: a trip to memory behind that
-// wait otherwise.  Groups of four, first and second layer: 1 M nodes 8.7 and 13.2 -> 6.9 and 11.1 us, 40 M 14.8 and 22.6 -> 12.5 and 21.4.
-constexpr int kAhead = 2;
+// wait otherwise.  Groups of four, first and second layer: 1 M nodes 8.7 and 13.2 -> 6.4 and 10.5 us, 40 M 14.8 and 22.6 -> 9.4 and 18.9.
+// Where the bitmap has a summary, tiles hold more new nodes and their extents are further away: four a turn, looked up together (two,
+// one by one: 12.0 and 20.3).  Smaller graphs gain nothing by it, and two launch sequences side by side lose 0.4 %.
+constexpr int kAhead = 2, kAheadFar = 4;
+
+struct NewNodes {
+    uint32_t node[kAheadFar];
+    RowExtent ext[kAheadFar];
+};
+
+// New nodes j, j + kBlock, ... (below hi; node 0 beyond it) of those whose words stand in LDS, `count` of them, the first at bitmap
+// word `base`.  j begins with the thread's place; the others are the same for the whole block.
+__device__ __forceinline__ void find_new(const FinishArgs& a, const uint64_t* s_word, const int32_t* s_widx, const int32_t* s_off, int32_t count,
+                                         int64_t base, int32_t j, int32_t hi, NewNodes& f)
+{
+#pragma unroll
+    for (int i = 0; i < kAheadFar; ++i) f.node[i] = 0u;
+    auto look_up = [&](auto turns) {
+        constexpr int kTurns = decltype(turns)::value;
+        int32_t q[kTurns], at[kTurns];
+#pragma unroll
+        for (int i = 0; i < kTurns; ++i) q[i] = j + i * kBlock < hi ? j + i * kBlock : hi - 1;
+        last_not_above(s_off, count, q, at);
+#pragma unroll
+        for (int i = 0; i < kTurns; ++i) f.node[i] = (uint32_t) ((base + s_widx[at[i]]) * 64 + select_bit64(s_word[at[i]], q[i] - s_off[at[i]]));
+    };
+    // (a look-up is 60 instructions: 0.6 us of the union step where tiles have fewer new nodes than threads and every thread took four)
+    const int32_t left = __builtin_amdgcn_readfirstlane(hi - j + (int32_t) (threadIdx.x & (kWave - 1)));
+    if (left > 2 * kBlock)  look_up(std::integral_constant<int, kAheadFar>());
+    else if (left > kBlock) look_up(std::integral_constant<int, 2>());
+    else if (left > 0)      look_up(std::integral_constant<int, 1>());
+#pragma unroll
+    for (int i = 0; i < kAheadFar; ++i) f.ext[i] = extent_of(a, f.node[i]);
+}
+
+__device__ __forceinline__ void emit_new_nodes(const FinishArgs& a, int32_t rows, int32_t j, int32_t hi, const NewNodes& f)
+{
+#pragma unroll
+    for (int i = 0; i < kAheadFar; ++i)
+        if (j + i * kBlock < hi) emit_new_node(a, rows + j + i * kBlock, f.node[i], f.ext[i]);
+}
 
 // Nodes of the batch behind the layer: its rows and the new nodes, as many as the list takes.
 __device__ __forceinline__ void publish_nodes(const FinishArgs& a, int32_t nodes)
@@ -231,30 +286,26 @@ __device__ __forceinline__ void union_sparse_tile(const FinishArgs& a, int32_t t
     __syncthreads();
     // marked words p0 .. p0 + kMarkCap - 1 into LDS, four consecutive ones per thread; returns the new nodes among them
     int32_t widx[kPer];
+    const uint64_t* seeds = a.seed_mark ? a.seed_mark : a.mark;
     auto load_pass = [&](int32_t p0, int32_t before) -> int32_t {
-        uint64_t w[kPer];
-        int32_t cnt = 0;
+        uint64_t w[kPer], seed[kPer];
+        int32_t cnt = 0, q[kPer], at[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) q[i] = p0 + tid * kPer + i;
+        last_not_above(s_pre, S, q, at);                     // last summary word with no more than q marked words before it
+        // (no read in a branch, in which it would be waited for: places past the last word read the tile's first)
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) widx[i] = q[i] < words ? at[i] * 64 + select_bit64(s_sum[at[i]], q[i] - s_pre[at[i]]) : -1;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) w[i] = a.mark[base + (widx[i] >= 0 ? widx[i] : 0)];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) seed[i] = seeds[base + (widx[i] >= 0 ? widx[i] : 0)];
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
-            const int32_t q = p0 + tid * kPer + i;
-            widx[i] = -1;
-            if (q < words) {
-                int lo = 0, hi = S;                          // last summary word with no more than q marked words before it
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (s_pre[mid] <= q) lo = mid; else hi = mid;
-                }
-                widx[i] = lo * 64 + select_bit64(s_sum[lo], q - s_pre[lo]);
-            }
+            if (a.seed_mark) w[i] &= ~seed[i];               // a marked seed is no new node
+            if (widx[i] < 0) w[i] = 0ull;
+            cnt += __popcll(w[i]);
         }
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) w[i] = widx[i] >= 0 ? a.mark[base + widx[i]] : 0ull;
-        if (a.seed_mark) {                                   // a marked seed is no new node
-#pragma unroll
-            for (int i = 0; i < kPer; ++i) w[i] &= widx[i] >= 0 ? ~a.seed_mark[base + widx[i]] : 0ull;
-        }
-#pragma unroll
-        for (int i = 0; i < kPer; ++i) cnt += __popcll(w[i]);
         int32_t total;
         int32_t off = before + block_exclusive_scan(cnt, smem, &total);
 #pragma unroll
@@ -273,15 +324,9 @@ __device__ __forceinline__ void union_sparse_tile(const FinishArgs& a, int32_t t
     if (tid == 0) publish_sum(a.tile_sums, tile, tag, (uint32_t) total);
     const bool last = tile == a.mark_tiles - 1;
     const int32_t ahead = words <= kMarkCap ? total : 0;     // nodes known from the words in LDS
-    uint32_t node[kAhead];
-    RowExtent ext[kAhead];
     __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kAhead; ++i) {
-        const int32_t j = i * kBlock + tid;
-        node[i] = ahead > 0 ? new_node(s_word, s_widx, s_off, words, base, j < ahead ? j : ahead - 1) : 0u;
-        ext[i] = extent_of(a, node[i]);
-    }
+    NewNodes f;
+    find_new(a, s_word, s_widx, s_off, ahead > 0 ? words : 0, base, tid, ahead, f);
     int32_t before = 0;
     if (total > 0 || last)
         before = sum_before(a.tile_sums, tag, tile, spins, smem, [&](int32_t t) { return count_tile(a, t); });
@@ -302,17 +347,12 @@ __device__ __forceinline__ void union_sparse_tile(const FinishArgs& a, int32_t t
         for (int i = 0; i < kPer; ++i)
             if (widx[i] >= 0) a.mark[base + widx[i]] = 0ull;                 // ready for the next layer
         const int32_t here = words - p0 < kMarkCap ? words - p0 : kMarkCap;
-        // one thread per new node
-        if (ahead > 0) {
-#pragma unroll
-            for (int i = 0; i < kAhead; ++i)
-                if (i * kBlock + tid < ahead) emit_new_node(a, R + before + i * kBlock + tid, node[i], ext[i]);
+        const int32_t hi = node_lo + in_pass;
+        for (int32_t j = node_lo + tid; j - tid < hi; j += kAheadFar * kBlock) {
+            if (ahead == 0 || j != tid) find_new(a, s_word, s_widx, s_off, here, base, j, hi, f);
+            emit_new_nodes(a, R + before, j, hi, f);
         }
-        for (int32_t j = node_lo + tid + (ahead > 0 ? kAhead * kBlock : 0); j < node_lo + in_pass; j += kBlock) {
-            const uint32_t u = new_node(s_word, s_widx, s_off, here, base, j);
-            emit_new_node(a, R + before + j, u, new_extent(a, u));
-        }
-        node_lo += in_pass;
+        node_lo = hi;
     }
 }
 
@@ -323,18 +363,22 @@ __device__ __forceinline__ uint16_t mark_bits(const uint4& m)
     return (uint16_t) (four(m.x) | four(m.y) << 4 | four(m.z) << 8 | four(m.w) << 12);
 }
 
-// New nodes lo, lo + step, ... below hi of those that `words` words of marks in LDS hold, with the marks before each word beside it:
-// calls f(node, its word, its bit) by the thread.
+// New nodes lo, lo + step, ... below hi of those that `words` words of marks in LDS hold, with the marks before each word beside it;
+// `nodes` are those of their slots.  Calls emit(j, node) by the thread.
 template <typename F>
-__device__ __forceinline__ void each_marked(const uint64_t* bits, const int32_t* before, int32_t words, int32_t lo, int32_t hi, int32_t step, F&& f)
+__device__ __forceinline__ void each_marked(const uint64_t* bits, const int32_t* before, int32_t words, const int32_t* nodes, int32_t lo, int32_t hi,
+                                            int32_t step, F&& emit)
 {
-    for (int32_t j = lo; j < hi; j += step) {
-        int32_t l = 0, h = words;                                // the last word with no more than j marks before it
-        while (h - l > 1) {
-            const int32_t mid = (l + h) >> 1;
-            if (before[mid] <= j) l = mid; else h = mid;
-        }
-        f(j, l, select_bit64(bits[l], j - before[l]));
+    for (int32_t j = lo; j < hi; j += kAheadFar * step) {
+        int32_t q[kAheadFar], at[kAheadFar], node[kAheadFar];
+#pragma unroll
+        for (int i = 0; i < kAheadFar; ++i) q[i] = j + i * step < hi ? j + i * step : hi - 1;
+        last_not_above(before, words, q, at);
+#pragma unroll
+        for (int i = 0; i < kAheadFar; ++i) node[i] = nodes[at[i] * 64 + select_bit64(bits[at[i]], q[i] - before[at[i]])];
+#pragma unroll
+        for (int i = 0; i < kAheadFar; ++i)
+            if (j + i * step < hi) emit(j + i * step, node[i]);
     }
 }
 
@@ -389,8 +433,8 @@ __device__ __forceinline__ void union_slot_tile(const FinishArgs& a, int32_t til
     if (last && tid == 0) publish_nodes(a, R + before + total);
     __syncthreads();
     for (int32_t i = tid; i < words; i += kBlock) a.slot_words[base / 64 + i] = {s_bits[i], before + s_before[i], 0};
-    each_marked(s_bits, s_before, words, tid, total, kBlock, [&](int32_t j, int32_t w, int bit) {
-        if (R + before + j < a.max_src) a.src_nodes[R + before + j] = a.cache_nodes[base + w * 64 + bit];
+    each_marked(s_bits, s_before, words, a.cache_nodes + base, tid, total, kBlock, [&](int32_t j, int32_t node) {
+        if (R + before + j < a.max_src) a.src_nodes[R + before + j] = node;
     });
 }
 
@@ -776,13 +820,13 @@ __global__ void __launch_bounds__(kBlock) k_finish_cached(LayerArgs g)
     }
     // the new nodes: a wave per word of marks, or where blocks are few by all their threads
     const int32_t blocks = (R + kBlock - 1) / kBlock, w0 = block * (kBlock / kWave) + wave;
-    auto emit = [&](int32_t n, int32_t word, int bit) {
-        if (R + n < a.max_src) a.src_nodes[R + n] = a.cache_nodes[word * 64 + bit];
+    auto emit = [&](int32_t n, int32_t node) {
+        if (R + n < a.max_src) a.src_nodes[R + n] = node;
     };
     if (words <= blocks * (kBlock / kWave)) {
-        if (w0 < words && (s_bits[w0] >> lane & 1ull)) emit(s_before[w0] + __popcll(s_bits[w0] & bits_below(lane)), w0, lane);
+        if (w0 < words && (s_bits[w0] >> lane & 1ull)) emit(s_before[w0] + __popcll(s_bits[w0] & bits_below(lane)), a.cache_nodes[w0 * 64 + lane]);
     } else {
-        each_marked(s_bits, s_before, words, base + tid, fresh, blocks * kBlock, emit);
+        each_marked(s_bits, s_before, words, a.cache_nodes, base + tid, fresh, blocks * kBlock, emit);
     }
     if (marked_seed >= 0) at<uint64_t>(g.b[b].ws, g.off.seed_mark)[marked_seed >> 6] = 0ull;
     if (base + kBlock >= R) {
