@@ -265,9 +265,10 @@ __device__ __forceinline__ void publish_nodes(const FinishArgs& a, int32_t nodes
 
 // The bitmap side of the union step on graphs whose bitmap has a summary.  A tile has far more words than marks there, so
 // the marked words are enumerated from the tile's summary words (bit q of them is found by a search over their counts in
-// LDS) and read one per thread and turn, kMarkCap at a time: one read of the summary and one of the marks in the chain,
+// LDS) and read four per thread together, kMarkCap at a time: one read of the summary and one of the marks in the chain,
 // where a thread that looked at 32 words of its own in turn made the layer 21 to 29 us long (groups of four on 40 M nodes;
-// 15 to 28 us now, bound by the scattered reads and writes per new node, and the same for tiles of 2048 to 8192 words).  Most tiles take one pass; others read their words once more when the ids are written.
+// 9 to 19 us now, bound by the scattered reads and writes per new node).  Most tiles take one pass; others read their words once more
+// when the ids are written.
 __device__ __forceinline__ void union_sparse_tile(const FinishArgs& a, int32_t tile, int32_t R, int spins, int32_t* smem,
                                                   uint64_t* s_word, int32_t* s_widx, int32_t* s_off)
 {

@@ -249,6 +249,27 @@ def test_hub_row_spanning_many_flag_words(hub_degree, policy, flag_mode):
         gns.close()
 
 
+@pytest.mark.parametrize("degrees", [(20000,) * 8, (63, 64, 65, 0, 1), (130_000, 0, 2000), (2048 * 64 - 63, 1)])
+def test_scan_plan_of_long_and_empty_rows(degrees):
+    """A tile's list of chunks longer and shorter than the 2048 entries that the block looks up at a time, and of that length; rows
+    that begin and end inside a chunk, rows without an entry first, in between and last."""
+    n = 140_000
+    rng = np.random.default_rng(sum(degrees))
+    deg = np.zeros(n, dtype=np.int64)
+    deg[1:1 + len(degrees)] = degrees
+    deg[1000:3000] = rng.integers(0, 5, size=2000)
+    ip = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(deg, out=ip[1:])
+    ix = np.concatenate([np.sort(rng.choice(n, size=d, replace=False)) for d in deg if d]).astype(np.int32)
+    gns = GpuGns(torch.from_numpy(ip), torch.from_numpy(ix), None, fanouts=(5,), policies=(C,), cache_size=900, max_seeds=600, flag_mode=0)
+    try:
+        first = np.arange(0, 2 + len(degrees))
+        for batch, seeds in enumerate((first, np.concatenate([first[::-1], np.arange(1000, 1500)]))):
+            full_parity(gns, cache_seed=2, epoch=batch, batch_seed=3 + batch, seeds=torch.from_numpy(seeds.astype(np.int32)))
+    finally:
+        gns.close()
+
+
 def test_rows_with_no_neighbors_and_no_cached_neighbors():
     # nodes 0..9 isolated, the rest a ring; tiny cache -> most rows have N_C = 0
     n = 200
