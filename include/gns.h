@@ -108,7 +108,7 @@ typedef struct {
     int64_t num_nodes;             /* n = |V|, 1 <= n < 2^31                                   */
     int64_t num_entries;           /* nnz = indptr[n], 1 <= nnz                                */
     const void* indptr;            /* device: int32[n+1] or int64[n+1]                          */
-    int32_t indptr_is_i64;         /* 0: int32 offsets, 1: int64 offsets                        */
+    int32_t indptr_is_i64;         /* 0: int32 offsets, any other value: int64 offsets          */
     const int32_t* indices;        /* device: int32[nnz] neighbor ids                           */
     int32_t feat_dim;              /* F >= 0 (0: no features, gather/cache table unavailable)   */
     const float* feat_dev;         /* device fp32[n x F] row-major, or NULL                     */

@@ -573,6 +573,7 @@ gns_status gns_create(gns_ctx** out_ctx, const gns_graph* graph, const gns_confi
     if (!c) { snprintf(g_create_err, sizeof(g_create_err), "host allocation failed"); return GNS_ENOMEM; }
     memset(c, 0, sizeof(*c));
     c->graph = *graph;
+    c->graph.indptr_is_i64 = graph->indptr_is_i64 != 0;      // kernels shift by it
     c->config = *config;
     c->lay = L;
     c->ws = scratch_begin(workspace, 0);

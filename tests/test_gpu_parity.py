@@ -70,6 +70,26 @@ def test_input_layer_marked_by_slots(n, cache, fanouts, seeds, tile_words, monke
         gns.close()
 
 
+@pytest.mark.parametrize("flag", [2, -1, 64, -2 ** 31])
+def test_any_flag_but_zero_means_64_bit_offsets(flag, monkeypatch):
+    """gns_graph.indptr_is_i64 comes from a C caller as it pleases; the union step's reads of new nodes' extents go by it without a branch."""
+    make_graph = B.make_graph
+
+    def flagged(*args):
+        g = make_graph(*args)
+        g.indptr_is_i64 = flag
+        return g
+
+    monkeypatch.setattr(B, "make_graph", flagged)
+    ip, ix = _small()
+    for flag_mode in (0, 1):
+        gns = GpuGns(ip.to(torch.int64), ix, None, fanouts=(9, 4, 3), policies=(U, U, C), cache_size=300, max_seeds=400, flag_mode=flag_mode)
+        try:
+            full_parity(gns, cache_seed=9, epoch=0, batch_seed=5, seeds=synth.uniform_seed_batch(ip.numel() - 1, 400, 6))
+        finally:
+            gns.close()
+
+
 @pytest.mark.parametrize("F", [1, 3, 4, 32, 64, 96, 100, 128, 256, 260, 1024])
 def test_feature_widths_and_host_store(F):
     ip, ix = _small(n=1500)
