@@ -205,7 +205,10 @@ struct AggBatch {
 struct AggGroup {
     AggBatch b[GNS_MAX_GROUP];
     int32_t feat_dim;
+    uint32_t first_window;          // windows of columns of the launches before
 };
+
+constexpr uint32_t kAggWindow = 1024;      // columns a block takes at most (64 lanes of four times four)
 
 // the view of one batch the kernel body works on
 struct AggArgs : AggBatch {
@@ -234,7 +237,8 @@ struct AggArgs : AggBatch {
 // kSlots edges, slots beyond the fourth) sit in branches.  Lanes past the last column (kRagged) stand aside in the last of the
 // kPer reads and stores all the same: what a read costs the texture addressers is more than the wait.
 // kOff32: every byte offset into x_src fits 32 bits and row index and row size fit 24 bits, so an address is
-// the uniform base plus one 32-bit vector offset (one multiply-add per load).
+// the uniform base plus one 32-bit vector offset (one multiply-add per load).  Offsets within a row are counted from the
+// window's first column: rows of 2^30 floats are 4 GB long.
 template <int kLanes, int kPer, bool kRagged, bool kQuotient, bool kOff32>
 __device__ __forceinline__ void aggregate_rows(const AggArgs& a, uint32_t col0, uint32_t group, uint32_t num_groups, uint32_t count,
                                                uint32_t num_src)
@@ -243,15 +247,16 @@ __device__ __forceinline__ void aggregate_rows(const AggArgs& a, uint32_t col0, 
     constexpr int kFlight = (kPer >= 3 && kSlots > 4) ? 5 : kSlots;     // source rows read together
     const int lane = (int) (threadIdx.x % kLanes);
     const uint32_t F = (uint32_t) a.feat_dim;
-    const uint32_t row_bytes = F * 4u;
+    const uint32_t row_bytes = F * 4u;                                  // (kOff32)
+    const uint32_t base = kLanes * kPer * 4 < kAggWindow ? 0u : col0 < F - 4u ? col0 : F - 4u;
     const bool in_last = !kRagged || col0 + 4u * ((uint32_t) lane + (uint32_t) (kPer - 1) * kLanes) < F;
     uint32_t col_bytes[kPer];
 #pragma unroll
     for (int p = 0; p < kPer; ++p) {
         const uint32_t c = col0 + 4u * ((uint32_t) lane + (uint32_t) p * kLanes);
-        col_bytes[p] = (c < F - 4u ? c : F - 4u) * 4u;
+        col_bytes[p] = ((c < F - 4u ? c : F - 4u) - base) * 4u;
     }
-    const char* x_bytes = reinterpret_cast<const char*>(a.x_src);
+    const char* x_bytes = reinterpret_cast<const char*>(a.x_src + base);
     const uint32_t trips = (count + num_groups - 1u) / num_groups;       // the same for every group (count > 0)
 
     // extent of the row this group visits in trip `it` (empty past the end)
@@ -305,7 +310,7 @@ __device__ __forceinline__ void aggregate_rows(const AggArgs& a, uint32_t col0, 
                             const uint32_t off = __umul24(j, row_bytes) + col_bytes[p];     // both factors < 2^24
                             x[u][p] = load_floats(x_bytes + off);
                         } else {
-                            const uint64_t off = (uint64_t) j * row_bytes + col_bytes[p];
+                            const uint64_t off = (uint64_t) j * F * 4u + col_bytes[p];
                             x[u][p] = load_floats(x_bytes + off);
                         }
                     }
@@ -363,7 +368,7 @@ __device__ __forceinline__ void aggregate_rows(const AggArgs& a, uint32_t col0, 
             const float left = fmaf(-q, n, x);
             return left == left ? fmaf(left, inv_n, q) : q;
         };
-        char* o = reinterpret_cast<char*>(a.out + (int64_t) row * F);
+        char* o = reinterpret_cast<char*>(a.out + (int64_t) row * F + base);
 #pragma unroll
         for (int p = 0; p < kPer; ++p) {
             if (kRagged && p == kPer - 1 && !in_last) continue;
@@ -396,7 +401,7 @@ __device__ __forceinline__ void aggregate_rows(const AggArgs& a, uint32_t col0, 
     visit(row, b0, e0, j0, w0, []() {}, [&](char* dst, const float4& r) { if (live) store_floats(dst, r); });
 }
 
-// Rows of more columns than the lanes take are visited once per window of columns (blockIdx.z).
+// Rows of more columns than a block takes at most are visited once per window of columns (blockIdx.z, behind those of the launches before).
 template <int kLanes, int kPer, bool kRagged, bool kQuotient>
 __global__ void __launch_bounds__(kBlock) k_aggregate(AggGroup g)
 {
@@ -412,13 +417,15 @@ __global__ void __launch_bounds__(kBlock) k_aggregate(AggGroup g)
     const uint32_t num_src = (uint32_t) (a.num_src_dev ? *a.num_src_dev : a.num_src);
     if (rows <= 0) return;
     const uint32_t count = (uint32_t) rows;
+    constexpr uint32_t kWindow = 4 * kLanes * kPer;
+    const uint32_t col0 = kWindow == kAggWindow ? (g.first_window + blockIdx.z) * kWindow : 0u;
     if (num_src == 0) {             // no source row to read (and none may be touched): every edge is skipped
+        const uint32_t end = col0 + kWindow < F ? col0 + kWindow : F;
         for (int64_t row = group; row < rows; row += num_groups)
-            for (uint32_t i = (uint32_t) lane; i < F; i += kLanes) a.out[row * F + i] = 0.f;
+            for (uint32_t i = col0 + (uint32_t) lane; i < end; i += kLanes) a.out[row * F + i] = 0.f;
         return;
     }
     const bool off32 = (uint64_t) num_src * F * 4u < ((uint64_t) 1 << 32) && num_src < (1u << 24) && F < (1u << 22);
-    const uint32_t col0 = blockIdx.z * (4 * kLanes * kPer);
     if (off32) aggregate_rows<kLanes, kPer, kRagged, kQuotient, true>(a, col0, group, num_groups, count, num_src);
     else       aggregate_rows<kLanes, kPer, kRagged, kQuotient, false>(a, col0, group, num_groups, count, num_src);
 }
@@ -557,11 +564,20 @@ hipError_t launch_aggregate(gns_ctx* const* ctxs, int count, const gns_block* co
     // a larger grid is no faster alone and 7 % slower next to another stream's kernels.
     const int64_t cap = (int64_t) c->num_cus * (thin ? 16 : 4);
     if (blocks > cap) blocks = cap;
-    const dim3 grid((unsigned) blocks, (unsigned) count, (unsigned) ((F4 + q.lanes * q.per - 1) / (q.lanes * q.per)));
-    if (thin) hipLaunchKernelGGL(k_aggregate_thin, grid, dim3(kBlock), 0, s, a);
-    // (32 lanes: the form for rows that leave lanes over is ahead where none are, 98 us for 105 at F = 256)
-    else      aggregate_dispatch(q, feat_dim == 4 * q.lanes * q.per && q.lanes != 32, quotient, grid, s, a);
-    return hipGetLastError();
+    if (thin) {
+        hipLaunchKernelGGL(k_aggregate_thin, dim3((unsigned) blocks, (unsigned) count), dim3(kBlock), 0, s, a);
+        return hipGetLastError();
+    }
+    const int64_t windows = ((int64_t) feat_dim + kAggWindow - 1) / kAggWindow, most_windows = 65535;      // of a grid
+    for (int64_t w = 0; w < windows; w += most_windows) {
+        a.first_window = (uint32_t) w;
+        const dim3 grid((unsigned) blocks, (unsigned) count, (unsigned) std::min(windows - w, most_windows));
+        // (32 lanes: the form for rows that leave lanes over is ahead where none are, 98 us for 105 at F = 256)
+        aggregate_dispatch(q, feat_dim == 4 * q.lanes * q.per && q.lanes != 32, quotient, grid, s, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace gns

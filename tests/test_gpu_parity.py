@@ -219,6 +219,26 @@ def test_aggregate_widths(F, shift):
         gns.close()
 
 
+@pytest.mark.parametrize("F", [1025, 65535 * 1024 + 1, 65536 * 1024 + 1030, 2 ** 30 + 5])
+def test_aggregate_of_rows_beyond_a_grid_and_beyond_4_gb(F):
+    """Rows of more columns than one grid has windows for, and of 2^32 bytes and more: the second of two source rows, copied by a
+    single edge of weight 1, and a row without edges; the last window has one column, six and five."""
+    dev = torch.device("cuda:0")
+    ip, ix = _small(n=300)
+    gns = GpuGns(ip, ix, None, fanouts=(2,), policies=(U,), cache_size=10, max_seeds=8)
+    try:
+        x = torch.empty((2, F), dtype=torch.float32, device=dev).uniform_(generator=torch.Generator(device=dev).manual_seed(F))
+        out = torch.full((2, F), 7.0, dtype=torch.float32, device=dev)
+        t = [torch.tensor(v, device=dev) for v in (np.array([0, 1, 1], np.int32), np.array([1], np.int32), np.array([1], np.float32))]
+        blk = B.gns_block()
+        blk.num_dst, blk.num_src, blk.num_edges = 2, 2, 1
+        blk.indptr, blk.indices, blk.weights = (v.data_ptr() for v in t)
+        B.gns_aggregate(gns.ctx, blk, x, F, out)
+        assert torch.equal(out[0], x[1]) and not out[1].any()
+    finally:
+        gns.close()
+
+
 @pytest.mark.parametrize("policies", [(U, C), (CF, CF)])
 def test_unbiased_weight_mode(policies):
     ip, ix = _small()
