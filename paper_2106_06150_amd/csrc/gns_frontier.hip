@@ -120,7 +120,7 @@ hipError_t launch_batch_begin(const Group& g, const BeginDyn& d, hipStream_t s)
 {
     LayerArgs a;
     fill_first_args(g, &a);
-    const dim3 grid = group_grid(g, a, (g.rows[0] + kBlock - 1) / kBlock);
+    const dim3 grid = group_grid(g, a, first_blocks(g, (g.rows[0] + kBlock - 1) / kBlock));
     hipLaunchKernelGGL(k_batch_begin, grid, dim3(kBlock), 0, s, a, d);
     return hipGetLastError();
 }

@@ -985,7 +985,7 @@ hipError_t launch_first_layer(const Group& g, const BeginDyn& d, hipStream_t s)
     LayerArgs a;
     fill_first_args(g, &a);
     const int rows_per_block = rows_per_sum(g, 0);
-    const dim3 grid = group_grid(g, a, (g.rows[0] + rows_per_block - 1) / rows_per_block);
+    const dim3 grid = group_grid(g, a, first_blocks(g, (g.rows[0] + rows_per_block - 1) / rows_per_block));
     with_unroll(a.s.fanout, [&](auto K) {
         with_list(c, 0, [&](auto kList) {
             with_one(g, [&](auto kOne) {

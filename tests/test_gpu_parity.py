@@ -4,6 +4,8 @@ Integer outputs (cache list, bitmap, draw count, block CSRs, src lists,
 eligible counts, gathered rows) must be bit-exact; fp32 weights within 1e-5
 relative; aggregates within 1e-5 of (1/n_v) * sum |w_e x_e| per element.
 """
+import functools
+
 import numpy as np
 import pytest
 import torch
@@ -88,6 +90,47 @@ def test_any_flag_but_zero_means_64_bit_offsets(flag, monkeypatch):
             full_parity(gns, cache_seed=9, epoch=0, batch_seed=5, seeds=synth.uniform_seed_batch(ip.numel() - 1, 400, 6))
         finally:
             gns.close()
+
+
+def _marked_by_slots(gns):
+    """Whether the context marks its input layer's new nodes by slots of the cache: its table of 1/p^C has 8 bytes a node then, and
+    the same context with an input layer that is not from the cache only 4."""
+    other = B.make_config(gns.fanouts, gns.policies[:-1] + [CF], gns.cache_size, gns.config.max_seeds, gns.wmode, gns.config.flag_mode)
+    return B.gns_workspace_bytes(gns.graph, gns.config) > B.gns_workspace_bytes(gns.graph, other)
+
+
+@functools.lru_cache(maxsize=None)
+def _graph_of_150k():
+    return _small(n=150_000, avg=20, seed=150)
+
+
+@pytest.mark.parametrize("cache", [60_000, 140_000])
+@pytest.mark.parametrize("fanouts", [(16, 8), (17, 5), (5, 5, 5)])
+@pytest.mark.parametrize("count", [1, 3])
+def test_few_seeds_and_a_large_cache(cache, fanouts, count):
+    """Mini-batches whose seeds take fewer blocks of the first launch (either kind of it) than clearing the marks by slot does, one after
+    the other: what the one before marked is gone."""
+    ip, ix = _graph_of_150k()
+    n = ip.numel() - 1
+    L = len(fanouts)
+    policies = (U,) * (L - 1) + (C,)
+    gns = GpuGns(ip, ix, None, fanouts=fanouts, policies=policies, cache_size=cache, max_seeds=64, flag_mode=1)
+    ctxs, keep, bufs, call = _group_setup(gns, count)
+    try:
+        assert _marked_by_slots(gns)
+        B.gns_sample_cache(gns.ctx, 47, 0)
+        bitmap = oracle.sample_cache(ip.numpy(), 47, 0, cache)[1]
+        for rnd in range(3):
+            seeds = [synth.uniform_seed_batch(n, 64 - b, 10 * rnd + b).cuda() for b in range(count)]
+            call.sample([90 * rnd + b for b in range(count)], seeds)
+            call.wait()
+            for b in range(count):
+                ref = oracle.sample_blocks(ip.numpy(), ix.numpy(), bitmap, cache, 90 * rnd + b, seeds[b].cpu().numpy(), list(fanouts), list(policies))
+                compare_blocks([bufs[b].views(j) for j in range(L)], ref)
+    finally:
+        for f in ctxs[1:]:
+            B.gns_destroy(f)
+        gns.close()
 
 
 @pytest.mark.parametrize("F", [1, 3, 4, 32, 64, 96, 100, 128, 256, 260, 1024])
