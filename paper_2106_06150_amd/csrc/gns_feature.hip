@@ -55,11 +55,12 @@ struct GatherArgs {
 //  - the chain of every row, node -> bitmap -> rank -> row.  A wave looks up the rows of its next kLanes turns at once, one
 //    per lane, and a turn is a read and a store.
 //  - what the copy left in the caches.  Cached rows are what the input layer's aggregation reads, some dozens of times each: stored
-//    plainly they are still there by then.  All other reads and stores pass the caches by, so as not to displace them.
+//    plainly they are still there by then.  All other stores pass the caches by, so as not to displace them, and so do the reads
+//    (kPastCaches) of a table that the caches do not hold anyway.
 // Groups of four, on states that change from call to call, this kernel and the aggregation behind it: 1 M nodes (4 x 90 K rows of
 // 512 bytes) 66.5 + 73 -> 68 + 52 us (all stores past the caches 65 + 85, reads plain 61 + 66, all stores plain 65 + 73), with the
 // upper layers cache first 34 + 38.5 -> 32 + 31, 40 M nodes 78 + 54 -> 66 + 52; one mini-batch of 90 K rows 21 + 21.5 -> 20.5 + 16.4.
-template <int kLanes>
+template <int kLanes, bool kPastCaches>
 __global__ void __launch_bounds__(kBlock) k_gather(GatherArgs a)
 {
     if (a.unless_negative && *a.unless_negative < 0) return;
@@ -96,7 +97,11 @@ __global__ void __launch_bounds__(kBlock) k_gather(GatherArgs a)
             for (int64_t c = 4 * (lane % kLanes); c < F; c += 4 * kLanes) {
                 const int64_t at = c < F - 4 ? c : F - 4;
                 Float4u v = {0.f, 0.f, 0.f, 0.f};
-                if (r != kNone) v = __builtin_nontemporal_load(reinterpret_cast<const Float4u*>(src + at));
+                if (r != kNone) {
+                    const Float4u* p = reinterpret_cast<const Float4u*>(src + at);
+                    if (kPastCaches) v = __builtin_nontemporal_load(p);
+                    else             v = *p;
+                }
                 if (r < 0) {
                     asm volatile("; cached row");            // (the two stores would become one, without the hint)
                     *reinterpret_cast<Float4u*>(dst + at) = v;
@@ -125,6 +130,16 @@ __global__ void __launch_bounds__(kBlock) k_gather_thin(GatherArgs a)
     }
 }
 
+// Bytes of a feature table (in HBM) that is read through the caches: what the infinity cache (256 MB) keeps from call to call.  us of a gather
+// alone, with reads through the caches and past them, and of a whole call (sampling, gather and aggregation of 1024 seeds):
+//   100 K nodes, 128 floats (49 MB)        9.0 and 10.3    64.5 and 66.1, four at a time 119.4 and 125.0
+//   200 K nodes, 256 floats (195 MB)      18.6 and 21.9    76.7 and 79.6                 188.1 and 194.7
+//   1 M nodes, 64 floats (244 MB)          9.0 and 10.9    69.4 and 68.6                 145.7 and 143.9
+//   1 M nodes, 128 floats (488 MB)        15.3 and 17.7    82.2 and 81.1                 188.1 and 188.4
+//   4 M nodes, 128 floats (1953 MB)       20.0 and 23.2   100.9 and 100.5                274.4 and 268.4
+// (Beyond, what the gather loses the aggregation gains.)
+constexpr double kKeptTable = 200.0 * 1024 * 1024;
+
 static inline int lanes_for(int64_t units)
 {
     int l = 4;
@@ -132,14 +147,15 @@ static inline int lanes_for(int64_t units)
     return l;
 }
 
+template <bool kPastCaches>
 static void gather_dispatch(int lanes, dim3 blocks, hipStream_t s, const GatherArgs& a)
 {
     switch (lanes) {
-        case 4:  hipLaunchKernelGGL((k_gather<4>), blocks, dim3(kBlock), 0, s, a); break;
-        case 8:  hipLaunchKernelGGL((k_gather<8>), blocks, dim3(kBlock), 0, s, a); break;
-        case 16: hipLaunchKernelGGL((k_gather<16>), blocks, dim3(kBlock), 0, s, a); break;
-        case 32: hipLaunchKernelGGL((k_gather<32>), blocks, dim3(kBlock), 0, s, a); break;
-        default: hipLaunchKernelGGL((k_gather<64>), blocks, dim3(kBlock), 0, s, a); break;
+        case 4:  hipLaunchKernelGGL((k_gather<4, kPastCaches>), blocks, dim3(kBlock), 0, s, a); break;
+        case 8:  hipLaunchKernelGGL((k_gather<8, kPastCaches>), blocks, dim3(kBlock), 0, s, a); break;
+        case 16: hipLaunchKernelGGL((k_gather<16, kPastCaches>), blocks, dim3(kBlock), 0, s, a); break;
+        case 32: hipLaunchKernelGGL((k_gather<32, kPastCaches>), blocks, dim3(kBlock), 0, s, a); break;
+        default: hipLaunchKernelGGL((k_gather<64, kPastCaches>), blocks, dim3(kBlock), 0, s, a); break;
     }
 }
 
@@ -185,7 +201,8 @@ hipError_t launch_gather(gns_ctx* const* ctxs, int count, const int32_t* const* 
     if (blocks > cap) blocks = cap;
     const dim3 grid((unsigned) blocks, (unsigned) count);
     if (thin) hipLaunchKernelGGL(k_gather_thin, grid, dim3(kBlock), 0, s, a);
-    else      gather_dispatch(lanes, grid, s, a);
+    else if (c->graph.feat_dev && (double) a.n * a.feat_dim * 4 <= kKeptTable) gather_dispatch<false>(lanes, grid, s, a);
+    else                                                                       gather_dispatch<true>(lanes, grid, s, a);
     return hipGetLastError();
 }
 

@@ -174,6 +174,30 @@ def test_gather_of_any_list(F, count, on_host):
         gns.close()
 
 
+@pytest.mark.parametrize("F", [5, 17, 33, 100, 130])
+@pytest.mark.parametrize("more", [0, 1])
+def test_gather_from_tables_that_the_caches_keep_and_do_not(F, more):
+    """gns_gather_features from a table in HBM of no more than 200 MB, which is read through the caches, and of more; a cached node's
+    row, another's, and rows of zeros."""
+    dev = torch.device("cuda:0")
+    n = 200 * 2 ** 20 // (4 * F) + more
+    ip = torch.arange(n + 1, dtype=torch.int32, device=dev) * 2
+    i = torch.arange(n, device=dev)
+    ix = torch.sort(torch.stack([(i - 1) % n, (i + 1) % n], 1), 1)[0].reshape(-1).to(torch.int32)
+    feat = torch.randn((n, F), device=dev, generator=torch.Generator(device=dev).manual_seed(F))
+    gns = GpuGns(ip, ix, feat, fanouts=(4, 3), policies=(U, C), cache_size=n // 3, max_seeds=8)
+    try:
+        B.gns_sample_cache(gns.ctx, 5, 0)
+        nodes = torch.randint(-3, n + 3, (150_000,), device=dev, generator=torch.Generator(device=dev).manual_seed(F + 1)).to(torch.int32)
+        nodes[:3] = torch.tensor([n - 1, n, -1])
+        out = torch.full((nodes.numel() + 1, F), 7.0, device=dev)
+        B.gns_gather_features(gns.ctx, nodes, nodes.numel(), out)
+        ok = (nodes >= 0) & (nodes < n)
+        assert torch.equal(out[:-1], torch.where(ok[:, None], feat[torch.where(ok, nodes, 0).long()], 0.0)) and (out[-1] == 7.0).all()
+    finally:
+        gns.close()
+
+
 @pytest.mark.parametrize("F,rows,max_deg", [(128, 70_000, 5), (128, 3_000, 20), (64, 40_000, 9), (256, 20_000, 12),
                                             (100, 40_000, 9), (8, 5_000, 20), (1024, 600, 9)])
 def test_aggregate_on_hand_made_blocks(F, rows, max_deg):
