@@ -261,7 +261,7 @@ __device__ __forceinline__ void aggregate_rows(const AggArgs& a, uint32_t col0, 
                                                uint32_t num_src)
 {
     constexpr int kSlots = kLanes < 8 ? kLanes : 8;                      // edges a round covers (one per lane)
-    constexpr int kFlight = (kPer >= 3 && kSlots > 4) ? 5 : kSlots;     // source rows read together
+    constexpr int kFlight = kLanes * kPer == 8 ? 6 : kPer >= 3 ? 5 : kSlots;     // source rows read together
     const int lane = (int) (threadIdx.x % kLanes);
     const uint32_t F = (uint32_t) a.feat_dim;
     const uint32_t row_bytes = F * 4u;                                  // (kOff32)
@@ -420,7 +420,7 @@ __device__ __forceinline__ void aggregate_rows(const AggArgs& a, uint32_t col0, 
 
 // Rows of more columns than a block takes at most are visited once per window of columns (blockIdx.z, behind those of the launches before).
 template <int kLanes, int kPer, bool kRagged, bool kQuotient>
-__global__ void __launch_bounds__(kBlock) k_aggregate(AggGroup g)
+__global__ void __launch_bounds__(kBlock, kLanes * kPer == 8 ? 6 : 1) k_aggregate(AggGroup g)
 {
     AggArgs a;
     static_cast<AggBatch&>(a) = g.b[blockIdx.y];
@@ -577,9 +577,14 @@ hipError_t launch_aggregate(gns_ctx* const* ctxs, int count, const gns_block* co
     const AggLanes q = aggregate_lanes(F4);
     const int64_t groups_per_block = kBlock / q.lanes;
     int64_t blocks = (most + groups_per_block - 1) / groups_per_block;
-    // About the blocks that are resident together (beyond that a group visits several rows, which its pipeline wants anyway);
-    // a larger grid is no faster alone and 7 % slower next to another stream's kernels.
-    const int64_t cap = (int64_t) c->num_cus * (thin ? 16 : 4);
+    // Beyond that a group visits several rows, which its pipeline wants anyway.  Four blocks a CU, where three or four are resident: a
+    // larger grid is no faster alone and 7 % slower next to another stream's kernels.  Rows of one column a lane are over sooner and read
+    // from the L2s, and there it is waves that count: as many as are resident, eight of four lanes a row, and six of eight with six source
+    // rows read together (five with eight; seven, of five rows, are the same).  One mini-batch of 78 K rows of F floats, four of them, and four
+    // of 21 K, on 1 M, 1 M and 100 K nodes, us with four blocks and so: F = 8 6.0 -> 5.1, 13.1 -> 12.1, 7.8 -> 7.8; F = 16 6.2 -> 5.4,
+    // 13.5 -> 12.6, 7.8 -> 7.8; F = 20 7.0 -> 6.6, 20.0 -> 19.2, 13.5 -> 10.8; F = 32 6.6 -> 6.5, 18.0 -> 18.1, 12.7 -> 10.8.  (12.6 K rows of
+    // up to 15 edges, F = 20 to 32: 4.1 to 4.6 us, 4.3 to 4.9 with six rows together.)
+    const int64_t cap = (int64_t) c->num_cus * (thin ? 16 : q.per > 1 ? 4 : q.lanes == 8 ? 6 : 8);
     if (blocks > cap) blocks = cap;
     if (thin) {
         hipLaunchKernelGGL(k_aggregate_thin, dim3((unsigned) blocks, (unsigned) count), dim3(kBlock), 0, s, a);

@@ -286,6 +286,57 @@ def test_aggregate_widths(F, shift):
         gns.close()
 
 
+# Rows that make every lane group of the grid visit three of them, the last ones not all (four lanes a row: eight blocks of 64 groups on
+# each of 256 CUs; eight lanes and one column each: six of 32; else four of 32, 16, 8 and 4).
+@pytest.mark.parametrize("F,rows", [(2, 600_001), (4, 290_001), (13, 290_001), (16, 290_001), (17, 110_001), (20, 110_001), (32, 110_001)] +
+                                   [(F, 72_001) for F in (36, 50, 64, 66, 80, 81, 96, 127, 128)] + [(F, 36_001) for F in (99, 100, 129, 160, 161, 192)] +
+                                   [(F, 18_001) for F in (193, 255, 256, 260, 384, 388, 448, 512)] + [(F, 9_001) for F in (516, 768, 772, 896, 1024, 1028, 2100)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_aggregate_rows_ahead(F, rows, shift):
+    """gns_aggregate with several rows per lane group, whose extents and edges are read ahead: rows of 0..9 edges and one of 40, two edges out of
+    range.  Weights and sources are whole numbers, so sums are exact and the mean is either the sum divided by the number of edges, rounded once
+    (widths and bases that are no multiple of four floats, and wide rows), or its product with the rounded reciprocal: to the last bit."""
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev).manual_seed(F)
+    num_src = rows + 100
+    deg = torch.randint(0, 10, (rows,), device=dev, generator=gen)
+    deg[0], deg[rows // 2] = 3, 40
+    indptr = torch.zeros(rows + 1, dtype=torch.int64, device=dev)
+    indptr[1:] = deg.cumsum(0)
+    E = int(indptr[-1])
+    indices = torch.randint(0, num_src, (E,), device=dev, generator=gen)
+    weights = torch.randint(1, 65, (E,), device=dev, generator=gen).double()
+    x = torch.randint(-1000, 1001, (num_src, F), device=dev, generator=gen).double()
+    owner = torch.repeat_interleave(torch.arange(rows, device=dev), deg)
+    w_ref = weights.clone()
+    w_ref[1] = w_ref[E - 1] = 0.0                                        # of the edges that are skipped
+    ref = torch.zeros((rows, F), dtype=torch.float64, device=dev)
+    step = max(1, 2 ** 26 // F)
+    for e in range(0, E, step):
+        ref.index_add_(0, owner[e:e + step], w_ref[e:e + step, None] * x[indices[e:e + step]])
+    n = deg.clamp(min=1).double()[:, None]
+    divided = F % 4 or shift or F > 1024 or (F > 256 and F % 32)
+    # (a quotient or a product of two floats, rounded to 53 bits and then to 24, is what it is rounded to 24 at once)
+    want = (ref / n if divided else ref * (1.0 / n).float().double()).float()
+    indices[1], indices[E - 1] = num_src, 2 ** 31 - 1
+    ip, ix = _small(n=300)
+    gns = GpuGns(ip, ix, None, fanouts=(2,), policies=(U,), cache_size=10, max_seeds=8)
+    try:
+        t = [v.contiguous() for v in (indptr.int(), indices.int(), weights.float())]
+        xs = torch.zeros(num_src * F + 4, dtype=torch.float32, device=dev)[shift:shift + num_src * F].view(num_src, F)
+        xs.copy_(x)
+        blk = B.gns_block()
+        blk.num_dst, blk.num_src, blk.num_edges = rows, num_src, E
+        blk.indptr, blk.indices, blk.weights = (v.data_ptr() for v in t)
+        buf = torch.full((rows * F + 8,), 7.0, dtype=torch.float32, device=dev)
+        out = buf[4 + shift:4 + shift + rows * F].view(rows, F)
+        B.gns_aggregate(gns.ctx, blk, xs, F, out)
+        assert torch.equal(out, want)
+        assert (buf[:4 + shift] == 7.0).all() and (buf[4 + shift + rows * F:] == 7.0).all()
+    finally:
+        gns.close()
+
+
 @pytest.mark.parametrize("F", [1025, 65535 * 1024 + 1, 65536 * 1024 + 1030, 2 ** 30 + 5])
 def test_aggregate_of_rows_beyond_a_grid_and_beyond_4_gb(F):
     """Rows of more columns than one grid has windows for, and of 2^32 bytes and more: the second of two source rows, copied by a
