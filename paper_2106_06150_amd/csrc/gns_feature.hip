@@ -378,7 +378,8 @@ __device__ __forceinline__ void aggregate_rows(const AggArgs& a, uint32_t col0, 
         const bool some = e > b;                                           // (a row without edges has read nothing: 0)
         const float n = some ? (float) (e - b) : 1.f;
         const float inv_n = some ? 1.0f / n : 0.f;                         // one division per row, then the products
-        // kQuotient: x / n to the last bit, from the product and what it leaves (not for infinities, whose product it is)
+        // kQuotient: x / n to the last bit, from the product and what it leaves (not for infinities, whose product it is; halfway
+        // between two numbers below the normal ones either may come out)
         auto mean = [&](float x) {
             const float q = x * inv_n;
             if (!kQuotient) return q;

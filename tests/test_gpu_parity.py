@@ -337,6 +337,48 @@ def test_aggregate_rows_ahead(F, rows, shift):
         gns.close()
 
 
+@pytest.mark.parametrize("F,shift", [(1, 0), (3, 0), (4, 0), (4, 1), (5, 0), (20, 1), (64, 0), (66, 0), (128, 1), (130, 0), (260, 0), (1028, 0)])
+def test_aggregate_of_infinities_nan_and_extremes(F, shift):
+    """Means of rows with infinities, NaN, the largest and the smallest floats, in the widths that divide and those that multiply: float by
+    float as numpy's fp32 sum and division, or product with 1 / n; results below the normal numbers within one unit of the smallest."""
+    big, tiny = np.finfo(np.float32).max, np.finfo(np.float32).tiny
+    vals = np.array([np.inf, -np.inf, np.nan, big, -big, tiny, 3 * tiny, 2.0 ** -149, 1.0, -7.0], np.float32)
+    rows = [[v] for v in range(10)] + [[0, 8, 8], [0, 1], [1, 9], [3, 3], [3, 4], [3, 8, 8], [4, 9, 9], [5, 5, 5, 7, 7], [6] * 7, [7] * 3, [7] * 6 + [5],
+            [3] + [7] * 9, [2, 8], [8] * 10 + [0], [9, 9, 8], []]
+    deg = np.array([len(r) for r in rows])
+    indptr = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32)
+    indices = np.array([v for r in rows for v in r], np.int32)
+    # column c of a source row is its value times 2^-(c % 3): all columns differ from their neighbors
+    x = (vals[:, None] * np.float32(0.5) ** (np.arange(F) % 3).astype(np.float32)).astype(np.float32)
+    x = np.concatenate([x, np.zeros((30, F), np.float32)])
+    divided = F % 4 or shift or F > 1024 or (F > 256 and F % 32)
+    want = np.zeros((len(rows), F), np.float32)
+    with np.errstate(all="ignore"):
+        for r, edges in enumerate(rows):
+            for v in edges:
+                want[r] = want[r] + x[v]                                 # weight 1: one rounding, as the fma
+            if edges:
+                want[r] = want[r] / np.float32(len(edges)) if divided else want[r] * (np.float32(1) / np.float32(len(edges)))
+    dev = torch.device("cuda:0")
+    ip, ix = _small(n=300)
+    gns = GpuGns(ip, ix, None, fanouts=(2,), policies=(U,), cache_size=10, max_seeds=8)
+    try:
+        t = [torch.from_numpy(v).to(dev) for v in (indptr, indices, np.ones(len(indices), np.float32))]
+        xs = torch.zeros(x.size + 4, dtype=torch.float32, device=dev)[shift:shift + x.size].view(x.shape)
+        xs.copy_(torch.from_numpy(x))
+        out = torch.zeros(len(rows) * F + 4, dtype=torch.float32, device=dev)[shift:shift + len(rows) * F].view(len(rows), F)
+        blk = B.gns_block()
+        blk.num_dst, blk.num_src, blk.num_edges = len(rows), x.shape[0], len(indices)
+        blk.indptr, blk.indices, blk.weights = (v.data_ptr() for v in t)
+        B.gns_aggregate(gns.ctx, blk, xs, F, out)
+        got = out.cpu().numpy()
+    finally:
+        gns.close()
+    small = np.abs(want) < tiny
+    assert np.array_equal(got[~small], want[~small], equal_nan=True)
+    assert (np.abs(got[small].astype(np.float64) - want[small]) <= 2.0 ** -149).all()
+
+
 @pytest.mark.parametrize("F", [1025, 65535 * 1024 + 1, 65536 * 1024 + 1030, 2 ** 30 + 5])
 def test_aggregate_of_rows_beyond_a_grid_and_beyond_4_gb(F):
     """Rows of more columns than one grid has windows for, and of 2^32 bytes and more: the second of two source rows, copied by a
