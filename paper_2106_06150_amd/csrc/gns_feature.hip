@@ -252,7 +252,8 @@ struct AggArgs : AggBatch {
 // of rows or edges that do not exist go to a valid address (the first extent) and their value is replaced,
 // and the last trip, in which some groups have no row, stands apart -- and only rare cases (a row with more than
 // kSlots edges, slots beyond the fourth) sit in branches.  Lanes past the last column (kRagged) stand aside in the last of the
-// kPer reads and stores all the same: what a read costs the texture addressers is more than the wait.
+// kPer reads and stores all the same: what a read costs the texture addressers is more than the wait.  (In the last of several windows lanes
+// can be past the last column in the reads before it too; there they repeat the last four columns.)
 // kOff32: every byte offset into x_src fits 32 bits and row index and row size fit 24 bits, so an address is
 // the uniform base plus one 32-bit vector offset (one multiply-add per load).  Offsets within a row are counted from the
 // window's first column: rows of 2^30 floats are 4 GB long.
@@ -510,32 +511,38 @@ static AggLanes aggregate_lanes(int64_t F4)
 
 static void aggregate_dispatch(AggLanes q, bool full, bool quotient, dim3 grid, hipStream_t s, const AggGroup& a)
 {
+    using std::integral_constant;
+    using Yes = std::true_type;
+    using No = std::false_type;
     auto go = [&](auto lanes, auto per, auto ragged, auto quotient) {
         hipLaunchKernelGGL((k_aggregate<decltype(lanes)::value, decltype(per)::value, decltype(ragged)::value, decltype(quotient)::value>), grid,
                            dim3(kBlock), 0, s, a);
     };
-    auto with = [&](auto lanes, auto per) {
-        if (quotient)  go(lanes, per, std::true_type(), std::true_type());
-        else if (full) go(lanes, per, std::false_type(), std::false_type());
-        else           go(lanes, per, std::true_type(), std::false_type());
+    // fills: whether rows that leave no lane over come here and gain by a form of their own (32 lanes: the one for rows that leave lanes
+    // over is ahead where none are, 98 us for 105 at F = 256); leaves: whether others do that are not divided
+    auto with = [&](auto lanes, auto per, auto fills, auto leaves) {
+        if (quotient) go(lanes, per, Yes(), Yes());
+        else if constexpr (!decltype(leaves)::value) go(lanes, per, No(), No());
+        else if constexpr (!decltype(fills)::value) go(lanes, per, Yes(), No());
+        else if (full) go(lanes, per, No(), No());
+        else go(lanes, per, Yes(), No());
     };
-    using std::integral_constant;
-    if (q.lanes == 4)       with(integral_constant<int, 4>(), integral_constant<int, 1>());
+    if (q.lanes == 4)       with(integral_constant<int, 4>(), integral_constant<int, 1>(), Yes(), Yes());
     else if (q.lanes == 8) {
-        if (q.per == 1)      with(integral_constant<int, 8>(), integral_constant<int, 1>());
-        else if (q.per == 2) with(integral_constant<int, 8>(), integral_constant<int, 2>());
-        else if (q.per == 3) with(integral_constant<int, 8>(), integral_constant<int, 3>());
-        else                 with(integral_constant<int, 8>(), integral_constant<int, 4>());
+        if (q.per == 1)      with(integral_constant<int, 8>(), integral_constant<int, 1>(), Yes(), Yes());
+        else if (q.per == 2) with(integral_constant<int, 8>(), integral_constant<int, 2>(), Yes(), Yes());
+        else if (q.per == 3) with(integral_constant<int, 8>(), integral_constant<int, 3>(), Yes(), Yes());
+        else                 with(integral_constant<int, 8>(), integral_constant<int, 4>(), Yes(), No());         // 128 columns only
     } else if (q.lanes == 16) {
-        if (q.per == 2)      with(integral_constant<int, 16>(), integral_constant<int, 2>());
-        else                 with(integral_constant<int, 16>(), integral_constant<int, 3>());
+        if (q.per == 2)      with(integral_constant<int, 16>(), integral_constant<int, 2>(), No(), Yes());        // 128 columns are not here
+        else                 with(integral_constant<int, 16>(), integral_constant<int, 3>(), Yes(), Yes());
     } else if (q.lanes == 32) {
-        if (q.per == 2)      with(integral_constant<int, 32>(), integral_constant<int, 2>());
-        else if (q.per == 3) with(integral_constant<int, 32>(), integral_constant<int, 3>());
-        else                 with(integral_constant<int, 32>(), integral_constant<int, 4>());
+        if (q.per == 2)      with(integral_constant<int, 32>(), integral_constant<int, 2>(), No(), Yes());
+        else if (q.per == 3) with(integral_constant<int, 32>(), integral_constant<int, 3>(), No(), Yes());
+        else                 with(integral_constant<int, 32>(), integral_constant<int, 4>(), No(), Yes());
     } else {
-        if (q.per == 3)      with(integral_constant<int, 64>(), integral_constant<int, 3>());
-        else                 with(integral_constant<int, 64>(), integral_constant<int, 4>());
+        if (q.per == 3)      with(integral_constant<int, 64>(), integral_constant<int, 3>(), Yes(), Yes());
+        else                 with(integral_constant<int, 64>(), integral_constant<int, 4>(), Yes(), Yes());
     }
 }
 
@@ -595,8 +602,7 @@ hipError_t launch_aggregate(gns_ctx* const* ctxs, int count, const gns_block* co
     for (int64_t w = 0; w < windows; w += most_windows) {
         a.first_window = (uint32_t) w;
         const dim3 grid((unsigned) blocks, (unsigned) count, (unsigned) std::min(windows - w, most_windows));
-        // (32 lanes: the form for rows that leave lanes over is ahead where none are, 98 us for 105 at F = 256)
-        aggregate_dispatch(q, feat_dim == 4 * q.lanes * q.per && q.lanes != 32, quotient, grid, s, a);
+        aggregate_dispatch(q, feat_dim == 4 * q.lanes * q.per, quotient, grid, s, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
