@@ -52,23 +52,72 @@ def test_small_graph_parity(offsets, fanouts, policies, flag_mode):
         gns.close()
 
 
-@pytest.mark.parametrize("n,cache,fanouts,seeds,tile_words", [
-    (3000, 64, (3, 9), 257, 0), (3000, 65, (4, 4, 8), 256, 0), (4000, 3000, (5, 17), 700, 0), (4000, 3900, (2, 64), 1100, 0),
-    (90_000, 65_536, (12, 5), 1500, 0), (90_000, 65_537, (12, 5), 1500, 0), (150_000, 140_000, (16, 5), 400, 0), (150_000, 140_000, (16, 20), 400, 512)])
-def test_input_layer_marked_by_slots(n, cache, fanouts, seeds, tile_words, monkeypatch):
+def _marked_by_slots(gns):
+    """Whether the context marks its input layer's new nodes by slots of the cache: its table of 1/p^C has 8 bytes a node then, and
+    the same context with an input layer that is not from the cache only 4."""
+    other = B.make_config(gns.fanouts, gns.policies[:-1] + [CF], gns.cache_size, gns.config.max_seeds, gns.wmode, gns.config.flag_mode)
+    return B.gns_workspace_bytes(gns.graph, gns.config) > B.gns_workspace_bytes(gns.graph, other)
+
+
+@functools.lru_cache(maxsize=None)
+def _graph_of_150k():
+    return _small(n=150_000, avg=20, seed=150)
+
+
+@pytest.mark.parametrize("n,avg,cache,fanouts,seeds,tile_words,by_slot", [
+    (3000, 9, 64, (3, 9), 257, 0, True), (3000, 9, 65, (4, 4, 8), 256, 0, True), (4000, 9, 3000, (5, 17), 700, 0, True),
+    (4000, 9, 3900, (2, 64), 1100, 0, True), (90_000, 9, 65_536, (12, 5), 1500, 0, True), (90_000, 9, 65_537, (12, 5), 1500, 0, True),
+    (150_000, 20, 140_000, (16, 5), 400, 0, True), (150_000, 20, 140_000, (16, 20), 400, 512, True), (150_000, 9, 140_000, (16, 5), 400, 0, False)])
+def test_input_layer_marked_by_slots(n, avg, cache, fanouts, seeds, tile_words, by_slot, monkeypatch):
     """Input layers from the cache only on the induced subgraph, whose new nodes are marked by their slots of the cache: caches up to
     what is finished in one launch and beyond (tiles of slots of the smallest and of the largest length), last words of marks that are
     full and not, rows around whole blocks, more slots a row than a thread has on its way; mini-batches one after the other, whose
-    marks are cleared in between, and a second cache, whose structures lie elsewhere."""
+    marks are cleared in between, and a second cache, whose structures lie elsewhere.  The last one has no place for the marks."""
     if tile_words:
         monkeypatch.setenv("GNS_MARK_TILE_WORDS", str(tile_words))
-    ip, ix = _small(n=n, avg=9, seed=n)
+    ip, ix = _small(n=n, avg=avg, seed=n)
     gns = GpuGns(ip, ix, None, fanouts=fanouts, policies=(U,) * (len(fanouts) - 1) + (C,), cache_size=cache, max_seeds=seeds, flag_mode=1)
     try:
+        assert _marked_by_slots(gns) == by_slot
         for trial in range(3):
             batch = synth.uniform_seed_batch(n, seeds - 75 * trial, trial)
             full_parity(gns, cache_seed=9, epoch=trial // 2, batch_seed=50 + trial, seeds=batch)
     finally:
+        gns.close()
+
+
+@pytest.mark.parametrize("spins", ["256", "0"])
+@pytest.mark.parametrize("tile_words", [64, 128, 256, 512])
+def test_group_marked_by_slots_of_a_large_cache(tile_words, spins, monkeypatch):
+    """Groups (the created context and forks of it) whose marks by slot are finished tile by tile, with tiles of 4096, 8192, 16,384 and 32,768
+    slots, and with the counts of other tiles taken from the marks; a fork on its own; the fixed scratch; a second cache."""
+    monkeypatch.setenv("GNS_MARK_TILE_WORDS", str(tile_words))
+    monkeypatch.setenv("GNS_UNION_SPINS", spins)
+    ip, ix = _graph_of_150k()
+    n, cache, fanouts, policies, count = ip.numel() - 1, 140_000, (12, 16, 5), (U, CF, C), 3
+    gns = GpuGns(ip, ix, None, fanouts=fanouts, policies=policies, cache_size=cache, max_seeds=150, flag_mode=1)
+    ctxs, keep, bufs, call = _group_setup(gns, count)
+    try:
+        assert _marked_by_slots(gns)
+        for epoch in range(2):
+            B.gns_sample_cache(gns.ctx, 48, epoch)
+            bitmap = oracle.sample_cache(ip.numpy(), 48, epoch, cache)[1]
+            batches = [synth.uniform_seed_batch(n, 150 - 40 * b, 10 * epoch + b) for b in range(count)]
+            refs = [oracle.sample_blocks(ip.numpy(), ix.numpy(), bitmap, cache, 70 + b, batches[b].numpy(), list(fanouts), list(policies))
+                    for b in range(count)]
+            on_gpu = [b.cuda() for b in batches]
+            for _ in range(2):
+                call.sample([70 + b for b in range(count)], on_gpu)
+                call.wait()
+                for b in range(count):
+                    compare_blocks([bufs[b].views(j) for j in range(3)], refs[b])
+            B.gns_sample_blocks(ctxs[2], 71, on_gpu[1], bufs[2].array)
+            compare_blocks([bufs[2].views(j) for j in range(3)], refs[1])
+            B.gns_sample_blocks_static(ctxs[1], 72, on_gpu[2], bufs[1].array)
+            compare_blocks([bufs[1].views(j) for j in range(3)], refs[2])
+    finally:
+        for f in ctxs[1:]:
+            B.gns_destroy(f)
         gns.close()
 
 
@@ -90,18 +139,6 @@ def test_any_flag_but_zero_means_64_bit_offsets(flag, monkeypatch):
             full_parity(gns, cache_seed=9, epoch=0, batch_seed=5, seeds=synth.uniform_seed_batch(ip.numel() - 1, 400, 6))
         finally:
             gns.close()
-
-
-def _marked_by_slots(gns):
-    """Whether the context marks its input layer's new nodes by slots of the cache: its table of 1/p^C has 8 bytes a node then, and
-    the same context with an input layer that is not from the cache only 4."""
-    other = B.make_config(gns.fanouts, gns.policies[:-1] + [CF], gns.cache_size, gns.config.max_seeds, gns.wmode, gns.config.flag_mode)
-    return B.gns_workspace_bytes(gns.graph, gns.config) > B.gns_workspace_bytes(gns.graph, other)
-
-
-@functools.lru_cache(maxsize=None)
-def _graph_of_150k():
-    return _small(n=150_000, avg=20, seed=150)
 
 
 @pytest.mark.parametrize("cache", [60_000, 140_000])
