@@ -156,9 +156,8 @@ __device__ __forceinline__ uint32_t count_tile(const FinishArgs& a, int32_t tile
     return n;
 }
 
-// Node `node` joins the batch's list at place `pos`.  Nodes that join in the last layer are
+// CSR extent of a node that joins the batch's list.  Nodes that join in the last layer are
 // no layer's rows: nothing reads their extents, and on a graph whose offsets fit no L2 the read of one is a trip to memory.
-// Behind repeated or invalid seeds the list can be longer than the graph has nodes; it is cut where its buffers end.
 __device__ __forceinline__ RowExtent new_extent(const FinishArgs& a, uint32_t node)
 {
     RowExtent ext = {0, 0};
@@ -179,6 +178,8 @@ __device__ __forceinline__ RowExtent extent_of(const FinishArgs& a, uint32_t nod
     return {(int64_t) ((uint64_t) (a.g_i64 ? start_hi : 0u) << 32 | start), (int64_t) ((uint64_t) (a.g_i64 ? end_hi : 0u) << 32 | end)};
 }
 
+// Node `node` joins the batch's list at place `pos`.  Behind repeated or invalid seeds the list can be longer than the graph has nodes; it is
+// cut where its buffers end.
 __device__ __forceinline__ void emit_new_node(const FinishArgs& a, int32_t pos, uint32_t node, const RowExtent& ext)
 {
     if (pos >= a.max_src) return;
